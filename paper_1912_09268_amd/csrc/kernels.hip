@@ -161,11 +161,13 @@ __device__ __forceinline__ float widen(_Float16 x) { return static_cast<float>(x
 // ---------------------------------------------------------------------------------------------
 // kernel arguments
 // ---------------------------------------------------------------------------------------------
+//
+// What a launch costs the host depends on the size of this block: up to 112 bytes an empty launch takes 2.4 us,
+// from 136 bytes on 3.3 us (the runtime writes the block into device memory), and a kernel that asks for gridDim
+// makes the runtime append 256 more.  So everything that can be derived from something else is, and the grid
+// size that the persistent form needs comes in as `turn`.
 template <typename GradT> struct Args {
-    const TileHdr* tiles;
-    const uint32_t* seg_n;
-    const int32_t* seg_layer;
-    const uint64_t* seg_off;
+    const TileHdr* tiles;            // the segment tables lie right below, see seg_off() and its neighbours
     const GradT* const* grad_ptrs;   // [P*L]
     GradT* const* merge_bufs;        // [P]
     float* reduced;                  // arena or null
@@ -173,14 +175,28 @@ template <typename GradT> struct Args {
     float* const* v_ptrs;            // [L]
     float lr, mu, inv_p;
     int32_t L, P;
+    int32_t n_seg;                   // segments of the model
     int32_t tile_first, tile_count;
-    int32_t xcd_contiguous;
-    int32_t tiles_per_wg;            // consecutive tiles one workgroup handles per turn, >= 1
     int32_t n_units;                 // ceil(tile_count / tiles_per_wg)
-    int32_t worker_split;            // 1: gridDim.y = P and every workgroup serves worker blockIdx.y alone
-    int32_t clipped;                 // 0: whole tiles; 1: only arena elements in [clip_lo, clip_hi)
-    int64_t clip_lo, clip_hi;
+    int32_t turn;                    // units from one of a workgroup's turns to its next: the workgroups of a walk
+    int16_t tiles_per_wg;            // consecutive tiles one workgroup handles per turn, >= 1
+    int8_t xcd_contiguous;
+    int8_t worker_split;             // 1: gridDim.y = P and every workgroup serves worker blockIdx.y alone
+    int16_t clip_lo, clip_hi;        // first element wanted of the first tile, end of those wanted of the last one
 };
+static_assert(sizeof(Args<float>) <= 112, "a larger block of arguments makes every launch 0.9 us dearer");
+
+// The tables of one model lie in one block: seg_layer[S], seg_n[S] and seg_off[S + 1], ending where the tile headers
+// begin, so that the address of the headers and S lead to all of them.
+template <typename GradT> __device__ __forceinline__ const uint64_t* seg_off(const Args<GradT>& A) {
+    return reinterpret_cast<const uint64_t*>(A.tiles) - (A.n_seg + 1);
+}
+template <typename GradT> __device__ __forceinline__ const uint32_t* seg_n(const Args<GradT>& A) {
+    return reinterpret_cast<const uint32_t*>(seg_off(A)) - A.n_seg;
+}
+template <typename GradT> __device__ __forceinline__ const int32_t* seg_layer(const Args<GradT>& A) {
+    return reinterpret_cast<const int32_t*>(seg_n(A)) - A.n_seg;
+}
 
 // First worker a workgroup serves.  PACK has no arithmetic across workers, so it is launched as P
 // single-worker copies side by side in gridDim.y: workgroups are dispatched x-fastest, the chip then
@@ -460,20 +476,20 @@ __device__ void general_tile(const Args<GradT>& A, const WorkerPtrs<GradT, PT>& 
         // j = 1 + 2*tid and j = 2 + 2*tid.
         const int j0 = 1 + 2 * tid, j1 = j0 + 1;
         int x0 = 0, x1 = 0;
-        if (j0 < nseg) x0 = (j0 == 1) ? h.first_end : static_cast<int>(ro(A.seg_n)[h.seg0 + j0 - 1]);
-        if (j1 < nseg) x1 = static_cast<int>(ro(A.seg_n)[h.seg0 + j1 - 1]);
+        if (j0 < nseg) x0 = (j0 == 1) ? h.first_end : static_cast<int>(ro(seg_n(A))[h.seg0 + j0 - 1]);
+        if (j1 < nseg) x1 = static_cast<int>(ro(seg_n(A))[h.seg0 + j1 - 1]);
         const int incl = block_inclusive_scan(x0 + x1, s_wave);
         if (j0 < nseg) s_loc[j0] = incl - x1;
         if (j1 < nseg) s_loc[j1] = incl;
-        for (int j = tid; j < nseg; j += BLOCK) s_layer[j] = ro(A.seg_layer)[h.seg0 + j];
+        for (int j = tid; j < nseg; j += BLOCK) s_layer[j] = ro(seg_layer(A))[h.seg0 + j];
         if (tid == 0) s_loc[nseg] = valid;
     }
     __syncthreads();
     auto start_of = [&](int j) -> int {         // j >= 1
-        return staged ? s_loc[j] : static_cast<int>(static_cast<int64_t>(ro(A.seg_off)[h.seg0 + j]) - tile_base);
+        return staged ? s_loc[j] : static_cast<int>(static_cast<int64_t>(ro(seg_off(A))[h.seg0 + j]) - tile_base);
     };
     auto end_of = [&](int j) -> int { return (j + 1 < nseg) ? start_of(j + 1) : valid; };
-    auto layer_of = [&](int j) -> int { return staged ? s_layer[j] : ro(A.seg_layer)[h.seg0 + j]; };
+    auto layer_of = [&](int j) -> int { return staged ? s_layer[j] : ro(seg_layer(A))[h.seg0 + j]; };
     auto owner_of = [&](int q) -> int {         // last j with start_of(j) <= q (segment 0 starts <= 0)
         int lo = 0, hi = nseg - 1;
         while (lo < hi) {
@@ -557,11 +573,11 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_stream_kernel(const Args<
         const int per_die = (n_units + 7) >> 3;
         u_begin = die * per_die + static_cast<int>(blockIdx.x >> 3);
         u_end = min(n_units, (die + 1) * per_die);
-        u_step = static_cast<int>(gridDim.x >> 3);
+        u_step = A.turn >> 3;
     } else {
         u_begin = blockIdx.x;
         u_end = n_units;
-        u_step = gridDim.x;
+        u_step = A.turn;
     }
     for (int u = u_begin; u < u_end; u += u_step) {
         const int t_end = min((u + 1) * K, A.tile_count);
@@ -569,13 +585,9 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_stream_kernel(const Args<
             const int tile = A.tile_first + t;
             const TileHdr h = load_header(A.tiles + tile);
             const int64_t tile_base = static_cast<int64_t>(tile) * TILE;
-            int clo = 0, chi = h.valid;
-            if (A.clipped) {                        // uniform over the workgroup
-                const int64_t l = A.clip_lo - tile_base, r = A.clip_hi - tile_base;
-                if (l > 0) clo = l < h.valid ? static_cast<int>(l) : h.valid;
-                if (r < h.valid) chi = r > 0 ? static_cast<int>(r) : 0;
-                if (chi <= clo) continue;
-            }
+            const int clo = t == 0 ? A.clip_lo : 0;
+            const int chi = t == A.tile_count - 1 ? min(h.valid, static_cast<int>(A.clip_hi)) : h.valid;
+            if (chi <= clo) continue;
             if (!(clo == 0 && chi == TILE && (!needs_owner(KIND) || h.nseg == 1))) {
                 general_tile<KIND, GradT, PT>(A, mrg, h, tile_base, clo, chi, s_loc, s_layer, s_wave, s_ragged, &s_nragged);
                 continue;
@@ -584,8 +596,9 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_stream_kernel(const Args<
             if constexpr (KIND == K_PACK && PACK_TILES > 1) {
                 // Pack is a plain copy and wants more bytes in flight per lane than one tile holds: when the next
                 // tiles of this workgroup's share are full tiles of the same tensor too, they are copied together.
-                if (!A.clipped && t + PACK_TILES <= t_end) {
-                    bool same = true;
+                // (A clip cuts into the first and the last tile only.)
+                if (t + PACK_TILES <= t_end) {
+                    bool same = t + PACK_TILES < A.tile_count || A.clip_hi == TILE;
 #pragma unroll
                     for (int k = 1; k < PACK_TILES; ++k) {
                         const TileHdr hk = load_header(A.tiles + tile + k);
@@ -653,10 +666,8 @@ struct mgwfbp_ctx {
     uint64_t resident_bytes = 0;      // budget of w + v bytes kept cacheable
     uint64_t serial = 0;              // changes whenever the tables change; never reused within a process
     // device copies
-    TileHdr* d_tiles = nullptr;
-    uint32_t* d_seg_n = nullptr;
-    int32_t* d_seg_layer = nullptr;
-    uint64_t* d_seg_off = nullptr;
+    unsigned char* d_tables = nullptr;   // one block, see table_parts()
+    TileHdr* d_tiles = nullptr;          // the tile headers in it
 };
 
 namespace {
@@ -686,15 +697,38 @@ void mark_resident_tiles(HostTables& h, uint64_t budget) {
     }
 }
 
-template <typename T> int upload(T** dst, const std::vector<T>& src) {
-    const size_t bytes = (src.empty() ? 1 : src.size()) * sizeof(T);
-    hipError_t e = hipMalloc(reinterpret_cast<void**>(dst), bytes);
+constexpr size_t round256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
+
+// The four tables as they lie in a device block (see Args): the segment tables below the tile headers, which start
+// on a multiple of 256 bytes.
+struct TableParts {
+    struct { size_t off, bytes; const void* src; } part[4];
+    size_t tiles_at, total;
+};
+TableParts table_parts(const HostTables& h) {
+    const size_t b_tiles = h.tiles.size() * sizeof(TileHdr), b_off = h.seg_off.size() * sizeof(uint64_t);
+    const size_t b_n = h.seg_n.size() * sizeof(uint32_t), b_layer = h.seg_layer.size() * sizeof(int32_t);
+    const size_t at = round256(b_layer + b_n + b_off);
+    return {{{at, b_tiles, h.tiles.data()},
+             {at - b_off, b_off, h.seg_off.data()},
+             {at - b_off - b_n, b_n, h.seg_n.data()},
+             {at - b_off - b_n - b_layer, b_layer, h.seg_layer.data()}}, at, at + b_tiles};
+}
+
+int upload_tables(mgwfbp_ctx* c) {
+    const TableParts t = table_parts(c->host);
+    hipError_t e = hipMalloc(reinterpret_cast<void**>(&c->d_tables), t.total);
     if (e != hipSuccess) {
-        *dst = nullptr;
+        c->d_tables = nullptr;
         g_last_hip_error = static_cast<int>(e);
         return e == hipErrorOutOfMemory ? MGWFBP_ENOMEM : MGWFBP_EHIP;
     }
-    if (!src.empty()) return note(hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice));
+    c->d_tiles = reinterpret_cast<TileHdr*>(c->d_tables + t.tiles_at);
+    for (const auto& p : t.part) {
+        if (p.bytes == 0) continue;
+        const int rc = note(hipMemcpy(c->d_tables + p.off, p.src, p.bytes, hipMemcpyHostToDevice));
+        if (rc != MGWFBP_OK) return rc;
+    }
     return MGWFBP_OK;
 }
 
@@ -723,11 +757,8 @@ int create_common(mgwfbp_ctx** out, const uint64_t* n_elems, int32_t L, const ui
         if (rc == MGWFBP_OK) rc = note(hipGetDeviceProperties(&prop, c->device));
         if (rc == MGWFBP_OK) {
             c->n_cu = prop.multiProcessorCount;
-            rc = upload(&c->d_tiles, c->host.tiles);
+            rc = upload_tables(c);
         }
-        if (rc == MGWFBP_OK) rc = upload(&c->d_seg_n, c->host.seg_n);
-        if (rc == MGWFBP_OK) rc = upload(&c->d_seg_layer, c->host.seg_layer);
-        if (rc == MGWFBP_OK) rc = upload(&c->d_seg_off, c->host.seg_off);
         if (rc != MGWFBP_OK) {
             mgwfbp_ctx_destroy(c);
             return rc;
@@ -821,14 +852,6 @@ int32_t default_workgroups_per_cu(int kind, int32_t dtype) {
     }
 }
 
-// Where the kernels find the tables: normally the context's own device copies.
-struct DevTables {
-    const TileHdr* tiles;
-    const uint32_t* seg_n;
-    const int32_t* seg_layer;
-    const uint64_t* seg_off;
-};
-
 // Tile range and element clip of one call: either a group (or all groups), or an arena interval.
 struct Span {
     int32_t t0 = 0, t1 = 0;
@@ -839,8 +862,8 @@ struct Span {
 template <int KIND>
 int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const* merge_bufs, float* reduced,
         float* const* w_ptrs, float* const* v_ptrs, float lr, float mu, void* stream_v,
-        const Span* span = nullptr, const DevTables* tabs = nullptr) {
-    if (c == nullptr || (tabs == nullptr && !c->on_device)) return MGWFBP_EINVAL;
+        const Span* span = nullptr, const TileHdr* static_tiles = nullptr) {
+    if (c == nullptr || (static_tiles == nullptr && !c->on_device)) return MGWFBP_EINVAL;
     if (span == nullptr && (group < -1 || group >= c->host.G)) return MGWFBP_EINVAL;
     if (reads_grads(KIND) && grad_ptrs == nullptr) return MGWFBP_EINVAL;
     if ((reads_merge(KIND) || writes_merge(KIND)) && merge_bufs == nullptr) return MGWFBP_EINVAL;
@@ -861,9 +884,10 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
     const int32_t count = t1 - t0;
     if (count <= 0) return MGWFBP_OK;             // nothing to move (empty group or empty model)
 
-    DevTables T{c->d_tiles, c->d_seg_n, c->d_seg_layer, c->d_seg_off};
-    if (tabs != nullptr) {
-        T = *tabs;                                    // the caller vouches for the current device
+    // where the kernels find the tables: normally the context's own device copies
+    const TileHdr* tiles = c->d_tiles;
+    if (static_tiles != nullptr) {
+        tiles = static_tiles;                         // the caller vouches for the current device
     } else {
         int dev = -1;
         int rc = note(hipGetDevice(&dev));
@@ -881,7 +905,7 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
     int grid = units;
     if (c->blocks_per_cu > 0 && c->n_cu > 0 && static_cast<int64_t>(c->n_cu) * c->blocks_per_cu < units)
         grid = c->n_cu * c->blocks_per_cu;
-    int32_t xcd = 0;
+    int8_t xcd = 0;
     if (c->xcd_contiguous && grid >= 64) {
         grid &= ~7;
         xcd = 1;
@@ -898,30 +922,33 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
     pc.lds_bytes = lds_for_workgroups_per_cu(wgs);
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     const float inv_p = 1.0f / static_cast<float>(c->P);
-    const int32_t clip_on = (span != nullptr && span->clipped) ? 1 : 0;
-    const int64_t clip_lo = span ? span->lo : 0, clip_hi = span ? span->hi : 0;
+    // a clip cuts into the first and the last tile only
+    const bool clipped = span != nullptr && span->clipped;
+    const int16_t clip_lo = static_cast<int16_t>(clipped ? span->lo - static_cast<int64_t>(t0) * TILE : 0);
+    const int16_t clip_hi = static_cast<int16_t>(clipped ? span->hi - static_cast<int64_t>(t1 - 1) * TILE : TILE);
+    const int32_t S = static_cast<int32_t>(c->host.seg_layer.size());
 
     if (c->dtype == MGWFBP_F32) {
-        Args<float> A{T.tiles, T.seg_n, T.seg_layer, T.seg_off,
+        Args<float> A{tiles,
                       reinterpret_cast<const float* const*>(grad_ptrs),
                       reinterpret_cast<float* const*>(merge_bufs), reduced, w_ptrs, v_ptrs,
-                      lr, mu, inv_p, c->host.L, c->P, t0, count, xcd, tpw, units, 0,
-                      clip_on, clip_lo, clip_hi};
+                      lr, mu, inv_p, c->host.L, c->P, S, t0, count, units, grid, static_cast<int16_t>(tpw), xcd, 0,
+                      clip_lo, clip_hi};
         return launch_by_p<KIND, float>(A, grid, stream, pc);
     }
     if (c->dtype == MGWFBP_F16) {
-        Args<_Float16> A{T.tiles, T.seg_n, T.seg_layer, T.seg_off,
+        Args<_Float16> A{tiles,
                          reinterpret_cast<const _Float16* const*>(grad_ptrs),
                          reinterpret_cast<_Float16* const*>(merge_bufs), reduced, w_ptrs, v_ptrs,
-                         lr, mu, inv_p, c->host.L, c->P, t0, count, xcd, tpw, units, 0,
-                         clip_on, clip_lo, clip_hi};
+                         lr, mu, inv_p, c->host.L, c->P, S, t0, count, units, grid, static_cast<int16_t>(tpw), xcd, 0,
+                         clip_lo, clip_hi};
         return launch_by_p<KIND, _Float16>(A, grid, stream, pc);
     }
-    Args<uint16_t> A{T.tiles, T.seg_n, T.seg_layer, T.seg_off,
+    Args<uint16_t> A{tiles,
                      reinterpret_cast<const uint16_t* const*>(grad_ptrs),
                      reinterpret_cast<uint16_t* const*>(merge_bufs), reduced, w_ptrs, v_ptrs,
-                     lr, mu, inv_p, c->host.L, c->P, t0, count, xcd, tpw, units, 0,
-                     clip_on, clip_lo, clip_hi};
+                     lr, mu, inv_p, c->host.L, c->P, S, t0, count, units, grid, static_cast<int16_t>(tpw), xcd, 0,
+                     clip_lo, clip_hi};
     return launch_by_p<KIND, uint16_t>(A, grid, stream, pc);
 }
 
@@ -952,10 +979,7 @@ int mgwfbp_ctx_create_host(mgwfbp_ctx** ctx_out, const uint64_t* n_elems, int32_
 
 void mgwfbp_ctx_destroy(mgwfbp_ctx* c) {
     if (c == nullptr) return;
-    if (c->d_tiles) (void)hipFree(c->d_tiles);
-    if (c->d_seg_n) (void)hipFree(c->d_seg_n);
-    if (c->d_seg_layer) (void)hipFree(c->d_seg_layer);
-    if (c->d_seg_off) (void)hipFree(c->d_seg_off);
+    if (c->d_tables) (void)hipFree(c->d_tables);
     delete c;
 }
 
@@ -1105,11 +1129,10 @@ int mgwfbp_group_pipeline_static(mgwfbp_ctx* c, int32_t group, const void* const
     if (c == nullptr) return MGWFBP_EINVAL;
     const HostTables& h = c->host;
     if (group < -1 || group >= h.G) return MGWFBP_EINVAL;
-    auto round256 = [](size_t x) { return (x + 255) & ~static_cast<size_t>(255); };
-    const size_t b_tiles = h.tiles.size() * sizeof(TileHdr), b_n = h.seg_n.size() * sizeof(uint32_t);
-    const size_t b_layer = h.seg_layer.size() * sizeof(int32_t), b_off = h.seg_off.size() * sizeof(uint64_t);
-    const size_t o_n = round256(b_tiles), o_layer = o_n + round256(b_n), o_off = o_layer + round256(b_layer);
-    if (o_off + round256(b_off) > MGWFBP_STATIC_TABLE_MAX_BYTES) return MGWFBP_ECAPACITY;
+    const TableParts parts = table_parts(h);
+    size_t needed = 0;                            // the documented limit: every table rounded up by itself
+    for (const auto& part : parts.part) needed += round256(part.bytes);
+    if (needed > MGWFBP_STATIC_TABLE_MAX_BYTES) return MGWFBP_ECAPACITY;
     if (h.tiles.empty()) return MGWFBP_OK;
 
     int dev = -1;
@@ -1129,10 +1152,7 @@ int mgwfbp_group_pipeline_static(mgwfbp_ctx* c, int32_t group, const void* const
     if (!(slot.loaded && slot.serial == c->serial && slot.stream == stream)) {
         // The array still holds the previous call's tables: overwrite them, in stream order, with this model's.
         slot.loaded = false;
-        const struct { size_t off, bytes; const void* src; } parts[4] = {
-            {0, b_tiles, h.tiles.data()}, {o_n, b_n, h.seg_n.data()},
-            {o_layer, b_layer, h.seg_layer.data()}, {o_off, b_off, h.seg_off.data()}};
-        for (const auto& part : parts) {
+        for (const auto& part : parts.part) {
             if (part.bytes == 0) continue;
             rc = note(hipMemcpyAsync(slot.ptr + part.off, part.src, part.bytes, hipMemcpyHostToDevice, stream));
             if (rc != MGWFBP_OK) return rc;
@@ -1141,11 +1161,8 @@ int mgwfbp_group_pipeline_static(mgwfbp_ctx* c, int32_t group, const void* const
         slot.serial = c->serial;
         slot.stream = stream;
     }
-    const DevTables T{reinterpret_cast<const TileHdr*>(slot.ptr), reinterpret_cast<const uint32_t*>(slot.ptr + o_n),
-                      reinterpret_cast<const int32_t*>(slot.ptr + o_layer),
-                      reinterpret_cast<const uint64_t*>(slot.ptr + o_off)};
     return run<K_PIPELINE>(c, group, d_grad_ptrs, d_merge_bufs, d_reduced, d_w_ptrs, d_v_ptrs, lr, momentum,
-                           hip_stream, nullptr, &T);
+                           hip_stream, nullptr, reinterpret_cast<const TileHdr*>(slot.ptr + parts.tiles_at));
 }
 
 int mgwfbp_handler_replay(mgwfbp_ctx* c, const double* group_ready_s, double time_scale,
