@@ -166,8 +166,7 @@ __device__ __forceinline__ float widen(_Float16 x) { return static_cast<float>(x
 // from 136 bytes on 3.3 us (the runtime writes the block into device memory), and a kernel that asks for gridDim
 // makes the runtime append 256 more.  So everything that can be derived from something else is, and the grid
 // size that the persistent form needs comes in as `turn`.
-template <typename GradT> struct Args {
-    const TileHdr* tiles;            // the segment tables lie right below, see seg_off() and its neighbours
+template <typename GradT> struct CallArgs {
     const GradT* const* grad_ptrs;   // [P*L]
     GradT* const* merge_bufs;        // [P]
     float* reduced;                  // arena or null
@@ -175,16 +174,27 @@ template <typename GradT> struct Args {
     float* const* v_ptrs;            // [L]
     float lr, mu, inv_p;
     int32_t L, P;
-    int32_t n_seg;                   // segments of the model
     int32_t tile_first, tile_count;
+    int16_t tiles_per_wg;            // consecutive tiles one workgroup handles per turn, >= 1
+    int16_t xcd_contiguous;
+};
+template <typename GradT> struct Args : CallArgs<GradT> {      // table form: what a tile holds is in the tables
+    const TileHdr* tiles;            // the segment tables lie right below, see seg_off() and its neighbours
+    int32_t n_seg;                   // segments of the model
     int32_t n_units;                 // ceil(tile_count / tiles_per_wg)
     int32_t turn;                    // units from one of a workgroup's turns to its next: the workgroups of a walk
-    int16_t tiles_per_wg;            // consecutive tiles one workgroup handles per turn, >= 1
-    int8_t xcd_contiguous;
-    int8_t worker_split;             // 1: gridDim.y = P and every workgroup serves worker blockIdx.y alone
     int16_t clip_lo, clip_hi;        // first element wanted of the first tile, end of those wanted of the last one
 };
-static_assert(sizeof(Args<float>) <= 112, "a larger block of arguments makes every launch 0.9 us dearer");
+constexpr int FEW = 8;
+template <typename GradT> struct FewArgs : CallArgs<GradT> {   // few-segments form: the segments come along
+    int32_t layer_hi;                // tensor of segment 0; segment j is tensor layer_hi - j
+    int16_t start0;                  // first element of segment 0; all positions count from the first tile's start
+    uint8_t n;                       // segments, 1..FEW
+    uint8_t closes;                  // bit j: segment j ends its group, the next one starts on the next tile
+    int32_t end[FEW];                // end of segment j
+};
+static_assert(sizeof(Args<float>) <= 112 && sizeof(FewArgs<float>) <= 112,
+              "a larger block of arguments makes every launch 0.9 us dearer");
 
 // The tables of one model lie in one block: seg_layer[S], seg_n[S] and seg_off[S + 1], ending where the tile headers
 // begin, so that the address of the headers and S lead to all of them.
@@ -202,8 +212,8 @@ template <typename GradT> __device__ __forceinline__ const int32_t* seg_layer(co
 // single-worker copies side by side in gridDim.y: workgroups are dispatched x-fastest, the chip then
 // streams one worker's gradients at a time (2 streams instead of 2P), which the memory system serves
 // faster.
-template <typename GradT> __device__ __forceinline__ int worker_base(const Args<GradT>& A) {
-    return A.worker_split ? static_cast<int>(blockIdx.y) : 0;
+template <int KIND> __device__ __forceinline__ int worker_base() {
+    return KIND == K_PACK ? static_cast<int>(blockIdx.y) : 0;
 }
 
 // Pointers of the P workers, either held in registers (P known at compile time) or re-read from the
@@ -250,7 +260,7 @@ template <typename T> struct WorkerPtrs<T, 0> {
 __device__ __forceinline__ void pace() { __builtin_amdgcn_sched_barrier(0); }
 
 template <int KIND, typename GradT, int PT, int W, int N, bool WVNT, bool TOGETHER = false>
-__device__ __forceinline__ void paced_step(const Args<GradT>& A, const WorkerPtrs<const GradT, PT>& src,
+__device__ __forceinline__ void paced_step(const CallArgs<GradT>& A, const WorkerPtrs<const GradT, PT>& src,
                                            const WorkerPtrs<GradT, PT>& mrg, float* wp, float* vp,
                                            int64_t soff, int64_t apos, int stride) {
     typedef typename VecOf<GradT, W>::type GV;
@@ -380,12 +390,12 @@ __device__ __forceinline__ void paced_step(const Args<GradT>& A, const WorkerPtr
 
 // one vector or element of the general path
 template <int KIND, typename GradT, int PT, int W>
-__device__ __forceinline__ void do_one(const Args<GradT>& A, const WorkerPtrs<GradT, PT>& mrg,
+__device__ __forceinline__ void do_one(const CallArgs<GradT>& A, const WorkerPtrs<GradT, PT>& mrg,
                                        int layer, int64_t soff, int64_t apos) {
     WorkerPtrs<const GradT, PT> src;
     float* wp = nullptr;
     float* vp = nullptr;
-    if constexpr (reads_grads(KIND)) src.fetch(A.grad_ptrs, A.L, layer, worker_base(A));
+    if constexpr (reads_grads(KIND)) src.fetch(A.grad_ptrs, A.L, layer, worker_base<KIND>());
     if constexpr (updates(KIND)) {
         wp = ro(A.w_ptrs)[layer];
         vp = ro(A.v_ptrs)[layer];
@@ -398,13 +408,13 @@ __device__ __forceinline__ void do_one(const Args<GradT>& A, const WorkerPtrs<Gr
 // vectors at a time; vector u of the chunk covers elements u * BLOCK * VEC + lane * VEC ...
 // ---------------------------------------------------------------------------------------------
 template <int KIND, typename GradT, int PT, bool WVNT, int STEPV>
-__device__ __forceinline__ void fast_chunk(const Args<GradT>& A, const WorkerPtrs<GradT, PT>& mrg,
+__device__ __forceinline__ void fast_chunk(const CallArgs<GradT>& A, const WorkerPtrs<GradT, PT>& mrg,
                                            int layer, int64_t tensor_off, int64_t tile_base, int nvec) {
     static_assert(STEPV == 0 || TVECS % STEPV == 0, "a tile is a whole number of steps");
     WorkerPtrs<const GradT, PT> src;
     float* wp = nullptr;
     float* vp = nullptr;
-    if constexpr (reads_grads(KIND)) src.fetch(A.grad_ptrs, A.L, layer, worker_base(A));
+    if constexpr (reads_grads(KIND)) src.fetch(A.grad_ptrs, A.L, layer, worker_base<KIND>());
     if constexpr (updates(KIND)) {
         wp = ro(A.w_ptrs)[layer];
         vp = ro(A.v_ptrs)[layer];
@@ -560,7 +570,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_stream_kernel(const Args<
     __shared__ int s_nragged;
 
     WorkerPtrs<GradT, PT> mrg;
-    if constexpr (reads_merge(KIND) || writes_merge(KIND)) mrg.fetch(A.merge_bufs, 1, 0, worker_base(A));
+    if constexpr (reads_merge(KIND) || writes_merge(KIND)) mrg.fetch(A.merge_bufs, 1, 0, worker_base<KIND>());
 
     // Work is dealt in units of `tiles_per_wg` consecutive tiles.
     const int K = A.tiles_per_wg;
@@ -606,7 +616,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_stream_kernel(const Args<
                     }
                     if (same) {
                         WorkerPtrs<const GradT, PT> src;
-                        src.fetch(A.grad_ptrs, A.L, h.layer0, worker_base(A));
+                        src.fetch(A.grad_ptrs, A.L, h.layer0, worker_base<KIND>());
                         const int lane_elem = static_cast<int>(threadIdx.x) * VEC;
                         paced_step<KIND, GradT, PT, VEC, PACK_TILES * TVECS, true>(
                             A, src, mrg, nullptr, nullptr, -h.first_start + lane_elem, tile_base + lane_elem, BLOCK * VEC);
@@ -633,6 +643,77 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_stream_kernel(const Args<
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// the same for a launch over at most FEW segments, which come along as arguments
+// ---------------------------------------------------------------------------------------------
+//
+// One group, or a tensor that has just arrived, is a handful of segments, and a launch over it is short enough
+// that the trips to memory in front of the first gradient count: the tile header, then the segment lengths of a
+// ragged tile, their prefix sum through LDS, and the search in it.  Here a workgroup works all of that out from
+// its arguments in scalar registers, so only the pointers lie between it and its data.  Segment j is tensor
+// layer_hi - j and starts where j - 1 ends, or on the next tile after the last segment of a group.  Kinds that
+// need no tensors (REDUCE) get whole groups as segments.
+template <typename GradT> __device__ __forceinline__ int few_start(const FewArgs<GradT>& A, int j) {   // j static
+    if (j == 0) return A.start0;
+    const int e = A.end[j - 1];
+    return (A.closes >> (j - 1)) & 1 ? (e + TILE - 1) & ~(TILE - 1) : e;
+}
+
+// Segment that element q belongs to if it belongs to any: the last one that starts at or before q, or segment 0.
+struct FewSeg { int j, start, end; };
+template <typename GradT> __device__ __forceinline__ FewSeg few_owner(const FewArgs<GradT>& A, int q) {
+    FewSeg s{0, A.start0, A.end[0]};
+#pragma unroll
+    for (int j = 1; j < FEW; ++j) {
+        const int start = few_start(A, j);
+        if (j < A.n && q >= start) s = FewSeg{j, start, A.end[j]};
+    }
+    return s;
+}
+
+template <int KIND, typename GradT, int PT, int STEPV>
+__global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_few_kernel(const FewArgs<GradT> A) {
+    static_assert(BLOCK == 64 && TVECS == 1, "a tile is one vector per lane of one wavefront");
+    WorkerPtrs<GradT, PT> mrg;
+    if constexpr (reads_merge(KIND) || writes_merge(KIND)) mrg.fetch(A.merge_bufs, 1, 0, worker_base<KIND>());
+    const int lane = threadIdx.x;
+    const int64_t arena = static_cast<int64_t>(A.tile_first) * TILE;
+    const int t_end = min((static_cast<int>(blockIdx.x) + 1) * A.tiles_per_wg, A.tile_count);
+    for (int t = blockIdx.x * A.tiles_per_wg; t < t_end; ++t) {
+        const int b = t * TILE;
+        const FewSeg s = few_owner(A, b);                                  // uniform
+        if (s.start <= b && b + TILE <= s.end) {                           // a full tile inside one segment
+            if constexpr (KIND == K_PACK && PACK_TILES > 1) {
+                if (t + PACK_TILES <= t_end && b + PACK_TILES * TILE <= s.end) {
+                    WorkerPtrs<const GradT, PT> src;
+                    src.fetch(A.grad_ptrs, A.L, A.layer_hi - s.j, worker_base<KIND>());
+                    paced_step<KIND, GradT, PT, VEC, PACK_TILES, true>(A, src, mrg, nullptr, nullptr, b - s.start + lane * VEC,
+                                                                       arena + b + lane * VEC, TILE);
+                    t += PACK_TILES - 1;
+                    continue;
+                }
+            }
+            fast_chunk<KIND, GradT, PT, true, STEPV>(A, mrg, A.layer_hi - s.j, b - s.start, arena + b, TVECS);
+            continue;
+        }
+        // Whole vectors first, then the wanted elements of the others, one per lane (see general_tile).
+        const int p = b + lane * VEC;
+        const FewSeg o = few_owner(A, p);
+        const bool whole = p >= o.start && p + VEC <= o.end;
+        const bool any = (p < o.end && p + VEC > o.start) || few_owner(A, p + VEC - 1).j != o.j;
+        const uint64_t ragged = __ballot(any && !whole);
+        if (whole) do_one<KIND, GradT, PT, VEC>(A, mrg, A.layer_hi - o.j, p - o.start, arena + p);
+        const int n_ragged = __popcll(ragged) * VEC;
+        for (int e = lane; e < n_ragged; e += BLOCK) {
+            uint64_t rest = ragged;
+            for (int k = e / VEC; k > 0; --k) rest &= rest - 1;
+            const int q = b + __builtin_ctzll(rest) * VEC + e % VEC;
+            const FewSeg r = few_owner(A, q);
+            if (q >= r.start && q < r.end) do_one<KIND, GradT, PT, 1>(A, mrg, A.layer_hi - r.j, q - r.start, arena + q);
+        }
+    }
+}
+
 thread_local int g_last_hip_error = 0;
 
 int note(hipError_t e) {
@@ -648,6 +729,10 @@ int mgwfbp_note_hip_result(int hip_error_code) { return note(static_cast<hipErro
 // ---------------------------------------------------------------------------------------------
 // context
 // ---------------------------------------------------------------------------------------------
+#ifndef MGWFBP_SMALL_PACK_TILES
+#define MGWFBP_SMALL_PACK_TILES 4096
+#endif
+constexpr int32_t SMALL_PACK_TILES = MGWFBP_SMALL_PACK_TILES;
 constexpr int32_t DEFAULT_BURST_TILES = 262144 / TILE;   // see run(): launches of at most 256 Ki elements
 
 struct mgwfbp_ctx {
@@ -776,6 +861,15 @@ struct Pace {
 };
 
 template <int KIND, typename GradT, int PT>
+int launch_one(const FewArgs<GradT>& A, int grid, hipStream_t stream, const Pace& pc, int grid_y = 1) {
+    if (pc.step_vecs <= 0)
+        hipLaunchKernelGGL((mgwfbp_few_kernel<KIND, GradT, PT, 0>), dim3(grid, grid_y), dim3(BLOCK), pc.lds_bytes, stream, A);
+    else
+        hipLaunchKernelGGL((mgwfbp_few_kernel<KIND, GradT, PT, 1>), dim3(grid, grid_y), dim3(BLOCK), pc.lds_bytes, stream, A);
+    return note(hipGetLastError());
+}
+
+template <int KIND, typename GradT, int PT>
 int launch_one(const Args<GradT>& A, int grid, hipStream_t stream, const Pace& pc, int grid_y = 1) {
     bool launched = false;
     if (pc.step_vecs <= 0) {
@@ -796,14 +890,12 @@ int launch_one(const Args<GradT>& A, int grid, hipStream_t stream, const Pace& p
     return note(hipGetLastError());
 }
 
-template <int KIND, typename GradT>
-int launch_by_p(const Args<GradT>& A, int grid, hipStream_t stream, const Pace& pc) {
+template <int KIND, typename GradT, template <typename> class ArgsT>
+int launch_by_p(const ArgsT<GradT>& A, int grid, hipStream_t stream, const Pace& pc) {
     if constexpr (KIND == K_UPDATE) {
         return launch_one<KIND, GradT, 0>(A, grid, stream, pc);   // no per-worker data
     } else if constexpr (KIND == K_PACK) {
-        Args<GradT> B = A;                                     // P independent single-worker copies
-        B.worker_split = 1;
-        return launch_one<KIND, GradT, 1>(B, grid, stream, pc, A.P);
+        return launch_one<KIND, GradT, 1>(A, grid, stream, pc, A.P);   // P independent single-worker copies
     } else {
         switch (A.P) {
             case 2: return launch_one<KIND, GradT, 2>(A, grid, stream, pc);
@@ -854,10 +946,75 @@ int32_t default_workgroups_per_cu(int kind, int32_t dtype) {
 
 // Tile range and element clip of one call: either a group (or all groups), or an arena interval.
 struct Span {
-    int32_t t0 = 0, t1 = 0;
+    int32_t t0 = 0, t1 = 0;               // tiles
+    int32_t s0 = 0, s1 = 0;               // segments
+    int32_t g0 = 0, g1 = 0;               // groups (not set for a clipped span)
     bool clipped = false;
     int64_t lo = 0, hi = 0;
 };
+
+Span span_of_groups(const HostTables& h, int32_t g0, int32_t g1) {
+    Span s;
+    s.t0 = h.group_tile[static_cast<size_t>(g0)];
+    s.t1 = h.group_tile[static_cast<size_t>(g1)];
+    s.s0 = h.group_seg[static_cast<size_t>(g0)];
+    s.s1 = h.group_seg[static_cast<size_t>(g1)];
+    s.g0 = g0;
+    s.g1 = g1;
+    return s;
+}
+
+// Fills in the segments of a launch if it can take the few-segments form: at most FEW of them, of consecutive
+// tensors (no empty tensor in between), less than 2^30 elements in all.
+bool few_segments(const HostTables& h, const Span& sp, bool whole_groups, int32_t& layer_hi, int16_t& start0, uint8_t& n_out,
+                  uint8_t& closes, int32_t* end) {
+    const int64_t base = static_cast<int64_t>(sp.t0) * TILE;
+    if (static_cast<int64_t>(sp.t1 - sp.t0) * TILE > (1 << 30)) return false;
+    int n = 0;
+    layer_hi = 0;
+    start0 = 0;
+    closes = 0;
+    if (whole_groups) {                                // REDUCE: a segment is all of a group
+        if (sp.g1 - sp.g0 > FEW) return false;
+        for (int32_t k = sp.g0; k < sp.g1; ++k) {
+            const size_t q = static_cast<size_t>(k);
+            if (h.group_elems[q] == 0) continue;
+            closes = static_cast<uint8_t>(closes | 1u << n);
+            end[n++] = static_cast<int32_t>(static_cast<int64_t>(h.group_base[q] + h.group_elems[q]) - base);
+        }
+    } else {
+        if (sp.s1 - sp.s0 > FEW) return false;
+        const size_t s0 = static_cast<size_t>(sp.s0);
+        layer_hi = h.seg_layer[s0];
+        start0 = static_cast<int16_t>(static_cast<int64_t>(h.seg_off[s0]) - base);
+        for (; n < sp.s1 - sp.s0; ++n) {
+            const size_t q = static_cast<size_t>(layer_hi - n);
+            if (h.seg_layer[s0 + static_cast<size_t>(n)] != layer_hi - n) return false;
+            if (n + 1 < sp.s1 - sp.s0 && h.tensor_group[q] != h.tensor_group[q - 1])
+                closes = static_cast<uint8_t>(closes | 1u << n);
+            end[n] = static_cast<int32_t>(static_cast<int64_t>(h.seg_off[s0 + static_cast<size_t>(n)] + h.tensor_n[q]) - base);
+        }
+    }
+    n_out = static_cast<uint8_t>(n);
+    for (int j = n; j < FEW; ++j) end[j] = end[n - 1];
+    return n > 0;
+}
+
+// Fills the argument block of the form the launch takes, and launches.
+template <int KIND, typename GradT>
+int launch(const mgwfbp_ctx* c, const Span& sp, const TileHdr* tiles, const CallArgs<GradT>& call, int32_t units,
+           int32_t grid, bool may_be_few, hipStream_t stream, const Pace& pc) {
+    if (may_be_few) {
+        FewArgs<GradT> A{call};
+        if (few_segments(c->host, sp, !needs_owner(KIND), A.layer_hi, A.start0, A.n, A.closes, A.end))
+            return launch_by_p<KIND, GradT, FewArgs>(A, grid, stream, pc);
+    }
+    // a clip cuts into the first and the last tile only
+    const int16_t clip_lo = static_cast<int16_t>(sp.clipped ? sp.lo - static_cast<int64_t>(sp.t0) * TILE : 0);
+    const int16_t clip_hi = static_cast<int16_t>(sp.clipped ? sp.hi - static_cast<int64_t>(sp.t1 - 1) * TILE : TILE);
+    const Args<GradT> A{call, tiles, static_cast<int32_t>(c->host.seg_layer.size()), units, grid, clip_lo, clip_hi};
+    return launch_by_p<KIND, GradT, Args>(A, grid, stream, pc);
+}
 
 template <int KIND>
 int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const* merge_bufs, float* reduced,
@@ -870,18 +1027,11 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
     if ((KIND == K_REDUCE || KIND == K_UPDATE) && reduced == nullptr) return MGWFBP_EINVAL;
     if (updates(KIND) && (w_ptrs == nullptr || v_ptrs == nullptr)) return MGWFBP_EINVAL;
 
-    int32_t t0, t1;
-    if (span != nullptr) {
-        t0 = span->t0;
-        t1 = span->t1;
-    } else if (group < 0) {
-        t0 = 0;
-        t1 = static_cast<int32_t>(c->host.tiles.size());
-    } else {
-        t0 = c->host.group_tile[static_cast<size_t>(group)];
-        t1 = c->host.group_tile[static_cast<size_t>(group) + 1];
-    }
-    const int32_t count = t1 - t0;
+    Span sp;
+    if (span != nullptr) sp = *span;
+    else if (group < 0) sp = span_of_groups(c->host, 0, c->host.G);
+    else sp = span_of_groups(c->host, group, group + 1);
+    const int32_t count = sp.t1 - sp.t0;
     if (count <= 0) return MGWFBP_OK;             // nothing to move (empty group or empty model)
 
     // where the kernels find the tables: normally the context's own device copies
@@ -900,12 +1050,13 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
     // takes one tile per workgroup.  More only stretches the set of bytes the chip has in flight: the window
     // the workgroups of a compute unit cover together should stay within a few hundred KiB per array.
     int32_t tpw = c->tiles_per_wg;
-    if (tpw <= 0) tpw = (KIND == K_PACK) ? std::max(1, 4096 / (TILE * (c->dtype == MGWFBP_F32 ? 4 : 2))) : 1;
+    if (tpw <= 0) tpw = (KIND == K_PACK && static_cast<int64_t>(count) * c->P > SMALL_PACK_TILES)
+                            ? std::max(1, 4096 / (TILE * (c->dtype == MGWFBP_F32 ? 4 : 2))) : 1;
     const int32_t units = (count + tpw - 1) / tpw;
     int grid = units;
     if (c->blocks_per_cu > 0 && c->n_cu > 0 && static_cast<int64_t>(c->n_cu) * c->blocks_per_cu < units)
         grid = c->n_cu * c->blocks_per_cu;
-    int8_t xcd = 0;
+    int16_t xcd = 0;
     if (c->xcd_contiguous && grid >= 64) {
         grid &= ~7;
         xcd = 1;
@@ -922,34 +1073,19 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
     pc.lds_bytes = lds_for_workgroups_per_cu(wgs);
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     const float inv_p = 1.0f / static_cast<float>(c->P);
-    // a clip cuts into the first and the last tile only
-    const bool clipped = span != nullptr && span->clipped;
-    const int16_t clip_lo = static_cast<int16_t>(clipped ? span->lo - static_cast<int64_t>(t0) * TILE : 0);
-    const int16_t clip_hi = static_cast<int16_t>(clipped ? span->hi - static_cast<int64_t>(t1 - 1) * TILE : TILE);
-    const int32_t S = static_cast<int32_t>(c->host.seg_layer.size());
-
-    if (c->dtype == MGWFBP_F32) {
-        Args<float> A{tiles,
-                      reinterpret_cast<const float* const*>(grad_ptrs),
-                      reinterpret_cast<float* const*>(merge_bufs), reduced, w_ptrs, v_ptrs,
-                      lr, mu, inv_p, c->host.L, c->P, S, t0, count, units, grid, static_cast<int16_t>(tpw), xcd, 0,
-                      clip_lo, clip_hi};
-        return launch_by_p<KIND, float>(A, grid, stream, pc);
-    }
-    if (c->dtype == MGWFBP_F16) {
-        Args<_Float16> A{tiles,
-                         reinterpret_cast<const _Float16* const*>(grad_ptrs),
-                         reinterpret_cast<_Float16* const*>(merge_bufs), reduced, w_ptrs, v_ptrs,
-                         lr, mu, inv_p, c->host.L, c->P, S, t0, count, units, grid, static_cast<int16_t>(tpw), xcd, 0,
-                         clip_lo, clip_hi};
-        return launch_by_p<KIND, _Float16>(A, grid, stream, pc);
-    }
-    Args<uint16_t> A{tiles,
-                     reinterpret_cast<const uint16_t* const*>(grad_ptrs),
-                     reinterpret_cast<uint16_t* const*>(merge_bufs), reduced, w_ptrs, v_ptrs,
-                     lr, mu, inv_p, c->host.L, c->P, S, t0, count, units, grid, static_cast<int16_t>(tpw), xcd, 0,
-                     clip_lo, clip_hi};
-    return launch_by_p<KIND, uint16_t>(A, grid, stream, pc);
+    // The few-segments form has no tile headers, so it serves neither the resident share of w and v, which they
+    // mark, nor the forms in which a workgroup goes on to tiles far from its first.
+    const bool may_be_few = grid == units && !xcd && !(updates(KIND) && c->resident_bytes > 0);
+    auto go = [&](auto grad) {
+        typedef decltype(grad) GradT;
+        const CallArgs<GradT> call{reinterpret_cast<const GradT* const*>(grad_ptrs), reinterpret_cast<GradT* const*>(merge_bufs),
+                                   reduced, w_ptrs, v_ptrs, lr, mu, inv_p, c->host.L, c->P, sp.t0, count,
+                                   static_cast<int16_t>(tpw), xcd};
+        return launch<KIND, GradT>(c, sp, tiles, call, units, grid, may_be_few, stream, pc);
+    };
+    if (c->dtype == MGWFBP_F32) return go(float{});
+    if (c->dtype == MGWFBP_F16) return go(_Float16{});
+    return go(uint16_t{});
 }
 
 // Per device: where that GPU's copy of `scratch` lives and whose tables it holds.
@@ -1065,23 +1201,19 @@ int mgwfbp_pack_tensors(mgwfbp_ctx* c, int32_t first_tensor, int32_t last_tensor
     if (c == nullptr || !c->on_device) return MGWFBP_EINVAL;
     const HostTables& h = c->host;
     if (last_tensor < 0 || first_tensor >= h.L || first_tensor < last_tensor) return MGWFBP_EINVAL;
-    // Tensors lie in the arena in arrival order, so the run first_tensor, ..., last_tensor occupies one
-    // arena interval (group padding inside it belongs to no tile's valid part and is skipped).
-    uint64_t lo = UINT64_MAX, hi = 0;
-    for (int32_t i = first_tensor; i >= last_tensor; --i) {
-        const size_t q = static_cast<size_t>(i);
-        if (h.tensor_n[q] == 0) continue;
-        const uint64_t start = h.group_base[static_cast<size_t>(h.tensor_group[q])] + h.tensor_off[q];
-        if (start < lo) lo = start;
-        if (start + h.tensor_n[q] > hi) hi = start + h.tensor_n[q];
-    }
-    if (hi <= lo) return MGWFBP_OK;                               // only empty tensors
+    // Tensors lie in the arena in arrival order, so the run first_tensor, ..., last_tensor is a run of segments and
+    // occupies one arena interval (group padding inside it belongs to no tile's valid part and is skipped).
+    const size_t last = static_cast<size_t>(last_tensor);
     Span s;
-    s.t0 = static_cast<int32_t>(lo / TILE);
-    s.t1 = static_cast<int32_t>((hi + TILE - 1) / TILE);
+    s.s0 = h.tensor_seg[static_cast<size_t>(first_tensor)];
+    s.s1 = h.tensor_seg[last] + (h.tensor_n[last] > 0 ? 1 : 0);
+    if (s.s1 <= s.s0) return MGWFBP_OK;                           // only empty tensors
+    const size_t end_layer = static_cast<size_t>(h.seg_layer[static_cast<size_t>(s.s1 - 1)]);
     s.clipped = true;
-    s.lo = static_cast<int64_t>(lo);
-    s.hi = static_cast<int64_t>(hi);
+    s.lo = static_cast<int64_t>(h.seg_off[static_cast<size_t>(s.s0)]);
+    s.hi = static_cast<int64_t>(h.seg_off[static_cast<size_t>(s.s1 - 1)] + h.tensor_n[end_layer]);
+    s.t0 = static_cast<int32_t>(s.lo / TILE);
+    s.t1 = static_cast<int32_t>((s.hi + TILE - 1) / TILE);
     return run<K_PACK>(c, 0, d_grad_ptrs, d_merge_bufs, nullptr, nullptr, nullptr, 0.f, 0.f, hip_stream, &s);
 }
 
@@ -1116,9 +1248,7 @@ int mgwfbp_group_pipeline_span(mgwfbp_ctx* c, int32_t group_first, int32_t group
                                void* hip_stream) {
     if (c == nullptr || !c->on_device) return MGWFBP_EINVAL;
     if (group_first < 0 || group_count < 0 || group_first > c->host.G - group_count) return MGWFBP_EINVAL;
-    Span s;                                   // consecutive groups own consecutive tiles
-    s.t0 = c->host.group_tile[static_cast<size_t>(group_first)];
-    s.t1 = c->host.group_tile[static_cast<size_t>(group_first + group_count)];
+    const Span s = span_of_groups(c->host, group_first, group_first + group_count);
     return run<K_PIPELINE>(c, 0, d_grad_ptrs, d_merge_bufs, d_reduced, d_w_ptrs, d_v_ptrs, lr, momentum,
                            hip_stream, &s);
 }
@@ -1211,9 +1341,7 @@ int mgwfbp_handler_replay(mgwfbp_ctx* c, const double* group_ready_s, double tim
         int32_t upto = next + 1;                  // everything that filled meanwhile goes into the same launch
         while (upto < G && time_scale * group_ready_s[upto] <= now &&
                (max_groups_per_launch == 0 || upto - next < max_groups_per_launch)) ++upto;
-        Span s;
-        s.t0 = c->host.group_tile[static_cast<size_t>(next)];
-        s.t1 = c->host.group_tile[static_cast<size_t>(upto)];
+        const Span s = span_of_groups(c->host, next, upto);
         rc = run<K_PIPELINE>(c, 0, d_grad_ptrs, d_merge_bufs, d_reduced, d_w_ptrs, d_v_ptrs, lr, momentum,
                              streams[j], &s);
         if (rc == MGWFBP_OK && throttle) rc = note(hipEventRecord(slot_done[slot], static_cast<hipStream_t>(streams[j])));

@@ -29,7 +29,9 @@ int mgwfbp_build_tables(const uint64_t* n_elems, int32_t L, const uint8_t* merge
         out.tensor_off.assign(static_cast<size_t>(L), 0);
         out.tensor_group.assign(static_cast<size_t>(L), 0);
         out.tensor_n.assign(n_elems, n_elems + L);
+        out.tensor_seg.assign(static_cast<size_t>(L), 0);
         out.group_tile.push_back(0);
+        out.group_seg.push_back(0);
         uint64_t next_tile = 0;                        // first free tile of the arena
         int32_t i = L - 1;
         while (i >= 0) {
@@ -41,6 +43,7 @@ int mgwfbp_build_tables(const uint64_t* n_elems, int32_t L, const uint8_t* merge
             for (;;) {
                 out.tensor_group[static_cast<size_t>(i)] = k;
                 out.tensor_off[static_cast<size_t>(i)] = fill;
+                out.tensor_seg[static_cast<size_t>(i)] = static_cast<int32_t>(out.seg_layer.size());
                 if (n_elems[i] > 0) {
                     out.seg_off.push_back(base + fill);
                     out.seg_n.push_back(static_cast<uint32_t>(std::min<uint64_t>(n_elems[i], 0xffffffffull)));
@@ -81,6 +84,7 @@ int mgwfbp_build_tables(const uint64_t* n_elems, int32_t L, const uint8_t* merge
             }
             next_tile += ntile;
             out.group_tile.push_back(static_cast<int32_t>(next_tile));
+            out.group_seg.push_back(static_cast<int32_t>(seg_end));
         }
         out.arena_elems = next_tile * TILE;
         out.seg_off.push_back(out.arena_elems);

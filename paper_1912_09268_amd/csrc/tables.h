@@ -43,10 +43,12 @@ struct HostTables {
     std::vector<uint64_t> tensor_off;     // [L] element offset inside the group's slice
     std::vector<int32_t> tensor_group;    // [L]
     std::vector<uint64_t> tensor_n;       // [L] element count
+    std::vector<int32_t> tensor_seg;      // [L] segments before it in arena order: its own, unless it is empty
     // per group (arrival order)
     std::vector<uint64_t> group_base;     // [G] arena element
     std::vector<uint64_t> group_elems;    // [G]
     std::vector<int32_t> group_tile;      // [G+1] first tile of each group
+    std::vector<int32_t> group_seg;       // [G+1] first segment of each group
     // per segment (arena order)
     std::vector<uint64_t> seg_off;        // [S+1] arena element of the segment start; seg_off[S] = arena_elems
     std::vector<uint32_t> seg_n;          // [S] elements, saturated at 2^32-1

@@ -505,6 +505,26 @@ def test_results_do_not_depend_on_the_small_launch_threshold(max_tiles):
         check_case(p, merged, mode, small_launch=max_tiles, label=f"small launch <= {max_tiles} tiles")
 
 
+@pytest.mark.parametrize("P,dtype", [(1, "f32"), (3, "bf16"), (8, "f32"), (4, "f16")])
+@pytest.mark.parametrize("mode", ["pipeline_per_group", "staged_per_group", "pipeline_spans", "direct_per_group_with_reduced"])
+def test_launches_over_few_segments(mode, P, dtype):
+    """Launches over at most eight segments carry them as arguments.  Groups of one tensor around the tile (256)
+    and the vector (4), of seven, eight and nine tensors whose ends fall on every place in a vector, and with an
+    empty tensor in between, so that both sides of the rule and all its edges occur."""
+    groups = [[1], [3], [4], [255], [256], [257], [1021], [5, 1, 250], [256, 256], [511, 1, 1], [1, 1, 1, 1, 1, 1, 1],
+              [2, 3, 5, 7, 11, 13, 200, 600], [64, 63, 62, 61, 6, 1000, 3, 513], [9, 8, 7, 6, 5, 4, 3, 2, 1], [100, 0, 300],
+              [0], [300000], [5000, 70003], [1] * 8, [255, 1], [1, 255, 0, 1], [2047, 2, 2, 2045]]
+    arrival = [n for g in groups for n in g]
+    merged = [m for g in groups for m in [1] * (len(g) - 1) + [0]]
+    rng = np.random.default_rng(11)
+    p = W.Profile("few", np.asarray(arrival[::-1], np.uint64), rng.uniform(1e-6, 1e-5, len(arrival)), 1e-4, 1e-9, P,
+                  dtype, 1.0)
+    check_case(p, merged[::-1], mode, misalign=3, label="few segments")
+    check_case(p, merged[::-1], mode, launch=(0, False, 3), label="few segments, three tiles per workgroup")
+    if mode == "staged_per_group":
+        _check_incremental(p, merged[::-1], lambda L: [1 + i % 10 for i in range(L)], misalign=5, label="runs of 1 to 10")
+
+
 # ------------------------------------------------------------------------------------------
 # the benchmark configurations at full size, in the launch configuration bench.py times
 # ------------------------------------------------------------------------------------------
