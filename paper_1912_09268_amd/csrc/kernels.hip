@@ -856,36 +856,63 @@ int create_common(mgwfbp_ctx** out, const uint64_t* n_elems, int32_t L, const ui
 
 // How a launch is paced (host side only).
 struct Pace {
-    size_t lds_bytes = 0;     // dynamic LDS per workgroup; unused by the kernel, it only bounds the workgroups per CU
+    int32_t wgs_per_cu = -1;  // workgroups that may share a compute unit; <= 0: no cap
     int step_vecs = 1;        // vectors per lane a fast tile is walked in: 1 or 2; 0 = burst (all at once)
 };
 
+// Dynamic LDS per workgroup that lets at most n workgroups share the 160 KiB of a compute unit.  A workgroup's
+// LDS (static + dynamic) is granted in blocks of 1280 bytes (a 128th of the compute unit's; seen in the cap
+// sweeps, where 12 and 13, 14 and 15, 16 and 17 behave alike); the total aimed at is the smallest multiple of
+// the block above 160 KiB / (n + 1), so n + 1 workgroups never fit, and n do wherever a multiple of the block
+// lies in (160 KiB / (n + 1), 160 KiB / n]: 32, 25, 21, 18, 16, 14, 12, 11, 10, 9, 8, ... are the caps that
+// exist, and a request in between gets the next lower one.  The request stays 64 bytes short of that total so
+// that padding of the static part cannot push it into the next block.  62 KiB keeps clear of the 64 KiB a launch may ask for without special arrangements (so n = 1 is
+// served as n = 2).  n <= 0 means no cap, and so does an n beyond what the waves of a compute unit allow anyway.
+size_t lds_for_workgroups_per_cu(int32_t n, size_t static_lds) {
+    constexpr int32_t MAX_WGS = 32 * 64 / BLOCK;         // 32 waves per compute unit
+    if (n <= 0 || n >= MAX_WGS) return 0;
+    if (n < 2) n = 2;
+    constexpr size_t CU_LDS = 160u << 10;
+    constexpr size_t GRAIN = 1280;
+    size_t total = (CU_LDS / static_cast<size_t>(n + 1) / GRAIN + 1) * GRAIN;
+    total = std::min<size_t>(total, 62u << 10);
+    if (total <= static_lds + 64 + GRAIN) return 0;
+    return total - static_lds - 64;
+}
+// LDS the kernels declare themselves: the table form for its general path (REDUCE needs less of it), the
+// few-segments form none.
+template <int KIND> constexpr size_t table_form_lds() {
+    return sizeof(int) * ((needs_owner(KIND) ? 2 * MAXSEG + 1 + BLOCK / 64 : 0) + TILE / VEC + 1);
+}
+
 template <int KIND, typename GradT, int PT>
 int launch_one(const FewArgs<GradT>& A, int grid, hipStream_t stream, const Pace& pc, int grid_y = 1) {
+    const size_t lds = lds_for_workgroups_per_cu(pc.wgs_per_cu, 0);
     if (pc.step_vecs <= 0)
-        hipLaunchKernelGGL((mgwfbp_few_kernel<KIND, GradT, PT, 0>), dim3(grid, grid_y), dim3(BLOCK), pc.lds_bytes, stream, A);
+        hipLaunchKernelGGL((mgwfbp_few_kernel<KIND, GradT, PT, 0>), dim3(grid, grid_y), dim3(BLOCK), lds, stream, A);
     else
-        hipLaunchKernelGGL((mgwfbp_few_kernel<KIND, GradT, PT, 1>), dim3(grid, grid_y), dim3(BLOCK), pc.lds_bytes, stream, A);
+        hipLaunchKernelGGL((mgwfbp_few_kernel<KIND, GradT, PT, 1>), dim3(grid, grid_y), dim3(BLOCK), lds, stream, A);
     return note(hipGetLastError());
 }
 
 template <int KIND, typename GradT, int PT>
 int launch_one(const Args<GradT>& A, int grid, hipStream_t stream, const Pace& pc, int grid_y = 1) {
+    const size_t lds = lds_for_workgroups_per_cu(pc.wgs_per_cu, table_form_lds<KIND>());
     bool launched = false;
     if (pc.step_vecs <= 0) {
-        hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, 0>), dim3(grid, grid_y), dim3(BLOCK), pc.lds_bytes,
+        hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, 0>), dim3(grid, grid_y), dim3(BLOCK), lds,
                            stream, A);
         launched = true;
     }
     if constexpr (TVECS % 2 == 0) {
         if (!launched && pc.step_vecs >= 2) {
-            hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, 2>), dim3(grid, grid_y), dim3(BLOCK), pc.lds_bytes,
+            hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, 2>), dim3(grid, grid_y), dim3(BLOCK), lds,
                                stream, A);
             launched = true;
         }
     }
     if (!launched)
-        hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, 1>), dim3(grid, grid_y), dim3(BLOCK), pc.lds_bytes,
+        hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, 1>), dim3(grid, grid_y), dim3(BLOCK), lds,
                            stream, A);
     return note(hipGetLastError());
 }
@@ -907,40 +934,38 @@ int launch_by_p(const ArgsT<GradT>& A, int grid, hipStream_t stream, const Pace&
     }
 }
 
-// Dynamic LDS per workgroup that lets at most n workgroups share the 160 KiB of a compute unit.  A workgroup's
-// LDS (static + dynamic) is granted in blocks of 1280 bytes (a 128th of the compute unit's; seen in the cap
-// sweeps, where 12 and 13, 14 and 15, 16 and 17 behave alike); the total aimed at is the smallest multiple of
-// the block above 160 KiB / (n + 1), so n + 1 workgroups never fit, and n do wherever a multiple of the block
-// lies in (160 KiB / (n + 1), 160 KiB / n]: 32, 25, 21, 18, 16, 14, 12, 11, 10, 9, 8, ... are the caps that
-// exist, and a request in between gets the next lower one.  The request stays 64 bytes short of that total so
-// that padding of the static part cannot push it into the next block.  62 KiB keeps clear of the 64 KiB a launch may ask for without special arrangements (so n = 1 is
-// served as n = 2).  n <= 0 means no cap, and so does an n beyond what the waves of a compute unit allow anyway.
-size_t lds_for_workgroups_per_cu(int32_t n) {
-    constexpr int32_t MAX_WGS = 32 * 64 / BLOCK;         // 32 waves per compute unit
-    if (n <= 0 || n >= MAX_WGS) return 0;
-    if (n < 2) n = 2;
-    constexpr size_t CU_LDS = 160u << 10;
-    constexpr size_t GRAIN = 1280;
-    constexpr size_t STATIC_LDS = sizeof(int) * (2 * MAXSEG + 1 + BLOCK / 64 + TILE / VEC + 1);
-    size_t total = (CU_LDS / static_cast<size_t>(n + 1) / GRAIN + 1) * GRAIN;
-    total = std::min<size_t>(total, 62u << 10);
-    if (total <= STATIC_LDS + 64 + GRAIN) return 0;
-    return total - STATIC_LDS - 64;
-}
-
-// Defaults measured with a cold memory-side cache on the DNN shapes (profiles/: pacing study).  With one
-// 16-byte load per lane in flight a wavefront has 1 KiB of a binary32 array under way (512 bytes of a 16-bit
-// one), so a cap of 16 wavefronts gives a compute unit 16 KiB; with 16-bit gradients every wave slot is needed
-// to get there, and the update alone (20 bytes per element, nothing per worker) runs best uncapped.
 int32_t default_step_vecs(int, int32_t) { return TVECS % 2 == 0 ? 2 : 1; }
-int32_t default_workgroups_per_cu(int kind, int32_t dtype) {
+
+// Default caps, measured on the ResNet-50 shape (25.6 M elements, cold) with every cap that exists, worker counts
+// 1, 2, 3, 4, 6, 8, 12, 16, 32 and both gradient widths; GB/s of the cap taken against its neighbours or "none".
+//   - What has to be found is the number of bytes a compute unit keeps under way.  A wavefront has N loads in
+//     flight, each 1 KiB of a binary32 array or 512 bytes of a 16-bit one: N = 1 in the pipeline, two workers' in
+//     the other kinds when P is not known at compile time, all P when it is (2, 4, 8, 16: nothing is stored between
+//     them, so the compiler issues them together).
+//   - With few workers a wavefront spends more of its life on the way to its first load (header, pointers) than
+//     loading, and more of them are needed: REDUCE, binary32, P = 1: 6158 uncapped against 4510 at 14, P = 3: 6278 /
+//     5303, P = 4: 6455 at 16 / 6153 uncapped, P = 8: 6562 at 14 / 6258 uncapped.
+//   - With many workers there are more arrays to switch between and a smaller window serves them better: pipeline,
+//     binary32, P = 4: 6317 at 18 / 6254 at 14, P = 8: 6299 at 14 / 6229 at 16, P = 12: 6260 / 6076, P = 32: 5899 / 5676.
+//   - A launch of a few rounds of the chip (256 compute units times the cap) should not end in a nearly empty one:
+//     below SHORT_LAUNCH_TILES the cap is 18 at least (pipeline, binary32, P = 8, one group of 4096 / 8192 / 16384
+//     tiles: 15.8 / 30.4 / 58.0 us at 18 against 19.4 / 32.3 / 58.0 us at 14).
+//   - 16-bit gradients need every wave slot (pipeline, P = 8: 5960 uncapped / 5528 at 16), but for REDUCE with all of
+//     8 or 16 workers' loads in flight (P = 16: 6381 at 16 / 6220 uncapped; P = 12, two at a time: 6512 / 5265).
+constexpr int32_t SHORT_LAUNCH_TILES = 16384;
+int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int32_t tiles) {
     const bool wide = dtype == MGWFBP_F32;
+    if (wide && tiles < SHORT_LAUNCH_TILES) {
+        const int32_t n = default_workgroups_per_cu(kind, dtype, P, SHORT_LAUNCH_TILES);
+        return n > 0 ? std::max(n, 18) : n;
+    }
     switch (kind) {
-        case K_REDUCE: return 14;
-        case K_UPDATE: return -1;
-        case K_PACK:
-        case K_REDUCE_UPDATE: return wide ? 14 : -1;
-        default: return wide ? 16 : -1;                  // pipeline, direct
+        case K_REDUCE: return wide ? (P < 4 ? -1 : P < 8 ? 16 : 14) : (P == 8 || P == 16 ? 16 : -1);
+        case K_UPDATE: return -1;                        // 20 bytes per element, nothing per worker
+        case K_PACK: return wide ? 14 : -1;
+        case K_REDUCE_UPDATE: return wide ? (P < 4 ? 25 : P < 8 ? 16 : 14) : -1;
+        case K_DIRECT: return wide ? (P < 4 ? 25 : P <= 8 ? 16 : 14) : -1;
+        default: return wide ? (P < 6 ? 18 : 14) : -1;   // pipeline
     }
 }
 
@@ -1069,8 +1094,8 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
     const bool burst = c->step_vecs < 0 || (c->step_vecs == 0 && c->burst_tiles > 0 && count <= c->burst_tiles);
     pc.step_vecs = burst ? 0 : (c->step_vecs > 0 ? c->step_vecs : default_step_vecs(KIND, c->dtype));
     const int32_t wgs = c->wg_per_cu != 0 ? c->wg_per_cu
-                                          : (burst ? -1 : default_workgroups_per_cu(KIND, c->dtype));
-    pc.lds_bytes = lds_for_workgroups_per_cu(wgs);
+                                          : (burst ? -1 : default_workgroups_per_cu(KIND, c->dtype, c->P, count));
+    pc.wgs_per_cu = wgs;
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     const float inv_p = 1.0f / static_cast<float>(c->P);
     // The few-segments form has no tile headers, so it serves neither the resident share of w and v, which they
