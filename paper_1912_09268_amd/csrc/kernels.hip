@@ -68,8 +68,8 @@
 #define MGWFBP_NT 3   // bit 0: non-temporal loads of gradients / merge / reduced, bit 1: non-temporal
                       // stores to merge / reduced, bit 2: non-temporal accesses to w and v
 #endif
-#ifndef MGWFBP_PACK_TILES
-#define MGWFBP_PACK_TILES 2       // consecutive full tiles of one tensor that PACK copies in one step
+#ifndef MGWFBP_JOIN_TILES
+#define MGWFBP_JOIN_TILES 2       // consecutive full tiles of one tensor that some kinds take in one step
 #endif
 #define MGWFBP_MAXSEG (2 * MGWFBP_BLOCK)   // segments per tile whose offsets are staged in LDS (two per lane)
 
@@ -87,7 +87,7 @@ constexpr int VEC = MGWFBP_VEC;
 constexpr int TVECS = MGWFBP_TILE_VECS;
 constexpr int TILE = MGWFBP_TILE_ELEMS;
 constexpr int MAXSEG = MGWFBP_MAXSEG;
-constexpr int PACK_TILES = MGWFBP_PACK_TILES;
+constexpr int JOIN = MGWFBP_JOIN_TILES;
 
 enum Kind { K_PACK = 0, K_REDUCE = 1, K_UPDATE = 2, K_REDUCE_UPDATE = 3, K_PIPELINE = 4, K_DIRECT = 5 };
 
@@ -106,10 +106,15 @@ typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint16_t u16x4 __attribute__((ext_vector_type(4), aligned(2)));   // bfloat16 bit patterns
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4), aligned(2)));   // IEEE binary16
 
+typedef uint16_t u16x8 __attribute__((ext_vector_type(8), aligned(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8), aligned(2)));
+
 template <typename T, int W> struct VecOf;
 template <> struct VecOf<float, 4> { typedef f32x4 type; };
 template <> struct VecOf<float, 1> { typedef float type; };
 template <> struct VecOf<uint16_t, 4> { typedef u16x4 type; };
+template <> struct VecOf<uint16_t, 8> { typedef u16x8 type; };
+template <> struct VecOf<_Float16, 8> { typedef f16x8 type; };
 template <> struct VecOf<uint16_t, 1> { typedef uint16_t type; };
 template <> struct VecOf<_Float16, 4> { typedef f16x4 type; };
 template <> struct VecOf<_Float16, 1> { typedef _Float16 type; };
@@ -259,6 +264,38 @@ template <typename T> struct WorkerPtrs<T, 0> {
 // keeps the compiler from moving the next group's loads above this group's arithmetic
 __device__ __forceinline__ void pace() { __builtin_amdgcn_sched_barrier(0); }
 
+// the last part of a paced step: v, then w
+template <int N, bool WVNT, typename GradT, typename FV>
+__device__ __forceinline__ void update_step(const CallArgs<GradT>& A, float* wp, float* vp, int64_t soff, int stride,
+                                            const FV* acc) {
+    constexpr int C = Lanes<FV>::n;
+    FV v[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = ld<WVNT, FV>(vp + soff + i * stride);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const float t1 = A.mu * comp(v[i], c);
+            setc(v[i], c, t1 + comp(acc[i], c));
+        }
+        st<WVNT, FV>(vp + soff + i * stride, v[i]);
+    }
+    pace();
+    FV w[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) w[i] = ld<WVNT, FV>(wp + soff + i * stride);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const float t2 = A.lr * comp(v[i], c);
+            setc(w[i], c, comp(w[i], c) - t2);
+        }
+        st<WVNT, FV>(wp + soff + i * stride, w[i]);
+    }
+}
+
 template <int KIND, typename GradT, int PT, int W, int N, bool WVNT, bool TOGETHER = false>
 __device__ __forceinline__ void paced_step(const CallArgs<GradT>& A, const WorkerPtrs<const GradT, PT>& src,
                                            const WorkerPtrs<GradT, PT>& mrg, float* wp, float* vp,
@@ -360,34 +397,9 @@ __device__ __forceinline__ void paced_step(const CallArgs<GradT>& A, const Worke
             st<WVNT, FV>(wp + soff + i * stride, w_early[i]);
         }
     } else if constexpr (updates(KIND)) {
-        FV v[N];
-#pragma unroll
-        for (int i = 0; i < N; ++i) v[i] = ld<WVNT, FV>(vp + soff + i * stride);
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-#pragma unroll
-            for (int c = 0; c < C; ++c) {
-                const float t1 = A.mu * comp(v[i], c);
-                setc(v[i], c, t1 + comp(acc[i], c));
-            }
-            st<WVNT, FV>(vp + soff + i * stride, v[i]);
-        }
-        pace();
-        FV w[N];
-#pragma unroll
-        for (int i = 0; i < N; ++i) w[i] = ld<WVNT, FV>(wp + soff + i * stride);
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-#pragma unroll
-            for (int c = 0; c < C; ++c) {
-                const float t2 = A.lr * comp(v[i], c);
-                setc(w[i], c, comp(w[i], c) - t2);
-            }
-            st<WVNT, FV>(wp + soff + i * stride, w[i]);
-        }
+        update_step<N, WVNT>(A, wp, vp, soff, stride, acc);
     }
 }
-
 // one vector or element of the general path
 template <int KIND, typename GradT, int PT, int W>
 __device__ __forceinline__ void do_one(const CallArgs<GradT>& A, const WorkerPtrs<GradT, PT>& mrg,
@@ -436,6 +448,69 @@ __device__ __forceinline__ void fast_chunk(const CallArgs<GradT>& A, const Worke
                                                           apos + static_cast<int64_t>(u) * STEP, STEP);
             pace();
         }
+    }
+}
+
+// Kinds whose wavefronts have too little under way with one tile take JOIN full tiles of one tensor in one step:
+// PACK, a plain copy, and the pipeline on 16-bit gradients, where a worker's share of a tile is 512 bytes.
+template <int KIND, typename GradT> constexpr bool joins() {
+    return KIND == K_PACK || (KIND == K_PIPELINE && sizeof(GradT) == 2);
+}
+constexpr int WIDE = 8;               // 16-bit gradients per lane in a joined pipeline step: 16 bytes
+constexpr int JOINED = JOIN * TILE;   // elements of a joined step
+template <int KIND, typename GradT> constexpr int joined_floats() {    // LDS of a joined step
+    return KIND == K_PIPELINE && sizeof(GradT) == 2 ? JOINED : 0;
+}
+
+template <int KIND, typename GradT, int PT>
+__device__ __forceinline__ void joined_tiles(const CallArgs<GradT>& A, const WorkerPtrs<GradT, PT>& mrg, int layer,
+                                             int64_t tensor_off, int64_t tile_base, float* s_sums) {
+    WorkerPtrs<const GradT, PT> src;
+    src.fetch(A.grad_ptrs, A.L, layer, worker_base<KIND>());
+    const int lane_elem = static_cast<int>(threadIdx.x) * VEC;
+    if constexpr (KIND == K_PACK) {
+        paced_step<KIND, GradT, PT, VEC, JOIN * TVECS, true>(A, src, mrg, nullptr, nullptr, tensor_off + lane_elem,
+                                                             tile_base + lane_elem, BLOCK * VEC);
+    } else {
+        // One worker at a time as in paced_step, with 16 bytes per lane, 8 consecutive elements: a worker's share
+        // is the 1 KiB it is with binary32.  The sums then change hands through LDS, so that the binary32 arrays,
+        // too, are accessed with consecutive 16 bytes per lane.
+        static_assert(JOINED == BLOCK * WIDE && BLOCK == 64, "one wavefront, 16 bytes per lane");
+        typedef typename VecOf<GradT, WIDE>::type GV;
+        constexpr int N = JOINED / (BLOCK * VEC);
+        float* wp = ro(A.w_ptrs)[layer];
+        float* vp = ro(A.v_ptrs)[layer];
+        const int wide_elem = static_cast<int>(threadIdx.x) * WIDE;
+        float sum[WIDE];
+        auto worker = [&](int w) {
+            const GV g = ld<NT_LD, GV>(src.get(w) + tensor_off + wide_elem);
+            pace();
+            st<NT_ST, GV>(mrg.get(w) + tile_base + wide_elem, g);
+#pragma unroll
+            for (int e = 0; e < WIDE; ++e) {
+                const float x = widen(static_cast<GradT>(g[e]));
+                sum[e] = w == 0 ? x : sum[e] + x;
+            }
+            pace();
+        };
+        if constexpr (PT > 0) {
+#pragma unroll
+            for (int w = 0; w < PT; ++w) worker(w);
+        } else {
+            for (int w = 0; w < A.P; ++w) worker(w);
+        }
+        __syncthreads();                       // the previous step's readers are done with LDS
+#pragma unroll
+        for (int e = 0; e < WIDE; ++e) s_sums[wide_elem + e] = sum[e] * A.inv_p;
+        __syncthreads();
+        f32x4 acc[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc[i] = *reinterpret_cast<const f32x4*>(s_sums + lane_elem + i * BLOCK * VEC);
+        if (A.reduced != nullptr) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) st<NT_ST, f32x4>(A.reduced + tile_base + lane_elem + i * BLOCK * VEC, acc[i]);
+        }
+        update_step<N, true>(A, wp, vp, tensor_off + lane_elem, BLOCK * VEC, acc);
     }
 }
 
@@ -568,6 +643,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_stream_kernel(const Args<
     __shared__ int s_wave[BLOCK / 64];
     __shared__ int s_ragged[TILE / VEC];
     __shared__ int s_nragged;
+    __shared__ __align__(16) float s_sums[joined_floats<KIND, GradT>() + 4];
 
     WorkerPtrs<GradT, PT> mrg;
     if constexpr (reads_merge(KIND) || writes_merge(KIND)) mrg.fetch(A.merge_bufs, 1, 0, worker_base<KIND>());
@@ -603,24 +679,20 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_stream_kernel(const Args<
                 continue;
             }
             // A full tile inside one tensor.
-            if constexpr (KIND == K_PACK && PACK_TILES > 1) {
-                // Pack is a plain copy and wants more bytes in flight per lane than one tile holds: when the next
-                // tiles of this workgroup's share are full tiles of the same tensor too, they are copied together.
+            if constexpr (joins<KIND, GradT>() && STEPV != 0) {
                 // (A clip cuts into the first and the last tile only.)
-                if (t + PACK_TILES <= t_end) {
-                    bool same = t + PACK_TILES < A.tile_count || A.clip_hi == TILE;
+                if (t + JOIN <= t_end) {
+                    bool same = t + JOIN < A.tile_count || A.clip_hi == TILE;
+                    int flags = h.flags;
 #pragma unroll
-                    for (int k = 1; k < PACK_TILES; ++k) {
+                    for (int k = 1; k < JOIN; ++k) {
                         const TileHdr hk = load_header(A.tiles + tile + k);
                         same = same && hk.valid == TILE && hk.nseg == 1 && hk.layer0 == h.layer0;
+                        flags |= hk.flags;
                     }
-                    if (same) {
-                        WorkerPtrs<const GradT, PT> src;
-                        src.fetch(A.grad_ptrs, A.L, h.layer0, worker_base<KIND>());
-                        const int lane_elem = static_cast<int>(threadIdx.x) * VEC;
-                        paced_step<KIND, GradT, PT, VEC, PACK_TILES * TVECS, true>(
-                            A, src, mrg, nullptr, nullptr, -h.first_start + lane_elem, tile_base + lane_elem, BLOCK * VEC);
-                        t += PACK_TILES - 1;
+                    if (same && (!updates(KIND) || !(flags & 1))) {
+                        joined_tiles<KIND, GradT, PT>(A, mrg, h.layer0, -h.first_start, tile_base, s_sums);
+                        t += JOIN - 1;
                         continue;
                     }
                 }
@@ -676,6 +748,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_few_kernel(const FewArgs<
     static_assert(BLOCK == 64 && TVECS == 1, "a tile is one vector per lane of one wavefront");
     WorkerPtrs<GradT, PT> mrg;
     if constexpr (reads_merge(KIND) || writes_merge(KIND)) mrg.fetch(A.merge_bufs, 1, 0, worker_base<KIND>());
+    __shared__ __align__(16) float s_sums[joined_floats<KIND, GradT>() + 4];
     const int lane = threadIdx.x;
     const int64_t arena = static_cast<int64_t>(A.tile_first) * TILE;
     const int t_end = min((static_cast<int>(blockIdx.x) + 1) * A.tiles_per_wg, A.tile_count);
@@ -683,13 +756,10 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_few_kernel(const FewArgs<
         const int b = t * TILE;
         const FewSeg s = few_owner(A, b);                                  // uniform
         if (s.start <= b && b + TILE <= s.end) {                           // a full tile inside one segment
-            if constexpr (KIND == K_PACK && PACK_TILES > 1) {
-                if (t + PACK_TILES <= t_end && b + PACK_TILES * TILE <= s.end) {
-                    WorkerPtrs<const GradT, PT> src;
-                    src.fetch(A.grad_ptrs, A.L, A.layer_hi - s.j, worker_base<KIND>());
-                    paced_step<KIND, GradT, PT, VEC, PACK_TILES, true>(A, src, mrg, nullptr, nullptr, b - s.start + lane * VEC,
-                                                                       arena + b + lane * VEC, TILE);
-                    t += PACK_TILES - 1;
+            if constexpr (joins<KIND, GradT>() && STEPV != 0) {
+                if (t + JOIN <= t_end && b + JOIN * TILE <= s.end) {
+                    joined_tiles<KIND, GradT, PT>(A, mrg, A.layer_hi - s.j, b - s.start, arena + b, s_sums);
+                    t += JOIN - 1;
                     continue;
                 }
             }
@@ -879,15 +949,16 @@ size_t lds_for_workgroups_per_cu(int32_t n, size_t static_lds) {
     if (total <= static_lds + 64 + GRAIN) return 0;
     return total - static_lds - 64;
 }
-// LDS the kernels declare themselves: the table form for its general path (REDUCE needs less of it), the
-// few-segments form none.
-template <int KIND> constexpr size_t table_form_lds() {
-    return sizeof(int) * ((needs_owner(KIND) ? 2 * MAXSEG + 1 + BLOCK / 64 : 0) + TILE / VEC + 1);
+// LDS the kernels declare themselves: the table form for its general path (REDUCE needs less of it), both forms for
+// the sums of joined steps.
+template <int KIND, typename GradT> constexpr size_t few_form_lds() { return sizeof(float) * joined_floats<KIND, GradT>(); }
+template <int KIND, typename GradT> constexpr size_t table_form_lds() {
+    return sizeof(int) * ((needs_owner(KIND) ? 2 * MAXSEG + 1 + BLOCK / 64 : 0) + TILE / VEC + 1) + few_form_lds<KIND, GradT>();
 }
 
 template <int KIND, typename GradT, int PT>
 int launch_one(const FewArgs<GradT>& A, int grid, hipStream_t stream, const Pace& pc, int grid_y = 1) {
-    const size_t lds = lds_for_workgroups_per_cu(pc.wgs_per_cu, 0);
+    const size_t lds = lds_for_workgroups_per_cu(pc.wgs_per_cu, few_form_lds<KIND, GradT>());
     if (pc.step_vecs <= 0)
         hipLaunchKernelGGL((mgwfbp_few_kernel<KIND, GradT, PT, 0>), dim3(grid, grid_y), dim3(BLOCK), lds, stream, A);
     else
@@ -897,7 +968,7 @@ int launch_one(const FewArgs<GradT>& A, int grid, hipStream_t stream, const Pace
 
 template <int KIND, typename GradT, int PT>
 int launch_one(const Args<GradT>& A, int grid, hipStream_t stream, const Pace& pc, int grid_y = 1) {
-    const size_t lds = lds_for_workgroups_per_cu(pc.wgs_per_cu, table_form_lds<KIND>());
+    const size_t lds = lds_for_workgroups_per_cu(pc.wgs_per_cu, table_form_lds<KIND, GradT>());
     bool launched = false;
     if (pc.step_vecs <= 0) {
         hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, 0>), dim3(grid, grid_y), dim3(BLOCK), lds,
@@ -950,9 +1021,21 @@ int32_t default_step_vecs(int, int32_t) { return TVECS % 2 == 0 ? 2 : 1; }
 //   - A launch of a few rounds of the chip (256 compute units times the cap) should not end in a nearly empty one:
 //     below SHORT_LAUNCH_TILES the cap is 18 at least (pipeline, binary32, P = 8, one group of 4096 / 8192 / 16384
 //     tiles: 15.8 / 30.4 / 58.0 us at 18 against 19.4 / 32.3 / 58.0 us at 14).
-//   - 16-bit gradients need every wave slot (pipeline, P = 8: 5960 uncapped / 5528 at 16), but for REDUCE with all of
-//     8 or 16 workers' loads in flight (P = 16: 6381 at 16 / 6220 uncapped; P = 12, two at a time: 6512 / 5265).
+//   - 16-bit gradients need every wave slot (direct, P = 8: 6559 uncapped / 5729 at 16), but for REDUCE with all of
+//     8 or 16 workers' loads in flight (P = 16: 6381 at 16 / 6220 uncapped; P = 12, two at a time: 6512 / 5265) and
+//     for the pipeline's joined steps, which have 1 KiB under way like binary32 (P = 8: 6164 at 14 / 5886 uncapped;
+//     transformer shape, 335 M elements, where the ends of the launch weigh less: 6232 at 12 / 6088 at 14).
 constexpr int32_t SHORT_LAUNCH_TILES = 16384;
+constexpr int32_t LONG_LAUNCH_TILES = 262144;
+
+// Whether a workgroup of the pipeline takes JOIN tiles in one step (see joined_tiles).  GB/s at 16-bit gradients,
+// ResNet-50 shape, joined at its best cap against single tiles uncapped: P = 1: 6250 / 6327, 2: 6221 / 6231,
+// 3: 6194 / 6127, 4: 6175 / 6038, 8: 6164 / 5881, 16: 6080 / 5737, 32: 5675 / 5554; with one or two workers the
+// binary32 arrays are most of the traffic.  A short launch needs its tiles spread over the chip.
+bool joined_pipeline(int32_t dtype, int32_t P, int32_t tiles) {
+    return dtype != MGWFBP_F32 && P >= 3 && tiles >= SHORT_LAUNCH_TILES;
+}
+
 int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int32_t tiles) {
     const bool wide = dtype == MGWFBP_F32;
     if (wide && tiles < SHORT_LAUNCH_TILES) {
@@ -965,7 +1048,9 @@ int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int32_t ti
         case K_PACK: return wide ? 14 : -1;
         case K_REDUCE_UPDATE: return wide ? (P < 4 ? 25 : P < 8 ? 16 : 14) : -1;
         case K_DIRECT: return wide ? (P < 4 ? 25 : P <= 8 ? 16 : 14) : -1;
-        default: return wide ? (P < 6 ? 18 : 14) : -1;   // pipeline
+        default:                                         // pipeline
+            if (wide) return P < 6 ? 18 : 14;
+            return !joined_pipeline(dtype, P, tiles) ? -1 : tiles < LONG_LAUNCH_TILES ? 14 : 12;
     }
 }
 
@@ -1075,8 +1160,13 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
     // takes one tile per workgroup.  More only stretches the set of bytes the chip has in flight: the window
     // the workgroups of a compute unit cover together should stay within a few hundred KiB per array.
     int32_t tpw = c->tiles_per_wg;
-    if (tpw <= 0) tpw = (KIND == K_PACK && static_cast<int64_t>(count) * c->P > SMALL_PACK_TILES)
-                            ? std::max(1, 4096 / (TILE * (c->dtype == MGWFBP_F32 ? 4 : 2))) : 1;
+    if (tpw <= 0) {
+        tpw = 1;
+        if (KIND == K_PACK && static_cast<int64_t>(count) * c->P > SMALL_PACK_TILES)
+            tpw = std::max(1, 4096 / (TILE * (c->dtype == MGWFBP_F32 ? 4 : 2)));
+        else if (KIND == K_PIPELINE && joined_pipeline(c->dtype, c->P, count))
+            tpw = JOIN;
+    }
     const int32_t units = (count + tpw - 1) / tpw;
     int grid = units;
     if (c->blocks_per_cu > 0 && c->n_cu > 0 && static_cast<int64_t>(c->n_cu) * c->blocks_per_cu < units)

@@ -525,6 +525,23 @@ def test_launches_over_few_segments(mode, P, dtype):
         _check_incremental(p, merged[::-1], lambda L: [1 + i % 10 for i in range(L)], misalign=5, label="runs of 1 to 10")
 
 
+@pytest.mark.parametrize("P,dtype", [(2, "bf16"), (3, "f16"), (8, "bf16"), (16, "f16")])
+def test_sixteen_bit_pipeline_takes_tiles_in_pairs(P, dtype):
+    """Long 16-bit pipeline launches take two full tiles (512 elements) of one tensor in one step.  Tensors that end
+    one tile, one element and one vector before and after a pair's end, in groups that start on even and on odd
+    tiles, with sources on every 2-byte offset; two and three tiles per workgroup force the pairing at any length."""
+    sizes = [512, 511, 513, 256, 1024, 1028, 767, 5 * 512 + 256, 3, 512 * 9 + 4, 255, 70001, 1 << 22, 777, 513, 1 << 20]
+    merged = [0, 1, 1, 0, 0, 1, 0, 1, 1, 0, 1, 0, 0, 1, 0, 0]
+    rng = np.random.default_rng(12)
+    p = W.Profile("pairs", np.asarray(sizes, np.uint64), rng.uniform(1e-6, 1e-5, len(sizes)), 1e-4, 1e-9, P, dtype, 1.0)
+    check_case(p, merged, "pipeline", misalign=3, label="long enough to pair")
+    small = W.Profile("pairs", np.asarray(sizes[:12], np.uint64), p.t_backward[:12], 1e-4, 1e-9, P, dtype, 1.0)
+    for tiles in (2, 3):
+        for mode in ("pipeline", "pipeline_no_reduced", "pipeline_per_group"):
+            check_case(small, merged[:12], mode, misalign=3, launch=(0, False, tiles), small_launch=0, label=f"{tiles} tiles")
+    check_case(small, merged[:12], "pipeline", launch=(1, True, 2), small_launch=0, resident=1 << 17, label="resident share")
+
+
 # ------------------------------------------------------------------------------------------
 # the benchmark configurations at full size, in the launch configuration bench.py times
 # ------------------------------------------------------------------------------------------
