@@ -821,7 +821,7 @@ struct mgwfbp_ctx {
     uint64_t resident_bytes = 0;      // budget of w + v bytes kept cacheable
     uint64_t serial = 0;              // changes whenever the tables change; never reused within a process
     // device copies
-    unsigned char* d_tables = nullptr;   // one block, see table_parts()
+    unsigned char* d_tables = nullptr;   // the segment tables and the tile headers, one block
     TileHdr* d_tiles = nullptr;          // the tile headers in it
 };
 
@@ -852,39 +852,20 @@ void mark_resident_tiles(HostTables& h, uint64_t budget) {
     }
 }
 
-constexpr size_t round256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
-
-// The four tables as they lie in a device block (see Args): the segment tables below the tile headers, which start
-// on a multiple of 256 bytes.
-struct TableParts {
-    struct { size_t off, bytes; const void* src; } part[4];
-    size_t tiles_at, total;
-};
-TableParts table_parts(const HostTables& h) {
-    const size_t b_tiles = h.tiles.size() * sizeof(TileHdr), b_off = h.seg_off.size() * sizeof(uint64_t);
-    const size_t b_n = h.seg_n.size() * sizeof(uint32_t), b_layer = h.seg_layer.size() * sizeof(int32_t);
-    const size_t at = round256(b_layer + b_n + b_off);
-    return {{{at, b_tiles, h.tiles.data()},
-             {at - b_off, b_off, h.seg_off.data()},
-             {at - b_off - b_n, b_n, h.seg_n.data()},
-             {at - b_off - b_n - b_layer, b_layer, h.seg_layer.data()}}, at, at + b_tiles};
-}
-
+// Both parts of the block start on multiples of 256 bytes.
 int upload_tables(mgwfbp_ctx* c) {
-    const TableParts t = table_parts(c->host);
-    hipError_t e = hipMalloc(reinterpret_cast<void**>(&c->d_tables), t.total);
+    const std::vector<unsigned char>& segs = c->host.seg_block;
+    const size_t b_tiles = c->host.tiles.size() * sizeof(TileHdr);
+    hipError_t e = hipMalloc(reinterpret_cast<void**>(&c->d_tables), segs.size() + b_tiles);
     if (e != hipSuccess) {
         c->d_tables = nullptr;
         g_last_hip_error = static_cast<int>(e);
         return e == hipErrorOutOfMemory ? MGWFBP_ENOMEM : MGWFBP_EHIP;
     }
-    c->d_tiles = reinterpret_cast<TileHdr*>(c->d_tables + t.tiles_at);
-    for (const auto& p : t.part) {
-        if (p.bytes == 0) continue;
-        const int rc = note(hipMemcpy(c->d_tables + p.off, p.src, p.bytes, hipMemcpyHostToDevice));
-        if (rc != MGWFBP_OK) return rc;
-    }
-    return MGWFBP_OK;
+    c->d_tiles = reinterpret_cast<TileHdr*>(c->d_tables + segs.size());
+    int rc = note(hipMemcpy(c->d_tables, segs.data(), segs.size(), hipMemcpyHostToDevice));
+    if (rc == MGWFBP_OK && b_tiles > 0) rc = note(hipMemcpy(c->d_tiles, c->host.tiles.data(), b_tiles, hipMemcpyHostToDevice));
+    return rc;
 }
 
 int create_common(mgwfbp_ctx** out, const uint64_t* n_elems, int32_t L, const uint8_t* merged, int32_t P,
@@ -1374,9 +1355,10 @@ int mgwfbp_group_pipeline_static(mgwfbp_ctx* c, int32_t group, const void* const
     if (c == nullptr) return MGWFBP_EINVAL;
     const HostTables& h = c->host;
     if (group < -1 || group >= h.G) return MGWFBP_EINVAL;
-    const TableParts parts = table_parts(h);
-    size_t needed = 0;                            // the documented limit: every table rounded up by itself
-    for (const auto& part : parts.part) needed += round256(part.bytes);
+    auto round256 = [](size_t x) { return (x + 255) & ~static_cast<size_t>(255); };
+    const size_t b_tiles = h.tiles.size() * sizeof(TileHdr);
+    const size_t needed = round256(b_tiles) + round256(h.seg_n.size() * sizeof(uint32_t)) +    // the documented limit
+                          round256(h.seg_layer.size() * sizeof(int32_t)) + round256(h.seg_off.size() * sizeof(uint64_t));
     if (needed > MGWFBP_STATIC_TABLE_MAX_BYTES) return MGWFBP_ECAPACITY;
     if (h.tiles.empty()) return MGWFBP_OK;
 
@@ -1397,17 +1379,16 @@ int mgwfbp_group_pipeline_static(mgwfbp_ctx* c, int32_t group, const void* const
     if (!(slot.loaded && slot.serial == c->serial && slot.stream == stream)) {
         // The array still holds the previous call's tables: overwrite them, in stream order, with this model's.
         slot.loaded = false;
-        for (const auto& part : parts.part) {
-            if (part.bytes == 0) continue;
-            rc = note(hipMemcpyAsync(slot.ptr + part.off, part.src, part.bytes, hipMemcpyHostToDevice, stream));
-            if (rc != MGWFBP_OK) return rc;
-        }
+        rc = note(hipMemcpyAsync(slot.ptr, h.seg_block.data(), h.seg_block.size(), hipMemcpyHostToDevice, stream));
+        if (rc != MGWFBP_OK) return rc;
+        rc = note(hipMemcpyAsync(slot.ptr + h.seg_block.size(), h.tiles.data(), b_tiles, hipMemcpyHostToDevice, stream));
+        if (rc != MGWFBP_OK) return rc;
         slot.loaded = true;
         slot.serial = c->serial;
         slot.stream = stream;
     }
     return run<K_PIPELINE>(c, group, d_grad_ptrs, d_merge_bufs, d_reduced, d_w_ptrs, d_v_ptrs, lr, momentum,
-                           hip_stream, nullptr, reinterpret_cast<const TileHdr*>(slot.ptr + parts.tiles_at));
+                           hip_stream, nullptr, reinterpret_cast<const TileHdr*>(slot.ptr + h.seg_block.size()));
 }
 
 int mgwfbp_handler_replay(mgwfbp_ctx* c, const double* group_ready_s, double time_scale,

@@ -6,6 +6,7 @@
 // end to end in arrival order.
 #include <algorithm>
 #include <cstdint>
+#include <cstring>
 #include <limits>
 
 #include "mgwfbp.h"
@@ -88,6 +89,15 @@ int mgwfbp_build_tables(const uint64_t* n_elems, int32_t L, const uint8_t* merge
         }
         out.arena_elems = next_tile * TILE;
         out.seg_off.push_back(out.arena_elems);
+
+        const size_t S = out.seg_layer.size();
+        out.seg_block.assign((16 * S + 8 + 255) / 256 * 256, 0);
+        unsigned char* at = out.seg_block.data() + out.seg_block.size();
+        std::memcpy(at -= 8 * (S + 1), out.seg_off.data(), 8 * (S + 1));
+        if (S > 0) {
+            std::memcpy(at -= 4 * S, out.seg_n.data(), 4 * S);
+            std::memcpy(at -= 4 * S, out.seg_layer.data(), 4 * S);
+        }
     } catch (const std::bad_alloc&) {
         return MGWFBP_ENOMEM;
     }

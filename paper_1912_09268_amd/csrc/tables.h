@@ -53,6 +53,9 @@ struct HostTables {
     std::vector<uint64_t> seg_off;        // [S+1] arena element of the segment start; seg_off[S] = arena_elems
     std::vector<uint32_t> seg_n;          // [S] elements, saturated at 2^32-1
     std::vector<int32_t> seg_layer;       // [S] tensor index
+    // seg_layer, seg_n and seg_off as the kernels find them: right below the tile headers, in a block of a multiple
+    // of 256 bytes that the tables end with
+    std::vector<unsigned char> seg_block;
     // per tile
     std::vector<TileHdr> tiles;           // [T]
 };
