@@ -181,7 +181,8 @@ template <typename GradT> struct CallArgs {
     int32_t L, P;
     int32_t tile_first, tile_count;
     int16_t tiles_per_wg;            // consecutive tiles one workgroup handles per turn, >= 1
-    int16_t xcd_contiguous;
+    int8_t xcd_contiguous;
+    int8_t run_log2;                 // a die's turn is 2^run_log2 consecutive units, see unit_of()
 };
 template <typename GradT> struct Args : CallArgs<GradT> {      // table form: what a tile holds is in the tables
     const TileHdr* tiles;            // the segment tables lie right below, see seg_off() and its neighbours
@@ -200,6 +201,23 @@ template <typename GradT> struct FewArgs : CallArgs<GradT> {   // few-segments f
 };
 static_assert(sizeof(Args<float>) <= 112 && sizeof(FewArgs<float>) <= 112,
               "a larger block of arguments makes every launch 0.9 us dearer");
+
+// Unit a workgroup starts with.  Workgroups are dealt round-robin to the 8 dies, each with an L2 of its own, so in
+// plain order neighbouring tiles belong to different dies.  Where tiles do not start on the 128-byte lines of the
+// tensors, two dies then fetch the line they share and each writes back its part of it.  Runs of a few consecutive
+// units per die (within every 8 runs of the dispatch order, so that the chip still moves through one window) let
+// all but one boundary of a run meet in one L2.  GB/s, 300 tensors of odd sizes around 100,000 elements as views of
+// flat buffers, 8 workers, runs of 1 / 4 / 8 / 16: direct bf16 5144 / 5716 / 5885 / 5937, unpack_update 5514 / 6042 /
+// 6085 / 6185, pipeline f32 5613 / 5888 / 5748 / 5664; on the ResNet-50 shape, nearly all of whose tiles start on lines:
+// pipeline f32 6224 / 6131 / 6005 / 5835, unpack_update 6468 / 6326 / 6344 / 6221.
+template <typename GradT> __device__ __forceinline__ int unit_of(const CallArgs<GradT>& A) {
+    const int b = static_cast<int>(blockIdx.x);
+    const int r = A.run_log2;
+    const int within = b & ((8 << r) - 1);
+    const int last = b - within + (8 << r) - 1;           // last unit of this set of eight runs
+    if (static_cast<int64_t>(last) * A.tiles_per_wg >= A.tile_count) return b;      // the launch ends before it
+    return b - within + ((within & 7) << r) + (within >> 3);
+}
 
 // The tables of one model lie in one block: seg_layer[S], seg_n[S] and seg_off[S + 1], ending where the tile headers
 // begin, so that the address of the headers and S lead to all of them.
@@ -661,7 +679,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_stream_kernel(const Args<
         u_end = min(n_units, (die + 1) * per_die);
         u_step = A.turn >> 3;
     } else {
-        u_begin = blockIdx.x;
+        u_begin = unit_of(A);
         u_end = n_units;
         u_step = A.turn;
     }
@@ -751,8 +769,10 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_few_kernel(const FewArgs<
     __shared__ __align__(16) float s_sums[joined_floats<KIND, GradT>() + 4];
     const int lane = threadIdx.x;
     const int64_t arena = static_cast<int64_t>(A.tile_first) * TILE;
-    const int t_end = min((static_cast<int>(blockIdx.x) + 1) * A.tiles_per_wg, A.tile_count);
-    for (int t = blockIdx.x * A.tiles_per_wg; t < t_end; ++t) {
+    const int K = A.tiles_per_wg;
+    const int u = unit_of(A);
+    const int t_end = min((u + 1) * K, A.tile_count);
+    for (int t = u * K; t < t_end; ++t) {
         const int b = t * TILE;
         const FewSeg s = few_owner(A, b);                                  // uniform
         if (s.start <= b && b + TILE <= s.end) {                           // a full tile inside one segment
@@ -810,6 +830,7 @@ struct mgwfbp_ctx {
     int32_t P = 0;
     int32_t dtype = 0;
     bool on_device = false;
+    bool off_lines = false;           // a good part of the tiles do not start on the lines of their tensors
     int device = -1;
     int n_cu = 0;
     int32_t blocks_per_cu = 0;
@@ -852,6 +873,28 @@ void mark_resident_tiles(HostTables& h, uint64_t budget) {
     }
 }
 
+// Whether tiles mostly start inside the 128-byte lines (32 binary32 elements) of their tensors: in a tensor that does
+// not begin on a multiple of 32 arena elements, and, as views of one flat buffer, in one whose neighbours' sizes are
+// no such multiples.  Both show in the sizes, weighted by what they hold.
+bool starts_off_lines(const HostTables& h) {
+    uint64_t off = 0, all = 0;
+    for (size_t i = 0; i < h.tensor_n.size(); ++i) {
+        all += h.tensor_n[i];
+        if ((h.tensor_n[i] | h.tensor_off[i]) % 32 != 0) off += h.tensor_n[i];
+    }
+    return off > all / 4;
+}
+
+// Units per die and turn (log2), where tiles start inside lines (see unit_of): the kinds that write w and v gain,
+// the pipeline, which writes whole lines of P arenas as well, less; PACK and REDUCE write whole lines only.
+int8_t run_log2_of(int kind) {
+    switch (kind) {
+        case K_PIPELINE: return 2;
+        case K_UPDATE: case K_REDUCE_UPDATE: case K_DIRECT: return 3;
+        default: return 0;
+    }
+}
+
 // Both parts of the block start on multiples of 256 bytes.
 int upload_tables(mgwfbp_ctx* c) {
     const std::vector<unsigned char>& segs = c->host.seg_block;
@@ -887,6 +930,7 @@ int create_common(mgwfbp_ctx** out, const uint64_t* n_elems, int32_t L, const ui
     c->resident_bytes = DEFAULT_RESIDENT_BYTES;
     c->serial = g_next_serial.fetch_add(1);
     mark_resident_tiles(c->host, c->resident_bytes);
+    c->off_lines = starts_off_lines(c->host);
     if (device) {
         hipDeviceProp_t prop;
         rc = note(hipGetDevice(&c->device));
@@ -1152,7 +1196,7 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
     int grid = units;
     if (c->blocks_per_cu > 0 && c->n_cu > 0 && static_cast<int64_t>(c->n_cu) * c->blocks_per_cu < units)
         grid = c->n_cu * c->blocks_per_cu;
-    int16_t xcd = 0;
+    int8_t xcd = 0;
     if (c->xcd_contiguous && grid >= 64) {
         grid &= ~7;
         xcd = 1;
@@ -1172,11 +1216,12 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
     // The few-segments form has no tile headers, so it serves neither the resident share of w and v, which they
     // mark, nor the forms in which a workgroup goes on to tiles far from its first.
     const bool may_be_few = grid == units && !xcd && !(updates(KIND) && c->resident_bytes > 0);
+    const int8_t run_log2 = grid == units && !xcd && c->off_lines ? run_log2_of(KIND) : int8_t{0};
     auto go = [&](auto grad) {
         typedef decltype(grad) GradT;
         const CallArgs<GradT> call{reinterpret_cast<const GradT* const*>(grad_ptrs), reinterpret_cast<GradT* const*>(merge_bufs),
                                    reduced, w_ptrs, v_ptrs, lr, mu, inv_p, c->host.L, c->P, sp.t0, count,
-                                   static_cast<int16_t>(tpw), xcd};
+                                   static_cast<int16_t>(tpw), xcd, run_log2};
         return launch<KIND, GradT>(c, sp, tiles, call, units, grid, may_be_few, stream, pc);
     };
     if (c->dtype == MGWFBP_F32) return go(float{});

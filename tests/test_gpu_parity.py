@@ -542,6 +542,21 @@ def test_sixteen_bit_pipeline_takes_tiles_in_pairs(P, dtype):
     check_case(small, merged[:12], "pipeline", launch=(1, True, 2), small_launch=0, resident=1 << 17, label="resident share")
 
 
+@pytest.mark.parametrize("mode", ["pipeline", "pipeline_per_group", "staged", "direct", "reduce_update"])
+@pytest.mark.parametrize("tiles", [63, 64, 65, 127, 128, 129, 200])
+def test_runs_of_tiles_per_die(mode, tiles):
+    """Models of odd sizes deal runs of units to the dies in sets of 32 or 64: launches of one unit less, as many and
+    one more than a set or two, in the table form (ten tensors) and the few-segments form (one), one to three tiles a
+    unit.  Every unit has to come exactly once, also in the incomplete last set."""
+    rng = np.random.default_rng(13)
+    cuts = [int(x) for x in rng.integers(1, tiles * 256 // 10, 9)]
+    sizes = [tiles * 256 - 3 - sum(cuts)] + cuts + [tiles * 256 - 1]
+    p = W.Profile("runs", np.asarray(sizes, np.uint64), rng.uniform(1e-6, 1e-5, len(sizes)), 1e-4, 1e-9, 3, "f32", 1.0)
+    merged = [0] + [1] * 9 + [0]
+    for per_wg in (0, 1, 2, 3):
+        check_case(p, merged, mode, misalign=3, launch=(0, False, per_wg), label=f"{tiles} tiles, {per_wg} per workgroup")
+
+
 # ------------------------------------------------------------------------------------------
 # the benchmark configurations at full size, in the launch configuration bench.py times
 # ------------------------------------------------------------------------------------------
