@@ -1,6 +1,7 @@
 """ctypes binding with the same names as the C ABI declared in include/mgwfbp.h.
 
-Argument marshalling only.  Device buffers are passed as integer addresses (e.g. torch's
+Argument marshalling only; the device calls, which a training loop makes once per group or tensor, do theirs in
+the extension module built from csrc/calls.cpp.  Device buffers are passed as integer addresses (e.g. torch's
 `tensor.data_ptr()`), streams as integer handles (e.g. `torch.cuda.current_stream().cuda_stream`)."""
 from __future__ import annotations
 
@@ -81,11 +82,17 @@ def lib() -> C.CDLL:
         path = library_path()
         if not os.path.exists(path):
             raise MgwfbpError(f"load {path} (not built; run `python -m paper_1912_09268_amd.build`)", -1)
+        try:
+            from . import _calls
+        except ImportError:
+            raise MgwfbpError("load _calls (not built; run `python -m paper_1912_09268_amd.build`)", -1) from None
         handle = C.CDLL(path)
         for name, (res, args) in _SIGNATURES.items():
             fn = getattr(handle, name)
             fn.restype = res
             fn.argtypes = args
+        _calls.install(Context)
+        _calls.set_functions(_check, {name: C.cast(getattr(handle, name), _vp).value for name in _SIGNATURES})
         _LIB = handle
     return _LIB
 
@@ -230,6 +237,7 @@ class Context:
         fn = "mgwfbp_ctx_create_host" if host_only else "mgwfbp_ctx_create"
         _check(fn, getattr(lib(), fn)(C.byref(self._h), _ptr(ne, _u64p), int(ne.shape[0]), _ptr(m, _u8p),
                                       int(P), int(grad_dtype)))
+        self._handle = self._h.value or 0
         L, G, Pq, dt, tile, nt = (C.c_int32() for _ in range(6))
         arena = C.c_uint64()
         _check("mgwfbp_ctx_dims", lib().mgwfbp_ctx_dims(self._h, C.byref(L), C.byref(G), C.byref(Pq), C.byref(dt),
@@ -239,6 +247,7 @@ class Context:
 
     def close(self) -> None:
         if self._h:
+            self._handle = 0
             lib().mgwfbp_ctx_destroy(self._h)
             self._h = _vp(None)
 
@@ -288,51 +297,9 @@ class Context:
         _check("mgwfbp_ctx_set_resident_bytes", lib().mgwfbp_ctx_set_resident_bytes(self._h, int(nbytes)))
 
     # ---- device calls: addresses are plain integers ---------------------------------------
-    def pack(self, group: int, d_grad_ptrs: int, d_merge_bufs: int, stream: int = 0) -> None:
-        _check("mgwfbp_pack", lib().mgwfbp_pack(self._h, int(group), _vp(d_grad_ptrs), _vp(d_merge_bufs), _vp(stream)))
-
-    def pack_tensors(self, first_tensor: int, last_tensor: int, d_grad_ptrs: int, d_merge_bufs: int,
-                     stream: int = 0) -> None:
-        _check("mgwfbp_pack_tensors", lib().mgwfbp_pack_tensors(self._h, int(first_tensor), int(last_tensor),
-                                                                _vp(d_grad_ptrs), _vp(d_merge_bufs), _vp(stream)))
-
-    def reduce(self, group: int, d_merge_bufs: int, d_reduced: int, stream: int = 0) -> None:
-        _check("mgwfbp_reduce", lib().mgwfbp_reduce(self._h, int(group), _vp(d_merge_bufs), _vp(d_reduced), _vp(stream)))
-
-    def unpack_update(self, group: int, d_reduced: int, d_w_ptrs: int, d_v_ptrs: int, lr: float, momentum: float,
-                      stream: int = 0) -> None:
-        _check("mgwfbp_unpack_update", lib().mgwfbp_unpack_update(
-            self._h, int(group), _vp(d_reduced), _vp(d_w_ptrs), _vp(d_v_ptrs), float(lr), float(momentum), _vp(stream)))
-
-    def reduce_update(self, group: int, d_merge_bufs: int, d_w_ptrs: int, d_v_ptrs: int, lr: float, momentum: float,
-                      stream: int = 0) -> None:
-        _check("mgwfbp_reduce_update", lib().mgwfbp_reduce_update(
-            self._h, int(group), _vp(d_merge_bufs), _vp(d_w_ptrs), _vp(d_v_ptrs), float(lr), float(momentum), _vp(stream)))
-
-    def group_pipeline(self, group: int, d_grad_ptrs: int, d_merge_bufs: int, d_reduced: int, d_w_ptrs: int,
-                       d_v_ptrs: int, lr: float, momentum: float, stream: int = 0) -> None:
-        _check("mgwfbp_group_pipeline", lib().mgwfbp_group_pipeline(
-            self._h, int(group), _vp(d_grad_ptrs), _vp(d_merge_bufs), _vp(d_reduced or None), _vp(d_w_ptrs),
-            _vp(d_v_ptrs), float(lr), float(momentum), _vp(stream)))
-
-    def direct_update(self, group: int, d_grad_ptrs: int, d_reduced: int, d_w_ptrs: int, d_v_ptrs: int,
-                      lr: float, momentum: float, stream: int = 0) -> None:
-        _check("mgwfbp_direct_update", lib().mgwfbp_direct_update(
-            self._h, int(group), _vp(d_grad_ptrs), _vp(d_reduced or None), _vp(d_w_ptrs), _vp(d_v_ptrs),
-            float(lr), float(momentum), _vp(stream)))
-
-    def group_pipeline_span(self, group_first: int, group_count: int, d_grad_ptrs: int, d_merge_bufs: int,
-                            d_reduced: int, d_w_ptrs: int, d_v_ptrs: int, lr: float, momentum: float,
-                            stream: int = 0) -> None:
-        _check("mgwfbp_group_pipeline_span", lib().mgwfbp_group_pipeline_span(
-            self._h, int(group_first), int(group_count), _vp(d_grad_ptrs), _vp(d_merge_bufs), _vp(d_reduced or None),
-            _vp(d_w_ptrs), _vp(d_v_ptrs), float(lr), float(momentum), _vp(stream)))
-
-    def group_pipeline_static(self, group: int, d_grad_ptrs: int, d_merge_bufs: int, d_reduced: int, d_w_ptrs: int,
-                              d_v_ptrs: int, lr: float, momentum: float, stream: int = 0) -> None:
-        _check("mgwfbp_group_pipeline_static", lib().mgwfbp_group_pipeline_static(
-            self._h, int(group), _vp(d_grad_ptrs), _vp(d_merge_bufs), _vp(d_reduced or None), _vp(d_w_ptrs),
-            _vp(d_v_ptrs), float(lr), float(momentum), _vp(stream)))
+    # pack, pack_tensors, reduce, unpack_update, reduce_update, group_pipeline, direct_update, group_pipeline_span and
+    # group_pipeline_static are methods of csrc/calls.cpp, put in here when the library is loaded, with the
+    # arguments of the C ABI's functions in their order, `stream=0` last.
 
     def handler_replay(self, group_ready_s: Sequence[float], time_scale: float, max_groups_per_launch: int,
                        streams: Sequence[int], d_grad_ptrs: int, d_merge_bufs: int, d_reduced: int, d_w_ptrs: int, d_v_ptrs: int,
@@ -347,3 +314,10 @@ class Context:
             self._h, _ptr(ready, _f64p), float(time_scale), int(max_groups_per_launch), table, len(streams), _vp(d_grad_ptrs), _vp(d_merge_bufs),
             _vp(d_reduced or None), _vp(d_w_ptrs), _vp(d_v_ptrs), float(lr), float(momentum), _ptr(stats, _f64p)))
         return int(stats[0]), float(stats[1]), float(stats[2]), float(stats[3])
+
+
+try:                     # at once where it is built, so that the class is whole before the library is loaded
+    from . import _calls
+    _calls.install(Context)
+except (ImportError, AttributeError):      # not built yet, or before its source changed: building imports this package
+    pass

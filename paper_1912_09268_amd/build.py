@@ -1,10 +1,11 @@
-"""Compiles the HIP/C++ sources under csrc/ into libmgwfbp.so next to this file, and the benchmark's
-measurement aid under bench_aid/ into its own shared object there (gfx950 only)."""
+"""Compiles the HIP/C++ sources under csrc/ into libmgwfbp.so and the extension module _calls next to this file,
+and the benchmark's measurement aid under bench_aid/ into its own shared object there (gfx950 only)."""
 from __future__ import annotations
 
 import os
 import shutil
 import subprocess
+import sysconfig
 from typing import Dict, Optional
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -48,6 +49,17 @@ def build_library(out: Optional[str] = None, defines: Optional[Dict[str, object]
     return out
 
 
+def build_calls() -> str:
+    """The extension module with the device calls of Context: host code only, no link to the library."""
+    out = os.path.join(HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
+    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-missing-field-initializers",
+           "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "calls.cpp"), "-o", out]
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"g++ failed ({res.returncode}):\n{res.stdout}")
+    return out
+
+
 def build_bench_aid(verbose: bool = False) -> str:
     """The stream probe and cache scrub that bench.py uses; kept out of libmgwfbp.so on purpose."""
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
@@ -62,4 +74,5 @@ def build_bench_aid(verbose: bool = False) -> str:
 
 if __name__ == "__main__":  # python -m paper_1912_09268_amd.build
     print(build_library(verbose=True))
+    print(build_calls())
     print(build_bench_aid(verbose=True))
