@@ -44,7 +44,7 @@
 //   - everything is streamed with non-temporal loads and stores; a caller may ask for a leading share of
 //     the weights and momenta to use ordinary accesses and stay in the 256 MB memory-side cache (tile flag);
 //   - PACK, which has no arithmetic across workers, runs as P single-worker copies (gridDim.y = P),
-//     so the chip streams 2 arrays at a time instead of 2P; a workgroup copies 4 KiB of its worker's data,
+//     so the chip streams 2 arrays at a time instead of 2P; a workgroup copies 2 to 4 KiB of its worker's data,
 //     two tiles per step (more per workgroup stretches the window its compute unit covers and costs 8 %).
 //
 // Arithmetic contract: binary32, one rounding per operation.  The file must be compiled with
@@ -831,6 +831,7 @@ struct mgwfbp_ctx {
     int32_t dtype = 0;
     bool on_device = false;
     bool off_lines = false;           // a good part of the tiles do not start on the lines of their tensors
+    double ragged = 0;                // share of the tiles that take the general path
     int device = -1;
     int n_cu = 0;
     int32_t blocks_per_cu = 0;
@@ -931,6 +932,7 @@ int create_common(mgwfbp_ctx** out, const uint64_t* n_elems, int32_t L, const ui
     c->serial = g_next_serial.fetch_add(1);
     mark_resident_tiles(c->host, c->resident_bytes);
     c->off_lines = starts_off_lines(c->host);
+    if (!c->host.tiles.empty()) c->ragged = static_cast<double>(c->host.n_ragged) / static_cast<double>(c->host.tiles.size());
     if (device) {
         hipDeviceProp_t prop;
         rc = note(hipGetDevice(&c->device));
@@ -1046,6 +1048,9 @@ int32_t default_step_vecs(int, int32_t) { return TVECS % 2 == 0 ? 2 : 1; }
 //   - A launch of a few rounds of the chip (256 compute units times the cap) should not end in a nearly empty one:
 //     below SHORT_LAUNCH_TILES the cap is 18 at least (pipeline, binary32, P = 8, one group of 4096 / 8192 / 16384
 //     tiles: 15.8 / 30.4 / 58.0 us at 18 against 19.4 / 32.3 / 58.0 us at 14).
+//   - A ragged tile (see general_tile) spends most of its time waiting for one thing after the other: a model that
+//     consists of them needs every wave slot (45 % ragged, binary32: pipeline P = 3: 4868 uncapped / 4204 at 18,
+//     reduce_update P = 8: 5801 / 5270 at 14; with 11 % the caps are as good or better).
 //   - 16-bit gradients need every wave slot (direct, P = 8: 6559 uncapped / 5729 at 16), but for REDUCE with all of
 //     8 or 16 workers' loads in flight (P = 16: 6381 at 16 / 6220 uncapped; P = 12, two at a time: 6512 / 5265) and
 //     for the pipeline's joined steps, which have 1 KiB under way like binary32 (P = 8: 6164 at 14 / 5886 uncapped;
@@ -1057,25 +1062,37 @@ constexpr int32_t LONG_LAUNCH_TILES = 262144;
 // ResNet-50 shape, joined at its best cap against single tiles uncapped: P = 1: 6250 / 6327, 2: 6221 / 6231,
 // 3: 6194 / 6127, 4: 6175 / 6038, 8: 6164 / 5881, 16: 6080 / 5737, 32: 5675 / 5554; with one or two workers the
 // binary32 arrays are most of the traffic.  A short launch needs its tiles spread over the chip.
-bool joined_pipeline(int32_t dtype, int32_t P, int32_t tiles) {
-    return dtype != MGWFBP_F32 && P >= 3 && tiles >= SHORT_LAUNCH_TILES;
+// Nor does a model of many ragged tiles, whose turns come one after the other in a pair: with 0.9 / 2 / 3 / 11 / 45 % of
+// its tiles ragged, bf16, P = 8: 5706 / 5583 / 5789 / 5408 / 4364 joined, 5528 / 5446 / 5891 / 5532 / 4640 not.
+bool joined_pipeline(int32_t dtype, int32_t P, int32_t tiles, double ragged) {
+    return dtype != MGWFBP_F32 && P >= 3 && tiles >= SHORT_LAUNCH_TILES && ragged < 0.025;
 }
 
-int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int32_t tiles) {
+// Tiles per workgroup of a long PACK, which copies two of them per step: 4 KiB of a worker's binary32 gradients at 14
+// workgroups per compute unit; 2 KiB uncapped where ragged tiles, which are copied one by one, are no rarity (P = 3,
+// 0.02 / 0.9 / 2 / 11 / 45 % ragged: 6399 / 6148 / 5829 / 4922 / 2499 with 4 KiB, 6397 / 6188 / 5938 / 5792 / 3745 with 2 KiB);
+// 2 KiB of 16-bit gradients (P = 3, same models: 6164 / 5758 / 5110 / 4207 / 2085, with 4 KiB 6022 / 5398 / 4678 / 3684 / 1967).
+constexpr double SOME_RAGGED = 0.005;
+int32_t pack_tiles_per_workgroup(int32_t dtype, double ragged) {
+    return dtype == MGWFBP_F32 && ragged > SOME_RAGGED ? 2 : 4;
+}
+
+int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int32_t tiles, double ragged) {
     const bool wide = dtype == MGWFBP_F32;
     if (wide && tiles < SHORT_LAUNCH_TILES) {
-        const int32_t n = default_workgroups_per_cu(kind, dtype, P, SHORT_LAUNCH_TILES);
+        const int32_t n = default_workgroups_per_cu(kind, dtype, P, SHORT_LAUNCH_TILES, ragged);
         return n > 0 ? std::max(n, 18) : n;
     }
+    if (ragged > 0.25 && kind != K_REDUCE) return -1;
     switch (kind) {
         case K_REDUCE: return wide ? (P < 4 ? -1 : P < 8 ? 16 : 14) : (P == 8 || P == 16 ? 16 : -1);
         case K_UPDATE: return -1;                        // 20 bytes per element, nothing per worker
-        case K_PACK: return wide ? 14 : -1;
+        case K_PACK: return wide && ragged <= SOME_RAGGED ? 14 : -1;
         case K_REDUCE_UPDATE: return wide ? (P < 4 ? 25 : P < 8 ? 16 : 14) : -1;
         case K_DIRECT: return wide ? (P < 4 ? 25 : P <= 8 ? 16 : 14) : -1;
         default:                                         // pipeline
             if (wide) return P < 6 ? 18 : 14;
-            return !joined_pipeline(dtype, P, tiles) ? -1 : tiles < LONG_LAUNCH_TILES ? 14 : 12;
+            return !joined_pipeline(dtype, P, tiles, ragged) ? -1 : tiles < LONG_LAUNCH_TILES ? 14 : 12;
     }
 }
 
@@ -1180,16 +1197,16 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
         if (dev != c->device) return MGWFBP_EINVAL;   // tables live on the device the context was made on
     }
 
-    // tiles per workgroup: PACK runs as single-worker copies, whose tiles are small (one array in, one out),
-    // so a workgroup takes 4 KiB of its worker's data (two tiles at a time, see the kernel); every other kind
-    // takes one tile per workgroup.  More only stretches the set of bytes the chip has in flight: the window
-    // the workgroups of a compute unit cover together should stay within a few hundred KiB per array.
+    // tiles per workgroup: PACK runs as single-worker copies, whose tiles are small (one array in, one out), so a
+    // workgroup takes several, two at a time; the 16-bit pipeline takes two at once; every other kind takes one tile
+    // per workgroup.  More only stretches the set of bytes the chip has in flight: the window the workgroups of a
+    // compute unit cover together should stay within a few hundred KiB per array.
     int32_t tpw = c->tiles_per_wg;
     if (tpw <= 0) {
         tpw = 1;
         if (KIND == K_PACK && static_cast<int64_t>(count) * c->P > SMALL_PACK_TILES)
-            tpw = std::max(1, 4096 / (TILE * (c->dtype == MGWFBP_F32 ? 4 : 2)));
-        else if (KIND == K_PIPELINE && joined_pipeline(c->dtype, c->P, count))
+            tpw = pack_tiles_per_workgroup(c->dtype, c->ragged);
+        else if (KIND == K_PIPELINE && joined_pipeline(c->dtype, c->P, count, c->ragged))
             tpw = JOIN;
     }
     const int32_t units = (count + tpw - 1) / tpw;
@@ -1209,7 +1226,7 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
     const bool burst = c->step_vecs < 0 || (c->step_vecs == 0 && c->burst_tiles > 0 && count <= c->burst_tiles);
     pc.step_vecs = burst ? 0 : (c->step_vecs > 0 ? c->step_vecs : default_step_vecs(KIND, c->dtype));
     const int32_t wgs = c->wg_per_cu != 0 ? c->wg_per_cu
-                                          : (burst ? -1 : default_workgroups_per_cu(KIND, c->dtype, c->P, count));
+                                          : (burst ? -1 : default_workgroups_per_cu(KIND, c->dtype, c->P, count, c->ragged));
     pc.wgs_per_cu = wgs;
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     const float inv_p = 1.0f / static_cast<float>(c->P);

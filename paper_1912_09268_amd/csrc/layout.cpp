@@ -82,6 +82,7 @@ int mgwfbp_build_tables(const uint64_t* n_elems, int32_t L, const uint8_t* merge
                 h.layer0 = out.seg_layer[s];
                 h.flags = 0;
                 out.tiles.push_back(h);
+                if (h.nseg > 1 || valid < TILE) ++out.n_ragged;
             }
             next_tile += ntile;
             out.group_tile.push_back(static_cast<int32_t>(next_tile));

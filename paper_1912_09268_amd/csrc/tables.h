@@ -58,6 +58,7 @@ struct HostTables {
     std::vector<unsigned char> seg_block;
     // per tile
     std::vector<TileHdr> tiles;           // [T]
+    uint64_t n_ragged = 0;                // tiles that several segments or a group's end cut into
 };
 
 // Records a failed HIP call for mgwfbp_last_hip_error() on this thread and returns MGWFBP_EHIP; returns

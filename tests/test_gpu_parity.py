@@ -557,6 +557,19 @@ def test_runs_of_tiles_per_die(mode, tiles):
         check_case(p, merged, mode, misalign=3, launch=(0, False, per_wg), label=f"{tiles} tiles, {per_wg} per workgroup")
 
 
+@pytest.mark.parametrize("P,dtype,median", [(3, "f32", 60), (3, "bf16", 60), (4, "f32", 900), (6, "f16", 900), (4, "bf16", 9000)])
+def test_long_launches_over_ragged_models(P, dtype, median):
+    """Launches long enough for the shares and caps of long ones, over models most, a tenth and a fiftieth of whose
+    tiles are ragged: each takes other tiles per workgroup and, in the 16-bit pipeline, pairs or no pairs."""
+    rng = np.random.default_rng(14)
+    L = 17000 * 256 // median
+    sizes = np.clip(np.rint(np.exp(rng.normal(np.log(median), 0.8, L))), 1, 20 * median).astype(np.uint64)
+    p = W.Profile("ragged", sizes, rng.uniform(1e-6, 1e-5, L), 1e-4, 1e-9, P, dtype, 1.0)
+    merged = [0] + [int(x) for x in (rng.random(L - 1) < 0.8)]
+    for mode in ("staged", "pipeline", "reduce_update"):
+        check_case(p, merged, mode, label=f"median {median}")
+
+
 # ------------------------------------------------------------------------------------------
 # the benchmark configurations at full size, in the launch configuration bench.py times
 # ------------------------------------------------------------------------------------------
