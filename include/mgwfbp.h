@@ -238,8 +238,8 @@ int mgwfbp_ctx_set_pacing(mgwfbp_ctx* ctx, int32_t workgroups_per_cu, int32_t ve
  * handler sends them) is bound by the latency of a tile, not by the memory system, and pacing only stretches
  * that latency: such a launch takes the burst form, in which a lane issues every load of its tile at once and
  * no cap on the workgroups per compute unit applies.  `max_tiles` is the largest launch (in tiles of 256
- * elements) that does so: 0 = none, < 0 = the library's default (1024 tiles = 256 Ki elements).  Ignored while vectors_per_step of
- * mgwfbp_ctx_set_pacing is not 0.  Results never depend on it. */
+ * elements) that does so: 0 = none, < 0 = the library's default (1024 to 3072 tiles, by kind of call, gradient type
+ * and worker count).  Ignored while vectors_per_step of mgwfbp_ctx_set_pacing is not 0.  Results never depend on it. */
 int mgwfbp_ctx_set_small_launch(mgwfbp_ctx* ctx, int32_t max_tiles);
 
 /* How many bytes of weights + momenta (8 per element, counted from the start of the arena) are accessed

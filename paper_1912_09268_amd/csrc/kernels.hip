@@ -819,11 +819,6 @@ int mgwfbp_note_hip_result(int hip_error_code) { return note(static_cast<hipErro
 // ---------------------------------------------------------------------------------------------
 // context
 // ---------------------------------------------------------------------------------------------
-#ifndef MGWFBP_SMALL_PACK_TILES
-#define MGWFBP_SMALL_PACK_TILES 4096
-#endif
-constexpr int32_t SMALL_PACK_TILES = MGWFBP_SMALL_PACK_TILES;
-constexpr int32_t DEFAULT_BURST_TILES = 262144 / TILE;   // see run(): launches of at most 256 Ki elements
 
 struct mgwfbp_ctx {
     HostTables host;
@@ -839,7 +834,7 @@ struct mgwfbp_ctx {
     int32_t tiles_per_wg = 0;         // 0 = per-kernel default
     int32_t wg_per_cu = 0;            // 0 = per-kernel default, > 0 = cap, < 0 = no cap
     int32_t step_vecs = 0;            // 0 = per-kernel default, 1 or 2 = paced steps, -1 = always the burst form
-    int32_t burst_tiles = DEFAULT_BURST_TILES;   // launches of at most this many tiles take the burst form
+    int32_t burst_tiles = -1;         // launches of at most this many tiles take the burst form; < 0 = per-kernel default
     uint64_t resident_bytes = 0;      // budget of w + v bytes kept cacheable
     uint64_t serial = 0;              // changes whenever the tables change; never reused within a process
     // device copies
@@ -954,7 +949,7 @@ int create_common(mgwfbp_ctx** out, const uint64_t* n_elems, int32_t L, const ui
 // How a launch is paced (host side only).
 struct Pace {
     int32_t wgs_per_cu = -1;  // workgroups that may share a compute unit; <= 0: no cap
-    int step_vecs = 1;        // vectors per lane a fast tile is walked in: 1 or 2; 0 = burst (all at once)
+    int step_vecs = 1;        // vectors per lane a fast tile is walked in: 1; 0 = burst (all at once)
 };
 
 // Dynamic LDS per workgroup that lets at most n workgroups share the 160 KiB of a compute unit.  A workgroup's
@@ -986,8 +981,9 @@ template <int KIND, typename GradT> constexpr size_t table_form_lds() {
 template <int KIND, typename GradT, int PT>
 int launch_one(const FewArgs<GradT>& A, int grid, hipStream_t stream, const Pace& pc, int grid_y = 1) {
     const size_t lds = lds_for_workgroups_per_cu(pc.wgs_per_cu, few_form_lds<KIND, GradT>());
+    constexpr int BURST = KIND == K_PACK ? 1 : 0;         // PACK has one form
     if (pc.step_vecs <= 0)
-        hipLaunchKernelGGL((mgwfbp_few_kernel<KIND, GradT, PT, 0>), dim3(grid, grid_y), dim3(BLOCK), lds, stream, A);
+        hipLaunchKernelGGL((mgwfbp_few_kernel<KIND, GradT, PT, BURST>), dim3(grid, grid_y), dim3(BLOCK), lds, stream, A);
     else
         hipLaunchKernelGGL((mgwfbp_few_kernel<KIND, GradT, PT, 1>), dim3(grid, grid_y), dim3(BLOCK), lds, stream, A);
     return note(hipGetLastError());
@@ -996,22 +992,11 @@ int launch_one(const FewArgs<GradT>& A, int grid, hipStream_t stream, const Pace
 template <int KIND, typename GradT, int PT>
 int launch_one(const Args<GradT>& A, int grid, hipStream_t stream, const Pace& pc, int grid_y = 1) {
     const size_t lds = lds_for_workgroups_per_cu(pc.wgs_per_cu, table_form_lds<KIND, GradT>());
-    bool launched = false;
-    if (pc.step_vecs <= 0) {
-        hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, 0>), dim3(grid, grid_y), dim3(BLOCK), lds,
-                           stream, A);
-        launched = true;
-    }
-    if constexpr (TVECS % 2 == 0) {
-        if (!launched && pc.step_vecs >= 2) {
-            hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, 2>), dim3(grid, grid_y), dim3(BLOCK), lds,
-                               stream, A);
-            launched = true;
-        }
-    }
-    if (!launched)
-        hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, 1>), dim3(grid, grid_y), dim3(BLOCK), lds,
-                           stream, A);
+    constexpr int BURST = KIND == K_PACK ? 1 : 0;
+    if (pc.step_vecs <= 0)
+        hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, BURST>), dim3(grid, grid_y), dim3(BLOCK), lds, stream, A);
+    else
+        hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, 1>), dim3(grid, grid_y), dim3(BLOCK), lds, stream, A);
     return note(hipGetLastError());
 }
 
@@ -1031,8 +1016,6 @@ int launch_by_p(const ArgsT<GradT>& A, int grid, hipStream_t stream, const Pace&
         }
     }
 }
-
-int32_t default_step_vecs(int, int32_t) { return TVECS % 2 == 0 ? 2 : 1; }
 
 // Default caps, measured on the ResNet-50 shape (25.6 M elements, cold) with every cap that exists, worker counts
 // 1, 2, 3, 4, 6, 8, 12, 16, 32 and both gradient widths; GB/s of the cap taken against its neighbours or "none".
@@ -1058,6 +1041,18 @@ int32_t default_step_vecs(int, int32_t) { return TVECS % 2 == 0 ? 2 : 1; }
 constexpr int32_t SHORT_LAUNCH_TILES = 16384;
 constexpr int32_t LONG_LAUNCH_TILES = 262144;
 
+// Longest launch, in tiles, that takes the burst form.  Up to here the time is the latency of a tile, beyond it the
+// loads of all tiles at once are more than the memory system likes.  us burst / paced, one group, at 1024, 1792, 2048
+// and 3072 tiles: pipeline f32 P = 8: 5.3 / 8.4, 8.8 / 9.6, 10.3 / 10.0, 13.3 / 12.8; P = 16: 7.7 / 13.5, 14.1 / 15.3,
+// 16.9 / 16.1, 22.3 / 20.8; P = 3: 3.8 / 5.4, 5.0 / 6.2, 5.8 / 6.6, 6.8 / 8.0; bf16 P = 8: 4.2 / 7.7, 6.0 / 8.8, 6.9 / 9.0,
+// 9.5 / 10.5; reduce_update f32 P = 8: 4.1 / 5.4, 5.6 / 6.2, 7.0 / 6.4, 8.1 / 7.8; unpack_update 3.3 / 3.4, 3.5 / 3.9, 3.7 /
+// 4.1, 4.5 / 4.6.  At 4096 tiles the paced form is level or ahead everywhere.  PACK has one form
+// (every load of a step under way, see joined_tiles); for it this is where the cap begins.
+int32_t default_burst_tiles(int kind, int32_t dtype, int32_t P) {
+    if (kind == K_PACK) return 1024;
+    return dtype != MGWFBP_F32 || P < 4 || kind == K_UPDATE ? 3072 : 1792;
+}
+
 // Whether a workgroup of the pipeline takes JOIN tiles in one step (see joined_tiles).  GB/s at 16-bit gradients,
 // ResNet-50 shape, joined at its best cap against single tiles uncapped: P = 1: 6250 / 6327, 2: 6221 / 6231,
 // 3: 6194 / 6127, 4: 6175 / 6038, 8: 6164 / 5881, 16: 6080 / 5737, 32: 5675 / 5554; with one or two workers the
@@ -1068,13 +1063,19 @@ bool joined_pipeline(int32_t dtype, int32_t P, int32_t tiles, double ragged) {
     return dtype != MGWFBP_F32 && P >= 3 && tiles >= SHORT_LAUNCH_TILES && ragged < 0.025;
 }
 
-// Tiles per workgroup of a long PACK, which copies two of them per step: 4 KiB of a worker's binary32 gradients at 14
+// Tiles per workgroup of a PACK, which copies two of them per step: 4 KiB of a worker's binary32 gradients at 14
 // workgroups per compute unit; 2 KiB uncapped where ragged tiles, which are copied one by one, are no rarity (P = 3,
 // 0.02 / 0.9 / 2 / 11 / 45 % ragged: 6399 / 6148 / 5829 / 4922 / 2499 with 4 KiB, 6397 / 6188 / 5938 / 5792 / 3745 with 2 KiB);
 // 2 KiB of 16-bit gradients (P = 3, same models: 6164 / 5758 / 5110 / 4207 / 2085, with 4 KiB 6022 / 5398 / 4678 / 3684 / 1967).
+// Up to 256 copies of tiles per compute unit a launch is over sooner with more workgroups (f32, us with 1 / 2 / 4
+// tiles each: P = 8, 1024 tiles 5.4 / 5.0 / 5.5, 4096 tiles 16.0 / 12.5 / 13.1, 16384 tiles 64.9 / 42.9 / 42.2; P = 1, 1024
+// tiles 2.9 / 2.9 / 3.4).  Up to 8 per compute unit two are no faster than one, and slower where the ends of what is
+// packed are ragged (a thousand tensors around 4096 elements as views, packed one by one: 6222 us with 2, 5877 with 1).
 constexpr double SOME_RAGGED = 0.005;
-int32_t pack_tiles_per_workgroup(int32_t dtype, double ragged) {
-    return dtype == MGWFBP_F32 && ragged > SOME_RAGGED ? 2 : 4;
+constexpr int64_t SINGLE_COPIES = 2048, FEW_COPIES = 65536;
+int32_t pack_tiles_per_workgroup(int32_t dtype, int64_t copies, double ragged) {
+    if (copies <= SINGLE_COPIES) return 1;
+    return copies <= FEW_COPIES || (dtype == MGWFBP_F32 && ragged > SOME_RAGGED) ? 2 : 4;
 }
 
 int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int32_t tiles, double ragged) {
@@ -1204,8 +1205,8 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
     int32_t tpw = c->tiles_per_wg;
     if (tpw <= 0) {
         tpw = 1;
-        if (KIND == K_PACK && static_cast<int64_t>(count) * c->P > SMALL_PACK_TILES)
-            tpw = pack_tiles_per_workgroup(c->dtype, c->ragged);
+        if (KIND == K_PACK)
+            tpw = pack_tiles_per_workgroup(c->dtype, static_cast<int64_t>(count) * c->P, c->ragged);
         else if (KIND == K_PIPELINE && joined_pipeline(c->dtype, c->P, count, c->ragged))
             tpw = JOIN;
     }
@@ -1223,8 +1224,9 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
     // A launch too small to fill the chip is bound by the latency of its tiles, not by the memory system: it
     // takes the burst form (every load of a tile at once, no cap) unless the caller has fixed the pacing.
     Pace pc;
-    const bool burst = c->step_vecs < 0 || (c->step_vecs == 0 && c->burst_tiles > 0 && count <= c->burst_tiles);
-    pc.step_vecs = burst ? 0 : (c->step_vecs > 0 ? c->step_vecs : default_step_vecs(KIND, c->dtype));
+    const int32_t burst_tiles = c->burst_tiles < 0 ? default_burst_tiles(KIND, c->dtype, c->P) : c->burst_tiles;
+    const bool burst = c->step_vecs < 0 || (c->step_vecs == 0 && count <= burst_tiles);
+    pc.step_vecs = burst ? 0 : 1;
     const int32_t wgs = c->wg_per_cu != 0 ? c->wg_per_cu
                                           : (burst ? -1 : default_workgroups_per_cu(KIND, c->dtype, c->P, count, c->ragged));
     pc.wgs_per_cu = wgs;
@@ -1334,7 +1336,7 @@ int mgwfbp_ctx_set_pacing(mgwfbp_ctx* c, int32_t workgroups_per_cu, int32_t vect
 
 int mgwfbp_ctx_set_small_launch(mgwfbp_ctx* c, int32_t max_tiles) {
     if (c == nullptr) return MGWFBP_EINVAL;
-    c->burst_tiles = max_tiles < 0 ? DEFAULT_BURST_TILES : max_tiles;
+    c->burst_tiles = max_tiles;
     return MGWFBP_OK;
 }
 
