@@ -1071,10 +1071,16 @@ bool joined_pipeline(int32_t dtype, int32_t P, int32_t tiles, double ragged) {
 // tiles each: P = 8, 1024 tiles 5.4 / 5.0 / 5.5, 4096 tiles 16.0 / 12.5 / 13.1, 16384 tiles 64.9 / 42.9 / 42.2; P = 1, 1024
 // tiles 2.9 / 2.9 / 3.4).  Up to 8 per compute unit two are no faster than one, and slower where the ends of what is
 // packed are ragged (a thousand tensors around 4096 elements as views, packed one by one: 6222 us with 2, 5877 with 1).
-constexpr double SOME_RAGGED = 0.005;
+// With 16-bit gradients of many workers and next to no ragged tiles 4 KiB at 21 workgroups per compute unit
+// are ahead (ResNet-50 shape, us: P = 32: 493 against 510 with 2 KiB uncapped, P = 16: 248 / 257, P = 8: 127 / 128).
+constexpr double SOME_RAGGED = 0.005, HARDLY_RAGGED = 0.001;
 constexpr int64_t SINGLE_COPIES = 2048, FEW_COPIES = 65536;
-int32_t pack_tiles_per_workgroup(int32_t dtype, int64_t copies, double ragged) {
+bool many_halves(int32_t dtype, int32_t P, int64_t copies, double ragged) {
+    return dtype != MGWFBP_F32 && P >= 8 && copies > FEW_COPIES && ragged < HARDLY_RAGGED;
+}
+int32_t pack_tiles_per_workgroup(int32_t dtype, int32_t P, int64_t copies, double ragged) {
     if (copies <= SINGLE_COPIES) return 1;
+    if (many_halves(dtype, P, copies, ragged)) return 8;
     return copies <= FEW_COPIES || (dtype == MGWFBP_F32 && ragged > SOME_RAGGED) ? 2 : 4;
 }
 
@@ -1088,7 +1094,9 @@ int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int32_t ti
     switch (kind) {
         case K_REDUCE: return wide ? (P < 4 ? -1 : P < 8 ? 16 : 14) : (P == 8 || P == 16 ? 16 : -1);
         case K_UPDATE: return -1;                        // 20 bytes per element, nothing per worker
-        case K_PACK: return wide && ragged <= SOME_RAGGED ? 14 : -1;
+        case K_PACK:
+            if (many_halves(dtype, P, static_cast<int64_t>(tiles) * P, ragged)) return 21;
+            return wide && ragged <= SOME_RAGGED ? 14 : -1;
         case K_REDUCE_UPDATE: return wide ? (P < 4 ? 25 : P < 8 ? 16 : 14) : -1;
         case K_DIRECT: return wide ? (P < 4 ? 25 : P <= 8 ? 16 : 14) : -1;
         default:                                         // pipeline
@@ -1206,7 +1214,7 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
     if (tpw <= 0) {
         tpw = 1;
         if (KIND == K_PACK)
-            tpw = pack_tiles_per_workgroup(c->dtype, static_cast<int64_t>(count) * c->P, c->ragged);
+            tpw = pack_tiles_per_workgroup(c->dtype, c->P, static_cast<int64_t>(count) * c->P, c->ragged);
         else if (KIND == K_PIPELINE && joined_pipeline(c->dtype, c->P, count, c->ragged))
             tpw = JOIN;
     }
