@@ -501,6 +501,8 @@ def measure_workload(name, args, scrub, headline: bool):
         "plan_us": round(plan_us, 2), "plan_us_through_python_binding": round(plan_us_binding, 2),
     }
     if not args.no_launch_forms and mode == "pipeline" and G > 0:
+        if tuned is not None:                             # tuned for one long launch: the others at the library's own
+            ctx.set_pacing(0, args.vectors_per_step)
         res["launch_forms"] = launch_forms(dm, p, merged, G, scrub, cold_ms, max(5, args.steps // 3))
     if args.all_modes or (headline and not args.no_other_modes):
         ctx.set_pacing(0, args.vectors_per_step)          # every other kind at the library's own pacing

@@ -26,6 +26,9 @@
 // the end of the group or the edge of the interval a call is clipped to are taken element by element,
 // one element per lane, after the whole vectors.
 //
+// A launch over at most eight segments (one group, a tensor that has just arrived) takes a second form of the kernel
+// that gets the segments as arguments and reads no tables (mgwfbp_few_kernel).
+//
 // This is bandwidth-bound streaming work (at most 4 flops per 12+ bytes), so there is no use for the
 // matrix cores; the job is to present the traffic to the memory system in the form it serves fastest:
 //   - SMALL LAUNCHES (too few tiles to fill the chip: one small group) are bound by the latency of a tile,
@@ -33,18 +36,21 @@
 //   - PACING.  For these read/write mixes MI355X delivers most when every compute unit keeps about
 //     16-24 KiB of loads in flight and a tenth less beyond that, so a lane has one 16-byte load outstanding
 //     (one worker's share of the tile; two workers' in the kinds that only read between their stores) and each
-//     launch asks for enough unused LDS that only about 16 workgroups share a compute unit (see run() and
-//     lds_for_workgroups_per_cu());
+//     launch asks for enough unused LDS that only so many workgroups share a compute unit, 12 to 25 or all of them
+//     by kind, gradient width, worker count and length (see default_workgroups_per_cu());
 //   - SMALL WORKGROUPS.  A workgroup is one wavefront and a tile the 256 elements it covers with one vector per
 //     lane: the same bytes in flight spread over sixteen independent wavefronts per compute unit, each at its
 //     own point of its walk, load the memory system more evenly than two workgroups of four wavefronts that
 //     move in step (3-5 % of the peak on every shape);
 //   - one workgroup per tile, dispatched in tile order, so that the bytes the chip has in flight form one
-//     contiguous moving window per array;
+//     contiguous moving window per array; where tiles start inside the lines of their tensors, runs of a few tiles
+//     per die inside that window (unit_of());
+//   - 16-BIT GRADIENTS: a long pipeline launch takes two tiles per workgroup, 16 bytes of gradients per lane, so
+//     that a wavefront has as much under way as with binary32 (joined_tiles);
 //   - everything is streamed with non-temporal loads and stores; a caller may ask for a leading share of
 //     the weights and momenta to use ordinary accesses and stay in the 256 MB memory-side cache (tile flag);
 //   - PACK, which has no arithmetic across workers, runs as P single-worker copies (gridDim.y = P),
-//     so the chip streams 2 arrays at a time instead of 2P; a workgroup copies 2 to 4 KiB of its worker's data,
+//     so the chip streams 2 arrays at a time instead of 2P; a workgroup copies 1 to 4 KiB of its worker's data,
 //     two tiles per step (more per workgroup stretches the window its compute unit covers and costs 8 %).
 //
 // Arithmetic contract: binary32, one rounding per operation.  The file must be compiled with
@@ -653,7 +659,7 @@ __device__ __forceinline__ TileHdr load_header(const TileHdr* p) {
     return h;
 }
 
-// STEPV: vectors per lane a fast tile is walked in (1 or 2, see paced_step), or 0 for the burst form.
+// STEPV: vectors per lane a fast tile is walked in (1, see paced_step), or 0 for the burst form.
 template <int KIND, typename GradT, int PT, int STEPV>
 __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_stream_kernel(const Args<GradT> A) {
     __shared__ int s_loc[MAXSEG + 1];
@@ -1037,7 +1043,8 @@ int launch_by_p(const ArgsT<GradT>& A, int grid, hipStream_t stream, const Pace&
 //   - 16-bit gradients need every wave slot (direct, P = 8: 6559 uncapped / 5729 at 16), but for REDUCE with all of
 //     8 or 16 workers' loads in flight (P = 16: 6381 at 16 / 6220 uncapped; P = 12, two at a time: 6512 / 5265) and
 //     for the pipeline's joined steps, which have 1 KiB under way like binary32 (P = 8: 6164 at 14 / 5886 uncapped;
-//     transformer shape, 335 M elements, where the ends of the launch weigh less: 6232 at 12 / 6088 at 14).
+//     transformer shape, 335 M elements, where the ends of the launch weigh less, with the reduced arena 6232 at 12 /
+//     6088 at 14, without it and with a cold memory-side cache 2.643 / 2.601 ms).
 constexpr int32_t SHORT_LAUNCH_TILES = 16384;
 constexpr int32_t LONG_LAUNCH_TILES = 262144;
 
@@ -1084,10 +1091,10 @@ int32_t pack_tiles_per_workgroup(int32_t dtype, int32_t P, int64_t copies, doubl
     return copies <= FEW_COPIES || (dtype == MGWFBP_F32 && ragged > SOME_RAGGED) ? 2 : 4;
 }
 
-int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int32_t tiles, double ragged) {
+int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int32_t tiles, double ragged, bool reduced) {
     const bool wide = dtype == MGWFBP_F32;
     if (wide && tiles < SHORT_LAUNCH_TILES) {
-        const int32_t n = default_workgroups_per_cu(kind, dtype, P, SHORT_LAUNCH_TILES, ragged);
+        const int32_t n = default_workgroups_per_cu(kind, dtype, P, SHORT_LAUNCH_TILES, ragged, reduced);
         return n > 0 ? std::max(n, 18) : n;
     }
     if (ragged > 0.25 && kind != K_REDUCE) return -1;
@@ -1101,7 +1108,7 @@ int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int32_t ti
         case K_DIRECT: return wide ? (P < 4 ? 25 : P <= 8 ? 16 : 14) : -1;
         default:                                         // pipeline
             if (wide) return P < 6 ? 18 : 14;
-            return !joined_pipeline(dtype, P, tiles, ragged) ? -1 : tiles < LONG_LAUNCH_TILES ? 14 : 12;
+            return !joined_pipeline(dtype, P, tiles, ragged) ? -1 : tiles < LONG_LAUNCH_TILES || !reduced ? 14 : 12;
     }
 }
 
@@ -1236,7 +1243,7 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
     const bool burst = c->step_vecs < 0 || (c->step_vecs == 0 && count <= burst_tiles);
     pc.step_vecs = burst ? 0 : 1;
     const int32_t wgs = c->wg_per_cu != 0 ? c->wg_per_cu
-                                          : (burst ? -1 : default_workgroups_per_cu(KIND, c->dtype, c->P, count, c->ragged));
+                                          : (burst ? -1 : default_workgroups_per_cu(KIND, c->dtype, c->P, count, c->ragged, reduced != nullptr));
     pc.wgs_per_cu = wgs;
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     const float inv_p = 1.0f / static_cast<float>(c->P);
