@@ -67,6 +67,7 @@
 #include <mutex>
 #include <new>
 
+#include "launch.h"
 #include "mgwfbp.h"
 #include "tables.h"
 
@@ -74,10 +75,6 @@
 #define MGWFBP_NT 3   // bit 0: non-temporal loads of gradients / merge / reduced, bit 1: non-temporal
                       // stores to merge / reduced, bit 2: non-temporal accesses to w and v
 #endif
-#ifndef MGWFBP_JOIN_TILES
-#define MGWFBP_JOIN_TILES 2       // consecutive full tiles of one tensor that some kinds take in one step
-#endif
-#define MGWFBP_MAXSEG (2 * MGWFBP_BLOCK)   // segments per tile whose offsets are staged in LDS (two per lane)
 
 // Table space of mgwfbp_group_pipeline_static: one copy per GPU, held until the process ends.  Host code must
 // not pass this name to a kernel or a copy (on the host it is only a stand-in for the symbol); the device
@@ -87,23 +84,6 @@
 static __device__ __align__(256) unsigned char scratch[MGWFBP_STATIC_TABLE_MAX_BYTES];
 
 namespace {
-
-constexpr int BLOCK = MGWFBP_BLOCK;
-constexpr int VEC = MGWFBP_VEC;
-constexpr int TVECS = MGWFBP_TILE_VECS;
-constexpr int TILE = MGWFBP_TILE_ELEMS;
-constexpr int MAXSEG = MGWFBP_MAXSEG;
-constexpr int JOIN = MGWFBP_JOIN_TILES;
-
-enum Kind { K_PACK = 0, K_REDUCE = 1, K_UPDATE = 2, K_REDUCE_UPDATE = 3, K_PIPELINE = 4, K_DIRECT = 5 };
-
-constexpr bool reads_grads(int k) { return k == K_PACK || k == K_PIPELINE || k == K_DIRECT; }
-constexpr bool reads_merge(int k) { return k == K_REDUCE || k == K_REDUCE_UPDATE; }
-constexpr bool writes_merge(int k) { return k == K_PACK || k == K_PIPELINE; }
-constexpr bool sums(int k) { return k == K_REDUCE || k == K_REDUCE_UPDATE || k == K_PIPELINE || k == K_DIRECT; }
-constexpr bool writes_reduced(int k) { return k == K_REDUCE || k == K_PIPELINE || k == K_DIRECT; }
-constexpr bool updates(int k) { return k == K_UPDATE || k == K_REDUCE_UPDATE || k == K_PIPELINE || k == K_DIRECT; }
-constexpr bool needs_owner(int k) { return k != K_REDUCE; }
 
 // ---------------------------------------------------------------------------------------------
 // vector types that promise only element alignment
@@ -475,16 +455,8 @@ __device__ __forceinline__ void fast_chunk(const CallArgs<GradT>& A, const Worke
     }
 }
 
-// Kinds whose wavefronts have too little under way with one tile take JOIN full tiles of one tensor in one step:
-// PACK, a plain copy, and the pipeline on 16-bit gradients, where a worker's share of a tile is 512 bytes.
-template <int KIND, typename GradT> constexpr bool joins() {
-    return KIND == K_PACK || (KIND == K_PIPELINE && sizeof(GradT) == 2);
-}
+// Kinds that take JOIN full tiles in one step (see joins()).
 constexpr int WIDE = 8;               // 16-bit gradients per lane in a joined pipeline step: 16 bytes
-constexpr int JOINED = JOIN * TILE;   // elements of a joined step
-template <int KIND, typename GradT> constexpr int joined_floats() {    // LDS of a joined step
-    return KIND == K_PIPELINE && sizeof(GradT) == 2 ? JOINED : 0;
-}
 
 template <int KIND, typename GradT, int PT>
 __device__ __forceinline__ void joined_tiles(const CallArgs<GradT>& A, const WorkerPtrs<GradT, PT>& mrg, int layer,
@@ -667,7 +639,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_stream_kernel(const Args<
     __shared__ int s_wave[BLOCK / 64];
     __shared__ int s_ragged[TILE / VEC];
     __shared__ int s_nragged;
-    __shared__ __align__(16) float s_sums[joined_floats<KIND, GradT>() + 4];
+    __shared__ __align__(16) float s_sums[joined_floats(KIND, sizeof(GradT) == 2) + 4];
 
     WorkerPtrs<GradT, PT> mrg;
     if constexpr (reads_merge(KIND) || writes_merge(KIND)) mrg.fetch(A.merge_bufs, 1, 0, worker_base<KIND>());
@@ -703,7 +675,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_stream_kernel(const Args<
                 continue;
             }
             // A full tile inside one tensor.
-            if constexpr (joins<KIND, GradT>() && STEPV != 0) {
+            if constexpr (joins(KIND, sizeof(GradT) == 2) && STEPV != 0) {
                 // (A clip cuts into the first and the last tile only.)
                 if (t + JOIN <= t_end) {
                     bool same = t + JOIN < A.tile_count || A.clip_hi == TILE;
@@ -772,7 +744,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_few_kernel(const FewArgs<
     static_assert(BLOCK == 64 && TVECS == 1, "a tile is one vector per lane of one wavefront");
     WorkerPtrs<GradT, PT> mrg;
     if constexpr (reads_merge(KIND) || writes_merge(KIND)) mrg.fetch(A.merge_bufs, 1, 0, worker_base<KIND>());
-    __shared__ __align__(16) float s_sums[joined_floats<KIND, GradT>() + 4];
+    __shared__ __align__(16) float s_sums[joined_floats(KIND, sizeof(GradT) == 2) + 4];
     const int lane = threadIdx.x;
     const int64_t arena = static_cast<int64_t>(A.tile_first) * TILE;
     const int K = A.tiles_per_wg;
@@ -782,7 +754,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_few_kernel(const FewArgs<
         const int b = t * TILE;
         const FewSeg s = few_owner(A, b);                                  // uniform
         if (s.start <= b && b + TILE <= s.end) {                           // a full tile inside one segment
-            if constexpr (joins<KIND, GradT>() && STEPV != 0) {
+            if constexpr (joins(KIND, sizeof(GradT) == 2) && STEPV != 0) {
                 if (t + JOIN <= t_end && b + JOIN * TILE <= s.end) {
                     joined_tiles<KIND, GradT, PT>(A, mrg, A.layer_hi - s.j, b - s.start, arena + b, s_sums);
                     t += JOIN - 1;
@@ -835,13 +807,7 @@ struct mgwfbp_ctx {
     double ragged = 0;                // share of the tiles that take the general path
     int device = -1;
     int n_cu = 0;
-    int32_t blocks_per_cu = 0;
-    int32_t xcd_contiguous = 0;
-    int32_t tiles_per_wg = 0;         // 0 = per-kernel default
-    int32_t wg_per_cu = 0;            // 0 = per-kernel default, > 0 = cap, < 0 = no cap
-    int32_t step_vecs = 0;            // 0 = per-kernel default, 1 or 2 = paced steps, -1 = always the burst form
-    int32_t burst_tiles = -1;         // launches of at most this many tiles take the burst form; < 0 = per-kernel default
-    uint64_t resident_bytes = 0;      // budget of w + v bytes kept cacheable
+    LaunchSettings set;
     uint64_t serial = 0;              // changes whenever the tables change; never reused within a process
     // device copies
     unsigned char* d_tables = nullptr;   // the segment tables and the tile headers, one block
@@ -849,15 +815,6 @@ struct mgwfbp_ctx {
 };
 
 namespace {
-
-// 0 = no cap: one workgroup per tile.  Workgroups are then dispatched in tile order, which keeps the
-// chip's accesses to each of the 2P+2 streams inside a narrow moving window; measured faster than a
-// persistent grid for every profile.
-constexpr int32_t DEFAULT_BLOCKS_PER_CU = 0;
-
-// Default share of the 256 MB memory-side cache given to weights and momenta: none.  In a training loop a
-// forward and a backward pass run between two updates, so nothing of one update is still cached at the next.
-constexpr uint64_t DEFAULT_RESIDENT_BYTES = 0;
 
 std::atomic<uint64_t> g_next_serial{1};
 
@@ -885,16 +842,6 @@ bool starts_off_lines(const HostTables& h) {
         if ((h.tensor_n[i] | h.tensor_off[i]) % 32 != 0) off += h.tensor_n[i];
     }
     return off > all / 4;
-}
-
-// Units per die and turn (log2), where tiles start inside lines (see unit_of): the kinds that write w and v gain,
-// the pipeline, which writes whole lines of P arenas as well, less; PACK and REDUCE write whole lines only.
-int8_t run_log2_of(int kind) {
-    switch (kind) {
-        case K_PIPELINE: return 2;
-        case K_UPDATE: case K_REDUCE_UPDATE: case K_DIRECT: return 3;
-        default: return 0;
-    }
 }
 
 // Both parts of the block start on multiples of 256 bytes.
@@ -928,10 +875,8 @@ int create_common(mgwfbp_ctx** out, const uint64_t* n_elems, int32_t L, const ui
     }
     c->P = P;
     c->dtype = dtype;
-    c->blocks_per_cu = DEFAULT_BLOCKS_PER_CU;
-    c->resident_bytes = DEFAULT_RESIDENT_BYTES;
     c->serial = g_next_serial.fetch_add(1);
-    mark_resident_tiles(c->host, c->resident_bytes);
+    mark_resident_tiles(c->host, c->set.resident_bytes);
     c->off_lines = starts_off_lines(c->host);
     if (!c->host.tiles.empty()) c->ragged = static_cast<double>(c->host.n_ragged) / static_cast<double>(c->host.tiles.size());
     if (device) {
@@ -952,163 +897,42 @@ int create_common(mgwfbp_ctx** out, const uint64_t* n_elems, int32_t L, const ui
     return MGWFBP_OK;
 }
 
-// How a launch is paced (host side only).
-struct Pace {
-    int32_t wgs_per_cu = -1;  // workgroups that may share a compute unit; <= 0: no cap
-    int step_vecs = 1;        // vectors per lane a fast tile is walked in: 1; 0 = burst (all at once)
-};
-
-// Dynamic LDS per workgroup that lets at most n workgroups share the 160 KiB of a compute unit.  A workgroup's
-// LDS (static + dynamic) is granted in blocks of 1280 bytes (a 128th of the compute unit's; seen in the cap
-// sweeps, where 12 and 13, 14 and 15, 16 and 17 behave alike); the total aimed at is the smallest multiple of
-// the block above 160 KiB / (n + 1), so n + 1 workgroups never fit, and n do wherever a multiple of the block
-// lies in (160 KiB / (n + 1), 160 KiB / n]: 32, 25, 21, 18, 16, 14, 12, 11, 10, 9, 8, ... are the caps that
-// exist, and a request in between gets the next lower one.  The request stays 64 bytes short of that total so
-// that padding of the static part cannot push it into the next block.  62 KiB keeps clear of the 64 KiB a launch may ask for without special arrangements (so n = 1 is
-// served as n = 2).  n <= 0 means no cap, and so does an n beyond what the waves of a compute unit allow anyway.
-size_t lds_for_workgroups_per_cu(int32_t n, size_t static_lds) {
-    constexpr int32_t MAX_WGS = 32 * 64 / BLOCK;         // 32 waves per compute unit
-    if (n <= 0 || n >= MAX_WGS) return 0;
-    if (n < 2) n = 2;
-    constexpr size_t CU_LDS = 160u << 10;
-    constexpr size_t GRAIN = 1280;
-    size_t total = (CU_LDS / static_cast<size_t>(n + 1) / GRAIN + 1) * GRAIN;
-    total = std::min<size_t>(total, 62u << 10);
-    if (total <= static_lds + 64 + GRAIN) return 0;
-    return total - static_lds - 64;
-}
-// LDS the kernels declare themselves: the table form for its general path (REDUCE needs less of it), both forms for
-// the sums of joined steps.
-template <int KIND, typename GradT> constexpr size_t few_form_lds() { return sizeof(float) * joined_floats<KIND, GradT>(); }
-template <int KIND, typename GradT> constexpr size_t table_form_lds() {
-    return sizeof(int) * ((needs_owner(KIND) ? 2 * MAXSEG + 1 + BLOCK / 64 : 0) + TILE / VEC + 1) + few_form_lds<KIND, GradT>();
-}
-
 template <int KIND, typename GradT, int PT>
-int launch_one(const FewArgs<GradT>& A, int grid, hipStream_t stream, const Pace& pc, int grid_y = 1) {
-    const size_t lds = lds_for_workgroups_per_cu(pc.wgs_per_cu, few_form_lds<KIND, GradT>());
+int launch_one(const FewArgs<GradT>& A, hipStream_t stream, const LaunchShape& s, int grid_y = 1) {
+    const size_t lds = lds_for_workgroups_per_cu(s.wgs_per_cu, static_lds(KIND, sizeof(GradT) == 2, true));
     constexpr int BURST = KIND == K_PACK ? 1 : 0;         // PACK has one form
-    if (pc.step_vecs <= 0)
-        hipLaunchKernelGGL((mgwfbp_few_kernel<KIND, GradT, PT, BURST>), dim3(grid, grid_y), dim3(BLOCK), lds, stream, A);
+    if (s.step_vecs <= 0)
+        hipLaunchKernelGGL((mgwfbp_few_kernel<KIND, GradT, PT, BURST>), dim3(s.grid, grid_y), dim3(BLOCK), lds, stream, A);
     else
-        hipLaunchKernelGGL((mgwfbp_few_kernel<KIND, GradT, PT, 1>), dim3(grid, grid_y), dim3(BLOCK), lds, stream, A);
+        hipLaunchKernelGGL((mgwfbp_few_kernel<KIND, GradT, PT, 1>), dim3(s.grid, grid_y), dim3(BLOCK), lds, stream, A);
     return note(hipGetLastError());
 }
 
 template <int KIND, typename GradT, int PT>
-int launch_one(const Args<GradT>& A, int grid, hipStream_t stream, const Pace& pc, int grid_y = 1) {
-    const size_t lds = lds_for_workgroups_per_cu(pc.wgs_per_cu, table_form_lds<KIND, GradT>());
+int launch_one(const Args<GradT>& A, hipStream_t stream, const LaunchShape& s, int grid_y = 1) {
+    const size_t lds = lds_for_workgroups_per_cu(s.wgs_per_cu, static_lds(KIND, sizeof(GradT) == 2, false));
     constexpr int BURST = KIND == K_PACK ? 1 : 0;
-    if (pc.step_vecs <= 0)
-        hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, BURST>), dim3(grid, grid_y), dim3(BLOCK), lds, stream, A);
+    if (s.step_vecs <= 0)
+        hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, BURST>), dim3(s.grid, grid_y), dim3(BLOCK), lds, stream, A);
     else
-        hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, 1>), dim3(grid, grid_y), dim3(BLOCK), lds, stream, A);
+        hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, 1>), dim3(s.grid, grid_y), dim3(BLOCK), lds, stream, A);
     return note(hipGetLastError());
 }
 
 template <int KIND, typename GradT, template <typename> class ArgsT>
-int launch_by_p(const ArgsT<GradT>& A, int grid, hipStream_t stream, const Pace& pc) {
+int launch_by_p(const ArgsT<GradT>& A, hipStream_t stream, const LaunchShape& s) {
     if constexpr (KIND == K_UPDATE) {
-        return launch_one<KIND, GradT, 0>(A, grid, stream, pc);   // no per-worker data
+        return launch_one<KIND, GradT, 0>(A, stream, s);   // no per-worker data
     } else if constexpr (KIND == K_PACK) {
-        return launch_one<KIND, GradT, 1>(A, grid, stream, pc, A.P);   // P independent single-worker copies
+        return launch_one<KIND, GradT, 1>(A, stream, s, A.P);   // P independent single-worker copies
     } else {
         switch (A.P) {
-            case 2: return launch_one<KIND, GradT, 2>(A, grid, stream, pc);
-            case 4: return launch_one<KIND, GradT, 4>(A, grid, stream, pc);
-            case 8: return launch_one<KIND, GradT, 8>(A, grid, stream, pc);
-            case 16: return launch_one<KIND, GradT, 16>(A, grid, stream, pc);
-            default: return launch_one<KIND, GradT, 0>(A, grid, stream, pc);
+            case 2: return launch_one<KIND, GradT, 2>(A, stream, s);
+            case 4: return launch_one<KIND, GradT, 4>(A, stream, s);
+            case 8: return launch_one<KIND, GradT, 8>(A, stream, s);
+            case 16: return launch_one<KIND, GradT, 16>(A, stream, s);
+            default: return launch_one<KIND, GradT, 0>(A, stream, s);
         }
-    }
-}
-
-// Default caps, measured on the ResNet-50 shape (25.6 M elements, cold) with every cap that exists, worker counts
-// 1, 2, 3, 4, 6, 8, 12, 16, 32 and both gradient widths; GB/s of the cap taken against its neighbours or "none".
-//   - What has to be found is the number of bytes a compute unit keeps under way.  A wavefront has N loads in
-//     flight, each 1 KiB of a binary32 array or 512 bytes of a 16-bit one: N = 1 in the pipeline, two workers' in
-//     the other kinds when P is not known at compile time, all P when it is (2, 4, 8, 16: nothing is stored between
-//     them, so the compiler issues them together).
-//   - With few workers a wavefront spends more of its life on the way to its first load (header, pointers) than
-//     loading, and more of them are needed: REDUCE, binary32, P = 1: 6158 uncapped against 4510 at 14, P = 3: 6278 /
-//     5303, P = 4: 6455 at 16 / 6153 uncapped, P = 8: 6562 at 14 / 6258 uncapped.
-//   - With many workers there are more arrays to switch between and a smaller window serves them better: pipeline,
-//     binary32, P = 4: 6317 at 18 / 6254 at 14, P = 8: 6299 at 14 / 6229 at 16, P = 12: 6260 / 6076, P = 32: 5899 / 5676.
-//   - A launch of a few rounds of the chip (256 compute units times the cap) should not end in a nearly empty one:
-//     below SHORT_LAUNCH_TILES the cap is 18 at least (pipeline, binary32, P = 8, one group of 4096 / 8192 / 16384
-//     tiles: 15.8 / 30.4 / 58.0 us at 18 against 19.4 / 32.3 / 58.0 us at 14).
-//   - A ragged tile (see general_tile) spends most of its time waiting for one thing after the other: a model that
-//     consists of them needs every wave slot (45 % ragged, binary32: pipeline P = 3: 4868 uncapped / 4204 at 18,
-//     reduce_update P = 8: 5801 / 5270 at 14; with 11 % the caps are as good or better).
-//   - 16-bit gradients need every wave slot (direct, P = 8: 6559 uncapped / 5729 at 16), but for REDUCE with all of
-//     8 or 16 workers' loads in flight (P = 16: 6381 at 16 / 6220 uncapped; P = 12, two at a time: 6512 / 5265) and
-//     for the pipeline's joined steps, which have 1 KiB under way like binary32 (P = 8: 6164 at 14 / 5886 uncapped;
-//     transformer shape, 335 M elements, where the ends of the launch weigh less, with the reduced arena 6232 at 12 /
-//     6088 at 14, without it and with a cold memory-side cache 2.643 / 2.601 ms).
-constexpr int32_t SHORT_LAUNCH_TILES = 16384;
-constexpr int32_t LONG_LAUNCH_TILES = 262144;
-
-// Longest launch, in tiles, that takes the burst form.  Up to here the time is the latency of a tile, beyond it the
-// loads of all tiles at once are more than the memory system likes.  us burst / paced, one group, at 1024, 1792, 2048
-// and 3072 tiles: pipeline f32 P = 8: 5.3 / 8.4, 8.8 / 9.6, 10.3 / 10.0, 13.3 / 12.8; P = 16: 7.7 / 13.5, 14.1 / 15.3,
-// 16.9 / 16.1, 22.3 / 20.8; P = 3: 3.8 / 5.4, 5.0 / 6.2, 5.8 / 6.6, 6.8 / 8.0; bf16 P = 8: 4.2 / 7.7, 6.0 / 8.8, 6.9 / 9.0,
-// 9.5 / 10.5; reduce_update f32 P = 8: 4.1 / 5.4, 5.6 / 6.2, 7.0 / 6.4, 8.1 / 7.8; unpack_update 3.3 / 3.4, 3.5 / 3.9, 3.7 /
-// 4.1, 4.5 / 4.6.  At 4096 tiles the paced form is level or ahead everywhere.  PACK has one form
-// (every load of a step under way, see joined_tiles); for it this is where the cap begins.
-int32_t default_burst_tiles(int kind, int32_t dtype, int32_t P) {
-    if (kind == K_PACK) return 1024;
-    return dtype != MGWFBP_F32 || P < 4 || kind == K_UPDATE ? 3072 : 1792;
-}
-
-// Whether a workgroup of the pipeline takes JOIN tiles in one step (see joined_tiles).  GB/s at 16-bit gradients,
-// ResNet-50 shape, joined at its best cap against single tiles uncapped: P = 1: 6250 / 6327, 2: 6221 / 6231,
-// 3: 6194 / 6127, 4: 6175 / 6038, 8: 6164 / 5881, 16: 6080 / 5737, 32: 5675 / 5554; with one or two workers the
-// binary32 arrays are most of the traffic.  A short launch needs its tiles spread over the chip.
-// Nor does a model of many ragged tiles, whose turns come one after the other in a pair: with 0.9 / 2 / 3 / 11 / 45 % of
-// its tiles ragged, bf16, P = 8: 5706 / 5583 / 5789 / 5408 / 4364 joined, 5528 / 5446 / 5891 / 5532 / 4640 not.
-bool joined_pipeline(int32_t dtype, int32_t P, int32_t tiles, double ragged) {
-    return dtype != MGWFBP_F32 && P >= 3 && tiles >= SHORT_LAUNCH_TILES && ragged < 0.025;
-}
-
-// Tiles per workgroup of a PACK, which copies two of them per step: 4 KiB of a worker's binary32 gradients at 14
-// workgroups per compute unit; 2 KiB uncapped where ragged tiles, which are copied one by one, are no rarity (P = 3,
-// 0.02 / 0.9 / 2 / 11 / 45 % ragged: 6399 / 6148 / 5829 / 4922 / 2499 with 4 KiB, 6397 / 6188 / 5938 / 5792 / 3745 with 2 KiB);
-// 2 KiB of 16-bit gradients (P = 3, same models: 6164 / 5758 / 5110 / 4207 / 2085, with 4 KiB 6022 / 5398 / 4678 / 3684 / 1967).
-// Up to 256 copies of tiles per compute unit a launch is over sooner with more workgroups (f32, us with 1 / 2 / 4
-// tiles each: P = 8, 1024 tiles 5.4 / 5.0 / 5.5, 4096 tiles 16.0 / 12.5 / 13.1, 16384 tiles 64.9 / 42.9 / 42.2; P = 1, 1024
-// tiles 2.9 / 2.9 / 3.4).  Up to 8 per compute unit two are no faster than one, and slower where the ends of what is
-// packed are ragged (a thousand tensors around 4096 elements as views, packed one by one: 6222 us with 2, 5877 with 1).
-// With 16-bit gradients of many workers and next to no ragged tiles 4 KiB at 21 workgroups per compute unit
-// are ahead (ResNet-50 shape, us: P = 32: 493 against 510 with 2 KiB uncapped, P = 16: 248 / 257, P = 8: 127 / 128).
-constexpr double SOME_RAGGED = 0.005, HARDLY_RAGGED = 0.001;
-constexpr int64_t SINGLE_COPIES = 2048, FEW_COPIES = 65536;
-bool many_halves(int32_t dtype, int32_t P, int64_t copies, double ragged) {
-    return dtype != MGWFBP_F32 && P >= 8 && copies > FEW_COPIES && ragged < HARDLY_RAGGED;
-}
-int32_t pack_tiles_per_workgroup(int32_t dtype, int32_t P, int64_t copies, double ragged) {
-    if (copies <= SINGLE_COPIES) return 1;
-    if (many_halves(dtype, P, copies, ragged)) return 8;
-    return copies <= FEW_COPIES || (dtype == MGWFBP_F32 && ragged > SOME_RAGGED) ? 2 : 4;
-}
-
-int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int32_t tiles, double ragged, bool reduced) {
-    const bool wide = dtype == MGWFBP_F32;
-    if (wide && tiles < SHORT_LAUNCH_TILES) {
-        const int32_t n = default_workgroups_per_cu(kind, dtype, P, SHORT_LAUNCH_TILES, ragged, reduced);
-        return n > 0 ? std::max(n, 18) : n;
-    }
-    if (ragged > 0.25 && kind != K_REDUCE) return -1;
-    switch (kind) {
-        case K_REDUCE: return wide ? (P < 4 ? -1 : P < 8 ? 16 : 14) : (P == 8 || P == 16 ? 16 : -1);
-        case K_UPDATE: return -1;                        // 20 bytes per element, nothing per worker
-        case K_PACK:
-            if (many_halves(dtype, P, static_cast<int64_t>(tiles) * P, ragged)) return 21;
-            return wide && ragged <= SOME_RAGGED ? 14 : -1;
-        case K_REDUCE_UPDATE: return wide ? (P < 4 ? 25 : P < 8 ? 16 : 14) : -1;
-        case K_DIRECT: return wide ? (P < 4 ? 25 : P <= 8 ? 16 : 14) : -1;
-        default:                                         // pipeline
-            if (wide) return P < 6 ? 18 : 14;
-            return !joined_pipeline(dtype, P, tiles, ragged) ? -1 : tiles < LONG_LAUNCH_TILES || !reduced ? 14 : 12;
     }
 }
 
@@ -1170,18 +994,18 @@ bool few_segments(const HostTables& h, const Span& sp, bool whole_groups, int32_
 
 // Fills the argument block of the form the launch takes, and launches.
 template <int KIND, typename GradT>
-int launch(const mgwfbp_ctx* c, const Span& sp, const TileHdr* tiles, const CallArgs<GradT>& call, int32_t units,
-           int32_t grid, bool may_be_few, hipStream_t stream, const Pace& pc) {
-    if (may_be_few) {
+int launch(const mgwfbp_ctx* c, const Span& sp, const TileHdr* tiles, const CallArgs<GradT>& call,
+           hipStream_t stream, const LaunchShape& s) {
+    if (s.may_be_few) {
         FewArgs<GradT> A{call};
         if (few_segments(c->host, sp, !needs_owner(KIND), A.layer_hi, A.start0, A.n, A.closes, A.end))
-            return launch_by_p<KIND, GradT, FewArgs>(A, grid, stream, pc);
+            return launch_by_p<KIND, GradT, FewArgs>(A, stream, s);
     }
     // a clip cuts into the first and the last tile only
     const int16_t clip_lo = static_cast<int16_t>(sp.clipped ? sp.lo - static_cast<int64_t>(sp.t0) * TILE : 0);
     const int16_t clip_hi = static_cast<int16_t>(sp.clipped ? sp.hi - static_cast<int64_t>(sp.t1 - 1) * TILE : TILE);
-    const Args<GradT> A{call, tiles, static_cast<int32_t>(c->host.seg_layer.size()), units, grid, clip_lo, clip_hi};
-    return launch_by_p<KIND, GradT, Args>(A, grid, stream, pc);
+    const Args<GradT> A{call, tiles, static_cast<int32_t>(c->host.seg_layer.size()), s.units, s.grid, clip_lo, clip_hi};
+    return launch_by_p<KIND, GradT, Args>(A, stream, s);
 }
 
 template <int KIND>
@@ -1213,50 +1037,15 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
         if (dev != c->device) return MGWFBP_EINVAL;   // tables live on the device the context was made on
     }
 
-    // tiles per workgroup: PACK runs as single-worker copies, whose tiles are small (one array in, one out), so a
-    // workgroup takes several, two at a time; the 16-bit pipeline takes two at once; every other kind takes one tile
-    // per workgroup.  More only stretches the set of bytes the chip has in flight: the window the workgroups of a
-    // compute unit cover together should stay within a few hundred KiB per array.
-    int32_t tpw = c->tiles_per_wg;
-    if (tpw <= 0) {
-        tpw = 1;
-        if (KIND == K_PACK)
-            tpw = pack_tiles_per_workgroup(c->dtype, c->P, static_cast<int64_t>(count) * c->P, c->ragged);
-        else if (KIND == K_PIPELINE && joined_pipeline(c->dtype, c->P, count, c->ragged))
-            tpw = JOIN;
-    }
-    const int32_t units = (count + tpw - 1) / tpw;
-    int grid = units;
-    if (c->blocks_per_cu > 0 && c->n_cu > 0 && static_cast<int64_t>(c->n_cu) * c->blocks_per_cu < units)
-        grid = c->n_cu * c->blocks_per_cu;
-    int8_t xcd = 0;
-    if (c->xcd_contiguous && grid >= 64) {
-        grid &= ~7;
-        xcd = 1;
-    }
-    // Pacing: how many vectors a lane moves per step and how many workgroups may share a compute unit.
-    // Together they set the loads a compute unit has in flight (step_vecs x 4 KiB x workgroups for binary32).
-    // A launch too small to fill the chip is bound by the latency of its tiles, not by the memory system: it
-    // takes the burst form (every load of a tile at once, no cap) unless the caller has fixed the pacing.
-    Pace pc;
-    const int32_t burst_tiles = c->burst_tiles < 0 ? default_burst_tiles(KIND, c->dtype, c->P) : c->burst_tiles;
-    const bool burst = c->step_vecs < 0 || (c->step_vecs == 0 && count <= burst_tiles);
-    pc.step_vecs = burst ? 0 : 1;
-    const int32_t wgs = c->wg_per_cu != 0 ? c->wg_per_cu
-                                          : (burst ? -1 : default_workgroups_per_cu(KIND, c->dtype, c->P, count, c->ragged, reduced != nullptr));
-    pc.wgs_per_cu = wgs;
+    const LaunchShape s = launch_shape(c->set, {KIND, c->dtype, c->P, count, c->ragged, c->off_lines, reduced != nullptr}, c->n_cu);
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     const float inv_p = 1.0f / static_cast<float>(c->P);
-    // The few-segments form has no tile headers, so it serves neither the resident share of w and v, which they
-    // mark, nor the forms in which a workgroup goes on to tiles far from its first.
-    const bool may_be_few = grid == units && !xcd && !(updates(KIND) && c->resident_bytes > 0);
-    const int8_t run_log2 = grid == units && !xcd && c->off_lines ? run_log2_of(KIND) : int8_t{0};
     auto go = [&](auto grad) {
         typedef decltype(grad) GradT;
         const CallArgs<GradT> call{reinterpret_cast<const GradT* const*>(grad_ptrs), reinterpret_cast<GradT* const*>(merge_bufs),
                                    reduced, w_ptrs, v_ptrs, lr, mu, inv_p, c->host.L, c->P, sp.t0, count,
-                                   static_cast<int16_t>(tpw), xcd, run_log2};
-        return launch<KIND, GradT>(c, sp, tiles, call, units, grid, may_be_few, stream, pc);
+                                   static_cast<int16_t>(s.tiles_per_wg), s.xcd_contiguous, s.run_log2};
+        return launch<KIND, GradT>(c, sp, tiles, call, stream, s);
     };
     if (c->dtype == MGWFBP_F32) return go(float{});
     if (c->dtype == MGWFBP_F16) return go(_Float16{});
@@ -1334,9 +1123,9 @@ int mgwfbp_ctx_tables(const mgwfbp_ctx* c, int32_t* n_segments, void* tiles_out,
 
 int mgwfbp_ctx_set_launch(mgwfbp_ctx* c, int32_t blocks_per_cu, int32_t xcd_contiguous, int32_t tiles_per_workgroup) {
     if (c == nullptr || blocks_per_cu > 4096 || tiles_per_workgroup > 1024) return MGWFBP_EINVAL;
-    c->tiles_per_wg = tiles_per_workgroup <= 0 ? 0 : tiles_per_workgroup;
-    c->blocks_per_cu = blocks_per_cu <= 0 ? DEFAULT_BLOCKS_PER_CU : blocks_per_cu;
-    c->xcd_contiguous = xcd_contiguous ? 1 : 0;
+    c->set.tiles_per_wg = tiles_per_workgroup <= 0 ? 0 : tiles_per_workgroup;
+    c->set.blocks_per_cu = blocks_per_cu <= 0 ? LaunchSettings{}.blocks_per_cu : blocks_per_cu;
+    c->set.xcd_contiguous = xcd_contiguous ? 1 : 0;
     return MGWFBP_OK;
 }
 
@@ -1344,20 +1133,20 @@ int mgwfbp_ctx_set_pacing(mgwfbp_ctx* c, int32_t workgroups_per_cu, int32_t vect
     if (c == nullptr || workgroups_per_cu > 64 || vectors_per_step < -1 || vectors_per_step > TVECS ||
         (vectors_per_step > 0 && TVECS % vectors_per_step != 0))
         return MGWFBP_EINVAL;
-    c->wg_per_cu = workgroups_per_cu;
-    c->step_vecs = vectors_per_step;
+    c->set.wg_per_cu = workgroups_per_cu;
+    c->set.step_vecs = vectors_per_step;
     return MGWFBP_OK;
 }
 
 int mgwfbp_ctx_set_small_launch(mgwfbp_ctx* c, int32_t max_tiles) {
     if (c == nullptr) return MGWFBP_EINVAL;
-    c->burst_tiles = max_tiles;
+    c->set.burst_tiles = max_tiles;
     return MGWFBP_OK;
 }
 
 int mgwfbp_ctx_set_resident_bytes(mgwfbp_ctx* c, uint64_t bytes) {
     if (c == nullptr) return MGWFBP_EINVAL;
-    c->resident_bytes = bytes;
+    c->set.resident_bytes = bytes;
     c->serial = g_next_serial.fetch_add(1);
     mark_resident_tiles(c->host, bytes);
     if (c->on_device && !c->host.tiles.empty())

@@ -1,0 +1,244 @@
+// How a launch is cut up and paced: the rules that turn what a call covers and what the caller has fixed into a grid, a
+// form of the kernel and a cap on the workgroups per compute unit.  Pure host code (not part of the C ABI).
+#ifndef MGWFBP_LAUNCH_H
+#define MGWFBP_LAUNCH_H
+
+#include <algorithm>
+#include <cstddef>
+#include <cstdint>
+
+#include "mgwfbp.h"
+#include "tables.h"
+
+#ifndef MGWFBP_JOIN_TILES
+#define MGWFBP_JOIN_TILES 2       // consecutive full tiles of one tensor that some kinds take in one step
+#endif
+#define MGWFBP_MAXSEG (2 * MGWFBP_BLOCK)   // segments per tile whose offsets are staged in LDS (two per lane)
+
+namespace {
+
+constexpr int BLOCK = MGWFBP_BLOCK;
+constexpr int VEC = MGWFBP_VEC;
+constexpr int TVECS = MGWFBP_TILE_VECS;
+constexpr int TILE = MGWFBP_TILE_ELEMS;
+constexpr int MAXSEG = MGWFBP_MAXSEG;
+constexpr int JOIN = MGWFBP_JOIN_TILES;
+
+enum Kind { K_PACK = 0, K_REDUCE = 1, K_UPDATE = 2, K_REDUCE_UPDATE = 3, K_PIPELINE = 4, K_DIRECT = 5 };
+
+constexpr bool reads_grads(int k) { return k == K_PACK || k == K_PIPELINE || k == K_DIRECT; }
+constexpr bool reads_merge(int k) { return k == K_REDUCE || k == K_REDUCE_UPDATE; }
+constexpr bool writes_merge(int k) { return k == K_PACK || k == K_PIPELINE; }
+constexpr bool sums(int k) { return k == K_REDUCE || k == K_REDUCE_UPDATE || k == K_PIPELINE || k == K_DIRECT; }
+constexpr bool writes_reduced(int k) { return k == K_REDUCE || k == K_PIPELINE || k == K_DIRECT; }
+constexpr bool updates(int k) { return k == K_UPDATE || k == K_REDUCE_UPDATE || k == K_PIPELINE || k == K_DIRECT; }
+constexpr bool needs_owner(int k) { return k != K_REDUCE; }
+
+// Kinds whose wavefronts have too little under way with one tile take JOIN full tiles of one tensor in one step:
+// PACK, a plain copy, and the pipeline on 16-bit gradients, where a worker's share of a tile is 512 bytes.
+constexpr bool joins(int kind, bool half) { return kind == K_PACK || (kind == K_PIPELINE && half); }
+constexpr int JOINED = JOIN * TILE;   // elements of a joined step
+constexpr int joined_floats(int kind, bool half) { return kind == K_PIPELINE && half ? JOINED : 0; }   // LDS of a joined step
+
+// Dynamic LDS per workgroup that lets at most n workgroups share the 160 KiB of a compute unit.  A workgroup's
+// LDS (static + dynamic) is granted in blocks of 1280 bytes (a 128th of the compute unit's; seen in the cap
+// sweeps, where 12 and 13, 14 and 15, 16 and 17 behave alike); the total aimed at is the smallest multiple of
+// the block above 160 KiB / (n + 1), so n + 1 workgroups never fit, and n do wherever a multiple of the block
+// lies in (160 KiB / (n + 1), 160 KiB / n]: 32, 25, 21, 18, 16, 14, 12, 11, 10, 9, 8, ... are the caps that
+// exist, and a request in between gets the next lower one.  The request stays 64 bytes short of that total so
+// that padding of the static part cannot push it into the next block.  62 KiB keeps clear of the 64 KiB a launch may ask for without special arrangements (so n = 1 is
+// served as n = 2).  n <= 0 means no cap, and so does an n beyond what the waves of a compute unit allow anyway.
+inline size_t lds_for_workgroups_per_cu(int32_t n, size_t static_lds) {
+    constexpr int32_t MAX_WGS = 32 * 64 / BLOCK;         // 32 waves per compute unit
+    if (n <= 0 || n >= MAX_WGS) return 0;
+    if (n < 2) n = 2;
+    constexpr size_t CU_LDS = 160u << 10;
+    constexpr size_t GRAIN = 1280;
+    size_t total = (CU_LDS / static_cast<size_t>(n + 1) / GRAIN + 1) * GRAIN;
+    total = std::min<size_t>(total, 62u << 10);
+    if (total <= static_lds + 64 + GRAIN) return 0;
+    return total - static_lds - 64;
+}
+
+// LDS the kernels declare themselves: the table form for its general path (REDUCE needs less of it), both forms for
+// the sums of joined steps.
+constexpr size_t static_lds(int kind, bool half, bool few) {
+    const size_t joined = sizeof(float) * static_cast<size_t>(joined_floats(kind, half));
+    return few ? joined : joined + sizeof(int) * static_cast<size_t>((needs_owner(kind) ? 2 * MAXSEG + 1 + BLOCK / 64 : 0) + TILE / VEC + 1);
+}
+
+// Default caps, measured on the ResNet-50 shape (25.6 M elements, cold) with every cap that exists, worker counts
+// 1, 2, 3, 4, 6, 8, 12, 16, 32 and both gradient widths; GB/s of the cap taken against its neighbours or "none".
+//   - What has to be found is the number of bytes a compute unit keeps under way.  A wavefront has N loads in
+//     flight, each 1 KiB of a binary32 array or 512 bytes of a 16-bit one: N = 1 in the pipeline, two workers' in
+//     the other kinds when P is not known at compile time, all P when it is (2, 4, 8, 16: nothing is stored between
+//     them, so the compiler issues them together).
+//   - With few workers a wavefront spends more of its life on the way to its first load (header, pointers) than
+//     loading, and more of them are needed: REDUCE, binary32, P = 1: 6158 uncapped against 4510 at 14, P = 3: 6278 /
+//     5303, P = 4: 6455 at 16 / 6153 uncapped, P = 8: 6562 at 14 / 6258 uncapped.
+//   - With many workers there are more arrays to switch between and a smaller window serves them better: pipeline,
+//     binary32, P = 4: 6317 at 18 / 6254 at 14, P = 8: 6299 at 14 / 6229 at 16, P = 12: 6260 / 6076, P = 32: 5899 / 5676.
+//   - A launch of a few rounds of the chip (256 compute units times the cap) should not end in a nearly empty one:
+//     below SHORT_LAUNCH_TILES the cap is 18 at least (pipeline, binary32, P = 8, one group of 4096 / 8192 / 16384
+//     tiles: 15.8 / 30.4 / 58.0 us at 18 against 19.4 / 32.3 / 58.0 us at 14).
+//   - A ragged tile (see general_tile) spends most of its time waiting for one thing after the other: a model that
+//     consists of them needs every wave slot (45 % ragged, binary32: pipeline P = 3: 4868 uncapped / 4204 at 18,
+//     reduce_update P = 8: 5801 / 5270 at 14; with 11 % the caps are as good or better).
+//   - 16-bit gradients need every wave slot (direct, P = 8: 6559 uncapped / 5729 at 16), but for REDUCE with all of
+//     8 or 16 workers' loads in flight (P = 16: 6381 at 16 / 6220 uncapped; P = 12, two at a time: 6512 / 5265) and
+//     for the pipeline's joined steps, which have 1 KiB under way like binary32 (P = 8: 6164 at 14 / 5886 uncapped;
+//     transformer shape, 335 M elements, where the ends of the launch weigh less, with the reduced arena 6232 at 12 /
+//     6088 at 14, without it and with a cold memory-side cache 2.643 / 2.601 ms).
+constexpr int32_t SHORT_LAUNCH_TILES = 16384;
+constexpr int32_t LONG_LAUNCH_TILES = 262144;
+
+// Longest launch, in tiles, that takes the burst form.  Up to here the time is the latency of a tile, beyond it the
+// loads of all tiles at once are more than the memory system likes.  us burst / paced, one group, at 1024, 1792, 2048
+// and 3072 tiles: pipeline f32 P = 8: 5.3 / 8.4, 8.8 / 9.6, 10.3 / 10.0, 13.3 / 12.8; P = 16: 7.7 / 13.5, 14.1 / 15.3,
+// 16.9 / 16.1, 22.3 / 20.8; P = 3: 3.8 / 5.4, 5.0 / 6.2, 5.8 / 6.6, 6.8 / 8.0; bf16 P = 8: 4.2 / 7.7, 6.0 / 8.8, 6.9 / 9.0,
+// 9.5 / 10.5; reduce_update f32 P = 8: 4.1 / 5.4, 5.6 / 6.2, 7.0 / 6.4, 8.1 / 7.8; unpack_update 3.3 / 3.4, 3.5 / 3.9, 3.7 /
+// 4.1, 4.5 / 4.6.  At 4096 tiles the paced form is level or ahead everywhere.  PACK has one form
+// (every load of a step under way, see joined_tiles); for it this is where the cap begins.
+inline int32_t default_burst_tiles(int kind, int32_t dtype, int32_t P) {
+    if (kind == K_PACK) return 1024;
+    return dtype != MGWFBP_F32 || P < 4 || kind == K_UPDATE ? 3072 : 1792;
+}
+
+// Whether a workgroup of the pipeline takes JOIN tiles in one step (see joined_tiles).  GB/s at 16-bit gradients,
+// ResNet-50 shape, joined at its best cap against single tiles uncapped: P = 1: 6250 / 6327, 2: 6221 / 6231,
+// 3: 6194 / 6127, 4: 6175 / 6038, 8: 6164 / 5881, 16: 6080 / 5737, 32: 5675 / 5554; with one or two workers the
+// binary32 arrays are most of the traffic.  A short launch needs its tiles spread over the chip.
+// Nor does a model of many ragged tiles, whose turns come one after the other in a pair: with 0.9 / 2 / 3 / 11 / 45 % of
+// its tiles ragged, bf16, P = 8: 5706 / 5583 / 5789 / 5408 / 4364 joined, 5528 / 5446 / 5891 / 5532 / 4640 not.
+inline bool joined_pipeline(int32_t dtype, int32_t P, int32_t tiles, double ragged) {
+    return dtype != MGWFBP_F32 && P >= 3 && tiles >= SHORT_LAUNCH_TILES && ragged < 0.025;
+}
+
+// Tiles per workgroup of a PACK, which copies two of them per step: 4 KiB of a worker's binary32 gradients at 14
+// workgroups per compute unit; 2 KiB uncapped where ragged tiles, which are copied one by one, are no rarity (P = 3,
+// 0.02 / 0.9 / 2 / 11 / 45 % ragged: 6399 / 6148 / 5829 / 4922 / 2499 with 4 KiB, 6397 / 6188 / 5938 / 5792 / 3745 with 2 KiB);
+// 2 KiB of 16-bit gradients (P = 3, same models: 6164 / 5758 / 5110 / 4207 / 2085, with 4 KiB 6022 / 5398 / 4678 / 3684 / 1967).
+// Up to 256 copies of tiles per compute unit a launch is over sooner with more workgroups (f32, us with 1 / 2 / 4
+// tiles each: P = 8, 1024 tiles 5.4 / 5.0 / 5.5, 4096 tiles 16.0 / 12.5 / 13.1, 16384 tiles 64.9 / 42.9 / 42.2; P = 1, 1024
+// tiles 2.9 / 2.9 / 3.4).  Up to 8 per compute unit two are no faster than one, and slower where the ends of what is
+// packed are ragged (a thousand tensors around 4096 elements as views, packed one by one: 6222 us with 2, 5877 with 1).
+// With 16-bit gradients of many workers and next to no ragged tiles 4 KiB at 21 workgroups per compute unit
+// are ahead (ResNet-50 shape, us: P = 32: 493 against 510 with 2 KiB uncapped, P = 16: 248 / 257, P = 8: 127 / 128).
+constexpr double SOME_RAGGED = 0.005, HARDLY_RAGGED = 0.001;
+constexpr int64_t SINGLE_COPIES = 2048, FEW_COPIES = 65536;
+inline bool many_halves(int32_t dtype, int32_t P, int64_t copies, double ragged) {
+    return dtype != MGWFBP_F32 && P >= 8 && copies > FEW_COPIES && ragged < HARDLY_RAGGED;
+}
+inline int32_t pack_tiles_per_workgroup(int32_t dtype, int32_t P, int64_t copies, double ragged) {
+    if (copies <= SINGLE_COPIES) return 1;
+    if (many_halves(dtype, P, copies, ragged)) return 8;
+    return copies <= FEW_COPIES || (dtype == MGWFBP_F32 && ragged > SOME_RAGGED) ? 2 : 4;
+}
+
+inline int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int32_t tiles, double ragged, bool reduced) {
+    const bool wide = dtype == MGWFBP_F32;
+    if (wide && tiles < SHORT_LAUNCH_TILES) {
+        const int32_t n = default_workgroups_per_cu(kind, dtype, P, SHORT_LAUNCH_TILES, ragged, reduced);
+        return n > 0 ? std::max(n, 18) : n;
+    }
+    if (ragged > 0.25 && kind != K_REDUCE) return -1;
+    switch (kind) {
+        case K_REDUCE: return wide ? (P < 4 ? -1 : P < 8 ? 16 : 14) : (P == 8 || P == 16 ? 16 : -1);
+        case K_UPDATE: return -1;                        // 20 bytes per element, nothing per worker
+        case K_PACK:
+            if (many_halves(dtype, P, static_cast<int64_t>(tiles) * P, ragged)) return 21;
+            return wide && ragged <= SOME_RAGGED ? 14 : -1;
+        case K_REDUCE_UPDATE: return wide ? (P < 4 ? 25 : P < 8 ? 16 : 14) : -1;
+        case K_DIRECT: return wide ? (P < 4 ? 25 : P <= 8 ? 16 : 14) : -1;
+        default:                                         // pipeline
+            if (wide) return P < 6 ? 18 : 14;
+            return !joined_pipeline(dtype, P, tiles, ragged) ? -1 : tiles < LONG_LAUNCH_TILES || !reduced ? 14 : 12;
+    }
+}
+
+// Units per die and turn (log2), where tiles start inside lines (see unit_of): the kinds that write w and v gain,
+// the pipeline, which writes whole lines of P arenas as well, less; PACK and REDUCE write whole lines only.
+inline int8_t run_log2_of(int kind) {
+    switch (kind) {
+        case K_PIPELINE: return 2;
+        case K_UPDATE: case K_REDUCE_UPDATE: case K_DIRECT: return 3;
+        default: return 0;
+    }
+}
+
+// What a caller has fixed (mgwfbp_ctx_set_*); the initial values are the library's defaults.
+struct LaunchSettings {
+    int32_t blocks_per_cu = 0;        // > 0: a persistent grid of that many workgroups per compute unit.  0 = one workgroup
+                                      // per unit, dispatched in tile order, which keeps the chip's accesses to each of the
+                                      // 2P+2 streams inside a narrow moving window; measured faster for every profile
+    int32_t xcd_contiguous = 0;
+    int32_t tiles_per_wg = 0;         // 0 = per-kernel default
+    int32_t wg_per_cu = 0;            // 0 = per-kernel default, > 0 = cap, < 0 = no cap
+    int32_t step_vecs = 0;            // 0 = per-kernel default, > 0 = paced steps, -1 = always the burst form
+    int32_t burst_tiles = -1;         // launches of at most this many tiles take the burst form; < 0 = per-kernel default
+    uint64_t resident_bytes = 0;      // budget of w + v bytes kept cacheable.  Default none: in a training loop a forward and a
+                                      // backward pass run between two updates, so nothing of one is still cached at the next
+};
+
+// What a call covers.
+struct LaunchWork {
+    int kind;
+    int32_t dtype, P;
+    int32_t tiles;                    // > 0
+    double ragged;                    // share of the tiles that take the general path
+    bool off_lines;                   // a good part of the tiles do not start on the lines of their tensors
+    bool reduced;                     // the reduced arena is written
+};
+
+struct LaunchShape {
+    int32_t tiles_per_wg, units, grid;
+    int8_t xcd_contiguous;
+    int8_t run_log2;                  // a die's turn is 2^run_log2 consecutive units
+    bool may_be_few;                  // the few-segments form may take it
+    int step_vecs;                    // vectors per lane a fast tile is walked in: 1; 0 = burst (all at once)
+    int32_t wgs_per_cu;               // workgroups that may share a compute unit; <= 0: no cap
+};
+
+inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, int n_cu) {
+    LaunchShape s{};
+    // Tiles per workgroup: PACK runs as single-worker copies, whose tiles are small (one array in, one out), so a
+    // workgroup takes several, two at a time; the 16-bit pipeline takes two at once; every other kind takes one tile
+    // per workgroup.  More only stretches the set of bytes the chip has in flight: the window the workgroups of a
+    // compute unit cover together should stay within a few hundred KiB per array.
+    s.tiles_per_wg = set.tiles_per_wg;
+    if (s.tiles_per_wg <= 0) {
+        s.tiles_per_wg = 1;
+        if (w.kind == K_PACK)
+            s.tiles_per_wg = pack_tiles_per_workgroup(w.dtype, w.P, static_cast<int64_t>(w.tiles) * w.P, w.ragged);
+        else if (w.kind == K_PIPELINE && joined_pipeline(w.dtype, w.P, w.tiles, w.ragged))
+            s.tiles_per_wg = JOIN;
+    }
+    s.units = (w.tiles + s.tiles_per_wg - 1) / s.tiles_per_wg;
+    s.grid = s.units;
+    if (set.blocks_per_cu > 0 && n_cu > 0 && static_cast<int64_t>(n_cu) * set.blocks_per_cu < s.units)
+        s.grid = n_cu * set.blocks_per_cu;
+    if (set.xcd_contiguous && s.grid >= 64) {
+        s.grid &= ~7;
+        s.xcd_contiguous = 1;
+    }
+    // Pacing: how many vectors a lane moves per step and how many workgroups may share a compute unit.
+    // Together they set the loads a compute unit has in flight (step_vecs x 4 KiB x workgroups for binary32).
+    // A launch too small to fill the chip is bound by the latency of its tiles, not by the memory system: it
+    // takes the burst form (every load of a tile at once, no cap) unless the caller has fixed the pacing.
+    const int32_t burst_tiles = set.burst_tiles < 0 ? default_burst_tiles(w.kind, w.dtype, w.P) : set.burst_tiles;
+    const bool burst = set.step_vecs < 0 || (set.step_vecs == 0 && w.tiles <= burst_tiles);
+    s.step_vecs = burst ? 0 : 1;
+    s.wgs_per_cu = set.wg_per_cu != 0 ? set.wg_per_cu
+                   : burst            ? -1
+                                      : default_workgroups_per_cu(w.kind, w.dtype, w.P, w.tiles, w.ragged, w.reduced);
+    // The few-segments form has no tile headers, so it serves neither the resident share of w and v, which they
+    // mark, nor the forms in which a workgroup goes on to tiles far from its first.
+    const bool one_turn = s.grid == s.units && !s.xcd_contiguous;
+    s.may_be_few = one_turn && !(updates(w.kind) && set.resident_bytes > 0);
+    s.run_log2 = one_turn && w.off_lines ? run_log2_of(w.kind) : int8_t{0};
+    return s;
+}
+
+}  // namespace
+
+#endif
