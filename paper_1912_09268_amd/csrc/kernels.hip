@@ -639,7 +639,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_stream_kernel(const Args<
     __shared__ int s_wave[BLOCK / 64];
     __shared__ int s_ragged[TILE / VEC];
     __shared__ int s_nragged;
-    __shared__ __align__(16) float s_sums[joined_floats(KIND, sizeof(GradT) == 2) + 4];
+    __shared__ __align__(16) float s_sums[joined_floats(KIND, sizeof(GradT) == 2, STEPV) + 4];
 
     WorkerPtrs<GradT, PT> mrg;
     if constexpr (reads_merge(KIND) || writes_merge(KIND)) mrg.fetch(A.merge_bufs, 1, 0, worker_base<KIND>());
@@ -744,7 +744,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_few_kernel(const FewArgs<
     static_assert(BLOCK == 64 && TVECS == 1, "a tile is one vector per lane of one wavefront");
     WorkerPtrs<GradT, PT> mrg;
     if constexpr (reads_merge(KIND) || writes_merge(KIND)) mrg.fetch(A.merge_bufs, 1, 0, worker_base<KIND>());
-    __shared__ __align__(16) float s_sums[joined_floats(KIND, sizeof(GradT) == 2) + 4];
+    __shared__ __align__(16) float s_sums[joined_floats(KIND, sizeof(GradT) == 2, STEPV) + 4];
     const int lane = threadIdx.x;
     const int64_t arena = static_cast<int64_t>(A.tile_first) * TILE;
     const int K = A.tiles_per_wg;
@@ -897,25 +897,22 @@ int create_common(mgwfbp_ctx** out, const uint64_t* n_elems, int32_t L, const ui
     return MGWFBP_OK;
 }
 
-template <int KIND, typename GradT, int PT>
-int launch_one(const FewArgs<GradT>& A, hipStream_t stream, const LaunchShape& s, int grid_y = 1) {
-    const size_t lds = lds_for_workgroups_per_cu(s.wgs_per_cu, static_lds(KIND, sizeof(GradT) == 2, true));
-    constexpr int BURST = KIND == K_PACK ? 1 : 0;         // PACK has one form
-    if (s.step_vecs <= 0)
-        hipLaunchKernelGGL((mgwfbp_few_kernel<KIND, GradT, PT, BURST>), dim3(s.grid, grid_y), dim3(BLOCK), lds, stream, A);
-    else
-        hipLaunchKernelGGL((mgwfbp_few_kernel<KIND, GradT, PT, 1>), dim3(s.grid, grid_y), dim3(BLOCK), lds, stream, A);
-    return note(hipGetLastError());
+template <int KIND, typename GradT, int PT, int STEPV>
+void start(const FewArgs<GradT>& A, hipStream_t stream, const LaunchShape& s, int grid_y) {
+    const size_t lds = lds_for_workgroups_per_cu(s.wgs_per_cu, static_lds(KIND, sizeof(GradT) == 2, true, STEPV));
+    hipLaunchKernelGGL((mgwfbp_few_kernel<KIND, GradT, PT, STEPV>), dim3(s.grid, grid_y), dim3(BLOCK), lds, stream, A);
+}
+template <int KIND, typename GradT, int PT, int STEPV>
+void start(const Args<GradT>& A, hipStream_t stream, const LaunchShape& s, int grid_y) {
+    const size_t lds = lds_for_workgroups_per_cu(s.wgs_per_cu, static_lds(KIND, sizeof(GradT) == 2, false, STEPV));
+    hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, STEPV>), dim3(s.grid, grid_y), dim3(BLOCK), lds, stream, A);
 }
 
-template <int KIND, typename GradT, int PT>
-int launch_one(const Args<GradT>& A, hipStream_t stream, const LaunchShape& s, int grid_y = 1) {
-    const size_t lds = lds_for_workgroups_per_cu(s.wgs_per_cu, static_lds(KIND, sizeof(GradT) == 2, false));
-    constexpr int BURST = KIND == K_PACK ? 1 : 0;
-    if (s.step_vecs <= 0)
-        hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, BURST>), dim3(s.grid, grid_y), dim3(BLOCK), lds, stream, A);
-    else
-        hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, 1>), dim3(s.grid, grid_y), dim3(BLOCK), lds, stream, A);
+template <int KIND, typename GradT, int PT, template <typename> class ArgsT>
+int launch_one(const ArgsT<GradT>& A, hipStream_t stream, const LaunchShape& s, int grid_y = 1) {
+    constexpr int BURST = KIND == K_PACK ? 1 : 0;         // PACK has one form
+    if (s.step_vecs <= 0) start<KIND, GradT, PT, BURST>(A, stream, s, grid_y);
+    else start<KIND, GradT, PT, 1>(A, stream, s, grid_y);
     return note(hipGetLastError());
 }
 

@@ -38,7 +38,9 @@ constexpr bool needs_owner(int k) { return k != K_REDUCE; }
 // PACK, a plain copy, and the pipeline on 16-bit gradients, where a worker's share of a tile is 512 bytes.
 constexpr bool joins(int kind, bool half) { return kind == K_PACK || (kind == K_PIPELINE && half); }
 constexpr int JOINED = JOIN * TILE;   // elements of a joined step
-constexpr int joined_floats(int kind, bool half) { return kind == K_PIPELINE && half ? JOINED : 0; }   // LDS of a joined step
+constexpr int joined_floats(int kind, bool half, int step_vecs) {      // LDS of a joined step; the burst form has none
+    return kind == K_PIPELINE && half && step_vecs != 0 ? JOINED : 0;
+}
 
 // Dynamic LDS per workgroup that lets at most n workgroups share the 160 KiB of a compute unit.  A workgroup's
 // LDS (static + dynamic) is granted in blocks of 1280 bytes (a 128th of the compute unit's; seen in the cap
@@ -62,8 +64,8 @@ inline size_t lds_for_workgroups_per_cu(int32_t n, size_t static_lds) {
 
 // LDS the kernels declare themselves: the table form for its general path (REDUCE needs less of it), both forms for
 // the sums of joined steps.
-constexpr size_t static_lds(int kind, bool half, bool few) {
-    const size_t joined = sizeof(float) * static_cast<size_t>(joined_floats(kind, half));
+constexpr size_t static_lds(int kind, bool half, bool few, int step_vecs) {
+    const size_t joined = sizeof(float) * static_cast<size_t>(joined_floats(kind, half, step_vecs));
     return few ? joined : joined + sizeof(int) * static_cast<size_t>((needs_owner(kind) ? 2 * MAXSEG + 1 + BLOCK / 64 : 0) + TILE / VEC + 1);
 }
 

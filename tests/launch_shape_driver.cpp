@@ -1,0 +1,35 @@
+// Prints what the launch rules (csrc/launch.h) answer to the questions on standard input, one line each.  Built and
+// asked by tests/test_launch_shape.py.
+#include <cstdio>
+#include <cstring>
+
+#include "launch.h"
+
+int main() {
+    char what[16];
+    while (std::scanf("%15s", what) == 1) {
+        if (!std::strcmp(what, "lds")) {              // lds kind half few step_vecs cap
+            int kind, half, few, step, cap;
+            if (std::scanf("%d %d %d %d %d", &kind, &half, &few, &step, &cap) != 5) return 1;
+            const size_t own = static_lds(kind, half != 0, few != 0, step);
+            std::printf("%zu %zu\n", own, lds_for_workgroups_per_cu(cap, own));
+        } else if (!std::strcmp(what, "shape")) {     // shape <work> <settings> n_cu
+            LaunchWork w{};
+            LaunchSettings set;
+            int off, reduced, n_cu;
+            long long resident;
+            if (std::scanf("%d %d %d %d %lf %d %d", &w.kind, &w.dtype, &w.P, &w.tiles, &w.ragged, &off, &reduced) != 7) return 1;
+            if (std::scanf("%d %d %d %d %d %d %lld %d", &set.blocks_per_cu, &set.xcd_contiguous, &set.tiles_per_wg, &set.wg_per_cu,
+                           &set.step_vecs, &set.burst_tiles, &resident, &n_cu) != 8) return 1;
+            w.off_lines = off != 0;
+            w.reduced = reduced != 0;
+            set.resident_bytes = static_cast<uint64_t>(resident);
+            const LaunchShape s = launch_shape(set, w, n_cu);
+            std::printf("%d %d %d %d %d %d %d %d\n", s.tiles_per_wg, s.units, s.grid, s.xcd_contiguous, s.run_log2, s.may_be_few,
+                        s.step_vecs, s.wgs_per_cu);
+        } else {
+            return 1;
+        }
+    }
+    return 0;
+}
