@@ -32,7 +32,7 @@
 // This is bandwidth-bound streaming work (at most 4 flops per 12+ bytes), so there is no use for the
 // matrix cores; the job is to present the traffic to the memory system in the form it serves fastest:
 //   - SMALL LAUNCHES (too few tiles to fill the chip: one small group) are bound by the latency of a tile,
-//     so they issue every load of a tile at once (the burst form, STEPV = 0); what follows is for the rest;
+//     so they issue every load of a tile at once (the burst form); what follows is for the rest;
 //   - PACING.  For these read/write mixes MI355X delivers most when every compute unit keeps about
 //     16-24 KiB of loads in flight and a tenth less beyond that, so a lane has one 16-byte load outstanding
 //     (one worker's share of the tile; two workers' in the kinds that only read between their stores) and each
@@ -455,7 +455,7 @@ __device__ __forceinline__ void fast_chunk(const CallArgs<GradT>& A, const Worke
     }
 }
 
-// Kinds that take JOIN full tiles in one step (see joins()).
+// JOIN full tiles of one tensor in one step (see joins()).
 constexpr int WIDE = 8;               // 16-bit gradients per lane in a joined pipeline step: 16 bytes
 
 template <int KIND, typename GradT, int PT>
@@ -631,15 +631,16 @@ __device__ __forceinline__ TileHdr load_header(const TileHdr* p) {
     return h;
 }
 
-// STEPV: vectors per lane a fast tile is walked in (1, see paced_step), or 0 for the burst form.
-template <int KIND, typename GradT, int PT, int STEPV>
+// FORM: vectors per lane a fast tile is walked in (1, see paced_step), BURST or PAIRS.
+template <int KIND, typename GradT, int PT, int FORM>
 __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_stream_kernel(const Args<GradT> A) {
+    constexpr int SINGLE = FORM == PAIRS ? 1 : FORM;     // single tiles
     __shared__ int s_loc[MAXSEG + 1];
     __shared__ int s_layer[MAXSEG];
     __shared__ int s_wave[BLOCK / 64];
     __shared__ int s_ragged[TILE / VEC];
     __shared__ int s_nragged;
-    __shared__ __align__(16) float s_sums[joined_floats(KIND, sizeof(GradT) == 2, STEPV) + 4];
+    __shared__ __align__(16) float s_sums[FORM == PAIRS ? JOINED : 4];
 
     WorkerPtrs<GradT, PT> mrg;
     if constexpr (reads_merge(KIND) || writes_merge(KIND)) mrg.fetch(A.merge_bufs, 1, 0, worker_base<KIND>());
@@ -675,7 +676,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_stream_kernel(const Args<
                 continue;
             }
             // A full tile inside one tensor.
-            if constexpr (joins(KIND, sizeof(GradT) == 2) && STEPV != 0) {
+            if constexpr (joins(KIND, FORM)) {
                 // (A clip cuts into the first and the last tile only.)
                 if (t + JOIN <= t_end) {
                     bool same = t + JOIN < A.tile_count || A.clip_hi == TILE;
@@ -700,11 +701,11 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_stream_kernel(const Args<
             const int64_t toff = -h.first_start;
             if (!updates(KIND) || (h.flags & 1)) {
                 asm volatile("; w and v cacheable" ::: "memory");
-                fast_chunk<KIND, GradT, PT, NT_WV, STEPV>(A, mrg, h.layer0, toff, tile_base, TVECS);
+                fast_chunk<KIND, GradT, PT, NT_WV, SINGLE>(A, mrg, h.layer0, toff, tile_base, TVECS);
                 asm volatile("; end w and v cacheable" ::: "memory");
             } else {
                 asm volatile("; w and v streamed" ::: "memory");
-                fast_chunk<KIND, GradT, PT, true, STEPV>(A, mrg, h.layer0, toff, tile_base, TVECS);
+                fast_chunk<KIND, GradT, PT, true, SINGLE>(A, mrg, h.layer0, toff, tile_base, TVECS);
                 asm volatile("; end w and v streamed" ::: "memory");
             }
         }
@@ -739,12 +740,13 @@ template <typename GradT> __device__ __forceinline__ FewSeg few_owner(const FewA
     return s;
 }
 
-template <int KIND, typename GradT, int PT, int STEPV>
+template <int KIND, typename GradT, int PT, int FORM>
 __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_few_kernel(const FewArgs<GradT> A) {
     static_assert(BLOCK == 64 && TVECS == 1, "a tile is one vector per lane of one wavefront");
+    constexpr int SINGLE = FORM == PAIRS ? 1 : FORM;
     WorkerPtrs<GradT, PT> mrg;
     if constexpr (reads_merge(KIND) || writes_merge(KIND)) mrg.fetch(A.merge_bufs, 1, 0, worker_base<KIND>());
-    __shared__ __align__(16) float s_sums[joined_floats(KIND, sizeof(GradT) == 2, STEPV) + 4];
+    __shared__ __align__(16) float s_sums[FORM == PAIRS ? JOINED : 4];
     const int lane = threadIdx.x;
     const int64_t arena = static_cast<int64_t>(A.tile_first) * TILE;
     const int K = A.tiles_per_wg;
@@ -754,14 +756,14 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_few_kernel(const FewArgs<
         const int b = t * TILE;
         const FewSeg s = few_owner(A, b);                                  // uniform
         if (s.start <= b && b + TILE <= s.end) {                           // a full tile inside one segment
-            if constexpr (joins(KIND, sizeof(GradT) == 2) && STEPV != 0) {
+            if constexpr (joins(KIND, FORM)) {
                 if (t + JOIN <= t_end && b + JOIN * TILE <= s.end) {
                     joined_tiles<KIND, GradT, PT>(A, mrg, A.layer_hi - s.j, b - s.start, arena + b, s_sums);
                     t += JOIN - 1;
                     continue;
                 }
             }
-            fast_chunk<KIND, GradT, PT, true, STEPV>(A, mrg, A.layer_hi - s.j, b - s.start, arena + b, TVECS);
+            fast_chunk<KIND, GradT, PT, true, SINGLE>(A, mrg, A.layer_hi - s.j, b - s.start, arena + b, TVECS);
             continue;
         }
         // Whole vectors first, then the wanted elements of the others, one per lane (see general_tile).
@@ -897,22 +899,33 @@ int create_common(mgwfbp_ctx** out, const uint64_t* n_elems, int32_t L, const ui
     return MGWFBP_OK;
 }
 
-template <int KIND, typename GradT, int PT, int STEPV>
+template <int KIND, typename GradT, int PT, int FORM>
 void start(const FewArgs<GradT>& A, hipStream_t stream, const LaunchShape& s, int grid_y) {
-    const size_t lds = lds_for_workgroups_per_cu(s.wgs_per_cu, static_lds(KIND, sizeof(GradT) == 2, true, STEPV));
-    hipLaunchKernelGGL((mgwfbp_few_kernel<KIND, GradT, PT, STEPV>), dim3(s.grid, grid_y), dim3(BLOCK), lds, stream, A);
+    const size_t lds = lds_for_workgroups_per_cu(s.wgs_per_cu, static_lds(KIND, true, FORM));
+    hipLaunchKernelGGL((mgwfbp_few_kernel<KIND, GradT, PT, FORM>), dim3(s.grid, grid_y), dim3(BLOCK), lds, stream, A);
 }
-template <int KIND, typename GradT, int PT, int STEPV>
+template <int KIND, typename GradT, int PT, int FORM>
 void start(const Args<GradT>& A, hipStream_t stream, const LaunchShape& s, int grid_y) {
-    const size_t lds = lds_for_workgroups_per_cu(s.wgs_per_cu, static_lds(KIND, sizeof(GradT) == 2, false, STEPV));
-    hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, STEPV>), dim3(s.grid, grid_y), dim3(BLOCK), lds, stream, A);
+    const size_t lds = lds_for_workgroups_per_cu(s.wgs_per_cu, static_lds(KIND, false, FORM));
+    hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, FORM>), dim3(s.grid, grid_y), dim3(BLOCK), lds, stream, A);
 }
 
 template <int KIND, typename GradT, int PT, template <typename> class ArgsT>
 int launch_one(const ArgsT<GradT>& A, hipStream_t stream, const LaunchShape& s, int grid_y = 1) {
-    constexpr int BURST = KIND == K_PACK ? 1 : 0;         // PACK has one form
-    if (s.step_vecs <= 0) start<KIND, GradT, PT, BURST>(A, stream, s, grid_y);
-    else start<KIND, GradT, PT, 1>(A, stream, s, grid_y);
+    bool started = false;
+    if constexpr (KIND != K_PACK) {                       // PACK has one form
+        if (s.form == BURST) {
+            start<KIND, GradT, PT, BURST>(A, stream, s, grid_y);
+            started = true;
+        }
+    }
+    if constexpr (KIND == K_PIPELINE && sizeof(GradT) == 2) {
+        if (s.form == PAIRS) {
+            start<KIND, GradT, PT, PAIRS>(A, stream, s, grid_y);
+            started = true;
+        }
+    }
+    if (!started) start<KIND, GradT, PT, 1>(A, stream, s, grid_y);
     return note(hipGetLastError());
 }
 

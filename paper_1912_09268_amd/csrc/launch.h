@@ -34,13 +34,16 @@ constexpr bool writes_reduced(int k) { return k == K_REDUCE || k == K_PIPELINE |
 constexpr bool updates(int k) { return k == K_UPDATE || k == K_REDUCE_UPDATE || k == K_PIPELINE || k == K_DIRECT; }
 constexpr bool needs_owner(int k) { return k != K_REDUCE; }
 
-// Kinds whose wavefronts have too little under way with one tile take JOIN full tiles of one tensor in one step:
-// PACK, a plain copy, and the pipeline on 16-bit gradients, where a worker's share of a tile is 512 bytes.
-constexpr bool joins(int kind, bool half) { return kind == K_PACK || (kind == K_PIPELINE && half); }
+// Forms of the fast path, beside the number of vectors per lane of a paced step (1 and up).
+constexpr int BURST = 0;              // every load of a tile under way at once
+constexpr int PAIRS = -1;             // JOIN full tiles of one tensor in one step, single ones in paced steps of one vector
 constexpr int JOINED = JOIN * TILE;   // elements of a joined step
-constexpr int joined_floats(int kind, bool half, int step_vecs) {      // LDS of a joined step; the burst form has none
-    return kind == K_PIPELINE && half && step_vecs != 0 ? JOINED : 0;
-}
+// Kinds whose wavefronts have too little under way with one tile can take joined steps: PACK, a plain copy, always, and
+// the pipeline on 16-bit gradients, where a worker's share of a tile is 512 bytes, in kernels of their own: beside the
+// joined step, whose sums change hands through LDS, the single-tile kernel would need 105 instead of 74 registers (16
+// workers; 77 instead of 57 with 8) and as uncapped launches hold 16 instead of 24 wavefronts per compute unit (16
+// workers, 6000 tiles: 30.0 us against 23.4).
+constexpr bool joins(int kind, int form) { return form == PAIRS || (kind == K_PACK && form != BURST); }
 
 // Dynamic LDS per workgroup that lets at most n workgroups share the 160 KiB of a compute unit.  A workgroup's
 // LDS (static + dynamic) is granted in blocks of 1280 bytes (a 128th of the compute unit's; seen in the cap
@@ -64,8 +67,8 @@ inline size_t lds_for_workgroups_per_cu(int32_t n, size_t static_lds) {
 
 // LDS the kernels declare themselves: the table form for its general path (REDUCE needs less of it), both forms for
 // the sums of joined steps.
-constexpr size_t static_lds(int kind, bool half, bool few, int step_vecs) {
-    const size_t joined = sizeof(float) * static_cast<size_t>(joined_floats(kind, half, step_vecs));
+constexpr size_t static_lds(int kind, bool few, int form) {
+    const size_t joined = form == PAIRS ? sizeof(float) * JOINED : 0;
     return few ? joined : joined + sizeof(int) * static_cast<size_t>((needs_owner(kind) ? 2 * MAXSEG + 1 + BLOCK / 64 : 0) + TILE / VEC + 1);
 }
 
@@ -197,7 +200,7 @@ struct LaunchShape {
     int8_t xcd_contiguous;
     int8_t run_log2;                  // a die's turn is 2^run_log2 consecutive units
     bool may_be_few;                  // the few-segments form may take it
-    int step_vecs;                    // vectors per lane a fast tile is walked in: 1; 0 = burst (all at once)
+    int form;                         // BURST, PAIRS or the vectors per lane of a paced step
     int32_t wgs_per_cu;               // workgroups that may share a compute unit; <= 0: no cap
 };
 
@@ -229,7 +232,7 @@ inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, 
     // takes the burst form (every load of a tile at once, no cap) unless the caller has fixed the pacing.
     const int32_t burst_tiles = set.burst_tiles < 0 ? default_burst_tiles(w.kind, w.dtype, w.P) : set.burst_tiles;
     const bool burst = set.step_vecs < 0 || (set.step_vecs == 0 && w.tiles <= burst_tiles);
-    s.step_vecs = burst ? 0 : 1;
+    s.form = burst ? BURST : w.kind == K_PIPELINE && w.dtype != MGWFBP_F32 && s.tiles_per_wg >= JOIN ? PAIRS : 1;
     s.wgs_per_cu = set.wg_per_cu != 0 ? set.wg_per_cu
                    : burst            ? -1
                                       : default_workgroups_per_cu(w.kind, w.dtype, w.P, w.tiles, w.ragged, w.reduced);

@@ -8,10 +8,10 @@
 int main() {
     char what[16];
     while (std::scanf("%15s", what) == 1) {
-        if (!std::strcmp(what, "lds")) {              // lds kind half few step_vecs cap
-            int kind, half, few, step, cap;
-            if (std::scanf("%d %d %d %d %d", &kind, &half, &few, &step, &cap) != 5) return 1;
-            const size_t own = static_lds(kind, half != 0, few != 0, step);
+        if (!std::strcmp(what, "lds")) {              // lds kind few form cap
+            int kind, few, form, cap;
+            if (std::scanf("%d %d %d %d", &kind, &few, &form, &cap) != 4) return 1;
+            const size_t own = static_lds(kind, few != 0, form);
             std::printf("%zu %zu\n", own, lds_for_workgroups_per_cu(cap, own));
         } else if (!std::strcmp(what, "shape")) {     // shape <work> <settings> n_cu
             LaunchWork w{};
@@ -26,7 +26,7 @@ int main() {
             set.resident_bytes = static_cast<uint64_t>(resident);
             const LaunchShape s = launch_shape(set, w, n_cu);
             std::printf("%d %d %d %d %d %d %d %d\n", s.tiles_per_wg, s.units, s.grid, s.xcd_contiguous, s.run_log2, s.may_be_few,
-                        s.step_vecs, s.wgs_per_cu);
+                        s.form, s.wgs_per_cu);
         } else {
             return 1;
         }

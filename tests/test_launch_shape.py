@@ -17,8 +17,8 @@ READELF = shutil.which("llvm-readelf") or "/opt/rocm/llvm/bin/llvm-readelf"
 KINDS = ["pack", "reduce", "update", "reduce_update", "pipeline", "direct"]
 DTYPES = ["f32", "bf16", "f16"]
 CU_LDS, LDS_GRAIN = 160 << 10, 1280
-Kernel = namedtuple("Kernel", "few kind half P step lds vgprs")
-Shape = namedtuple("Shape", "tiles_per_wg units grid xcd_contiguous run_log2 may_be_few step_vecs wgs_per_cu")
+Kernel = namedtuple("Kernel", "few kind half P form lds vgprs")
+Shape = namedtuple("Shape", "tiles_per_wg units grid xcd_contiguous run_log2 may_be_few form wgs_per_cu")
 
 
 @pytest.fixture(scope="module")
@@ -68,7 +68,7 @@ def test_caps_hold_for_every_kernel(ask, kernels):
     """At most the workgroups asked for fit into a compute unit with the LDS the kernel really has, and as many as the
     grain of 1280 bytes allows."""
     caps = list(range(2, 32))
-    answers = iter(ask([f"lds {k.kind} {int(k.half)} {int(k.few)} {k.step} {n}" for k in kernels for n in caps]))
+    answers = iter(ask([f"lds {k.kind} {int(k.few)} {k.form} {n}" for k in kernels for n in caps]))
     for k in kernels:
         for n in caps:
             own, extra = next(answers)
@@ -76,3 +76,13 @@ def test_caps_hold_for_every_kernel(ask, kernels):
             grains = -(-(k.lds + extra) // LDS_GRAIN)
             assert CU_LDS // (grains * LDS_GRAIN) <= n, (k, n)
             assert CU_LDS // ((grains - 1) * LDS_GRAIN) > n or n == 2, (k, n)
+
+
+def test_sixteen_bit_pipeline_of_single_tiles_keeps_its_wave_slots(kernels):
+    """Single tiles of 16-bit gradients run uncapped because they need every wavefront a compute unit can hold: eight per
+    SIMD (512 registers, granted in eights), six with the addresses of 16 workers, and no LDS for joined steps."""
+    single = [k for k in kernels if KINDS[k.kind] == "pipeline" and k.half and k.form == 1]
+    assert len(single) == 20
+    for k in single:
+        assert 512 // (-(-k.vgprs // 8) * 8) >= (6 if k.P == 16 else 8), k
+        assert k.lds <= (0 if k.few else 1296), k
