@@ -810,6 +810,7 @@ struct mgwfbp_ctx {
     int device = -1;
     int n_cu = 0;
     LaunchSettings set;
+    int32_t resident_end = 0;         // tiles up to here are resident, but for a few that did not fit
     uint64_t serial = 0;              // changes whenever the tables change; never reused within a process
     // device copies
     unsigned char* d_tables = nullptr;   // the segment tables and the tile headers, one block
@@ -820,18 +821,21 @@ namespace {
 
 std::atomic<uint64_t> g_next_serial{1};
 
-// Marks the leading tiles whose w + v bytes (8 per element) fit into the budget.
-void mark_resident_tiles(HostTables& h, uint64_t budget) {
+// Marks the leading tiles whose w + v bytes (8 per element) fit into the budget; the end of the last one marked.
+int32_t mark_resident_tiles(HostTables& h, uint64_t budget) {
     uint64_t used = 0;
-    for (TileHdr& t : h.tiles) {
-        const uint64_t need = static_cast<uint64_t>(t.valid) * 8u;
+    int32_t end = 0;
+    for (size_t i = 0; i < h.tiles.size(); ++i) {
+        const uint64_t need = static_cast<uint64_t>(h.tiles[i].valid) * 8u;
         if (used + need <= budget) {
-            t.flags = 1;
+            h.tiles[i].flags = 1;
             used += need;
+            end = static_cast<int32_t>(i + 1);
         } else {
-            t.flags = 0;
+            h.tiles[i].flags = 0;
         }
     }
+    return end;
 }
 
 // Whether tiles mostly start inside the 128-byte lines (32 binary32 elements) of their tensors: in a tensor that does
@@ -878,7 +882,7 @@ int create_common(mgwfbp_ctx** out, const uint64_t* n_elems, int32_t L, const ui
     c->P = P;
     c->dtype = dtype;
     c->serial = g_next_serial.fetch_add(1);
-    mark_resident_tiles(c->host, c->set.resident_bytes);
+    c->resident_end = mark_resident_tiles(c->host, c->set.resident_bytes);
     c->off_lines = starts_off_lines(c->host);
     if (!c->host.tiles.empty()) c->ragged = static_cast<double>(c->host.n_ragged) / static_cast<double>(c->host.tiles.size());
     if (device) {
@@ -1047,7 +1051,9 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
         if (dev != c->device) return MGWFBP_EINVAL;   // tables live on the device the context was made on
     }
 
-    const LaunchShape s = launch_shape(c->set, {KIND, c->dtype, c->P, count, c->ragged, c->off_lines, reduced != nullptr}, c->n_cu);
+    const double resident = static_cast<double>(std::min(std::max(c->resident_end - sp.t0, 0), count)) / count;
+    const LaunchWork work{KIND, c->dtype, c->P, count, c->ragged, c->off_lines, reduced != nullptr, resident};
+    const LaunchShape s = launch_shape(c->set, work, c->n_cu);
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     const float inv_p = 1.0f / static_cast<float>(c->P);
     auto go = [&](auto grad) {
@@ -1158,7 +1164,7 @@ int mgwfbp_ctx_set_resident_bytes(mgwfbp_ctx* c, uint64_t bytes) {
     if (c == nullptr) return MGWFBP_EINVAL;
     c->set.resident_bytes = bytes;
     c->serial = g_next_serial.fetch_add(1);
-    mark_resident_tiles(c->host, bytes);
+    c->resident_end = mark_resident_tiles(c->host, bytes);
     if (c->on_device && !c->host.tiles.empty())
         return note(hipMemcpy(c->d_tiles, c->host.tiles.data(), c->host.tiles.size() * sizeof(TileHdr),
                               hipMemcpyHostToDevice));

@@ -140,10 +140,10 @@ inline int32_t pack_tiles_per_workgroup(int32_t dtype, int32_t P, int64_t copies
     return copies <= FEW_COPIES || (dtype == MGWFBP_F32 && ragged > SOME_RAGGED) ? 2 : 4;
 }
 
-inline int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int32_t tiles, double ragged, bool reduced) {
+inline int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int32_t tiles, double ragged, bool reduced, int form) {
     const bool wide = dtype == MGWFBP_F32;
     if (wide && tiles < SHORT_LAUNCH_TILES) {
-        const int32_t n = default_workgroups_per_cu(kind, dtype, P, SHORT_LAUNCH_TILES, ragged, reduced);
+        const int32_t n = default_workgroups_per_cu(kind, dtype, P, SHORT_LAUNCH_TILES, ragged, reduced, form);
         return n > 0 ? std::max(n, 18) : n;
     }
     if (ragged > 0.25 && kind != K_REDUCE) return -1;
@@ -157,7 +157,8 @@ inline int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int
         case K_DIRECT: return wide ? (P < 4 ? 25 : P <= 8 ? 16 : 14) : -1;
         default:                                         // pipeline
             if (wide) return P < 6 ? 18 : 14;
-            return !joined_pipeline(dtype, P, tiles, ragged) ? -1 : tiles < LONG_LAUNCH_TILES || !reduced ? 14 : 12;
+            if (form != PAIRS || tiles < SHORT_LAUNCH_TILES) return -1;
+            return tiles < LONG_LAUNCH_TILES || !reduced ? 14 : 12;
     }
 }
 
@@ -193,6 +194,7 @@ struct LaunchWork {
     double ragged;                    // share of the tiles that take the general path
     bool off_lines;                   // a good part of the tiles do not start on the lines of their tensors
     bool reduced;                     // the reduced arena is written
+    double resident;                  // share of the tiles whose w and v are kept cacheable
 };
 
 struct LaunchShape {
@@ -206,18 +208,25 @@ struct LaunchShape {
 
 inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, int n_cu) {
     LaunchShape s{};
+    // A launch too small to fill the chip is bound by the latency of its tiles, not by the memory system: it takes the
+    // burst form (every load of a tile at once, no cap) unless the caller has fixed the pacing.
+    const int32_t burst_tiles = set.burst_tiles < 0 ? default_burst_tiles(w.kind, w.dtype, w.P) : set.burst_tiles;
+    const bool burst = set.step_vecs < 0 || (set.step_vecs == 0 && w.tiles <= burst_tiles);
+    // Pairs of tiles: where the rule says so or the caller has asked for several tiles per workgroup, and neither in the
+    // burst form, which takes one tile at a time, nor where more than an eighth of the tiles are resident, which are taken
+    // one by one (bfloat16, 8 workers, 100,000 tiles: none resident 216 us in pairs against 227 in single tiles, half of
+    // them 242 / 213; the lines between cross at 15 %).
+    const bool pairs = w.kind == K_PIPELINE && w.dtype != MGWFBP_F32 && !burst && w.resident <= 0.125 &&
+                       (set.tiles_per_wg > 0 ? set.tiles_per_wg >= JOIN : joined_pipeline(w.dtype, w.P, w.tiles, w.ragged));
+    s.form = burst ? BURST : pairs ? PAIRS : 1;
     // Tiles per workgroup: PACK runs as single-worker copies, whose tiles are small (one array in, one out), so a
-    // workgroup takes several, two at a time; the 16-bit pipeline takes two at once; every other kind takes one tile
+    // workgroup takes several, two at a time; pairs take two at once; every other kind takes one tile
     // per workgroup.  More only stretches the set of bytes the chip has in flight: the window the workgroups of a
     // compute unit cover together should stay within a few hundred KiB per array.
-    s.tiles_per_wg = set.tiles_per_wg;
-    if (s.tiles_per_wg <= 0) {
-        s.tiles_per_wg = 1;
-        if (w.kind == K_PACK)
-            s.tiles_per_wg = pack_tiles_per_workgroup(w.dtype, w.P, static_cast<int64_t>(w.tiles) * w.P, w.ragged);
-        else if (w.kind == K_PIPELINE && joined_pipeline(w.dtype, w.P, w.tiles, w.ragged))
-            s.tiles_per_wg = JOIN;
-    }
+    s.tiles_per_wg = set.tiles_per_wg > 0 ? set.tiles_per_wg
+                     : w.kind == K_PACK   ? pack_tiles_per_workgroup(w.dtype, w.P, static_cast<int64_t>(w.tiles) * w.P, w.ragged)
+                     : pairs              ? JOIN
+                                          : 1;
     s.units = (w.tiles + s.tiles_per_wg - 1) / s.tiles_per_wg;
     s.grid = s.units;
     if (set.blocks_per_cu > 0 && n_cu > 0 && static_cast<int64_t>(n_cu) * set.blocks_per_cu < s.units)
@@ -226,16 +235,11 @@ inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, 
         s.grid &= ~7;
         s.xcd_contiguous = 1;
     }
-    // Pacing: how many vectors a lane moves per step and how many workgroups may share a compute unit.
-    // Together they set the loads a compute unit has in flight (step_vecs x 4 KiB x workgroups for binary32).
-    // A launch too small to fill the chip is bound by the latency of its tiles, not by the memory system: it
-    // takes the burst form (every load of a tile at once, no cap) unless the caller has fixed the pacing.
-    const int32_t burst_tiles = set.burst_tiles < 0 ? default_burst_tiles(w.kind, w.dtype, w.P) : set.burst_tiles;
-    const bool burst = set.step_vecs < 0 || (set.step_vecs == 0 && w.tiles <= burst_tiles);
-    s.form = burst ? BURST : w.kind == K_PIPELINE && w.dtype != MGWFBP_F32 && s.tiles_per_wg >= JOIN ? PAIRS : 1;
+    // With the form, the workgroups that may share a compute unit set the loads it has in flight (1 KiB of a binary32 array
+    // per vector of a step and workgroup, half that of a 16-bit one).
     s.wgs_per_cu = set.wg_per_cu != 0 ? set.wg_per_cu
                    : burst            ? -1
-                                      : default_workgroups_per_cu(w.kind, w.dtype, w.P, w.tiles, w.ragged, w.reduced);
+                                      : default_workgroups_per_cu(w.kind, w.dtype, w.P, w.tiles, w.ragged, w.reduced, s.form);
     // The few-segments form has no tile headers, so it serves neither the resident share of w and v, which they
     // mark, nor the forms in which a workgroup goes on to tiles far from its first.
     const bool one_turn = s.grid == s.units && !s.xcd_contiguous;

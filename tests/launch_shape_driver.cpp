@@ -17,13 +17,14 @@ int main() {
             LaunchWork w{};
             LaunchSettings set;
             int off, reduced, n_cu;
-            long long resident;
-            if (std::scanf("%d %d %d %d %lf %d %d", &w.kind, &w.dtype, &w.P, &w.tiles, &w.ragged, &off, &reduced) != 7) return 1;
+            long long resident_bytes;
+            if (std::scanf("%d %d %d %d %lf %d %d %lf", &w.kind, &w.dtype, &w.P, &w.tiles, &w.ragged, &off, &reduced,
+                           &w.resident) != 8) return 1;
             if (std::scanf("%d %d %d %d %d %d %lld %d", &set.blocks_per_cu, &set.xcd_contiguous, &set.tiles_per_wg, &set.wg_per_cu,
-                           &set.step_vecs, &set.burst_tiles, &resident, &n_cu) != 8) return 1;
+                           &set.step_vecs, &set.burst_tiles, &resident_bytes, &n_cu) != 8) return 1;
             w.off_lines = off != 0;
             w.reduced = reduced != 0;
-            set.resident_bytes = static_cast<uint64_t>(resident);
+            set.resident_bytes = static_cast<uint64_t>(resident_bytes);
             const LaunchShape s = launch_shape(set, w, n_cu);
             std::printf("%d %d %d %d %d %d %d %d\n", s.tiles_per_wg, s.units, s.grid, s.xcd_contiguous, s.run_log2, s.may_be_few,
                         s.form, s.wgs_per_cu);

@@ -542,6 +542,16 @@ def test_sixteen_bit_pipeline_takes_tiles_in_pairs(P, dtype):
     check_case(small, merged[:12], "pipeline", launch=(1, True, 2), small_launch=0, resident=1 << 17, label="resident share")
 
 
+@pytest.mark.parametrize("P,dtype,resident", [(4, "bf16", 1 << 20), (3, "f16", 8), (8, "bf16", 12 << 20), (8, "f16", 1 << 30)])
+def test_resident_share_where_tiles_would_pair(P, dtype, resident):
+    """A pipeline launch long enough to take 16-bit tiles in pairs, with a part, next to nothing and all of w and v
+    kept cacheable: resident tiles go one by one, and all do beside many of them."""
+    sizes = [1 << 20, 513, 777, 1 << 22, 256, 511]
+    rng = np.random.default_rng(15)
+    p = W.Profile("resident", np.asarray(sizes, np.uint64), rng.uniform(1e-6, 1e-5, len(sizes)), 1e-4, 1e-9, P, dtype, 1.0)
+    check_case(p, [0, 1, 1, 0, 0, 1], "pipeline", misalign=3, resident=resident, label=f"{resident} bytes resident")
+
+
 @pytest.mark.parametrize("mode", ["pipeline", "pipeline_per_group", "staged", "direct", "reduce_update"])
 @pytest.mark.parametrize("tiles", [63, 64, 65, 127, 128, 129, 200])
 def test_runs_of_tiles_per_die(mode, tiles):

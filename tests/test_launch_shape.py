@@ -86,3 +86,46 @@ def test_sixteen_bit_pipeline_of_single_tiles_keeps_its_wave_slots(kernels):
     for k in single:
         assert 512 // (-(-k.vgprs // 8) * 8) >= (6 if k.P == 16 else 8), k
         assert k.lds <= (0 if k.few else 1296), k
+
+
+def shapes(ask, cases):
+    """launch_shape of each case: a dict of what differs from an even f32 pipeline of 8 workers at the defaults."""
+    lines = []
+    for c in cases:
+        c = dict(kind="pipeline", dtype="f32", P=8, tiles=65536, ragged=0.0, off_lines=0, reduced=1, resident=0.0,
+                 blocks_per_cu=0, xcd_contiguous=0, tiles_per_wg=0, wg_per_cu=0, step_vecs=0, burst_tiles=-1,
+                 resident_bytes=0, n_cu=256) | c
+        lines.append("shape %d %d %d %d %r %d %d %r %d %d %d %d %d %d %d %d" % (
+            KINDS.index(c["kind"]), DTYPES.index(c["dtype"]), c["P"], c["tiles"], c["ragged"], c["off_lines"], c["reduced"],
+            c["resident"], c["blocks_per_cu"], c["xcd_contiguous"], c["tiles_per_wg"], c["wg_per_cu"], c["step_vecs"],
+            c["burst_tiles"], c["resident_bytes"], c["n_cu"]))
+    return [Shape(*x) for x in ask(lines)]
+
+
+PAIRS, BURST, SINGLE = -1, 0, 1
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_pairs_and_their_cap_go_together(ask, dtype):
+    """A 16-bit pipeline is capped where its workgroups take pairs of tiles, and nowhere else."""
+    def of(**c):
+        return shapes(ask, [dict(dtype=dtype, **c)])[0]
+    long = of()
+    assert (long.form, long.tiles_per_wg, long.wgs_per_cu) == (PAIRS, 2, 14)
+    assert of(tiles=1 << 18).wgs_per_cu == 12 and of(tiles=1 << 18, reduced=0).wgs_per_cu == 14
+    for single in (of(tiles_per_wg=1), of(resident=0.2, resident_bytes=1 << 20), of(P=2), of(tiles=16383), of(ragged=0.03)):
+        assert (single.form, single.tiles_per_wg, single.wgs_per_cu) == (SINGLE, 1, -1)
+    for burst in (of(step_vecs=-1), of(burst_tiles=1 << 20), of(tiles=3072), of(step_vecs=-1, tiles_per_wg=2)):
+        assert (burst.form, burst.wgs_per_cu) == (BURST, -1)
+    assert of(step_vecs=-1).units == 65536                    # and one tile per workgroup
+    few = of(resident=0.1, resident_bytes=1 << 20)
+    assert (few.form, few.wgs_per_cu) == (PAIRS, 14)
+    asked = of(tiles_per_wg=2, P=2)
+    assert (asked.form, asked.wgs_per_cu) == (PAIRS, 14)
+    asked = of(tiles_per_wg=3, tiles=9000)                    # too short for a cap: every workgroup fits
+    assert (asked.form, asked.units, asked.wgs_per_cu) == (PAIRS, 3000, -1)
+    assert of(wg_per_cu=21).wgs_per_cu == 21 and of(resident=0.2, wg_per_cu=21).wgs_per_cu == 21
+    for kind in KINDS:
+        if kind != "pipeline":
+            assert of(kind=kind).form == SINGLE and of(kind=kind, tiles_per_wg=2).form == SINGLE
+    assert shapes(ask, [dict(tiles_per_wg=2)])[0].form == SINGLE
