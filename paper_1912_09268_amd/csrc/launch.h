@@ -83,9 +83,8 @@ constexpr size_t static_lds(int kind, bool few, int form) {
 //     5303, P = 4: 6455 at 16 / 6153 uncapped, P = 8: 6562 at 14 / 6258 uncapped.
 //   - With many workers there are more arrays to switch between and a smaller window serves them better: pipeline,
 //     binary32, P = 4: 6317 at 18 / 6254 at 14, P = 8: 6299 at 14 / 6229 at 16, P = 12: 6260 / 6076, P = 32: 5899 / 5676.
-//   - A launch of a few rounds of the chip (256 compute units times the cap) should not end in a nearly empty one:
-//     below SHORT_LAUNCH_TILES the cap is 18 at least (pipeline, binary32, P = 8, one group of 4096 / 8192 / 16384
-//     tiles: 15.8 / 30.4 / 58.0 us at 18 against 19.4 / 32.3 / 58.0 us at 14).
+//   - A launch of a few rounds of the chip (the compute units times the cap) should not end in a nearly empty one, see
+//     short_launch_cap().
 //   - A ragged tile (see general_tile) spends most of its time waiting for one thing after the other: a model that
 //     consists of them needs every wave slot (45 % ragged, binary32: pipeline P = 3: 4868 uncapped / 4204 at 18,
 //     reduce_update P = 8: 5801 / 5270 at 14; with 11 % the caps are as good or better).
@@ -142,17 +141,14 @@ inline int32_t pack_tiles_per_workgroup(int32_t dtype, int32_t P, int64_t copies
 
 inline int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int32_t tiles, double ragged, bool reduced, int form) {
     const bool wide = dtype == MGWFBP_F32;
-    if (wide && tiles < SHORT_LAUNCH_TILES) {
-        const int32_t n = default_workgroups_per_cu(kind, dtype, P, SHORT_LAUNCH_TILES, ragged, reduced, form);
-        return n > 0 ? std::max(n, 18) : n;
-    }
     if (ragged > 0.25 && kind != K_REDUCE) return -1;
     switch (kind) {
         case K_REDUCE: return wide ? (P < 4 ? -1 : P < 8 ? 16 : 14) : (P == 8 || P == 16 ? 16 : -1);
         case K_UPDATE: return -1;                        // 20 bytes per element, nothing per worker
         case K_PACK:
             if (many_halves(dtype, P, static_cast<int64_t>(tiles) * P, ragged)) return 21;
-            return wide && ragged <= SOME_RAGGED ? 14 : -1;
+            if (!wide || ragged > SOME_RAGGED) return -1;
+            return tiles < SHORT_LAUNCH_TILES ? 18 : 14;
         case K_REDUCE_UPDATE: return wide ? (P < 4 ? 25 : P < 8 ? 16 : 14) : -1;
         case K_DIRECT: return wide ? (P < 4 ? 25 : P <= 8 ? 16 : 14) : -1;
         default:                                         // pipeline
@@ -160,6 +156,24 @@ inline int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int
             if (form != PAIRS || tiles < SHORT_LAUNCH_TILES) return -1;
             return tiles < LONG_LAUNCH_TILES || !reduced ? 14 : 12;
     }
+}
+
+// The cap of a binary32 launch of a few rounds, next to the `cap` of long ones: all workgroups at once where 25 per
+// compute unit hold them (20 with 16 workers, whose kernels have registers for 16 to 20), else the neighbour whose rounds
+// come out fullest.  Pipeline, 8 workers, one tensor of 5000 tiles (19.5 per compute unit): 21.4 / 22.1 / 22.5 us in two
+// rounds at 14 / 16 / 18, 19.1 in one.  Per cent above the best of 14 / 16 / 18 / 21, mean of reduce, direct and pipeline with
+// 8, 12, 16 and 32 workers: 7100 tiles 0.2 / 0.7 / 2.9 / 5.0, 7200 12.0 / 0.3 / 1.9 / 3.4, 8250 6.0 / 9.4 / 0.0 / 1.7, 9250 0.3 / 4.2 / 7.8 /
+// 1.8, 11000 7.5 / 0.0 / 2.3 / 6.6, 13000 1.4 / 5.3 / 0.3 / 2.2, 13900 0.5 / 2.8 / 5.7 / 1.9, 18000 2.3 / 1.5 / 0.4 / 3.0, 24000 0.9 / 0.2 /
+// 3.0 / 2.4; from some 50,000 tiles on the rounds have blurred (direct, 8 workers, 65,000 tiles: 123.7 us at the cap of long
+// launches, 127.8 at the fuller neighbour).  A cap that suits few workers (25, none) holds at any length.
+constexpr int32_t FEW_ROUNDS_TILES = 49152;
+inline int32_t short_launch_cap(int32_t cap, int32_t P, int32_t units, int n_cu) {
+    if (cap <= 0 || cap >= 25) return cap;
+    const int32_t per_cu = (units + n_cu - 1) / n_cu;
+    if (per_cu <= (P == 16 ? 20 : 25)) return 25;
+    auto slots = [&](int32_t n) { return (per_cu + n - 1) / n * n; };      // of all rounds, per compute unit
+    auto fuller = [&](int32_t a, int32_t b) { return slots(a) <= slots(b) ? a : b; };
+    return cap < 16 ? fuller(fuller(14, 16), 18) : fuller(18, 21);
 }
 
 // Units per die and turn (log2), where tiles start inside lines (see unit_of): the kinds that write w and v gain,
@@ -237,9 +251,12 @@ inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, 
     }
     // With the form, the workgroups that may share a compute unit set the loads it has in flight (1 KiB of a binary32 array
     // per vector of a step and workgroup, half that of a 16-bit one).
-    s.wgs_per_cu = set.wg_per_cu != 0 ? set.wg_per_cu
-                   : burst            ? -1
-                                      : default_workgroups_per_cu(w.kind, w.dtype, w.P, w.tiles, w.ragged, w.reduced, s.form);
+    s.wgs_per_cu = set.wg_per_cu;
+    if (s.wgs_per_cu == 0) {
+        s.wgs_per_cu = burst ? -1 : default_workgroups_per_cu(w.kind, w.dtype, w.P, w.tiles, w.ragged, w.reduced, s.form);
+        if (w.dtype == MGWFBP_F32 && w.kind != K_PACK && w.tiles < FEW_ROUNDS_TILES)
+            s.wgs_per_cu = short_launch_cap(s.wgs_per_cu, w.P, s.units, n_cu > 0 ? n_cu : 256);
+    }
     // The few-segments form has no tile headers, so it serves neither the resident share of w and v, which they
     // mark, nor the forms in which a workgroup goes on to tiles far from its first.
     const bool one_turn = s.grid == s.units && !s.xcd_contiguous;

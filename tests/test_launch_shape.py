@@ -129,3 +129,25 @@ def test_pairs_and_their_cap_go_together(ask, dtype):
         if kind != "pipeline":
             assert of(kind=kind).form == SINGLE and of(kind=kind, tiles_per_wg=2).form == SINGLE
     assert shapes(ask, [dict(tiles_per_wg=2)])[0].form == SINGLE
+
+
+@pytest.mark.parametrize("kind,P,long", [("pipeline", 8, 14), ("reduce", 16, 14), ("reduce_update", 32, 14), ("direct", 12, 14),
+                                         ("pipeline", 4, 18), ("reduce", 4, 16), ("direct", 8, 16)])
+def test_short_binary32_launches_fill_their_rounds(ask, kind, P, long):
+    """From the burst form up to 49151 tiles no neighbour of the cap taken would have fuller rounds, and a launch that
+    fits at once runs at once; longer ones keep the cap of long launches."""
+    tiles = list(range(3073, 49152, 197)) + [4096, 5120, 5121, 6400, 6401, 7168, 8192, 49151]
+    got = shapes(ask, [dict(kind=kind, P=P, tiles=t) for t in tiles])
+    near = (14, 16, 18) if long == 14 else (18, 21)
+    for t, s in zip(tiles, got):
+        per_cu = -(-t // 256)
+        if per_cu <= (20 if P == 16 else 25):
+            assert s.wgs_per_cu == 25, t
+        else:
+            assert s.wgs_per_cu in near, t
+            assert -(-per_cu // s.wgs_per_cu) * s.wgs_per_cu == min(-(-per_cu // n) * n for n in near), t
+    assert {s.wgs_per_cu for s in shapes(ask, [dict(kind=kind, P=P, tiles=t) for t in (49152, 1 << 20)])} == {long}
+    assert shapes(ask, [dict(kind=kind, P=P, tiles=6000, n_cu=0)]) == shapes(ask, [dict(kind=kind, P=P, tiles=6000)])
+    assert shapes(ask, [dict(kind=kind, P=P, tiles=6000, wg_per_cu=11)])[0].wgs_per_cu == 11
+    for few in ("reduce", "reduce_update", "direct"):              # few workers: the cap of long launches at any length
+        assert shapes(ask, [dict(kind=few, P=3, tiles=9000)])[0].wgs_per_cu == (-1 if few == "reduce" else 25)
