@@ -177,7 +177,6 @@ template <typename GradT> struct Args : CallArgs<GradT> {      // table form: wh
     int32_t turn;                    // units from one of a workgroup's turns to its next: the workgroups of a walk
     int16_t clip_lo, clip_hi;        // first element wanted of the first tile, end of those wanted of the last one
 };
-constexpr int FEW = 8;
 template <typename GradT> struct FewArgs : CallArgs<GradT> {   // few-segments form: the segments come along
     int32_t layer_hi;                // tensor of segment 0; segment j is tensor layer_hi - j
     int16_t start0;                  // first element of segment 0; all positions count from the first tile's start
@@ -1052,7 +1051,7 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
     }
 
     const double resident = static_cast<double>(std::min(std::max(c->resident_end - sp.t0, 0), count)) / count;
-    const LaunchWork work{KIND, c->dtype, c->P, count, c->ragged, c->off_lines, reduced != nullptr, resident};
+    const LaunchWork work{KIND, c->dtype, c->P, count, c->ragged, c->off_lines, reduced != nullptr, resident, sp.s1 - sp.s0};
     const LaunchShape s = launch_shape(c->set, work, c->n_cu);
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     const float inv_p = 1.0f / static_cast<float>(c->P);

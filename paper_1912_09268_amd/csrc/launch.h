@@ -159,7 +159,7 @@ inline int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int
 }
 
 // The cap of a binary32 launch of a few rounds, next to the `cap` of long ones: all workgroups at once where 25 per
-// compute unit hold them (20 with 16 workers, whose kernels have registers for 16 to 20), else the neighbour whose rounds
+// compute unit hold them (20 and 16 in the few-segments and the table form with 16 workers: their registers), else the neighbour whose rounds
 // come out fullest.  Pipeline, 8 workers, one tensor of 5000 tiles (19.5 per compute unit): 21.4 / 22.1 / 22.5 us in two
 // rounds at 14 / 16 / 18, 19.1 in one.  Per cent above the best of 14 / 16 / 18 / 21, mean of reduce, direct and pipeline with
 // 8, 12, 16 and 32 workers: 7100 tiles 0.2 / 0.7 / 2.9 / 5.0, 7200 12.0 / 0.3 / 1.9 / 3.4, 8250 6.0 / 9.4 / 0.0 / 1.7, 9250 0.3 / 4.2 / 7.8 /
@@ -167,13 +167,14 @@ inline int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int
 // 3.0 / 2.4; from some 50,000 tiles on the rounds have blurred (direct, 8 workers, 65,000 tiles: 123.7 us at the cap of long
 // launches, 127.8 at the fuller neighbour).  A cap that suits few workers (25, none) holds at any length.
 constexpr int32_t FEW_ROUNDS_TILES = 49152;
-inline int32_t short_launch_cap(int32_t cap, int32_t P, int32_t units, int n_cu) {
+inline int32_t short_launch_cap(int32_t cap, int32_t P, bool few, int32_t per_cu) {
     if (cap <= 0 || cap >= 25) return cap;
-    const int32_t per_cu = (units + n_cu - 1) / n_cu;
-    if (per_cu <= (P == 16 ? 20 : 25)) return 25;
+    const int32_t most = P != 16 ? 25 : few ? 20 : 16;
+    if (per_cu <= most) return 25;
     auto slots = [&](int32_t n) { return (per_cu + n - 1) / n * n; };      // of all rounds, per compute unit
     auto fuller = [&](int32_t a, int32_t b) { return slots(a) <= slots(b) ? a : b; };
-    return cap < 16 ? fuller(fuller(14, 16), 18) : fuller(18, 21);
+    if (cap >= 16) return fuller(18, 21);
+    return most < 18 ? fuller(14, 16) : fuller(fuller(14, 16), 18);
 }
 
 // Units per die and turn (log2), where tiles start inside lines (see unit_of): the kinds that write w and v gain,
@@ -184,6 +185,29 @@ inline int8_t run_log2_of(int kind) {
         case K_UPDATE: case K_REDUCE_UPDATE: case K_DIRECT: return 3;
         default: return 0;
     }
+}
+
+// Which of the launches that could take the few-segments form do.  It reaches a ragged tile's data several memory trips
+// sooner (a launch of up to 1000 tiles over five tensors takes 0.76-0.9 of the table form's time, over one tensor that ends in a
+// ragged tile 0.9-1.0), but full tiles cost it a little more, and that adds up where every wavefront counts.  Time over that
+// of the table form, launches over one tensor unless said otherwise:
+//   - REDUCE has no ragged tiles but at the groups' ends: 0.94-1.04 up to 2000 tiles; 1 worker at 3500 / 14000 / 60000 tiles
+//     binary32 1.08 / 1.10 / 1.09, bfloat16 1.05 / 1.17 / 1.26, 3 workers bfloat16 1.09 / 1.14 / 1.16.
+//   - 16-bit PACK, 2 workers: copies of tiles up to 4096 1.05-1.10 (ragged end: 0.95), 7000 / 18000 / 48000 1.11 / 1.12 / 1.08
+//     (1.00 / 1.03 / 1.06), beyond 65536 0.97-1.00.
+//   - The other kinds on 16-bit gradients, which run uncapped: direct, 2 / 4 / 8 workers, 3500 tiles 1.05 / 1.06 / 1.06, 5500 1.06 /
+//     1.06 / 1.05, 10500 1.05 / 1.04 / 1.04, 60000 1.01 / 1.01 / 1.03 (reduce_update 1.01-1.04, pipeline 1.01-1.02); but its kernels take
+//     fewer registers and hold 28 to 32 wavefronts per compute unit instead of 24 to 28, so that 25 to 32 tiles per compute
+//     unit run at once: 6800 tiles direct 1.06 / 1.05 / 0.86, reduce_update 0.97 / 1.03 / 0.84, 7800 tiles 0.94 / 0.91 / 0.93; and 49 to 56
+//     in two rounds: reduce_update 32 workers 0.86.  Over five tensors 0.9-1.03.
+//   - binary32: 0.95-1.04 over one tensor, 0.9-1.02 over five.
+constexpr int FEW = 8;                // segments that fit into a launch's arguments
+inline bool few_form_pays(int kind, int32_t dtype, int32_t P, int32_t tiles, int32_t segments, int32_t per_cu) {
+    if (kind == K_REDUCE) return tiles <= 2048;
+    if (dtype == MGWFBP_F32 || segments > 1) return true;
+    const int64_t copies = static_cast<int64_t>(tiles) * P;
+    if (kind == K_PACK) return copies <= 4096 || copies > FEW_COPIES;
+    return tiles <= 3072 || (per_cu > 24 && per_cu <= 32) || (per_cu > 48 && per_cu <= 56);
 }
 
 // What a caller has fixed (mgwfbp_ctx_set_*); the initial values are the library's defaults.
@@ -209,6 +233,7 @@ struct LaunchWork {
     bool off_lines;                   // a good part of the tiles do not start on the lines of their tensors
     bool reduced;                     // the reduced arena is written
     double resident;                  // share of the tiles whose w and v are kept cacheable
+    int32_t segments;
 };
 
 struct LaunchShape {
@@ -249,18 +274,21 @@ inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, 
         s.grid &= ~7;
         s.xcd_contiguous = 1;
     }
+    const int compute_units = n_cu > 0 ? n_cu : 256;
+    const int32_t per_cu = (s.units + compute_units - 1) / compute_units;
+    // The few-segments form has no tile headers, so it serves neither the resident share of w and v, which they
+    // mark, nor the forms in which a workgroup goes on to tiles far from its first.
+    const bool one_turn = s.grid == s.units && !s.xcd_contiguous;
+    s.may_be_few = one_turn && !(updates(w.kind) && set.resident_bytes > 0) && (w.segments <= FEW || !needs_owner(w.kind)) &&
+                   few_form_pays(w.kind, w.dtype, w.P, w.tiles, w.segments, per_cu);
     // With the form, the workgroups that may share a compute unit set the loads it has in flight (1 KiB of a binary32 array
     // per vector of a step and workgroup, half that of a 16-bit one).
     s.wgs_per_cu = set.wg_per_cu;
     if (s.wgs_per_cu == 0) {
         s.wgs_per_cu = burst ? -1 : default_workgroups_per_cu(w.kind, w.dtype, w.P, w.tiles, w.ragged, w.reduced, s.form);
         if (w.dtype == MGWFBP_F32 && w.kind != K_PACK && w.tiles < FEW_ROUNDS_TILES)
-            s.wgs_per_cu = short_launch_cap(s.wgs_per_cu, w.P, s.units, n_cu > 0 ? n_cu : 256);
+            s.wgs_per_cu = short_launch_cap(s.wgs_per_cu, w.P, s.may_be_few, per_cu);
     }
-    // The few-segments form has no tile headers, so it serves neither the resident share of w and v, which they
-    // mark, nor the forms in which a workgroup goes on to tiles far from its first.
-    const bool one_turn = s.grid == s.units && !s.xcd_contiguous;
-    s.may_be_few = one_turn && !(updates(w.kind) && set.resident_bytes > 0);
     s.run_log2 = one_turn && w.off_lines ? run_log2_of(w.kind) : int8_t{0};
     return s;
 }

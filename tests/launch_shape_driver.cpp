@@ -18,8 +18,8 @@ int main() {
             LaunchSettings set;
             int off, reduced, n_cu;
             long long resident_bytes;
-            if (std::scanf("%d %d %d %d %lf %d %d %lf", &w.kind, &w.dtype, &w.P, &w.tiles, &w.ragged, &off, &reduced,
-                           &w.resident) != 8) return 1;
+            if (std::scanf("%d %d %d %d %lf %d %d %lf %d", &w.kind, &w.dtype, &w.P, &w.tiles, &w.ragged, &off, &reduced,
+                           &w.resident, &w.segments) != 9) return 1;
             if (std::scanf("%d %d %d %d %d %d %lld %d", &set.blocks_per_cu, &set.xcd_contiguous, &set.tiles_per_wg, &set.wg_per_cu,
                            &set.step_vecs, &set.burst_tiles, &resident_bytes, &n_cu) != 8) return 1;
             w.off_lines = off != 0;

@@ -92,12 +92,12 @@ def shapes(ask, cases):
     """launch_shape of each case: a dict of what differs from an even f32 pipeline of 8 workers at the defaults."""
     lines = []
     for c in cases:
-        c = dict(kind="pipeline", dtype="f32", P=8, tiles=65536, ragged=0.0, off_lines=0, reduced=1, resident=0.0,
+        c = dict(kind="pipeline", dtype="f32", P=8, tiles=65536, ragged=0.0, off_lines=0, reduced=1, resident=0.0, segments=9,
                  blocks_per_cu=0, xcd_contiguous=0, tiles_per_wg=0, wg_per_cu=0, step_vecs=0, burst_tiles=-1,
                  resident_bytes=0, n_cu=256) | c
-        lines.append("shape %d %d %d %d %r %d %d %r %d %d %d %d %d %d %d %d" % (
+        lines.append("shape %d %d %d %d %r %d %d %r %d %d %d %d %d %d %d %d %d" % (
             KINDS.index(c["kind"]), DTYPES.index(c["dtype"]), c["P"], c["tiles"], c["ragged"], c["off_lines"], c["reduced"],
-            c["resident"], c["blocks_per_cu"], c["xcd_contiguous"], c["tiles_per_wg"], c["wg_per_cu"], c["step_vecs"],
+            c["resident"], c["segments"], c["blocks_per_cu"], c["xcd_contiguous"], c["tiles_per_wg"], c["wg_per_cu"], c["step_vecs"],
             c["burst_tiles"], c["resident_bytes"], c["n_cu"]))
     return [Shape(*x) for x in ask(lines)]
 
@@ -136,18 +136,45 @@ def test_pairs_and_their_cap_go_together(ask, dtype):
 def test_short_binary32_launches_fill_their_rounds(ask, kind, P, long):
     """From the burst form up to 49151 tiles no neighbour of the cap taken would have fuller rounds, and a launch that
     fits at once runs at once; longer ones keep the cap of long launches."""
-    tiles = list(range(3073, 49152, 197)) + [4096, 5120, 5121, 6400, 6401, 7168, 8192, 49151]
+    end = 49152
+    tiles = list(range(3073, end, 97)) + [4096, 5120, 5121, 6400, 6401, 7168, 8192, end - 1]
     got = shapes(ask, [dict(kind=kind, P=P, tiles=t) for t in tiles])
-    near = (14, 16, 18) if long == 14 else (18, 21)
+    near = (18, 21) if long != 14 else (14, 16) if P == 16 else (14, 16, 18)      # 16 workers: registers for 16
     for t, s in zip(tiles, got):
         per_cu = -(-t // 256)
-        if per_cu <= (20 if P == 16 else 25):
+        if per_cu <= (16 if P == 16 else 25):
             assert s.wgs_per_cu == 25, t
         else:
             assert s.wgs_per_cu in near, t
             assert -(-per_cu // s.wgs_per_cu) * s.wgs_per_cu == min(-(-per_cu // n) * n for n in near), t
-    assert {s.wgs_per_cu for s in shapes(ask, [dict(kind=kind, P=P, tiles=t) for t in (49152, 1 << 20)])} == {long}
+    assert {s.wgs_per_cu for s in shapes(ask, [dict(kind=kind, P=P, tiles=t) for t in (end, 1 << 20)])} == {long}
     assert shapes(ask, [dict(kind=kind, P=P, tiles=6000, n_cu=0)]) == shapes(ask, [dict(kind=kind, P=P, tiles=6000)])
     assert shapes(ask, [dict(kind=kind, P=P, tiles=6000, wg_per_cu=11)])[0].wgs_per_cu == 11
     for few in ("reduce", "reduce_update", "direct"):              # few workers: the cap of long launches at any length
         assert shapes(ask, [dict(kind=few, P=3, tiles=9000)])[0].wgs_per_cu == (-1 if few == "reduce" else 25)
+
+
+def test_few_segments_form_where_it_pays(ask):
+    """The few-segments form is left to the launches it is no slower for: not reductions and single 16-bit tensors
+    longer than it pays, and never more segments than the arguments hold."""
+    def few(**c):
+        return bool(shapes(ask, [dict(segments=1) | c])[0].may_be_few)
+    for dtype in DTYPES:
+        for P in (1, 3, 8):
+            assert few(kind="reduce", tiles=2048, dtype=dtype, P=P, segments=40)       # its segments are groups
+            assert not few(kind="reduce", tiles=2049, dtype=dtype, P=P)
+    for kind in ("update", "reduce_update", "pipeline", "direct"):
+        assert all(few(kind=kind, tiles=t) for t in (1, 3072, 3073, 1 << 20))
+        assert few(kind=kind, tiles=100, segments=8) and not few(kind=kind, tiles=100, segments=9)
+        assert not few(kind=kind, tiles=100, resident_bytes=8) and not few(kind=kind, tiles=1000, xcd_contiguous=1)
+        for dtype in ("bf16", "f16"):
+            per_wg = dict(tiles_per_wg=1)
+            assert all(few(kind=kind, dtype=dtype, tiles=t, **per_wg) for t in (1, 3072, 6145, 8192, 12289, 14336))
+            assert not any(few(kind=kind, dtype=dtype, tiles=t, **per_wg) for t in (3073, 6144, 8193, 12288, 14337, 1 << 20))
+            assert all(few(kind=kind, dtype=dtype, tiles=t, segments=2) for t in (3073, 6144, 8193, 1 << 20))
+    assert few(kind="pack", tiles=1 << 20) and few(kind="pack", dtype="bf16", tiles=512) and few(kind="pack", dtype="bf16", tiles=8193)
+    assert not few(kind="pack", dtype="bf16", tiles=513) and not few(kind="pack", dtype="bf16", tiles=8192)
+    assert few(kind="pack", dtype="bf16", tiles=513, segments=2)
+    # with 16 workers the table form has registers for 16 wavefronts per compute unit, the few-segments form for 20
+    caps = shapes(ask, [dict(P=16, tiles=t, segments=n) for t, n in ((4096, 9), (4097, 9), (5120, 1), (5121, 1))])
+    assert [s.wgs_per_cu for s in caps] == [25, 14, 25, 14]
