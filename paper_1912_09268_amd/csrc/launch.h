@@ -164,9 +164,10 @@ inline int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int
 // rounds at 14 / 16 / 18, 19.1 in one.  Per cent above the best of 14 / 16 / 18 / 21, mean of reduce, direct and pipeline with
 // 8, 12, 16 and 32 workers: 7100 tiles 0.2 / 0.7 / 2.9 / 5.0, 7200 12.0 / 0.3 / 1.9 / 3.4, 8250 6.0 / 9.4 / 0.0 / 1.7, 9250 0.3 / 4.2 / 7.8 /
 // 1.8, 11000 7.5 / 0.0 / 2.3 / 6.6, 13000 1.4 / 5.3 / 0.3 / 2.2, 13900 0.5 / 2.8 / 5.7 / 1.9, 18000 2.3 / 1.5 / 0.4 / 3.0, 24000 0.9 / 0.2 /
-// 3.0 / 2.4; from some 50,000 tiles on the rounds have blurred (direct, 8 workers, 65,000 tiles: 123.7 us at the cap of long
-// launches, 127.8 at the fuller neighbour).  A cap that suits few workers (25, none) holds at any length.
-constexpr int32_t FEW_ROUNDS_TILES = 49152;
+// 3.0 / 2.4.  The longer a tile takes and the more rounds there are, the more these blur (direct, 8 workers, 65,000 tiles:
+// 123.7 us at the cap of long launches, 127.8 at the fuller neighbour; pipeline, 32 workers, 18,000 tiles 219.8 / 227.8,
+// 16,000 184.5 / 184.1; 12 workers, 40,000 tiles 192.0 / 189.0).  A cap that suits few workers (25, none) holds at any length.
+inline bool few_rounds(int32_t tiles, int32_t P) { return tiles < 49152 && static_cast<int64_t>(tiles) * P < 500000; }
 inline int32_t short_launch_cap(int32_t cap, int32_t P, bool few, int32_t per_cu) {
     if (cap <= 0 || cap >= 25) return cap;
     const int32_t most = P != 16 ? 25 : few ? 20 : 16;
@@ -286,7 +287,7 @@ inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, 
     s.wgs_per_cu = set.wg_per_cu;
     if (s.wgs_per_cu == 0) {
         s.wgs_per_cu = burst ? -1 : default_workgroups_per_cu(w.kind, w.dtype, w.P, w.tiles, w.ragged, w.reduced, s.form);
-        if (w.dtype == MGWFBP_F32 && w.kind != K_PACK && w.tiles < FEW_ROUNDS_TILES)
+        if (w.dtype == MGWFBP_F32 && w.kind != K_PACK && few_rounds(w.tiles, w.P))
             s.wgs_per_cu = short_launch_cap(s.wgs_per_cu, w.P, s.may_be_few, per_cu);
     }
     s.run_log2 = one_turn && w.off_lines ? run_log2_of(w.kind) : int8_t{0};

@@ -134,9 +134,9 @@ def test_pairs_and_their_cap_go_together(ask, dtype):
 @pytest.mark.parametrize("kind,P,long", [("pipeline", 8, 14), ("reduce", 16, 14), ("reduce_update", 32, 14), ("direct", 12, 14),
                                          ("pipeline", 4, 18), ("reduce", 4, 16), ("direct", 8, 16)])
 def test_short_binary32_launches_fill_their_rounds(ask, kind, P, long):
-    """From the burst form up to 49151 tiles no neighbour of the cap taken would have fuller rounds, and a launch that
+    """From the burst form up to 49151 tiles, less with many workers, no neighbour of the cap taken would have fuller rounds, and a launch that
     fits at once runs at once; longer ones keep the cap of long launches."""
-    end = 49152
+    end = min(49152, -(-500000 // P))
     tiles = list(range(3073, end, 97)) + [4096, 5120, 5121, 6400, 6401, 7168, 8192, end - 1]
     got = shapes(ask, [dict(kind=kind, P=P, tiles=t) for t in tiles])
     near = (18, 21) if long != 14 else (14, 16) if P == 16 else (14, 16, 18)      # 16 workers: registers for 16
