@@ -114,8 +114,14 @@ inline int32_t default_burst_tiles(int kind, int32_t dtype, int32_t P) {
 // binary32 arrays are most of the traffic.  A short launch needs its tiles spread over the chip.
 // Nor does a model of many ragged tiles, whose turns come one after the other in a pair: with 0.9 / 2 / 3 / 11 / 45 % of
 // its tiles ragged, bf16, P = 8: 5706 / 5583 / 5789 / 5408 / 4364 joined, 5528 / 5446 / 5891 / 5532 / 4640 not.
+// In launches of up to twice SHORT_LAUNCH_TILES a single ragged tile counts where the worker count is not a compiled one: it
+// takes its workers four at a time, after or before the other tile of its pair, and the launch waits for it (bfloat16, one
+// tensor that ends in a ragged second half of a pair, time over that of single tiles: 16,500 tiles 6 / 12 / 32 workers 1.09 /
+// 1.13 / 1.17, 4 / 8 / 16 workers 1.01 / 1.02 / 1.02; 24,000 tiles 1.04 / 1.06 / 1.08; 31,000 tiles 1.00 / 1.00 / 1.01, from 45,000 on
+// below 1; without it 0.9-1.0).
 inline bool joined_pipeline(int32_t dtype, int32_t P, int32_t tiles, double ragged) {
-    return dtype != MGWFBP_F32 && P >= 3 && tiles >= SHORT_LAUNCH_TILES && ragged < 0.025;
+    const bool compiled = P == 4 || P == 8 || P == 16;
+    return dtype != MGWFBP_F32 && P >= 3 && tiles >= (compiled || ragged == 0 ? 1 : 2) * SHORT_LAUNCH_TILES && ragged < 0.025;
 }
 
 // Tiles per workgroup of a PACK, which copies two of them per step: 4 KiB of a worker's binary32 gradients at 14
@@ -158,15 +164,16 @@ inline int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int
     }
 }
 
-// The cap of a binary32 launch of a few rounds, next to the `cap` of long ones: all workgroups at once where 25 per
-// compute unit hold them (20 and 16 in the few-segments and the table form with 16 workers: their registers), else the neighbour whose rounds
+// The cap of a launch of a few rounds, binary32 or in pairs of tiles, next to the `cap` of long ones: all workgroups at once where 25 per
+// compute unit hold them (16 workers: 20 in the few-segments form, 16 in the table form and in pairs, by their registers), else the neighbour whose rounds
 // come out fullest.  Pipeline, 8 workers, one tensor of 5000 tiles (19.5 per compute unit): 21.4 / 22.1 / 22.5 us in two
 // rounds at 14 / 16 / 18, 19.1 in one.  Per cent above the best of 14 / 16 / 18 / 21, mean of reduce, direct and pipeline with
 // 8, 12, 16 and 32 workers: 7100 tiles 0.2 / 0.7 / 2.9 / 5.0, 7200 12.0 / 0.3 / 1.9 / 3.4, 8250 6.0 / 9.4 / 0.0 / 1.7, 9250 0.3 / 4.2 / 7.8 /
 // 1.8, 11000 7.5 / 0.0 / 2.3 / 6.6, 13000 1.4 / 5.3 / 0.3 / 2.2, 13900 0.5 / 2.8 / 5.7 / 1.9, 18000 2.3 / 1.5 / 0.4 / 3.0, 24000 0.9 / 0.2 /
 // 3.0 / 2.4.  The longer a tile takes and the more rounds there are, the more these blur (direct, 8 workers, 65,000 tiles:
 // 123.7 us at the cap of long launches, 127.8 at the fuller neighbour; pipeline, 32 workers, 18,000 tiles 219.8 / 227.8,
-// 16,000 184.5 / 184.1; 12 workers, 40,000 tiles 192.0 / 189.0).  A cap that suits few workers (25, none) holds at any length.
+// 16,000 184.5 / 184.1; 12 workers, 40,000 tiles 192.0 / 189.0).  Pairs, bfloat16, 16,000 tiles at 14 / 16 / 18: 8 workers 38.7 / 36.3 /
+// 37.1 us, 32 workers 111.1 / 100.9 / 103.2; 40,000 tiles 86.2 / 87.0 / 87.7, 253.3 / 254.1 / 262.8.  A cap that suits few workers (25, none) holds at any length.
 inline bool few_rounds(int32_t tiles, int32_t P) { return tiles < 49152 && static_cast<int64_t>(tiles) * P < 500000; }
 inline int32_t short_launch_cap(int32_t cap, int32_t P, bool few, int32_t per_cu) {
     if (cap <= 0 || cap >= 25) return cap;
@@ -287,8 +294,8 @@ inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, 
     s.wgs_per_cu = set.wg_per_cu;
     if (s.wgs_per_cu == 0) {
         s.wgs_per_cu = burst ? -1 : default_workgroups_per_cu(w.kind, w.dtype, w.P, w.tiles, w.ragged, w.reduced, s.form);
-        if (w.dtype == MGWFBP_F32 && w.kind != K_PACK && few_rounds(w.tiles, w.P))
-            s.wgs_per_cu = short_launch_cap(s.wgs_per_cu, w.P, s.may_be_few, per_cu);
+        if (s.form == PAIRS ? w.tiles < 2 * SHORT_LAUNCH_TILES : w.dtype == MGWFBP_F32 && w.kind != K_PACK && few_rounds(w.tiles, w.P))
+            s.wgs_per_cu = short_launch_cap(s.wgs_per_cu, w.P, s.may_be_few && s.form != PAIRS, per_cu);
     }
     s.run_log2 = one_turn && w.off_lines ? run_log2_of(w.kind) : int8_t{0};
     return s;

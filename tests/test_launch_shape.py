@@ -125,6 +125,13 @@ def test_pairs_and_their_cap_go_together(ask, dtype):
     asked = of(tiles_per_wg=3, tiles=9000)                    # too short for a cap: every workgroup fits
     assert (asked.form, asked.units, asked.wgs_per_cu) == (PAIRS, 3000, -1)
     assert of(wg_per_cu=21).wgs_per_cu == 21 and of(resident=0.2, wg_per_cu=21).wgs_per_cu == 21
+    assert [of(tiles=t).wgs_per_cu for t in (16384, 16500, 17000, 20000, 32767, 32768)] == [16, 18, 18, 14, 16, 14]     # rounds
+    for P in (3, 6, 12, 32, 64):                              # not compiled: a ragged tile keeps short launches from pairing
+        assert of(P=P, tiles=16384).form == PAIRS and of(P=P, tiles=32767, ragged=1e-5).form == SINGLE
+        assert of(P=P, tiles=32768, ragged=0.02).form == PAIRS
+    for P in (4, 8, 16):
+        assert of(P=P, tiles=16384, ragged=0.02).form == PAIRS
+    assert of(P=16, tiles=16500, segments=1).wgs_per_cu == 14                         # registers for 16
     for kind in KINDS:
         if kind != "pipeline":
             assert of(kind=kind).form == SINGLE and of(kind=kind, tiles_per_wg=2).form == SINGLE
