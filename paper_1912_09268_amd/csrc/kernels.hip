@@ -804,8 +804,6 @@ struct mgwfbp_ctx {
     int32_t P = 0;
     int32_t dtype = 0;
     bool on_device = false;
-    bool off_lines = false;           // a good part of the tiles do not start on the lines of their tensors
-    double ragged = 0;                // share of the tiles that take the general path
     int device = -1;
     int n_cu = 0;
     LaunchSettings set;
@@ -835,18 +833,6 @@ int32_t mark_resident_tiles(HostTables& h, uint64_t budget) {
         }
     }
     return end;
-}
-
-// Whether tiles mostly start inside the 128-byte lines (32 binary32 elements) of their tensors: in a tensor that does
-// not begin on a multiple of 32 arena elements, and, as views of one flat buffer, in one whose neighbours' sizes are
-// no such multiples.  Both show in the sizes, weighted by what they hold.
-bool starts_off_lines(const HostTables& h) {
-    uint64_t off = 0, all = 0;
-    for (size_t i = 0; i < h.tensor_n.size(); ++i) {
-        all += h.tensor_n[i];
-        if ((h.tensor_n[i] | h.tensor_off[i]) % 32 != 0) off += h.tensor_n[i];
-    }
-    return off > all / 4;
 }
 
 // Both parts of the block start on multiples of 256 bytes.
@@ -882,8 +868,6 @@ int create_common(mgwfbp_ctx** out, const uint64_t* n_elems, int32_t L, const ui
     c->dtype = dtype;
     c->serial = g_next_serial.fetch_add(1);
     c->resident_end = mark_resident_tiles(c->host, c->set.resident_bytes);
-    c->off_lines = starts_off_lines(c->host);
-    if (!c->host.tiles.empty()) c->ragged = static_cast<double>(c->host.n_ragged) / static_cast<double>(c->host.tiles.size());
     if (device) {
         hipDeviceProp_t prop;
         rc = note(hipGetDevice(&c->device));
@@ -1051,7 +1035,8 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
     }
 
     const double resident = static_cast<double>(std::min(std::max(c->resident_end - sp.t0, 0), count)) / count;
-    const LaunchWork work{KIND, c->dtype, c->P, count, c->ragged, c->off_lines, reduced != nullptr, resident, sp.s1 - sp.s0};
+    const LaunchShares shares = shares_of(c->host, sp.s0, sp.s1, count);
+    const LaunchWork work{KIND, c->dtype, c->P, count, shares.ragged, shares.off_lines, reduced != nullptr, resident, sp.s1 - sp.s0};
     const LaunchShape s = launch_shape(c->set, work, c->n_cu);
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     const float inv_p = 1.0f / static_cast<float>(c->P);

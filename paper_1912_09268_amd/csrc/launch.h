@@ -232,6 +232,17 @@ struct LaunchSettings {
                                       // backward pass run between two updates, so nothing of one is still cached at the next
 };
 
+// What the segments [s0, s1) of a launch over `tiles` tiles are like.  Of the launch and not of the model: a large even
+// group sent by itself is paced as such whatever the rest of the model looks like.
+struct LaunchShares {
+    double ragged;
+    bool off_lines;
+};
+inline LaunchShares shares_of(const HostTables& h, int32_t s0, int32_t s1, int32_t tiles) {
+    const HostTables::SegSums &a = h.seg_sums[static_cast<size_t>(s0)], &b = h.seg_sums[static_cast<size_t>(s1)];
+    return {std::min(1.0, static_cast<double>(b.ragged - a.ragged) / tiles), b.off_lines - a.off_lines > (b.elems - a.elems) / 4};
+}
+
 // What a call covers.
 struct LaunchWork {
     int kind;

@@ -33,6 +33,7 @@ int mgwfbp_build_tables(const uint64_t* n_elems, int32_t L, const uint8_t* merge
         out.tensor_seg.assign(static_cast<size_t>(L), 0);
         out.group_tile.push_back(0);
         out.group_seg.push_back(0);
+        out.seg_sums.push_back({});
         uint64_t next_tile = 0;                        // first free tile of the arena
         int32_t i = L - 1;
         while (i >= 0) {
@@ -49,6 +50,14 @@ int mgwfbp_build_tables(const uint64_t* n_elems, int32_t L, const uint8_t* merge
                     out.seg_off.push_back(base + fill);
                     out.seg_n.push_back(static_cast<uint32_t>(std::min<uint64_t>(n_elems[i], 0xffffffffull)));
                     out.seg_layer.push_back(i);
+                    // Tiles start inside 128-byte lines (32 binary32 elements) of a tensor that does not begin on a
+                    // multiple of 32 arena elements, and, where tensors are views of one flat buffer, of one whose
+                    // size, like its neighbours' presumably, is no such multiple.
+                    HostTables::SegSums sums = out.seg_sums.back();
+                    sums.elems += n_elems[i];
+                    sums.ragged = 0;
+                    if ((n_elems[i] | fill) % 32 != 0) sums.off_lines += n_elems[i];
+                    out.seg_sums.push_back(sums);
                     fill += n_elems[i];
                 }
                 const bool closes = merged[i] == 0;
@@ -82,8 +91,10 @@ int mgwfbp_build_tables(const uint64_t* n_elems, int32_t L, const uint8_t* merge
                 h.layer0 = out.seg_layer[s];
                 h.flags = 0;
                 out.tiles.push_back(h);
-                if (h.nseg > 1 || valid < TILE) ++out.n_ragged;
+                if (h.nseg > 1 || valid < TILE) ++out.seg_sums[e + 1].ragged;
             }
+            // counted per segment so far; the sums run on
+            for (size_t q = seg_begin; q < seg_end; ++q) out.seg_sums[q + 1].ragged += out.seg_sums[q].ragged;
             next_tile += ntile;
             out.group_tile.push_back(static_cast<int32_t>(next_tile));
             out.group_seg.push_back(static_cast<int32_t>(seg_end));

@@ -53,12 +53,18 @@ struct HostTables {
     std::vector<uint64_t> seg_off;        // [S+1] arena element of the segment start; seg_off[S] = arena_elems
     std::vector<uint32_t> seg_n;          // [S] elements, saturated at 2^32-1
     std::vector<int32_t> seg_layer;       // [S] tensor index
+    // what the launch rules ask of the segments before s, [S+1]
+    struct SegSums {
+        uint64_t elems = 0;
+        uint64_t off_lines = 0;           // elements of tensors whose tiles start inside the lines of the tensor
+        uint64_t ragged = 0;              // tiles that several segments or a group's end cut into, by their last segment
+    };
+    std::vector<SegSums> seg_sums;
     // seg_layer, seg_n and seg_off as the kernels find them: right below the tile headers, in a block of a multiple
     // of 256 bytes that the tables end with
     std::vector<unsigned char> seg_block;
     // per tile
     std::vector<TileHdr> tiles;           // [T]
-    uint64_t n_ragged = 0;                // tiles that several segments or a group's end cut into
 };
 
 // Records a failed HIP call for mgwfbp_last_hip_error() on this thread and returns MGWFBP_EHIP; returns

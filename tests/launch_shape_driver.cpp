@@ -2,6 +2,7 @@
 // asked by tests/test_launch_shape.py.
 #include <cstdio>
 #include <cstring>
+#include <vector>
 
 #include "launch.h"
 
@@ -28,6 +29,24 @@ int main() {
             const LaunchShape s = launch_shape(set, w, n_cu);
             std::printf("%d %d %d %d %d %d %d %d\n", s.tiles_per_wg, s.units, s.grid, s.xcd_contiguous, s.run_log2, s.may_be_few,
                         s.form, s.wgs_per_cu);
+        } else if (!std::strcmp(what, "shares")) {    // shares L {n merged}... g0 g1: of the launch over groups [g0, g1)
+            int L, g0, g1;
+            if (std::scanf("%d", &L) != 1) return 1;
+            std::vector<uint64_t> n(static_cast<size_t>(L));
+            std::vector<uint8_t> merged(static_cast<size_t>(L));
+            for (size_t i = 0; i < n.size(); ++i) {
+                unsigned long long elems;
+                int m;
+                if (std::scanf("%llu %d", &elems, &m) != 2) return 1;
+                n[i] = elems;
+                merged[i] = static_cast<uint8_t>(m);
+            }
+            HostTables h;
+            if (std::scanf("%d %d", &g0, &g1) != 2 || mgwfbp_build_tables(n.data(), L, merged.data(), h) != MGWFBP_OK) return 1;
+            const size_t a = static_cast<size_t>(g0), b = static_cast<size_t>(g1 < 0 ? h.G : g1);
+            const int32_t tiles = h.group_tile[b] - h.group_tile[a];
+            const LaunchShares s = shares_of(h, h.group_seg[a], h.group_seg[b], tiles);
+            std::printf("%d %.0f %d\n", tiles, s.ragged * tiles, s.off_lines);
         } else {
             return 1;
         }

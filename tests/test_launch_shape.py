@@ -7,6 +7,7 @@ import struct
 import subprocess
 from collections import namedtuple
 
+import numpy as np
 import pytest
 
 import paper_1912_09268_amd as M
@@ -25,7 +26,7 @@ Shape = namedtuple("Shape", "tiles_per_wg units grid xcd_contiguous run_log2 may
 def ask(tmp_path_factory):
     exe = str(tmp_path_factory.mktemp("launch") / "driver")
     r = subprocess.run(["g++", "-std=c++17", "-Wall", "-Wno-unused-function", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-                        os.path.join(ROOT, "tests", "launch_shape_driver.cpp"), "-o", exe], capture_output=True, text=True)
+                        os.path.join(ROOT, "tests", "launch_shape_driver.cpp"), os.path.join(CSRC, "layout.cpp"), "-o", exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
 
     def ask(lines):
@@ -185,3 +186,33 @@ def test_few_segments_form_where_it_pays(ask):
     # with 16 workers the table form has registers for 16 wavefronts per compute unit, the few-segments form for 20
     caps = shapes(ask, [dict(P=16, tiles=t, segments=n) for t, n in ((4096, 9), (4097, 9), (5120, 1), (5121, 1))])
     assert [s.wgs_per_cu for s in caps] == [25, 14, 25, 14]
+
+
+def test_shares_are_of_the_launch_and_not_of_the_model(ask):
+    """Ragged tiles and tensors off their lines are counted over the groups a call covers: against the tile table and
+    the layout for random models, and for an even group beside a thousand odd tensors."""
+    rng = np.random.default_rng(1912)
+    lines, want = [], []
+    models = [([256 * 40000] + [301] * 1000, [0, 0] + [1] * 999)]
+    for _ in range(60):
+        L = int(rng.integers(1, 40))
+        unit = int(rng.choice([1, 1, 32]))
+        models.append(([int(x) // unit * unit for x in np.exp(rng.uniform(0, 9, L)) * (rng.random(L) > 0.1)],
+                       [0] + [int(x) for x in rng.random(L - 1) < 0.6]))
+    for n, merged in models:
+        ctx = M.Context(n, merged, 2, M.F32, host_only=True)
+        tables = ctx.tables()
+        tiles, group_tile = tables["tiles"], tables["group_tile"]
+        off, group, _, _ = ctx.layout()
+        G = ctx.n_groups
+        for g0, g1 in [(0, G), (0, 1), (G - 1, G), tuple(sorted(int(x) for x in rng.integers(0, G + 1, 2)))]:
+            part = tiles[group_tile[g0]:group_tile[g1]]
+            if len(part) == 0:
+                continue
+            elems = [(n[i], (n[i] | int(off[i])) % 32 != 0) for i in range(len(n)) if g0 <= group[i] < g1]
+            lines.append("shares %d %s %d %d" % (len(n), " ".join(f"{x} {m}" for x, m in zip(n, merged)), g0, g1))
+            want.append((len(part), int(((part["nseg"] > 1) | (part["valid"] < 256)).sum()),
+                         int(sum(x for x, o in elems if o) > sum(x for x, _ in elems) // 4)))
+        ctx.close()
+    assert ask(lines) == want
+    assert want[1] == (1176, 997, 1) and want[2] == (40000, 0, 0)      # the odd tensors first, the even group last
