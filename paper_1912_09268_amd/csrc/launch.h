@@ -85,9 +85,13 @@ constexpr size_t static_lds(int kind, bool few, int form) {
 //     binary32, P = 4: 6317 at 18 / 6254 at 14, P = 8: 6299 at 14 / 6229 at 16, P = 12: 6260 / 6076, P = 32: 5899 / 5676.
 //   - A launch of a few rounds of the chip (the compute units times the cap) should not end in a nearly empty one, see
 //     short_launch_cap().
-//   - A ragged tile (see general_tile) spends most of its time waiting for one thing after the other: a model that
-//     consists of them needs every wave slot (45 % ragged, binary32: pipeline P = 3: 4868 uncapped / 4204 at 18,
-//     reduce_update P = 8: 5801 / 5270 at 14; with 11 % the caps are as good or better).
+//   - A ragged tile (see general_tile) spends most of its time waiting for one thing after the other, longest where the
+//     worker count is not a compiled one (four workers' loads at a time): a launch that consists of them needs every wave
+//     slot.  Time uncapped over capped, binary32, log-normal sizes with 45 and 17 % of the tiles ragged: pipeline 1 / 3 / 6 / 12 /
+//     32 workers 0.95 / 0.97 / 0.90 / 0.90 / 0.97 and 0.99 / 0.99 / 0.98 / 0.98 / 0.98, reduce_update 6 / 12 / 32 workers 0.97 / 0.92 / 0.97
+//     and 1.00 / 0.97 / 1.00, direct 0.95 / 0.81 / 0.87 and 0.99 / 0.87 / 0.93.  With 8 workers it is no gain (45 %: pipeline 1.04,
+//     reduce_update 0.99, direct 1.01; equal tensors, 25 / 40 / 60 % ragged: pipeline 1.06 / 1.03 / 1.05, reduce_update 1.00 / 1.07 / 1.02,
+//     direct 0.99 / 1.05 / 1.03), and with 16 the registers cap it anyway.
 //   - 16-bit gradients need every wave slot (direct, P = 8: 6559 uncapped / 5729 at 16), but for REDUCE with all of
 //     8 or 16 workers' loads in flight (P = 16: 6381 at 16 / 6220 uncapped; P = 12, two at a time: 6512 / 5265) and
 //     for the pipeline's joined steps, which have 1 KiB under way like binary32 (P = 8: 6164 at 14 / 5886 uncapped;
@@ -147,7 +151,7 @@ inline int32_t pack_tiles_per_workgroup(int32_t dtype, int32_t P, int64_t copies
 
 inline int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int32_t tiles, double ragged, bool reduced, int form) {
     const bool wide = dtype == MGWFBP_F32;
-    if (ragged > 0.25 && kind != K_REDUCE) return -1;
+    if (ragged > 0.25 && kind != K_REDUCE && (kind == K_PACK || (P != 8 && P != 16))) return -1;
     switch (kind) {
         case K_REDUCE: return wide ? (P < 4 ? -1 : P < 8 ? 16 : 14) : (P == 8 || P == 16 ? 16 : -1);
         case K_UPDATE: return -1;                        // 20 bytes per element, nothing per worker

@@ -216,3 +216,11 @@ def test_shares_are_of_the_launch_and_not_of_the_model(ask):
         ctx.close()
     assert ask(lines) == want
     assert want[1] == (1176, 997, 1) and want[2] == (40000, 0, 0)      # the odd tensors first, the even group last
+
+
+def test_ragged_launches_run_uncapped_where_that_helps(ask):
+    for kind in ("pipeline", "reduce_update", "direct"):
+        caps = shapes(ask, [dict(kind=kind, P=P, ragged=r) for P in (3, 6, 12, 32, 4, 8, 16) for r in (0.2, 0.3)])
+        assert all(a.wgs_per_cu > 0 for a in caps[::2]) and all(b.wgs_per_cu == -1 for b in caps[1:10:2])
+        assert [b.wgs_per_cu for b in caps[11::2]] == [a.wgs_per_cu for a in caps[10::2]]     # 8 and 16 workers
+    assert shapes(ask, [dict(kind="reduce", P=6, ragged=0.9)])[0].wgs_per_cu == 16            # nothing ragged about it
