@@ -136,12 +136,15 @@ inline bool joined_pipeline(int32_t dtype, int32_t P, int32_t tiles, double ragg
 // tiles each: P = 8, 1024 tiles 5.4 / 5.0 / 5.5, 4096 tiles 16.0 / 12.5 / 13.1, 16384 tiles 64.9 / 42.9 / 42.2; P = 1, 1024
 // tiles 2.9 / 2.9 / 3.4).  Up to 8 per compute unit two are no faster than one, and slower where the ends of what is
 // packed are ragged (a thousand tensors around 4096 elements as views, packed one by one: 6222 us with 2, 5877 with 1).
-// With 16-bit gradients of many workers and next to no ragged tiles 4 KiB at 21 workgroups per compute unit
-// are ahead (ResNet-50 shape, us: P = 32: 493 against 510 with 2 KiB uncapped, P = 16: 248 / 257, P = 8: 127 / 128).
-constexpr double SOME_RAGGED = 0.005, HARDLY_RAGGED = 0.001;
-constexpr int64_t SINGLE_COPIES = 2048, FEW_COPIES = 65536;
+// With 16-bit gradients of many workers, next to no ragged tiles and a million copies of tiles 4 KiB at 21 workgroups per
+// compute unit are ahead (ResNet-50 shape, 0.017 % ragged, us: P = 32: 493 against 510 with 2 KiB uncapped, P = 16: 248 / 257, P = 8:
+// 127 / 128; one tensor of 100,000 tiles P = 24: 373 / 382, P = 12: 186 / 190, P = 8: 125 / 125).  Not in shorter launches (30,000
+// tiles P = 8 / 16 / 24: 40.4 / 38.9, 75.9 / 74.0, 112.8 / 112.7; 10,000 tiles 16.0 / 14.8, 28.6 / 27.0, 40.4 / 38.9), nor reliably with more
+// ragged tiles (100,000 tiles, 0.05 / 0.1 / 0.2 / 1 %: P = 16 270.7 / 269.0, 273.3 / 266.7, 264.9 / 267.6, 280.2 / 273.9).
+constexpr double SOME_RAGGED = 0.005, HARDLY_RAGGED = 0.0004;
+constexpr int64_t SINGLE_COPIES = 2048, FEW_COPIES = 65536, MANY_COPIES = 1 << 20;
 inline bool many_halves(int32_t dtype, int32_t P, int64_t copies, double ragged) {
-    return dtype != MGWFBP_F32 && P >= 8 && copies > FEW_COPIES && ragged < HARDLY_RAGGED;
+    return dtype != MGWFBP_F32 && P >= 12 && copies > MANY_COPIES && ragged < HARDLY_RAGGED;
 }
 inline int32_t pack_tiles_per_workgroup(int32_t dtype, int32_t P, int64_t copies, double ragged) {
     if (copies <= SINGLE_COPIES) return 1;

@@ -224,3 +224,14 @@ def test_ragged_launches_run_uncapped_where_that_helps(ask):
         assert all(a.wgs_per_cu > 0 for a in caps[::2]) and all(b.wgs_per_cu == -1 for b in caps[1:10:2])
         assert [b.wgs_per_cu for b in caps[11::2]] == [a.wgs_per_cu for a in caps[10::2]]     # 8 and 16 workers
     assert shapes(ask, [dict(kind="reduce", P=6, ragged=0.9)])[0].wgs_per_cu == 16            # nothing ragged about it
+
+
+def test_shares_of_sixteen_bit_packs(ask):
+    """Eight tiles per workgroup at a cap of 21 in the longest even launches of many workers only."""
+    def share(**c):
+        s = shapes(ask, [dict(kind="pack", dtype="bf16") | c])[0]
+        return s.tiles_per_wg, s.wgs_per_cu
+    assert share(P=32, tiles=99832, ragged=0.00017) == (8, 21) and share(P=12, tiles=87400) == (8, 21)
+    for c in (dict(P=8, tiles=200000), dict(P=12, tiles=87000), dict(P=32, tiles=32768), dict(P=32, tiles=99832, ragged=0.0005)):
+        assert share(**c) == (4, -1), c
+    assert share(P=8, tiles=8192) == (2, -1) and share(P=2, tiles=1024) == (1, -1)
