@@ -193,13 +193,23 @@ inline int32_t short_launch_cap(int32_t cap, int32_t P, bool few, int32_t per_cu
 }
 
 // Units per die and turn (log2), where tiles start inside lines (see unit_of): the kinds that write w and v gain,
-// the pipeline, which writes whole lines of P arenas as well, less; PACK and REDUCE write whole lines only.
-inline int8_t run_log2_of(int kind) {
-    switch (kind) {
-        case K_PIPELINE: return 2;
-        case K_UPDATE: case K_REDUCE_UPDATE: case K_DIRECT: return 3;
-        default: return 0;
-    }
+// the pipeline, which writes whole lines of P arenas as well, less; PACK and REDUCE write whole lines only.  `off_lines` is the
+// share of the elements of tensors off their lines, as far as sizes and places in the arena show it: a tensor of odd size
+// that begins its group lies off its lines as a view of a flat buffer (100,000 tiles: pipeline 0.91-0.99 of the time with runs,
+// direct 0.83-0.92), but on them in an allocation of its own (pipeline 0.99-1.02, direct and reduce_update 0.95-1.05).  Time with
+// runs over that without by share, binary32, 60,000 tiles, 0.1 / 0.3 / 0.45 / 0.7 / 1: pipeline 3 workers 1.00 / 0.99 / 0.98 / 0.96 / 0.94, 8
+// workers 1.00 / 0.99 / 0.99 / 0.97 / 0.97; update 0.99 / 0.98 / 0.97 / 0.94 / 0.94; direct 3 workers 1.00 / 0.98 / 0.96 / 0.91 / 0.90, 8 workers
+// 1.02 / 1.00 / 0.98 / 0.94 / 0.90, 16 workers 1.03 / 1.01 / 0.99 / 0.95 / 0.93; reduce_update 3 workers 1.01 / 1.00 / 0.98 / 0.94 / 0.93, 8
+// workers 1.02 / 1.02 / 1.01 / 0.99 / 0.97, 16 workers 1.04 / 1.03 / 1.04 / 1.01 / 1.01, 32 workers 1.05 at 1; bfloat16, 8 workers, at most 1.00
+// throughout.  What a line's other half costs is one part in the many arrays that reduce_update of many workers reads.
+inline int8_t run_log2_of(int kind, int32_t dtype, int32_t P, double off_lines) {
+    if (kind == K_PACK || kind == K_REDUCE) return 0;
+    const bool wide = dtype == MGWFBP_F32;
+    const int32_t bytes = P * (wide ? 4 : 2);             // of gradients per element
+    if (kind == K_REDUCE_UPDATE && bytes > 32) return 0;
+    const bool late = wide && bytes >= 32 && (kind == K_REDUCE_UPDATE || kind == K_DIRECT);
+    if (off_lines <= (late ? 0.5 : 0.25)) return 0;
+    return kind == K_PIPELINE ? 2 : 3;
 }
 
 // Which of the launches that could take the few-segments form do.  It reaches a ragged tile's data several memory trips
@@ -242,12 +252,12 @@ struct LaunchSettings {
 // What the segments [s0, s1) of a launch over `tiles` tiles are like.  Of the launch and not of the model: a large even
 // group sent by itself is paced as such whatever the rest of the model looks like.
 struct LaunchShares {
-    double ragged;
-    bool off_lines;
+    double ragged, off_lines;
 };
 inline LaunchShares shares_of(const HostTables& h, int32_t s0, int32_t s1, int32_t tiles) {
     const HostTables::SegSums &a = h.seg_sums[static_cast<size_t>(s0)], &b = h.seg_sums[static_cast<size_t>(s1)];
-    return {std::min(1.0, static_cast<double>(b.ragged - a.ragged) / tiles), b.off_lines - a.off_lines > (b.elems - a.elems) / 4};
+    return {std::min(1.0, static_cast<double>(b.ragged - a.ragged) / tiles),
+            b.elems > a.elems ? static_cast<double>(b.off_lines - a.off_lines) / static_cast<double>(b.elems - a.elems) : 0.0};
 }
 
 // What a call covers.
@@ -256,7 +266,7 @@ struct LaunchWork {
     int32_t dtype, P;
     int32_t tiles;                    // > 0
     double ragged;                    // share of the tiles that take the general path
-    bool off_lines;                   // a good part of the tiles do not start on the lines of their tensors
+    double off_lines;                 // share of the elements of tensors whose tiles start inside the lines of the tensor
     bool reduced;                     // the reduced arena is written
     double resident;                  // share of the tiles whose w and v are kept cacheable
     int32_t segments;
@@ -315,7 +325,7 @@ inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, 
         if (s.form == PAIRS ? w.tiles < 2 * SHORT_LAUNCH_TILES : w.dtype == MGWFBP_F32 && w.kind != K_PACK && few_rounds(w.tiles, w.P))
             s.wgs_per_cu = short_launch_cap(s.wgs_per_cu, w.P, s.may_be_few && s.form != PAIRS, per_cu);
     }
-    s.run_log2 = one_turn && w.off_lines ? run_log2_of(w.kind) : int8_t{0};
+    s.run_log2 = one_turn ? run_log2_of(w.kind, w.dtype, w.P, w.off_lines) : int8_t{0};
     return s;
 }
 

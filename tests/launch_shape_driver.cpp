@@ -17,13 +17,12 @@ int main() {
         } else if (!std::strcmp(what, "shape")) {     // shape <work> <settings> n_cu
             LaunchWork w{};
             LaunchSettings set;
-            int off, reduced, n_cu;
+            int reduced, n_cu;
             long long resident_bytes;
-            if (std::scanf("%d %d %d %d %lf %d %d %lf %d", &w.kind, &w.dtype, &w.P, &w.tiles, &w.ragged, &off, &reduced,
+            if (std::scanf("%d %d %d %d %lf %lf %d %lf %d", &w.kind, &w.dtype, &w.P, &w.tiles, &w.ragged, &w.off_lines, &reduced,
                            &w.resident, &w.segments) != 9) return 1;
             if (std::scanf("%d %d %d %d %d %d %lld %d", &set.blocks_per_cu, &set.xcd_contiguous, &set.tiles_per_wg, &set.wg_per_cu,
                            &set.step_vecs, &set.burst_tiles, &resident_bytes, &n_cu) != 8) return 1;
-            w.off_lines = off != 0;
             w.reduced = reduced != 0;
             set.resident_bytes = static_cast<uint64_t>(resident_bytes);
             const LaunchShape s = launch_shape(set, w, n_cu);
@@ -46,7 +45,7 @@ int main() {
             const size_t a = static_cast<size_t>(g0), b = static_cast<size_t>(g1 < 0 ? h.G : g1);
             const int32_t tiles = h.group_tile[b] - h.group_tile[a];
             const LaunchShares s = shares_of(h, h.group_seg[a], h.group_seg[b], tiles);
-            std::printf("%d %.0f %d\n", tiles, s.ragged * tiles, s.off_lines);
+            std::printf("%d %.0f %.0f\n", tiles, s.ragged * tiles, s.off_lines * 1e6);
         } else {
             return 1;
         }

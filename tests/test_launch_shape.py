@@ -93,10 +93,10 @@ def shapes(ask, cases):
     """launch_shape of each case: a dict of what differs from an even f32 pipeline of 8 workers at the defaults."""
     lines = []
     for c in cases:
-        c = dict(kind="pipeline", dtype="f32", P=8, tiles=65536, ragged=0.0, off_lines=0, reduced=1, resident=0.0, segments=9,
+        c = dict(kind="pipeline", dtype="f32", P=8, tiles=65536, ragged=0.0, off_lines=0.0, reduced=1, resident=0.0, segments=9,
                  blocks_per_cu=0, xcd_contiguous=0, tiles_per_wg=0, wg_per_cu=0, step_vecs=0, burst_tiles=-1,
                  resident_bytes=0, n_cu=256) | c
-        lines.append("shape %d %d %d %d %r %d %d %r %d %d %d %d %d %d %d %d %d" % (
+        lines.append("shape %d %d %d %d %r %r %d %r %d %d %d %d %d %d %d %d %d" % (
             KINDS.index(c["kind"]), DTYPES.index(c["dtype"]), c["P"], c["tiles"], c["ragged"], c["off_lines"], c["reduced"],
             c["resident"], c["segments"], c["blocks_per_cu"], c["xcd_contiguous"], c["tiles_per_wg"], c["wg_per_cu"], c["step_vecs"],
             c["burst_tiles"], c["resident_bytes"], c["n_cu"]))
@@ -212,10 +212,10 @@ def test_shares_are_of_the_launch_and_not_of_the_model(ask):
             elems = [(n[i], (n[i] | int(off[i])) % 32 != 0) for i in range(len(n)) if g0 <= group[i] < g1]
             lines.append("shares %d %s %d %d" % (len(n), " ".join(f"{x} {m}" for x, m in zip(n, merged)), g0, g1))
             want.append((len(part), int(((part["nseg"] > 1) | (part["valid"] < 256)).sum()),
-                         int(sum(x for x, o in elems if o) > sum(x for x, _ in elems) // 4)))
+                         round(1e6 * sum(x for x, o in elems if o) / sum(x for x, _ in elems))))
         ctx.close()
     assert ask(lines) == want
-    assert want[1] == (1176, 997, 1) and want[2] == (40000, 0, 0)      # the odd tensors first, the even group last
+    assert want[1] == (1176, 997, 1000000) and want[2] == (40000, 0, 0)      # the odd tensors first, the even group last
 
 
 def test_ragged_launches_run_uncapped_where_that_helps(ask):
@@ -235,3 +235,13 @@ def test_shares_of_sixteen_bit_packs(ask):
     for c in (dict(P=8, tiles=200000), dict(P=12, tiles=87000), dict(P=32, tiles=32768), dict(P=32, tiles=99832, ragged=0.0005)):
         assert share(**c) == (4, -1), c
     assert share(P=8, tiles=8192) == (2, -1) and share(P=2, tiles=1024) == (1, -1)
+
+
+def test_runs_per_die_where_they_help(ask):
+    def run(kind, P, off, dtype="f32", **c):
+        return shapes(ask, [dict(kind=kind, P=P, off_lines=off, dtype=dtype) | c])[0].run_log2
+    assert [run(k, 3, 0.26) for k in KINDS] == [0, 0, 3, 3, 2, 3] and not any(run(k, 3, 0.25) for k in KINDS)
+    assert [run(k, 8, 0.5) for k in KINDS] == [0, 0, 3, 0, 2, 0] and [run(k, 8, 0.51) for k in KINDS] == [0, 0, 3, 3, 2, 3]
+    assert [run(k, 12, 1.0) for k in KINDS] == [0, 0, 3, 0, 2, 3]          # reduce_update of many workers: never
+    assert [run(k, 16, 0.26, "bf16") for k in KINDS] == [0, 0, 3, 3, 2, 3] and run("reduce_update", 24, 1.0, "bf16") == 0
+    assert run("update", 1, 1.0, xcd_contiguous=1) == 0 and run("update", 1, 1.0, blocks_per_cu=4) == 0
