@@ -454,7 +454,7 @@ __device__ __forceinline__ void fast_chunk(const CallArgs<GradT>& A, const Worke
     }
 }
 
-// JOIN full tiles of one tensor in one step (see joins()).
+// Several full tiles of one tensor in one step (see joined_tiles_of()).
 constexpr int WIDE = 8;               // 16-bit gradients per lane in a joined pipeline step: 16 bytes
 
 template <int KIND, typename GradT, int PT>
@@ -464,15 +464,15 @@ __device__ __forceinline__ void joined_tiles(const CallArgs<GradT>& A, const Wor
     src.fetch(A.grad_ptrs, A.L, layer, worker_base<KIND>());
     const int lane_elem = static_cast<int>(threadIdx.x) * VEC;
     if constexpr (KIND == K_PACK) {
-        paced_step<KIND, GradT, PT, VEC, JOIN * TVECS, true>(A, src, mrg, nullptr, nullptr, tensor_off + lane_elem,
+        paced_step<KIND, GradT, PT, VEC, PACK_TILES * TVECS, true>(A, src, mrg, nullptr, nullptr, tensor_off + lane_elem,
                                                              tile_base + lane_elem, BLOCK * VEC);
     } else {
         // One worker at a time as in paced_step, with 16 bytes per lane, 8 consecutive elements: a worker's share
         // is the 1 KiB it is with binary32.  The sums then change hands through LDS, so that the binary32 arrays,
         // too, are accessed with consecutive 16 bytes per lane.
-        static_assert(JOINED == BLOCK * WIDE && BLOCK == 64, "one wavefront, 16 bytes per lane");
+        static_assert(PAIRED == BLOCK * WIDE, "16 bytes per lane");
         typedef typename VecOf<GradT, WIDE>::type GV;
-        constexpr int N = JOINED / (BLOCK * VEC);
+        constexpr int N = PAIRED / (BLOCK * VEC);
         float* wp = ro(A.w_ptrs)[layer];
         float* vp = ro(A.v_ptrs)[layer];
         const int wide_elem = static_cast<int>(threadIdx.x) * WIDE;
@@ -634,12 +634,13 @@ __device__ __forceinline__ TileHdr load_header(const TileHdr* p) {
 template <int KIND, typename GradT, int PT, int FORM>
 __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_stream_kernel(const Args<GradT> A) {
     constexpr int SINGLE = FORM == PAIRS ? 1 : FORM;     // single tiles
+    constexpr int JOIN = joined_tiles_of(KIND, FORM);
     __shared__ int s_loc[MAXSEG + 1];
     __shared__ int s_layer[MAXSEG];
     __shared__ int s_wave[BLOCK / 64];
     __shared__ int s_ragged[TILE / VEC];
     __shared__ int s_nragged;
-    __shared__ __align__(16) float s_sums[FORM == PAIRS ? JOINED : 4];
+    __shared__ __align__(16) float s_sums[FORM == PAIRS ? PAIRED : 4];
 
     WorkerPtrs<GradT, PT> mrg;
     if constexpr (reads_merge(KIND) || writes_merge(KIND)) mrg.fetch(A.merge_bufs, 1, 0, worker_base<KIND>());
@@ -675,7 +676,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_stream_kernel(const Args<
                 continue;
             }
             // A full tile inside one tensor.
-            if constexpr (joins(KIND, FORM)) {
+            if constexpr (JOIN > 1) {
                 // (A clip cuts into the first and the last tile only.)
                 if (t + JOIN <= t_end) {
                     bool same = t + JOIN < A.tile_count || A.clip_hi == TILE;
@@ -741,11 +742,12 @@ template <typename GradT> __device__ __forceinline__ FewSeg few_owner(const FewA
 
 template <int KIND, typename GradT, int PT, int FORM>
 __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_few_kernel(const FewArgs<GradT> A) {
-    static_assert(BLOCK == 64 && TVECS == 1, "a tile is one vector per lane of one wavefront");
+    static_assert(KIND >= 0 && HAVE_FEW, "a tile is one vector per lane of one wavefront");
     constexpr int SINGLE = FORM == PAIRS ? 1 : FORM;
+    constexpr int JOIN = joined_tiles_of(KIND, FORM);
     WorkerPtrs<GradT, PT> mrg;
     if constexpr (reads_merge(KIND) || writes_merge(KIND)) mrg.fetch(A.merge_bufs, 1, 0, worker_base<KIND>());
-    __shared__ __align__(16) float s_sums[FORM == PAIRS ? JOINED : 4];
+    __shared__ __align__(16) float s_sums[FORM == PAIRS ? PAIRED : 4];
     const int lane = threadIdx.x;
     const int64_t arena = static_cast<int64_t>(A.tile_first) * TILE;
     const int K = A.tiles_per_wg;
@@ -755,7 +757,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_few_kernel(const FewArgs<
         const int b = t * TILE;
         const FewSeg s = few_owner(A, b);                                  // uniform
         if (s.start <= b && b + TILE <= s.end) {                           // a full tile inside one segment
-            if constexpr (joins(KIND, FORM)) {
+            if constexpr (JOIN > 1) {
                 if (t + JOIN <= t_end && b + JOIN * TILE <= s.end) {
                     joined_tiles<KIND, GradT, PT>(A, mrg, A.layer_hi - s.j, b - s.start, arena + b, s_sums);
                     t += JOIN - 1;
@@ -906,7 +908,13 @@ int launch_one(const ArgsT<GradT>& A, hipStream_t stream, const LaunchShape& s, 
             started = true;
         }
     }
-    if constexpr (KIND == K_PIPELINE && sizeof(GradT) == 2) {
+    if constexpr (TVECS % 2 == 0) {
+        if (s.form == 2) {
+            start<KIND, GradT, PT, 2>(A, stream, s, grid_y);
+            started = true;
+        }
+    }
+    if constexpr (HAVE_PAIRS && KIND == K_PIPELINE && sizeof(GradT) == 2) {
         if (s.form == PAIRS) {
             start<KIND, GradT, PT, PAIRS>(A, stream, s, grid_y);
             started = true;
@@ -993,9 +1001,9 @@ bool few_segments(const HostTables& h, const Span& sp, bool whole_groups, int32_
 template <int KIND, typename GradT>
 int launch(const mgwfbp_ctx* c, const Span& sp, const TileHdr* tiles, const CallArgs<GradT>& call,
            hipStream_t stream, const LaunchShape& s) {
-    if (s.may_be_few) {
+    if constexpr (HAVE_FEW) {
         FewArgs<GradT> A{call};
-        if (few_segments(c->host, sp, !needs_owner(KIND), A.layer_hi, A.start0, A.n, A.closes, A.end))
+        if (s.may_be_few && few_segments(c->host, sp, !needs_owner(KIND), A.layer_hi, A.start0, A.n, A.closes, A.end))
             return launch_by_p<KIND, GradT, FewArgs>(A, stream, s);
     }
     // a clip cuts into the first and the last tile only

@@ -10,8 +10,8 @@
 #include "mgwfbp.h"
 #include "tables.h"
 
-#ifndef MGWFBP_JOIN_TILES
-#define MGWFBP_JOIN_TILES 2       // consecutive full tiles of one tensor that some kinds take in one step
+#ifndef MGWFBP_PACK_TILES
+#define MGWFBP_PACK_TILES 2       // consecutive full tiles of one tensor that PACK copies in one step
 #endif
 #define MGWFBP_MAXSEG (2 * MGWFBP_BLOCK)   // segments per tile whose offsets are staged in LDS (two per lane)
 
@@ -22,7 +22,7 @@ constexpr int VEC = MGWFBP_VEC;
 constexpr int TVECS = MGWFBP_TILE_VECS;
 constexpr int TILE = MGWFBP_TILE_ELEMS;
 constexpr int MAXSEG = MGWFBP_MAXSEG;
-constexpr int JOIN = MGWFBP_JOIN_TILES;
+constexpr int PACK_TILES = MGWFBP_PACK_TILES;
 
 enum Kind { K_PACK = 0, K_REDUCE = 1, K_UPDATE = 2, K_REDUCE_UPDATE = 3, K_PIPELINE = 4, K_DIRECT = 5 };
 
@@ -36,14 +36,18 @@ constexpr bool needs_owner(int k) { return k != K_REDUCE; }
 
 // Forms of the fast path, beside the number of vectors per lane of a paced step (1 and up).
 constexpr int BURST = 0;              // every load of a tile under way at once
-constexpr int PAIRS = -1;             // JOIN full tiles of one tensor in one step, single ones in paced steps of one vector
-constexpr int JOINED = JOIN * TILE;   // elements of a joined step
+constexpr int PAIRS = -1;             // two full tiles of one tensor in one step, single ones in paced steps of one vector
+constexpr int PAIR = 2;
+constexpr int PAIRED = PAIR * TILE;   // elements of a pair
+// What needs tiles of one vector per lane, and of one wavefront, is left out of builds with other tiles.
+constexpr bool HAVE_PAIRS = TVECS == 1;
+constexpr bool HAVE_FEW = TVECS == 1 && BLOCK == 64;
 // Kinds whose wavefronts have too little under way with one tile can take joined steps: PACK, a plain copy, always, and
 // the pipeline on 16-bit gradients, where a worker's share of a tile is 512 bytes, in kernels of their own: beside the
 // joined step, whose sums change hands through LDS, the single-tile kernel would need 105 instead of 74 registers (16
 // workers; 77 instead of 57 with 8) and as uncapped launches hold 16 instead of 24 wavefronts per compute unit (16
 // workers, 6000 tiles: 30.0 us against 23.4).
-constexpr bool joins(int kind, int form) { return form == PAIRS || (kind == K_PACK && form != BURST); }
+constexpr int joined_tiles_of(int kind, int form) { return form == PAIRS ? PAIR : kind == K_PACK && form != BURST ? PACK_TILES : 1; }
 
 // Dynamic LDS per workgroup that lets at most n workgroups share the 160 KiB of a compute unit.  A workgroup's
 // LDS (static + dynamic) is granted in blocks of 1280 bytes (a 128th of the compute unit's; seen in the cap
@@ -68,7 +72,7 @@ inline size_t lds_for_workgroups_per_cu(int32_t n, size_t static_lds) {
 // LDS the kernels declare themselves: the table form for its general path (REDUCE needs less of it), both forms for
 // the sums of joined steps.
 constexpr size_t static_lds(int kind, bool few, int form) {
-    const size_t joined = form == PAIRS ? sizeof(float) * JOINED : 0;
+    const size_t joined = form == PAIRS ? sizeof(float) * PAIRED : 0;
     return few ? joined : joined + sizeof(int) * static_cast<size_t>((needs_owner(kind) ? 2 * MAXSEG + 1 + BLOCK / 64 : 0) + TILE / VEC + 1);
 }
 
@@ -112,7 +116,7 @@ inline int32_t default_burst_tiles(int kind, int32_t dtype, int32_t P) {
     return dtype != MGWFBP_F32 || P < 4 || kind == K_UPDATE ? 3072 : 1792;
 }
 
-// Whether a workgroup of the pipeline takes JOIN tiles in one step (see joined_tiles).  GB/s at 16-bit gradients,
+// Whether a workgroup of the pipeline takes two tiles in one step (see joined_tiles).  GB/s at 16-bit gradients,
 // ResNet-50 shape, joined at its best cap against single tiles uncapped: P = 1: 6250 / 6327, 2: 6221 / 6231,
 // 3: 6194 / 6127, 4: 6175 / 6038, 8: 6164 / 5881, 16: 6080 / 5737, 32: 5675 / 5554; with one or two workers the
 // binary32 arrays are most of the traffic.  A short launch needs its tiles spread over the chip.
@@ -283,24 +287,27 @@ struct LaunchShape {
 
 inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, int n_cu) {
     LaunchShape s{};
+    // The rules count tiles of 256 elements, the size they were measured with.
+    const int32_t length = static_cast<int32_t>(std::min<int64_t>(static_cast<int64_t>(w.tiles) * (TILE / 256), INT32_MAX));
     // A launch too small to fill the chip is bound by the latency of its tiles, not by the memory system: it takes the
     // burst form (every load of a tile at once, no cap) unless the caller has fixed the pacing.
-    const int32_t burst_tiles = set.burst_tiles < 0 ? default_burst_tiles(w.kind, w.dtype, w.P) : set.burst_tiles;
-    const bool burst = set.step_vecs < 0 || (set.step_vecs == 0 && w.tiles <= burst_tiles);
+    const bool short_enough = set.burst_tiles < 0 ? length <= default_burst_tiles(w.kind, w.dtype, w.P) : w.tiles <= set.burst_tiles;
+    const bool burst = set.step_vecs < 0 || (set.step_vecs == 0 && short_enough);
     // Pairs of tiles: where the rule says so or the caller has asked for several tiles per workgroup, and neither in the
     // burst form, which takes one tile at a time, nor where more than an eighth of the tiles are resident, which are taken
     // one by one (bfloat16, 8 workers, 100,000 tiles: none resident 216 us in pairs against 227 in single tiles, half of
     // them 242 / 213; the lines between cross at 15 %).
-    const bool pairs = w.kind == K_PIPELINE && w.dtype != MGWFBP_F32 && !burst && w.resident <= 0.125 &&
-                       (set.tiles_per_wg > 0 ? set.tiles_per_wg >= JOIN : joined_pipeline(w.dtype, w.P, w.tiles, w.ragged));
-    s.form = burst ? BURST : pairs ? PAIRS : 1;
+    const bool pairs = HAVE_PAIRS && w.kind == K_PIPELINE && w.dtype != MGWFBP_F32 && !burst && w.resident <= 0.125 &&
+                       (set.tiles_per_wg > 0 ? set.tiles_per_wg >= PAIR : joined_pipeline(w.dtype, w.P, length, w.ragged));
+    const int32_t step = set.step_vecs > 0 ? set.step_vecs : TVECS;
+    s.form = burst ? BURST : pairs ? PAIRS : TVECS % 2 == 0 && step >= 2 ? 2 : 1;
     // Tiles per workgroup: PACK runs as single-worker copies, whose tiles are small (one array in, one out), so a
     // workgroup takes several, two at a time; pairs take two at once; every other kind takes one tile
     // per workgroup.  More only stretches the set of bytes the chip has in flight: the window the workgroups of a
     // compute unit cover together should stay within a few hundred KiB per array.
     s.tiles_per_wg = set.tiles_per_wg > 0 ? set.tiles_per_wg
-                     : w.kind == K_PACK   ? pack_tiles_per_workgroup(w.dtype, w.P, static_cast<int64_t>(w.tiles) * w.P, w.ragged)
-                     : pairs              ? JOIN
+                     : w.kind == K_PACK   ? std::max(1, pack_tiles_per_workgroup(w.dtype, w.P, static_cast<int64_t>(length) * w.P, w.ragged) * 256 / TILE)
+                     : pairs              ? PAIR
                                           : 1;
     s.units = (w.tiles + s.tiles_per_wg - 1) / s.tiles_per_wg;
     s.grid = s.units;
@@ -315,14 +322,14 @@ inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, 
     // The few-segments form has no tile headers, so it serves neither the resident share of w and v, which they
     // mark, nor the forms in which a workgroup goes on to tiles far from its first.
     const bool one_turn = s.grid == s.units && !s.xcd_contiguous;
-    s.may_be_few = one_turn && !(updates(w.kind) && set.resident_bytes > 0) && (w.segments <= FEW || !needs_owner(w.kind)) &&
-                   few_form_pays(w.kind, w.dtype, w.P, w.tiles, w.segments, per_cu);
+    s.may_be_few = HAVE_FEW && one_turn && !(updates(w.kind) && set.resident_bytes > 0) && (w.segments <= FEW || !needs_owner(w.kind)) &&
+                   few_form_pays(w.kind, w.dtype, w.P, length, w.segments, per_cu);
     // With the form, the workgroups that may share a compute unit set the loads it has in flight (1 KiB of a binary32 array
     // per vector of a step and workgroup, half that of a 16-bit one).
     s.wgs_per_cu = set.wg_per_cu;
     if (s.wgs_per_cu == 0) {
-        s.wgs_per_cu = burst ? -1 : default_workgroups_per_cu(w.kind, w.dtype, w.P, w.tiles, w.ragged, w.reduced, s.form);
-        if (s.form == PAIRS ? w.tiles < 2 * SHORT_LAUNCH_TILES : w.dtype == MGWFBP_F32 && w.kind != K_PACK && few_rounds(w.tiles, w.P))
+        s.wgs_per_cu = burst ? -1 : default_workgroups_per_cu(w.kind, w.dtype, w.P, length, w.ragged, w.reduced, s.form);
+        if (s.form == PAIRS ? length < 2 * SHORT_LAUNCH_TILES : w.dtype == MGWFBP_F32 && w.kind != K_PACK && few_rounds(length, w.P))
             s.wgs_per_cu = short_launch_cap(s.wgs_per_cu, w.P, s.may_be_few && s.form != PAIRS, per_cu);
     }
     s.run_log2 = one_turn ? run_log2_of(w.kind, w.dtype, w.P, w.off_lines) : int8_t{0};

@@ -245,3 +245,17 @@ def test_runs_per_die_where_they_help(ask):
     assert [run(k, 12, 1.0) for k in KINDS] == [0, 0, 3, 0, 2, 3]          # reduce_update of many workers: never
     assert [run(k, 16, 0.26, "bf16") for k in KINDS] == [0, 0, 3, 3, 2, 3] and run("reduce_update", 24, 1.0, "bf16") == 0
     assert run("update", 1, 1.0, xcd_contiguous=1) == 0 and run("update", 1, 1.0, blocks_per_cu=4) == 0
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not available")
+def test_builds_with_other_tiles_compile():
+    """What a tuning build may override (build_library's `defines`): every kernel is instantiated, none compiled."""
+    from paper_1912_09268_amd import build as B
+    runs = [subprocess.Popen(["hipcc", *B.HIPCC_FLAGS, "-w", *(f"-D{d}" for d in defines), "-I", os.path.join(ROOT, "include"),
+                              "-I", CSRC, "-x", "hip", "-fsyntax-only", os.path.join(CSRC, "kernels.hip")],
+                             stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+            for defines in (["MGWFBP_TILE_VECS=2"], ["MGWFBP_TILE_VECS=4", "MGWFBP_PACK_TILES=1"], ["MGWFBP_BLOCK=128"],
+                            ["MGWFBP_BLOCK=256", "MGWFBP_TILE_VECS=2", "MGWFBP_PACK_TILES=4"])]
+    for run in runs:
+        out = run.communicate(timeout=120)[0]
+        assert run.returncode == 0, out
