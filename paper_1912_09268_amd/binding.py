@@ -1,15 +1,22 @@
 """ctypes binding with the same names as the C ABI declared in include/mgwfbp.h.
 
 Argument marshalling only; the device calls, which a training loop makes once per group or tensor, do theirs in
-the extension module built from csrc/calls.cpp.  Device buffers are passed as integer addresses (e.g. torch's
+the extension module built from csrc/calls.cpp where that is there (a call takes 2.75 us instead of 3.4-3.7).  Device buffers are passed as integer addresses (e.g. torch's
 `tensor.data_ptr()`), streams as integer handles (e.g. `torch.cuda.current_stream().cuda_stream`)."""
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from typing import Optional, Sequence, Tuple
 
 import numpy as np
+
+try:
+    from . import _calls
+    _calls.DeviceCall
+except (ImportError, AttributeError):    # not built for this Python, or before its source changed: plain ctypes calls
+    _calls = None
 
 F32 = 0
 BF16 = 1
@@ -75,6 +82,24 @@ _SIGNATURES = {
 }
 
 
+class _Library(C.CDLL):
+    """The native device calls go to the addresses of the entry points; one that is replaced here (by a stand-in, say) is
+    called as it is, through the plain method, until the original is put back."""
+    _entries: dict = {}
+
+    def __setattr__(self, name, value):
+        super().__setattr__(name, value)
+        if _calls is not None and name in self._entries:
+            _calls.set_entry(name, C.cast(value, _vp).value if value is self._entries[name] else 0)
+
+
+def _device_call(plain):
+    """The method that converts its arguments in native code, in front of the plain one."""
+    if _calls is None:
+        return plain
+    return functools.update_wrapper(_calls.DeviceCall("mgwfbp_" + plain.__name__, plain), plain)
+
+
 def lib() -> C.CDLL:
     """The loaded library.  Raises if it is missing: there is no fallback path."""
     global _LIB
@@ -82,17 +107,14 @@ def lib() -> C.CDLL:
         path = library_path()
         if not os.path.exists(path):
             raise MgwfbpError(f"load {path} (not built; run `python -m paper_1912_09268_amd.build`)", -1)
-        try:
-            from . import _calls
-        except ImportError:
-            raise MgwfbpError("load _calls (not built; run `python -m paper_1912_09268_amd.build`)", -1) from None
-        handle = C.CDLL(path)
+        handle = _Library(path)
         for name, (res, args) in _SIGNATURES.items():
             fn = getattr(handle, name)
             fn.restype = res
             fn.argtypes = args
-        _calls.install(Context)
-        _calls.set_functions(_check, {name: C.cast(getattr(handle, name), _vp).value for name in _SIGNATURES})
+        handle._entries = {name: getattr(handle, name) for name in _SIGNATURES}
+        if _calls is not None:
+            _calls.set_functions(_check, {name: C.cast(fn, _vp).value for name, fn in handle._entries.items()})
         _LIB = handle
     return _LIB
 
@@ -297,9 +319,60 @@ class Context:
         _check("mgwfbp_ctx_set_resident_bytes", lib().mgwfbp_ctx_set_resident_bytes(self._h, int(nbytes)))
 
     # ---- device calls: addresses are plain integers ---------------------------------------
-    # pack, pack_tensors, reduce, unpack_update, reduce_update, group_pipeline, direct_update, group_pipeline_span and
-    # group_pipeline_static are methods of csrc/calls.cpp, put in here when the library is loaded, with the
-    # arguments of the C ABI's functions in their order, `stream=0` last.
+    @_device_call
+    def pack(self, group: int, d_grad_ptrs: int, d_merge_bufs: int, stream: int = 0) -> None:
+        _check("mgwfbp_pack", lib().mgwfbp_pack(self._h, int(group), _vp(d_grad_ptrs), _vp(d_merge_bufs), _vp(stream)))
+
+    @_device_call
+    def pack_tensors(self, first_tensor: int, last_tensor: int, d_grad_ptrs: int, d_merge_bufs: int,
+                     stream: int = 0) -> None:
+        _check("mgwfbp_pack_tensors", lib().mgwfbp_pack_tensors(self._h, int(first_tensor), int(last_tensor),
+                                                                _vp(d_grad_ptrs), _vp(d_merge_bufs), _vp(stream)))
+
+    @_device_call
+    def reduce(self, group: int, d_merge_bufs: int, d_reduced: int, stream: int = 0) -> None:
+        _check("mgwfbp_reduce", lib().mgwfbp_reduce(self._h, int(group), _vp(d_merge_bufs), _vp(d_reduced), _vp(stream)))
+
+    @_device_call
+    def unpack_update(self, group: int, d_reduced: int, d_w_ptrs: int, d_v_ptrs: int, lr: float, momentum: float,
+                      stream: int = 0) -> None:
+        _check("mgwfbp_unpack_update", lib().mgwfbp_unpack_update(
+            self._h, int(group), _vp(d_reduced), _vp(d_w_ptrs), _vp(d_v_ptrs), float(lr), float(momentum), _vp(stream)))
+
+    @_device_call
+    def reduce_update(self, group: int, d_merge_bufs: int, d_w_ptrs: int, d_v_ptrs: int, lr: float, momentum: float,
+                      stream: int = 0) -> None:
+        _check("mgwfbp_reduce_update", lib().mgwfbp_reduce_update(
+            self._h, int(group), _vp(d_merge_bufs), _vp(d_w_ptrs), _vp(d_v_ptrs), float(lr), float(momentum), _vp(stream)))
+
+    @_device_call
+    def group_pipeline(self, group: int, d_grad_ptrs: int, d_merge_bufs: int, d_reduced: int, d_w_ptrs: int,
+                       d_v_ptrs: int, lr: float, momentum: float, stream: int = 0) -> None:
+        _check("mgwfbp_group_pipeline", lib().mgwfbp_group_pipeline(
+            self._h, int(group), _vp(d_grad_ptrs), _vp(d_merge_bufs), _vp(d_reduced or None), _vp(d_w_ptrs),
+            _vp(d_v_ptrs), float(lr), float(momentum), _vp(stream)))
+
+    @_device_call
+    def direct_update(self, group: int, d_grad_ptrs: int, d_reduced: int, d_w_ptrs: int, d_v_ptrs: int,
+                      lr: float, momentum: float, stream: int = 0) -> None:
+        _check("mgwfbp_direct_update", lib().mgwfbp_direct_update(
+            self._h, int(group), _vp(d_grad_ptrs), _vp(d_reduced or None), _vp(d_w_ptrs), _vp(d_v_ptrs),
+            float(lr), float(momentum), _vp(stream)))
+
+    @_device_call
+    def group_pipeline_span(self, group_first: int, group_count: int, d_grad_ptrs: int, d_merge_bufs: int,
+                            d_reduced: int, d_w_ptrs: int, d_v_ptrs: int, lr: float, momentum: float,
+                            stream: int = 0) -> None:
+        _check("mgwfbp_group_pipeline_span", lib().mgwfbp_group_pipeline_span(
+            self._h, int(group_first), int(group_count), _vp(d_grad_ptrs), _vp(d_merge_bufs), _vp(d_reduced or None),
+            _vp(d_w_ptrs), _vp(d_v_ptrs), float(lr), float(momentum), _vp(stream)))
+
+    @_device_call
+    def group_pipeline_static(self, group: int, d_grad_ptrs: int, d_merge_bufs: int, d_reduced: int, d_w_ptrs: int,
+                              d_v_ptrs: int, lr: float, momentum: float, stream: int = 0) -> None:
+        _check("mgwfbp_group_pipeline_static", lib().mgwfbp_group_pipeline_static(
+            self._h, int(group), _vp(d_grad_ptrs), _vp(d_merge_bufs), _vp(d_reduced or None), _vp(d_w_ptrs),
+            _vp(d_v_ptrs), float(lr), float(momentum), _vp(stream)))
 
     def handler_replay(self, group_ready_s: Sequence[float], time_scale: float, max_groups_per_launch: int,
                        streams: Sequence[int], d_grad_ptrs: int, d_merge_bufs: int, d_reduced: int, d_w_ptrs: int, d_v_ptrs: int,
@@ -315,9 +388,3 @@ class Context:
             _vp(d_reduced or None), _vp(d_w_ptrs), _vp(d_v_ptrs), float(lr), float(momentum), _ptr(stats, _f64p)))
         return int(stats[0]), float(stats[1]), float(stats[2]), float(stats[3])
 
-
-try:                     # at once where it is built, so that the class is whole before the library is loaded
-    from . import _calls
-    _calls.install(Context)
-except (ImportError, AttributeError):      # not built yet, or before its source changed: building imports this package
-    pass

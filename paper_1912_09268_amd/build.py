@@ -75,5 +75,5 @@ def build_bench_aid(verbose: bool = False) -> str:
 
 if __name__ == "__main__":  # python -m paper_1912_09268_amd.build
     print(build_library(verbose=True))
-    print(build_calls())
     print(build_bench_aid(verbose=True))
+    print(build_calls())

@@ -3,14 +3,15 @@
 // A device call enqueues a kernel and returns, and a training loop makes one per group or per tensor, so what the
 // binding adds to each counts: ctypes took 0.85 us (pack_tensors) to 1.15 us (group_pipeline) beside the 2.5 us the
 // HIP runtime needs for a launch; the conversions below take about 0.1 us.  The module has no link to the library:
-// binding.py loads that through ctypes and hands over the addresses of its entry points.  The methods are put into
-// the class Context (install), whose `_handle` is the address of the context, 0 after close().
+// binding.py loads that through ctypes and hands over the addresses of its entry points.  Each device call of the class
+// Context is a DeviceCall in front of the plain ctypes method; `_handle` of an instance is the address of the context, 0 after close().
 //
 // Conversions are those of the ctypes signatures: integers through int(), kept to 32 bits; addresses and streams
 // from an int or None; floats through float().  The interpreter lock is released during a call.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
+#include <cstddef>
 #include <cstdint>
 #include <cstring>
 
@@ -139,16 +140,26 @@ int enter(int which, void* fn, void* c, const Value* v) {
     }
 }
 
-template <int WHICH>
-PyObject* call(PyObject* self, PyObject* const* args, Py_ssize_t nargs, PyObject* kwnames) {
+// A device call as an attribute of the class: a function of its own, bound like one (the calls of an instance pass it as
+// first argument, without a bound method in between).  Where the native way is not open -- the library not loaded yet, its
+// entry point replaced -- the plain Python function it stands for is called instead.
+struct DeviceCall {
+    PyObject_HEAD
+    vectorcallfunc vectorcall;
+    int which;
+    PyObject* plain;
+    PyObject* dict;           // what functools.update_wrapper sets: name, docstring, annotations, __wrapped__
+};
+
+PyObject* call(PyObject* callable, PyObject* const* args, size_t nargsf, PyObject* kwnames) {
+    const DeviceCall* self = reinterpret_cast<DeviceCall*>(callable);
+    const int which = self->which;
+    void* const fn = g_entry[which];
+    const Py_ssize_t nargs = PyVectorcall_NARGS(nargsf);
+    if (fn == nullptr || nargs == 0) return PyObject_Vectorcall(self->plain, args, nargsf, kwnames);
     Value v[MAX_ARGS];
-    if (!parse(CALLS[WHICH], args, nargs, kwnames, v)) return nullptr;
-    void* const fn = g_entry[WHICH];
-    if (fn == nullptr) {
-        PyErr_SetString(PyExc_RuntimeError, "the library has not been loaded");
-        return nullptr;
-    }
-    PyObject* handle = PyObject_GetAttr(self, g_handle);
+    if (!parse(CALLS[which], args + 1, nargs - 1, kwnames, v)) return nullptr;
+    PyObject* handle = PyObject_GetAttr(args[0], g_handle);
     if (handle == nullptr) return nullptr;
     const unsigned long long address = PyLong_AsUnsignedLongLongMask(handle);
     Py_DECREF(handle);
@@ -156,10 +167,81 @@ PyObject* call(PyObject* self, PyObject* const* args, Py_ssize_t nargs, PyObject
     void* const ctx = reinterpret_cast<void*>(static_cast<uintptr_t>(address));
     int status;
     Py_BEGIN_ALLOW_THREADS
-    status = enter(WHICH, fn, ctx, v);
+    status = enter(which, fn, ctx, v);
     Py_END_ALLOW_THREADS
     if (status == 0) Py_RETURN_NONE;
-    return PyObject_CallFunction(g_raise, "si", CALLS[WHICH].fn, status);     // raises
+    return PyObject_CallFunction(g_raise, "si", CALLS[which].fn, status);     // raises
+}
+
+int call_index(const char* fn) {
+    for (int i = 0; i < N_CALLS; ++i)
+        if (std::strcmp(fn, CALLS[i].fn) == 0) return i;
+    return -1;
+}
+
+// DeviceCall(name of the entry point, plain function)
+PyObject* device_call_new(PyTypeObject* type, PyObject* args, PyObject* kwargs) {
+    const char* fn;
+    PyObject* plain;
+    if (kwargs != nullptr && PyDict_GET_SIZE(kwargs) > 0) {
+        PyErr_SetString(PyExc_TypeError, "DeviceCall() takes no keyword arguments");
+        return nullptr;
+    }
+    if (!PyArg_ParseTuple(args, "sO", &fn, &plain)) return nullptr;
+    const int which = call_index(fn);
+    if (which < 0) {
+        PyErr_Format(PyExc_KeyError, "%s", fn);
+        return nullptr;
+    }
+    DeviceCall* self = reinterpret_cast<DeviceCall*>(type->tp_alloc(type, 0));
+    if (self == nullptr) return nullptr;
+    self->vectorcall = call;
+    self->which = which;
+    Py_INCREF(plain);
+    self->plain = plain;
+    return reinterpret_cast<PyObject*>(self);
+}
+int device_call_traverse(PyObject* o, visitproc visit, void* arg) {
+    Py_VISIT(reinterpret_cast<DeviceCall*>(o)->plain);
+    Py_VISIT(reinterpret_cast<DeviceCall*>(o)->dict);
+    return 0;
+}
+int device_call_clear(PyObject* o) {
+    Py_CLEAR(reinterpret_cast<DeviceCall*>(o)->plain);
+    Py_CLEAR(reinterpret_cast<DeviceCall*>(o)->dict);
+    return 0;
+}
+void device_call_dealloc(PyObject* o) {
+    PyObject_GC_UnTrack(o);
+    device_call_clear(o);
+    Py_TYPE(o)->tp_free(o);
+}
+PyObject* device_call_get(PyObject* o, PyObject* obj, PyObject*) {
+    if (obj == nullptr || obj == Py_None) {
+        Py_INCREF(o);
+        return o;
+    }
+    return PyMethod_New(o, obj);
+}
+PyGetSetDef device_call_getset[] = {{"__dict__", PyObject_GenericGetDict, PyObject_GenericSetDict, nullptr, nullptr},
+                                    {nullptr, nullptr, nullptr, nullptr, nullptr}};
+PyTypeObject DeviceCallType = {PyVarObject_HEAD_INIT(nullptr, 0)};
+
+bool ready_device_call() {
+    PyTypeObject& t = DeviceCallType;
+    t.tp_name = "paper_1912_09268_amd._calls.DeviceCall";
+    t.tp_basicsize = sizeof(DeviceCall);
+    t.tp_flags = Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_GC | Py_TPFLAGS_HAVE_VECTORCALL | Py_TPFLAGS_METHOD_DESCRIPTOR;
+    t.tp_new = device_call_new;
+    t.tp_call = PyVectorcall_Call;
+    t.tp_vectorcall_offset = offsetof(DeviceCall, vectorcall);
+    t.tp_dictoffset = offsetof(DeviceCall, dict);
+    t.tp_getset = device_call_getset;
+    t.tp_descr_get = device_call_get;
+    t.tp_traverse = device_call_traverse;
+    t.tp_clear = device_call_clear;
+    t.tp_dealloc = device_call_dealloc;
+    return PyType_Ready(&t) == 0;
 }
 
 // set_functions(check, {name: address})
@@ -181,43 +263,18 @@ PyObject* set_functions(PyObject*, PyObject* args) {
     Py_RETURN_NONE;
 }
 
-#define METHOD(name, which, doc) \
-    {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(call<which>)), METH_FASTCALL | METH_KEYWORDS, doc}
-PyMethodDef methods[] = {
-    METHOD("pack", PACK, "pack(group, d_grad_ptrs, d_merge_bufs, stream=0)"),
-    METHOD("pack_tensors", PACK_TENSORS, "pack_tensors(first_tensor, last_tensor, d_grad_ptrs, d_merge_bufs, stream=0)"),
-    METHOD("reduce", REDUCE, "reduce(group, d_merge_bufs, d_reduced, stream=0)"),
-    METHOD("unpack_update", UNPACK_UPDATE, "unpack_update(group, d_reduced, d_w_ptrs, d_v_ptrs, lr, momentum, stream=0)"),
-    METHOD("reduce_update", REDUCE_UPDATE, "reduce_update(group, d_merge_bufs, d_w_ptrs, d_v_ptrs, lr, momentum, stream=0)"),
-    METHOD("group_pipeline", GROUP_PIPELINE,
-           "group_pipeline(group, d_grad_ptrs, d_merge_bufs, d_reduced, d_w_ptrs, d_v_ptrs, lr, momentum, stream=0)"),
-    METHOD("direct_update", DIRECT_UPDATE,
-           "direct_update(group, d_grad_ptrs, d_reduced, d_w_ptrs, d_v_ptrs, lr, momentum, stream=0)"),
-    METHOD("group_pipeline_span", GROUP_PIPELINE_SPAN,
-           "group_pipeline_span(group_first, group_count, d_grad_ptrs, d_merge_bufs, d_reduced, d_w_ptrs, d_v_ptrs, "
-           "lr, momentum, stream=0)"),
-    METHOD("group_pipeline_static", GROUP_PIPELINE_STATIC,
-           "group_pipeline_static(group, d_grad_ptrs, d_merge_bufs, d_reduced, d_w_ptrs, d_v_ptrs, lr, momentum, stream=0)"),
-    {nullptr, nullptr, 0, nullptr}};
-
-// install(cls): puts the device calls into the class
-PyObject* install(PyObject*, PyObject* cls) {
-    if (!PyType_Check(cls)) {
-        PyErr_SetString(PyExc_TypeError, "install() takes a class");
-        return nullptr;
-    }
-    for (PyMethodDef* m = methods; m->ml_name != nullptr; ++m) {
-        PyObject* d = PyDescr_NewMethod(reinterpret_cast<PyTypeObject*>(cls), m);
-        if (d == nullptr) return nullptr;
-        const int rc = PyObject_SetAttrString(cls, m->ml_name, d);
-        Py_DECREF(d);
-        if (rc < 0) return nullptr;
-    }
+// set_entry(name, address): one entry point, 0 for the plain function in its place
+PyObject* set_entry(PyObject*, PyObject* args) {
+    const char* fn;
+    unsigned long long address;
+    if (!PyArg_ParseTuple(args, "sK", &fn, &address)) return nullptr;
+    const int which = call_index(fn);
+    if (which >= 0) g_entry[which] = reinterpret_cast<void*>(static_cast<uintptr_t>(address));
     Py_RETURN_NONE;
 }
 
 PyMethodDef functions[] = {{"set_functions", set_functions, METH_VARARGS, "set_functions(check, {name: address})"},
-                           {"install", install, METH_O, "install(cls): puts the device calls into the class"},
+                           {"set_entry", set_entry, METH_VARARGS, "set_entry(name, address)"},
                            {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", "device calls of Context", -1, functions,
                       nullptr, nullptr, nullptr, nullptr};
@@ -226,5 +283,14 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", "device calls of Context"
 
 PyMODINIT_FUNC PyInit__calls(void) {
     if (g_handle == nullptr) g_handle = PyUnicode_InternFromString("_handle");
-    return g_handle == nullptr ? nullptr : PyModule_Create(&module);
+    if (g_handle == nullptr || !ready_device_call()) return nullptr;
+    PyObject* m = PyModule_Create(&module);
+    if (m == nullptr) return nullptr;
+    Py_INCREF(&DeviceCallType);
+    if (PyModule_AddObject(m, "DeviceCall", reinterpret_cast<PyObject*>(&DeviceCallType)) < 0) {
+        Py_DECREF(&DeviceCallType);
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
 }

@@ -1,12 +1,19 @@
 """The native device calls of Context convert their arguments as the ctypes signatures of the C ABI do.  No GPU:
 the entry points are stood in for by a function that writes down what arrives."""
 import ctypes as C
+import inspect
+import os
+import subprocess
+import sys
+import typing
 
 import numpy as np
 import pytest
 
 import paper_1912_09268_amd as M
 from paper_1912_09268_amd import binding
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 CALLS = {
     "pack": ["group", "d_grad_ptrs", "d_merge_bufs"],
@@ -113,4 +120,89 @@ def test_subclasses_override_device_calls():
     with pytest.raises(M.MgwfbpError):
         ctx.pack(0, 1, 2)                    # a host-only context: the library refuses
     assert ctx.calls == 1
+    ctx.close()
+
+
+def _in_a_fresh_interpreter(code):
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
+    return r.stdout
+
+
+def test_without_the_extension_module_everything_goes_through_ctypes():
+    """No module for this Python: planning, contexts and device calls work as they do with it."""
+    out = _in_a_fresh_interpreter("""
+import sys
+sys.modules["paper_1912_09268_amd._calls"] = None          # importing it raises ImportError
+import paper_1912_09268_amd as M
+merged, groups = M.plan([4, 4000, 4], [1e-3] * 3, 1e-2, 1e-9)
+ctx = M.Context([1, 1000, 1], merged, 2, M.F32, host_only=True)
+try:
+    ctx.group_pipeline(0, 1, 2, 0, 3, 4, 0.1, 0.9)
+except M.MgwfbpError as e:
+    print(len(merged), e.status, type(M.Context.pack).__name__)
+""")
+    assert out.split() == ["3", "-1", "function"]
+
+
+def test_device_calls_are_methods_from_the_start_and_stay_as_patched():
+    """What is put in place of a device call before the library is loaded is still there afterwards."""
+    out = _in_a_fresh_interpreter("""
+import paper_1912_09268_amd as M
+real = M.Context.pack
+def counting(self, *args):
+    print("counted", args)
+    return real(self, *args)
+M.Context.pack = counting
+ctx = M.Context([4], [0], 1, M.F32, host_only=True)
+try:
+    ctx.pack(0, 1, 2)
+except M.MgwfbpError as e:
+    print(e.status, M.Context.pack is counting)
+""")
+    assert out.splitlines() == ["counted (0, 1, 2)", "-1 True"]
+
+
+@pytest.mark.parametrize("name", sorted(CALLS))
+def test_signatures_and_hints(name):
+    call = getattr(M.Context, name)
+    sig = inspect.signature(call)
+    assert list(sig.parameters) == ["self", *CALLS[name], "stream"] and sig.parameters["stream"].default == 0
+    hints = typing.get_type_hints(call)
+    assert hints.pop("return") is type(None)
+    assert hints == {n: float if n in ("lr", "momentum") else int for n in CALLS[name] + ["stream"]}
+    assert call.__name__ == name and call.__qualname__ == f"Context.{name}" and call.__module__ == binding.__name__
+    ctx = M.Context([10], [0], 1, M.F32, host_only=True)
+    assert list(inspect.signature(getattr(ctx, name)).parameters) == [*CALLS[name], "stream"]
+    ctx.close()
+
+
+def test_a_replaced_entry_point_is_the_one_called(monkeypatch):
+    ctx = M.Context([10], [0], 1, M.F32, host_only=True)
+    seen = []
+    with monkeypatch.context() as m:
+        m.setattr(M.lib(), "mgwfbp_pack", lambda *args: seen.append(args) or 0)
+        ctx.pack(0, 1, 2)
+        assert len(seen) == 1 and seen[0][1] == 0 and seen[0][2].value == 1
+        with pytest.raises(M.MgwfbpError):
+            ctx.reduce(0, 1, 2)                  # the others are the library's
+    with pytest.raises(M.MgwfbpError):
+        ctx.pack(0, 1, 2)                        # and this one again
+    assert len(seen) == 1
+    ctx.close()
+
+
+def test_a_call_keeps_no_reference():
+    ctx = M.Context([10], [0], 1, M.F32, host_only=True)
+    before = sys.getrefcount(ctx)
+    bound = ctx.pack
+    for _ in range(100):
+        with pytest.raises(M.MgwfbpError):
+            bound(0, 1, 2)
+        with pytest.raises(TypeError):
+            ctx.pack(0, "a", 2)
+        with pytest.raises(AttributeError):
+            M.Context.pack(object(), 0, 1, 2)    # no context at all
+    del bound
+    assert sys.getrefcount(ctx) == before
     ctx.close()
