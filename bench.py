@@ -48,9 +48,9 @@ ALL_WORKLOADS = ("vgg16", "resnet50", "transformer", "tiny_layers", "toy_mlp")
 # Bytes that crossed the L2 <-> fabric boundary per pipeline launch, from two rocprofv3 --pmc runs (FETCH_SIZE,
 # then WRITE_SIZE), each scaled by what the same counter reads for a plain device copy of known size; the runs
 # are summarised in profiles/.  These counters sit in front of the memory-side cache, so this is what the
-# kernel asks of the memory system, not a count of DRAM transactions.  A figure is only valid for the kernel
-# source it was measured on: the key is the git blob hash of csrc/kernels.hip, and bench.py reports null when
-# the file has changed since.
+# kernel asks of the memory system, not a count of DRAM transactions.  A figure is only valid for the source it
+# was measured on: the key is the git blob hashes of csrc/kernels.hip and of the launch rules in csrc/launch.h,
+# and bench.py reports null when either has changed since.
 MEASURED_FABRIC_BYTES = {
     "fd3d0ccd1e08a7bcb203b5eab8bf6a152efaba89": {
         ("vgg16", "pipeline"): 1.11378e+10,
@@ -244,9 +244,11 @@ def achievable_references(P: int, reps: int = 6):
 
 
 def kernel_source_hash() -> str:
-    """git's blob hash of the kernel source, computed without git."""
-    data = open(os.path.join(ROOT, "paper_1912_09268_amd", "csrc", "kernels.hip"), "rb").read()
-    return hashlib.sha1(b"blob %d\0" % len(data) + data).hexdigest()
+    """git's blob hashes of the kernels and of the rules that launch them, computed without git."""
+    def blob(name):
+        data = open(os.path.join(ROOT, "paper_1912_09268_amd", "csrc", name), "rb").read()
+        return hashlib.sha1(b"blob %d\0" % len(data) + data).hexdigest()
+    return blob("kernels.hip") + "+" + blob("launch.h")
 
 
 def _cpu_model() -> str:
@@ -697,7 +699,7 @@ def main() -> int:
                      "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": traffic,
                      "traffic_is": "bytes at the L2-fabric boundary per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, "
                                    "scaled by a plain copy), in front of the memory-side cache; null if "
-                                   "csrc/kernels.hip changed since it was measured",
+                                   "csrc/kernels.hip or csrc/launch.h changed since it was measured",
                      "kernel_source_blob": khash,
                      "kernel": "mgwfbp_stream_kernel<%s>" % args.mode, "avg_launch_ms": round(kernel_ms, 5),
                      "algorithmic_bytes_per_launch": head["bytes_per_step"] // nl,

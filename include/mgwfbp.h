@@ -210,7 +210,7 @@ int mgwfbp_ctx_tables(const mgwfbp_ctx* ctx, int32_t* n_segments, void* tiles_ou
 
 /* Launch shape.  A tile is 256 consecutive arena elements.  By default a call launches one workgroup of 64 lanes
  * (one wavefront) per tile it covers; mgwfbp_pack, which runs as P single-worker copies, gives a workgroup one to
- * eight tiles of its worker's data and a long pipeline launch on 16-bit gradients two, and a model whose tiles mostly
+ * eight tiles of its worker's data and a long pipeline launch on 16-bit gradients two, and a launch whose tiles mostly
  * start inside the 128-byte lines of its tensors deals runs of 4 or 8 consecutive tiles to each accelerator die.
  *   blocks_per_cu > 0        caps the grid at compute units * blocks_per_cu workgroups, which then stride
  *                            over the work; <= 0 restores the default
@@ -228,7 +228,7 @@ int mgwfbp_ctx_set_launch(mgwfbp_ctx* ctx, int32_t blocks_per_cu, int32_t xcd_co
  * compute unit keeps in flight; MI355X serves the mixes of this library fastest at about 16 KiB and about a
  * tenth slower beyond 20 KiB.
  *   workgroups_per_cu  2..31 = cap; 0 = the library's default for the kind of call, the gradient type, the worker
- *                      count and the launch's length; < 0 or >= 32 = no cap
+ *                      count, the launch's length and its share of ragged tiles; < 0 or >= 32 = no cap
  *                      (a compute unit holds 32 wavefronts).  LDS is granted in blocks, so the caps that exist
  *                      are 25, 21, 18, 16, 14, 12, 11, 10, 9, 8, ...; a value in between acts as the next lower one.
  *   vectors_per_step   1 (the only paced step of a one-vector tile); 0 = the library's default; -1 = the burst

@@ -37,7 +37,7 @@
 //     16-24 KiB of loads in flight and a tenth less beyond that, so a lane has one 16-byte load outstanding
 //     (one worker's share of the tile; two workers' in the kinds that only read between their stores) and each
 //     launch asks for enough unused LDS that only so many workgroups share a compute unit, 12 to 25 or all of them
-//     by kind, gradient width, worker count and length (see default_workgroups_per_cu());
+//     by kind, gradient width, worker count, length and what the launch covers (the rules are in launch.h);
 //   - SMALL WORKGROUPS.  A workgroup is one wavefront and a tile the 256 elements it covers with one vector per
 //     lane: the same bytes in flight spread over sixteen independent wavefronts per compute unit, each at its
 //     own point of its walk, load the memory system more evenly than two workgroups of four wavefronts that
@@ -256,7 +256,7 @@ template <typename T> struct WorkerPtrs<T, 0> {
 // time), and that is the point: the memory system serves this traffic fastest when each compute unit keeps
 // only 16-24 KiB of loads in flight (the exact figure differs a little from one machine to the next) and about
 // a tenth slower beyond.  N x 16 bytes per lane of the workgroup times the workgroups a compute unit is allowed
-// to hold (see run()) sets that budget.
+// to hold (see launch.h) sets that budget.
 #ifndef MGWFBP_READ_GROUP
 #define MGWFBP_READ_GROUP 2
 #endif

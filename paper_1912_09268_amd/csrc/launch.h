@@ -83,7 +83,7 @@ constexpr size_t static_lds(int kind, bool few, int form) {
 //     the other kinds when P is not known at compile time, all P when it is (2, 4, 8, 16: nothing is stored between
 //     them, so the compiler issues them together).
 //   - With few workers a wavefront spends more of its life on the way to its first load (header, pointers) than
-//     loading, and more of them are needed: REDUCE, binary32, P = 1: 6158 uncapped against 4510 at 14, P = 3: 6278 /
+//     loading, and more of them are needed: REDUCE, binary32, P = 1: 6500 uncapped against 4390 at 14, P = 3: 6278 /
 //     5303, P = 4: 6455 at 16 / 6153 uncapped, P = 8: 6562 at 14 / 6258 uncapped.
 //   - With many workers there are more arrays to switch between and a smaller window serves them better: pipeline,
 //     binary32, P = 4: 6317 at 18 / 6254 at 14, P = 8: 6299 at 14 / 6229 at 16, P = 12: 6260 / 6076, P = 32: 5899 / 5676.
@@ -98,18 +98,24 @@ constexpr size_t static_lds(int kind, bool few, int form) {
 //     direct 0.99 / 1.05 / 1.03), and with 16 the registers cap it anyway.
 //   - 16-bit gradients need every wave slot (direct, P = 8: 6559 uncapped / 5729 at 16), but for REDUCE with all of
 //     8 or 16 workers' loads in flight (P = 16: 6381 at 16 / 6220 uncapped; P = 12, two at a time: 6512 / 5265) and
-//     for the pipeline's joined steps, which have 1 KiB under way like binary32 (P = 8: 6164 at 14 / 5886 uncapped;
-//     transformer shape, 335 M elements, where the ends of the launch weigh less, with the reduced arena 6232 at 12 /
-//     6088 at 14, without it and with a cold memory-side cache 2.643 / 2.601 ms).
+//     for the pipeline's joined steps, which have 1 KiB under way like binary32 (P = 8: 6164 at 14 / 5886 uncapped).
+//     The longest of those like a smaller window where they write the reduced arena as well.  us at 12 / 14, P = 8, with it: 46 M
+//     elements 390.4 / 389.1, 67 M 553.1 / 561.0, 102 M 859 / 871, 333 M 2831 / 2894, and with a cold memory-side cache 67 M 564 / 567, 102 M
+//     882 / 896, 333 M 2881 / 2940; P = 4, 67 M 378.7 / 383.8; P = 16 927.8 / 932.9.  Without it the two are level: 67 M 504.9 / 506.1, 102 M 787 /
+//     789, 333 M 2568 / 2589, cold 519.2 / 515.5, 800 / 800, 2630 / 2634.
 constexpr int32_t SHORT_LAUNCH_TILES = 16384;
-constexpr int32_t LONG_LAUNCH_TILES = 262144;
+constexpr int32_t LONG_LAUNCH_TILES = 262144;       // 67 M elements
 
 // Longest launch, in tiles, that takes the burst form.  Up to here the time is the latency of a tile, beyond it the
-// loads of all tiles at once are more than the memory system likes.  us burst / paced, one group, at 1024, 1792, 2048
-// and 3072 tiles: pipeline f32 P = 8: 5.3 / 8.4, 8.8 / 9.6, 10.3 / 10.0, 13.3 / 12.8; P = 16: 7.7 / 13.5, 14.1 / 15.3,
-// 16.9 / 16.1, 22.3 / 20.8; P = 3: 3.8 / 5.4, 5.0 / 6.2, 5.8 / 6.6, 6.8 / 8.0; bf16 P = 8: 4.2 / 7.7, 6.0 / 8.8, 6.9 / 9.0,
-// 9.5 / 10.5; reduce_update f32 P = 8: 4.1 / 5.4, 5.6 / 6.2, 7.0 / 6.4, 8.1 / 7.8; unpack_update 3.3 / 3.4, 3.5 / 3.9, 3.7 /
-// 4.1, 4.5 / 4.6.  At 4096 tiles the paced form is level or ahead everywhere.  PACK has one form
+// loads of all tiles at once are more than the memory system likes.  us burst / paced, one tensor, at 1024, 1792, 2048, 3072
+// and 4096 tiles: binary32 pipeline P = 8: 5.3 / 8.3, 9.0 / 9.6, 10.6 / 10.1, 13.3 / 12.7, 18.7 / 16.0; P = 16: 7.7 / 13.3, 14.2 /
+// 15.2, 17.9 / 16.1, 22.0 / 21.1, 32.7 / 26.5; P = 4: 4.5 / 5.9, 5.6 / 6.7, 6.8 / 7.1, 8.9 / 8.7, 12.2 / 10.7; P = 3: 3.7 / 5.3, 4.9 / 6.2, 6.0 /
+// 6.5, 6.8 / 7.9, 10.8 / 9.7; reduce_update P = 8: 4.0 / 5.3, 5.6 / 6.1, 7.6 / 6.3, 7.9 / 7.7, 11.5 / 9.9; unpack_update 3.1 / 3.5, 3.5 / 3.9,
+// 3.8 / 4.0, 4.5 / 4.6, 5.6 / 5.4.  bfloat16 pipeline P = 8: 4.3 / 7.6, 5.7 / 8.5, 7.1 / 8.8, 9.5 / 10.3, 11.7 / 11.6; P = 16: 5.7 / 12.0, 9.4 / 13.4,
+// 10.0 / 13.9, 13.8 / 16.0, 17.3 / 18.0; P = 4: 3.5 / 5.6, 4.7 / 6.1, 5.2 / 6.4, 6.8 / 7.6, 8.9 / 8.5; direct P = 8: 3.7 / 5.5, 4.6 / 6.1, 5.0 / 6.2,
+// 6.3 / 7.1, 7.9 / 7.6.  The lines lie where the burst form is ahead or level for every worker count they cover; some would bear
+// a later one (4096 tiles: bfloat16 pipeline P = 1 5.7 / 6.6, P = 3 7.4 / 8.1, P = 12 14.6 / 15.3, P = 32 29.3 / 30.9, reduce P = 12 6.6 / 7.3;
+// 2048 and 2560 tiles: binary32 pipeline P = 12 12.7 / 13.4 and 14.6 / 15.0, P = 32 26.1 / 28.5 and 32.2 / 33.5).  PACK has one form
 // (every load of a step under way, see joined_tiles); for it this is where the cap begins.
 inline int32_t default_burst_tiles(int kind, int32_t dtype, int32_t P) {
     if (kind == K_PACK) return 1024;
