@@ -189,9 +189,10 @@ static_assert(sizeof(Args<float>) <= 112 && sizeof(FewArgs<float>) <= 112,
 
 // Unit a workgroup starts with.  Workgroups are dealt round-robin to the 8 dies, each with an L2 of its own, so in
 // plain order neighbouring tiles belong to different dies.  Where tiles do not start on the 128-byte lines of the
-// tensors, two dies then fetch the line they share and each writes back its part of it.  Runs of a few consecutive
-// units per die (within every 8 runs of the dispatch order, so that the chip still moves through one window) let
-// all but one boundary of a run meet in one L2.  GB/s, 300 tensors of odd sizes around 100,000 elements as views of
+// tensors, two dies then fetch the line they share.  Runs of a few consecutive units per die (within every 8 runs of
+// the dispatch order, so that the chip still moves through one window) let all but one boundary of a run meet in one L2
+// (bytes the L2s fetch over those needed, 300 views of odd sizes, 8 workers: pipeline 1.139 -> 1.046, update 1.126 ->
+// 1.036, direct 1.138 -> 1.030; what they write stays at 1.01-1.04).  GB/s, 300 tensors of odd sizes around 100,000 elements as views of
 // flat buffers, 8 workers, runs of 1 / 4 / 8 / 16: direct bf16 5144 / 5716 / 5885 / 5937, unpack_update 5514 / 6042 /
 // 6085 / 6185, pipeline f32 5613 / 5888 / 5748 / 5664; on the ResNet-50 shape, nearly all of whose tiles start on lines:
 // pipeline f32 6224 / 6131 / 6005 / 5835, unpack_update 6468 / 6326 / 6344 / 6221.

@@ -55,8 +55,9 @@ constexpr int joined_tiles_of(int kind, int form) { return form == PAIRS ? PAIR 
 // the block above 160 KiB / (n + 1), so n + 1 workgroups never fit, and n do wherever a multiple of the block
 // lies in (160 KiB / (n + 1), 160 KiB / n]: 32, 25, 21, 18, 16, 14, 12, 11, 10, 9, 8, ... are the caps that
 // exist, and a request in between gets the next lower one.  The request stays 64 bytes short of that total so
-// that padding of the static part cannot push it into the next block.  62 KiB keeps clear of the 64 KiB a launch may ask for without special arrangements (so n = 1 is
-// served as n = 2).  n <= 0 means no cap, and so does an n beyond what the waves of a compute unit allow anyway.
+// that padding of the static part cannot push it into the next block.  62 KiB keeps clear of the 64 KiB a launch may
+// ask for without special arrangements (so n = 1 is served as n = 2).  n <= 0 means no cap, and so does an n beyond
+// what the waves of a compute unit allow anyway.
 inline size_t lds_for_workgroups_per_cu(int32_t n, size_t static_lds) {
     constexpr int32_t MAX_WGS = 32 * 64 / BLOCK;         // 32 waves per compute unit
     if (n <= 0 || n >= MAX_WGS) return 0;
@@ -181,20 +182,21 @@ inline int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int
     }
 }
 
-// The cap of a launch of a few rounds, binary32 or in pairs of tiles, next to the `cap` of long ones: all workgroups at once where 25 per
-// compute unit hold them (16 workers: 20 in the few-segments form, 16 in the table form and in pairs, by their registers), else the neighbour whose rounds
-// come out fullest.  Pipeline, 8 workers, one tensor of 5000 tiles (19.5 per compute unit): 21.4 / 22.1 / 22.5 us in two
+// The cap of a launch of a few rounds, binary32 or in pairs of tiles, next to the `cap` of long ones: all workgroups at
+// once where 25 per compute unit hold them (16 workers, but for REDUCE: 20 in the few-segments form, 16 in the table form
+// and in pairs, by their registers), else the neighbour whose rounds come out fullest.  Pipeline, 8 workers, one tensor of 5000 tiles (19.5 per compute unit): 21.4 / 22.1 / 22.5 us in two
 // rounds at 14 / 16 / 18, 19.1 in one.  Per cent above the best of 14 / 16 / 18 / 21, mean of reduce, direct and pipeline with
 // 8, 12, 16 and 32 workers: 7100 tiles 0.2 / 0.7 / 2.9 / 5.0, 7200 12.0 / 0.3 / 1.9 / 3.4, 8250 6.0 / 9.4 / 0.0 / 1.7, 9250 0.3 / 4.2 / 7.8 /
 // 1.8, 11000 7.5 / 0.0 / 2.3 / 6.6, 13000 1.4 / 5.3 / 0.3 / 2.2, 13900 0.5 / 2.8 / 5.7 / 1.9, 18000 2.3 / 1.5 / 0.4 / 3.0, 24000 0.9 / 0.2 /
 // 3.0 / 2.4.  The longer a tile takes and the more rounds there are, the more these blur (direct, 8 workers, 65,000 tiles:
 // 123.7 us at the cap of long launches, 127.8 at the fuller neighbour; pipeline, 32 workers, 18,000 tiles 219.8 / 227.8,
 // 16,000 184.5 / 184.1; 12 workers, 40,000 tiles 192.0 / 189.0).  Pairs, bfloat16, 16,000 tiles at 14 / 16 / 18: 8 workers 38.7 / 36.3 /
-// 37.1 us, 32 workers 111.1 / 100.9 / 103.2; 40,000 tiles 86.2 / 87.0 / 87.7, 253.3 / 254.1 / 262.8.  A cap that suits few workers (25, none) holds at any length.
+// 37.1 us, 32 workers 111.1 / 100.9 / 103.2; 40,000 tiles 86.2 / 87.0 / 87.7, 253.3 / 254.1 / 262.8.  A cap that suits few
+// workers (25, none) holds at any length.
 inline bool few_rounds(int32_t tiles, int32_t P) { return tiles < 49152 && static_cast<int64_t>(tiles) * P < 500000; }
-inline int32_t short_launch_cap(int32_t cap, int32_t P, bool few, int32_t per_cu) {
+inline int32_t short_launch_cap(int32_t cap, int kind, int32_t P, bool few, int32_t per_cu) {
     if (cap <= 0 || cap >= 25) return cap;
-    const int32_t most = P != 16 ? 25 : few ? 20 : 16;
+    const int32_t most = P != 16 || kind == K_REDUCE ? 25 : few ? 20 : 16;
     if (per_cu <= most) return 25;
     auto slots = [&](int32_t n) { return (per_cu + n - 1) / n * n; };      // of all rounds, per compute unit
     auto fuller = [&](int32_t a, int32_t b) { return slots(a) <= slots(b) ? a : b; };
@@ -211,7 +213,7 @@ inline int32_t short_launch_cap(int32_t cap, int32_t P, bool few, int32_t per_cu
 // workers 1.00 / 0.99 / 0.99 / 0.97 / 0.97; update 0.99 / 0.98 / 0.97 / 0.94 / 0.94; direct 3 workers 1.00 / 0.98 / 0.96 / 0.91 / 0.90, 8 workers
 // 1.02 / 1.00 / 0.98 / 0.94 / 0.90, 16 workers 1.03 / 1.01 / 0.99 / 0.95 / 0.93; reduce_update 3 workers 1.01 / 1.00 / 0.98 / 0.94 / 0.93, 8
 // workers 1.02 / 1.02 / 1.01 / 0.99 / 0.97, 16 workers 1.04 / 1.03 / 1.04 / 1.01 / 1.01, 32 workers 1.05 at 1; bfloat16, 8 workers, at most 1.00
-// throughout.  What a line's other half costs is one part in the many arrays that reduce_update of many workers reads.
+// throughout.
 inline int8_t run_log2_of(int kind, int32_t dtype, int32_t P, double off_lines) {
     if (kind == K_PACK || kind == K_REDUCE) return 0;
     const bool wide = dtype == MGWFBP_F32;
@@ -336,7 +338,7 @@ inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, 
     if (s.wgs_per_cu == 0) {
         s.wgs_per_cu = burst ? -1 : default_workgroups_per_cu(w.kind, w.dtype, w.P, length, w.ragged, w.reduced, s.form);
         if (s.form == PAIRS ? length < 2 * SHORT_LAUNCH_TILES : w.dtype == MGWFBP_F32 && w.kind != K_PACK && few_rounds(length, w.P))
-            s.wgs_per_cu = short_launch_cap(s.wgs_per_cu, w.P, s.may_be_few && s.form != PAIRS, per_cu);
+            s.wgs_per_cu = short_launch_cap(s.wgs_per_cu, w.kind, w.P, s.may_be_few && s.form != PAIRS, per_cu);
     }
     s.run_log2 = one_turn ? run_log2_of(w.kind, w.dtype, w.P, w.off_lines) : int8_t{0};
     return s;
