@@ -88,6 +88,10 @@ constexpr size_t static_lds(int kind, bool few, int form) {
 //     5303, P = 4: 6455 at 16 / 6153 uncapped, P = 8: 6562 at 14 / 6258 uncapped.
 //   - With many workers there are more arrays to switch between and a smaller window serves them better: pipeline,
 //     binary32, P = 4: 6317 at 18 / 6254 at 14, P = 8: 6299 at 14 / 6229 at 16, P = 12: 6260 / 6076, P = 32: 5899 / 5676.
+//     That is with the reduced arena; without it there is one array less, and up to 12 workers like 16 better.  ms at 14 / 16, cold
+//     and back to back: ResNet-50 shape, P = 6 0.273 / 0.265 and 0.261 / 0.256, P = 8 0.331 / 0.326 and 0.321 / 0.321, P = 12 0.469 / 0.464 and
+//     0.461 / 0.465, P = 16 0.604 / 0.611 and 0.600 / 0.610, P = 32 1.159 / 1.194 and 1.170 / 1.199; VGG-16 shape, P = 8 1.777 / 1.767 and 1.778 /
+//     1.747; a thousand small layers, P = 12 0.261 / 0.254 and 0.253 / 0.251, P = 16 0.325 / 0.329 and 0.323 / 0.328.
 //   - A launch of a few rounds of the chip (the compute units times the cap) should not end in a nearly empty one, see
 //     short_launch_cap().
 //   - A ragged tile (see general_tile) spends most of its time waiting for one thing after the other, longest where the
@@ -176,7 +180,7 @@ inline int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int
         case K_REDUCE_UPDATE: return wide ? (P < 4 ? 25 : P < 8 ? 16 : 14) : -1;
         case K_DIRECT: return wide ? (P < 4 ? 25 : P <= 8 ? 16 : 14) : -1;
         default:                                         // pipeline
-            if (wide) return P < 6 ? 18 : 14;
+            if (wide) return P < 6 ? 18 : !reduced && P <= 12 ? 16 : 14;
             if (form != PAIRS || tiles < SHORT_LAUNCH_TILES) return -1;
             return tiles < LONG_LAUNCH_TILES || !reduced ? 14 : 12;
     }
@@ -200,7 +204,7 @@ inline int32_t short_launch_cap(int32_t cap, int kind, int32_t P, bool few, int3
     if (per_cu <= most) return 25;
     auto slots = [&](int32_t n) { return (per_cu + n - 1) / n * n; };      // of all rounds, per compute unit
     auto fuller = [&](int32_t a, int32_t b) { return slots(a) <= slots(b) ? a : b; };
-    if (cap >= 16) return fuller(18, 21);
+    if (cap >= (kind == K_PIPELINE ? 18 : 16)) return fuller(18, 21);
     return most < 18 ? fuller(14, 16) : fuller(fuller(14, 16), 18);
 }
 

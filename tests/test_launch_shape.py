@@ -260,3 +260,11 @@ def test_builds_with_other_tiles_compile():
     for run in runs:
         out = run.communicate(timeout=120)[0]
         assert run.returncode == 0, out
+
+
+def test_binary32_pipelines_without_the_reduced_arena_take_a_wider_window(ask):
+    for P, with_it, without in ((4, 18, 18), (6, 14, 16), (8, 14, 16), (12, 14, 16), (16, 14, 14), (32, 14, 14)):
+        long = shapes(ask, [dict(P=P, tiles=99832, reduced=r) for r in (1, 0)])
+        assert [s.wgs_per_cu for s in long] == [with_it, without], P
+        short = shapes(ask, [dict(P=P, tiles=t, reduced=r) for t in range(3073, 30000, 311) for r in (1, 0)])
+        assert short[::2] == short[1::2]                     # where the rounds decide they decide alike
