@@ -19,7 +19,8 @@
 //
 // A tile that lies entirely inside one tensor takes the fast path: tensor index and source offset
 // come from the tile header, the pointer table is read once with wave-uniform addresses, and the tile is
-// walked in paced steps, one worker at a time (see paced_step).  Any other tile takes the general path:
+// walked in paced steps, one worker at a time (see paced_step).  Any other tile that holds a few pieces of tensors (nearly
+// always one: the end of a group) is taken piece by piece (one_piece, several_pieces).  What is left takes the general path:
 // the tile-local start offsets of the segments it intersects are produced by a workgroup-wide prefix sum
 // (wavefront scans via cross-lane shifts, combined through LDS) over the segment lengths, staged in LDS,
 // and each lane finds the owner of its vector by binary search there.  Vectors that straddle two tensors,
@@ -199,6 +200,7 @@ static_assert(sizeof(Args<float>) <= 112 && sizeof(FewArgs<float>) <= 112,
 template <typename GradT> __device__ __forceinline__ int unit_of(const CallArgs<GradT>& A) {
     const int b = static_cast<int>(blockIdx.x);
     const int r = A.run_log2;
+    if (r == 0) return b;
     const int within = b & ((8 << r) - 1);
     const int last = b - within + (8 << r) - 1;           // last unit of this set of eight runs
     if (static_cast<int64_t>(last) * A.tiles_per_wg >= A.tile_count) return b;      // the launch ends before it
@@ -261,9 +263,14 @@ template <typename T> struct WorkerPtrs<T, 0> {
 #ifndef MGWFBP_READ_GROUP
 #define MGWFBP_READ_GROUP 2
 #endif
+#ifndef MGWFBP_TOGETHER
+#define MGWFBP_TOGETHER 8         // workers whose loads go out together in the burst form and in ragged tiles of one tensor
+#endif                            // where the worker count is not compiled (where it is: all of them)
 #ifndef MGWFBP_GENERAL_GROUP
 #define MGWFBP_GENERAL_GROUP 64   // workers whose loads the general path issues together (64: all of them)
 #endif
+
+constexpr int SOME = 4;               // the same where every lane has pointers of its own
 
 // keeps the compiler from moving the next group's loads above this group's arithmetic
 __device__ __forceinline__ void pace() { __builtin_amdgcn_sched_barrier(0); }
@@ -300,7 +307,16 @@ __device__ __forceinline__ void update_step(const CallArgs<GradT>& A, float* wp,
     }
 }
 
-template <int KIND, typename GradT, int PT, int W, int N, bool WVNT, bool TOGETHER = false>
+template <int N> struct Int { static constexpr int value = N; };
+// f(Int<n>()) for an n of 1 .. MOST; nothing for 0.
+template <int MOST, typename F> __device__ __forceinline__ void some_sizes(int n, F&& f) {
+    if constexpr (MOST > 0) {
+        if (n == MOST) f(Int<MOST>());
+        else some_sizes<MOST - 1>(n, f);
+    }
+}
+
+template <int KIND, typename GradT, int PT, int W, int N, bool WVNT, int TOGETHER = 0>
 __device__ __forceinline__ void paced_step(const CallArgs<GradT>& A, const WorkerPtrs<const GradT, PT>& src,
                                            const WorkerPtrs<GradT, PT>& mrg, float* wp, float* vp,
                                            int64_t soff, int64_t apos, int stride) {
@@ -309,9 +325,9 @@ __device__ __forceinline__ void paced_step(const CallArgs<GradT>& A, const Worke
     constexpr int C = Lanes<GV>::n;
     FV acc[N];
     // the general path wants everything under way at once: its v and w loads go out before the gradients'
-    constexpr int NE = (updates(KIND) && TOGETHER) ? N : 1;
+    constexpr int NE = (updates(KIND) && TOGETHER > 0) ? N : 1;
     FV v_early[NE], w_early[NE];
-    if constexpr (updates(KIND) && TOGETHER) {
+    if constexpr (updates(KIND) && TOGETHER > 0) {
 #pragma unroll
         for (int i = 0; i < N; ++i) v_early[i] = ld<WVNT, FV>(vp + soff + i * stride);
 #pragma unroll
@@ -319,56 +335,55 @@ __device__ __forceinline__ void paced_step(const CallArgs<GradT>& A, const Worke
     }
     if constexpr (reads_grads(KIND) || reads_merge(KIND)) {
         // workers whose loads are issued together: one (kinds that store each worker's share before the next
-        // load), MGWFBP_READ_GROUP (kinds that only read them), or all of them / four at a time (TOGETHER: the
-        // general path, whose lanes also have to fetch their own pointers and gain from overlapping all of that)
-        constexpr int GW = TOGETHER ? (PT > 0 ? (PT < MGWFBP_GENERAL_GROUP ? PT : MGWFBP_GENERAL_GROUP) : 4) : (writes_merge(KIND) ? 1 : MGWFBP_READ_GROUP);
-        auto some_workers = [&](int w0, int count) {      // workers w0 .. w0 + count - 1, count <= GW
-            GV g[GW][N];
+        // load), MGWFBP_READ_GROUP (kinds that only read them), or all of them / TOGETHER at a time (the burst form and
+        // the ragged tiles, whose time is the chain of trips to memory)
+        constexpr int GW = TOGETHER > 0 ? (PT > 0 ? (PT < MGWFBP_GENERAL_GROUP ? PT : MGWFBP_GENERAL_GROUP) : TOGETHER) : (writes_merge(KIND) ? 1 : MGWFBP_READ_GROUP);
+        auto some_workers = [&](auto size, int w0) {      // workers w0 .. w0 + size - 1
+            constexpr int COUNT = decltype(size)::value;
+            GV g[COUNT][N];
 #pragma unroll
-            for (int j = 0; j < GW; ++j) {
-                if (j < count) {
-                    const GradT* from;
-                    if constexpr (reads_grads(KIND)) from = src.get(w0 + j) + soff;
-                    else from = mrg.get(w0 + j) + apos;
+            for (int j = 0; j < COUNT; ++j) {
+                const GradT* from;
+                if constexpr (reads_grads(KIND)) from = src.get(w0 + j) + soff;
+                else from = mrg.get(w0 + j) + apos;
 #pragma unroll
-                    for (int i = 0; i < N; ++i) g[j][i] = ld<NT_LD, GV>(from + i * stride);
-                }
+                for (int i = 0; i < N; ++i) g[j][i] = ld<NT_LD, GV>(from + i * stride);
             }
             // kinds that store and add each worker's share: every load of the step is issued before the first
             // value is used (left alone, the scheduler now and then puts an add, and with it a wait for the
             // first load, in front of the second load)
             if constexpr (writes_merge(KIND) && sums(KIND)) pace();
 #pragma unroll
-            for (int j = 0; j < GW; ++j) {
-                if (j < count) {
-                    if constexpr (writes_merge(KIND)) {
-                        GradT* to = mrg.get(w0 + j) + apos;
+            for (int j = 0; j < COUNT; ++j) {
+                if constexpr (writes_merge(KIND)) {
+                    GradT* to = mrg.get(w0 + j) + apos;
 #pragma unroll
-                        for (int i = 0; i < N; ++i) st<NT_ST, GV>(to + i * stride, g[j][i]);
-                    }
-                    if constexpr (sums(KIND)) {
+                    for (int i = 0; i < N; ++i) st<NT_ST, GV>(to + i * stride, g[j][i]);
+                }
+                if constexpr (sums(KIND)) {
 #pragma unroll
-                        for (int i = 0; i < N; ++i)
+                    for (int i = 0; i < N; ++i)
 #pragma unroll
-                            for (int c = 0; c < C; ++c) {
-                                const float x = widen(comp(g[j][i], c));
-                                setc(acc[i], c, (w0 + j == 0) ? x : comp(acc[i], c) + x);
-                            }
-                    }
+                        for (int c = 0; c < C; ++c) {
+                            const float x = widen(comp(g[j][i], c));
+                            setc(acc[i], c, (w0 + j == 0) ? x : comp(acc[i], c) + x);
+                        }
                 }
             }
+            pace();
         };
         if constexpr (PT > 0) {
 #pragma unroll
             for (int w0 = 0; w0 < PT; w0 += GW) {
-                some_workers(w0, PT - w0 < GW ? PT - w0 : GW);
-                pace();
+                if (w0 + GW <= PT) some_workers(Int<GW>(), w0);
+                else some_workers(Int<PT % GW + (PT % GW == 0)>(), w0);
             }
         } else {
-            for (int w0 = 0; w0 < A.P; w0 += GW) {
-                some_workers(w0, A.P - w0 < GW ? A.P - w0 : GW);
-                pace();
-            }
+            // A worker count that is not compiled: whole groups, then one of the size that is left, so that no worker
+            // costs a branch and none waits for another group that it could have been part of.
+            int w0 = 0;
+            for (; w0 + GW <= A.P; w0 += GW) some_workers(Int<GW>(), w0);
+            some_sizes<GW - 1>(A.P - w0, [&](auto size) { some_workers(size, w0); });
         }
         if constexpr (sums(KIND)) {
 #pragma unroll
@@ -387,7 +402,7 @@ __device__ __forceinline__ void paced_step(const CallArgs<GradT>& A, const Worke
             for (int i = 0; i < N; ++i) st<NT_ST, FV>(A.reduced + apos + i * stride, acc[i]);
         }
     }
-    if constexpr (updates(KIND) && TOGETHER) {
+    if constexpr (updates(KIND) && TOGETHER > 0) {
 #pragma unroll
         for (int i = 0; i < N; ++i) {
 #pragma unroll
@@ -416,7 +431,7 @@ __device__ __forceinline__ void do_one(const CallArgs<GradT>& A, const WorkerPtr
         wp = ro(A.w_ptrs)[layer];
         vp = ro(A.v_ptrs)[layer];
     }
-    paced_step<KIND, GradT, PT, W, 1, NT_WV, true>(A, src, mrg, wp, vp, soff, apos, 0);
+    paced_step<KIND, GradT, PT, W, 1, NT_WV, SOME>(A, src, mrg, wp, vp, soff, apos, 0);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -443,7 +458,7 @@ __device__ __forceinline__ void fast_chunk(const CallArgs<GradT>& A, const Worke
         // burst: every load of the tile under way at once.  The form for a launch too small to fill the chip,
         // where the time is the tile's own latency and not the memory system's throughput.
         for (int u = 0; u < nvec; u += TVECS)
-            paced_step<KIND, GradT, PT, VEC, TVECS, WVNT, true>(A, src, mrg, wp, vp,
+            paced_step<KIND, GradT, PT, VEC, TVECS, WVNT, MGWFBP_TOGETHER>(A, src, mrg, wp, vp,
                                                                 soff + static_cast<int64_t>(u) * STEP,
                                                                 apos + static_cast<int64_t>(u) * STEP, STEP);
     } else {
@@ -507,6 +522,76 @@ __device__ __forceinline__ void joined_tiles(const CallArgs<GradT>& A, const Wor
             for (int i = 0; i < N; ++i) st<NT_ST, f32x4>(A.reduced + tile_base + lane_elem + i * BLOCK * VEC, acc[i]);
         }
         update_step<N, true>(A, wp, vp, tensor_off + lane_elem, BLOCK * VEC, acc);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// ragged tiles: a few pieces of tensors
+// ---------------------------------------------------------------------------------------------
+//
+// What a ragged tile takes is the chain of trips to memory in front of its last store: in a launch of a few tiles nothing
+// else is under way, and in one of many such tiles a wavefront does nothing but wait.  The general path has five such trips
+// and more (segment lengths, pointers, whole vectors; pointers and values of the single elements left over) and runs some 400
+// instructions; a tile of one piece here has two, its pointers through the scalar unit and all of its data.  GPU time per
+// launch, us, before and after (an empty launch takes 1.54): one tensor of 101 elements, 8 workers, binary32: pack 2.97 /
+// 2.00, pipeline 2.90 / 2.05, unpack_update 2.43 / 1.61; 10 tiles and a ragged one, 3 workers: pipeline 3.59 / 2.26, 12 workers
+// 6.47 / 2.99, 32 workers 13.0 / 5.8.  In the table form, 600 tensors of 301 elements, each a group: pipeline 3 workers 6.2 /
+// 3.9, 8 workers 7.5 / 5.5, 16 workers 10.0 / 8.7; in groups of eight 7.2 / 5.6, 7.1 / 6.4, 9.4 / 8.4.
+
+// Tile-local elements [lo, hi) are the elements from `off` on of tensor `layer`.
+struct Piece {
+    int layer, lo, hi;
+    int64_t off;
+    __device__ __forceinline__ int len() const { return hi - lo; }
+    __device__ __forceinline__ int lanes() const { return (hi - lo + VEC - 1) / VEC; }
+    // First element of the vector lane k takes.  The last one ends with the piece and so overlaps the one before it where
+    // the piece is no whole number of vectors.  That is harmless: both belong to one wavefront, which has read all it
+    // needs of them before it writes, and both lanes write the same values.
+    __device__ __forceinline__ int element(int k) const { return min(k * VEC, len() - VEC); }
+};
+
+// One piece by itself: its pointers are the same for all lanes.  Of a full tile, too, in the burst form.
+template <int KIND, typename GradT, int PT, bool WVNT>
+__device__ __forceinline__ void one_piece(const CallArgs<GradT>& A, const WorkerPtrs<GradT, PT>& mrg, int64_t tile_base, const Piece& s) {
+    WorkerPtrs<const GradT, PT> src;
+    float* wp = nullptr;
+    float* vp = nullptr;
+    if constexpr (reads_grads(KIND)) src.fetch(A.grad_ptrs, A.L, s.layer, worker_base<KIND>());
+    if constexpr (updates(KIND)) {
+        wp = ro(A.w_ptrs)[s.layer];
+        vp = ro(A.v_ptrs)[s.layer];
+    }
+    const int lane = static_cast<int>(threadIdx.x);
+    if (lane < s.lanes()) {
+        const int e = s.element(lane);
+        paced_step<KIND, GradT, PT, VEC, 1, WVNT, MGWFBP_TOGETHER>(A, src, mrg, wp, vp, s.off + e, tile_base + s.lo + e, 0);
+    }
+}
+
+// Several pieces: each lane takes a vector of one of them and fetches that tensor's pointers itself; pieces shorter than a
+// vector go element by element.  The vectors of a full tile are one too many for the lanes where two tensors meet inside a
+// vector: then the pieces are taken as many at a time as there are lanes for (a piece never in two parts, see element()).
+template <int KIND, typename GradT, int PT, typename Pieces>
+__device__ __forceinline__ void several_pieces(const CallArgs<GradT>& A, const WorkerPtrs<GradT, PT>& mrg, int64_t tile_base, Pieces pieces) {
+    const int lane = static_cast<int>(threadIdx.x);
+    Piece s;
+    bool more = pieces.next(s);
+    while (more) {
+        int used = 0, layer = 0, at = 0;
+        int64_t off = 0;
+        for (; more && used + s.lanes() <= BLOCK; more = pieces.next(s)) {
+            if (s.len() < VEC) {
+                if (lane < s.len()) do_one<KIND, GradT, PT, 1>(A, mrg, s.layer, s.off + lane, tile_base + s.lo + lane);
+                continue;
+            }
+            if (lane >= used) {                            // lanes past this piece get the next one's, or stay idle
+                layer = s.layer;
+                at = s.lo + s.element(lane - used);
+                off = s.off + s.element(lane - used);
+            }
+            used += s.lanes();
+        }
+        if (lane < used) do_one<KIND, GradT, PT, VEC>(A, mrg, layer, off, tile_base + at);
     }
 }
 
@@ -631,9 +716,47 @@ __device__ __forceinline__ TileHdr load_header(const TileHdr* p) {
     return h;
 }
 
+// The pieces of a tile in the table form.
+template <int KIND, typename GradT> struct TablePieces {
+    const Args<GradT>& A;
+    const TileHdr& h;
+    int clo, chi;
+    int j = 0, end = 0;
+    __device__ __forceinline__ bool only(Piece& s) const {
+        if constexpr (needs_owner(KIND)) {
+            s = Piece{h.layer0, clo, chi, clo - h.first_start};
+            return h.nseg == 1;
+        } else {
+            s = Piece{0, clo, chi, 0};
+            return true;
+        }
+    }
+    __device__ __forceinline__ bool next(Piece& s) {
+        if constexpr (!needs_owner(KIND)) {
+            s = Piece{0, clo, chi, 0};
+            return j++ == 0;
+        }
+        if (j >= h.nseg) return false;
+        int64_t start = h.first_start;
+        s.layer = h.layer0;
+        if (j == 0) {
+            end = h.first_end;
+        } else {
+            start = end;
+            s.layer = ro(seg_layer(A))[h.seg0 + j];
+            end = j + 1 < h.nseg ? end + static_cast<int>(ro(seg_n(A))[h.seg0 + j]) : h.valid;
+        }
+        s.lo = j == 0 ? clo : max(static_cast<int>(start), clo);
+        s.hi = min(end, chi);
+        s.off = s.lo - start;
+        ++j;
+        return true;
+    }
+};
+
 // FORM: vectors per lane a fast tile is walked in (1, see paced_step), BURST or PAIRS.
 template <int KIND, typename GradT, int PT, int FORM>
-__global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_stream_kernel(const Args<GradT> A) {
+__global__ void __launch_bounds__(MGWFBP_BLOCK, KIND == K_PIPELINE && sizeof(GradT) == 2 && PT == 0 && FORM == 1 ? 8 : 1) mgwfbp_stream_kernel(const Args<GradT> A) {
     constexpr int SINGLE = FORM == PAIRS ? 1 : FORM;     // single tiles
     constexpr int JOIN = joined_tiles_of(KIND, FORM);
     __shared__ int s_loc[MAXSEG + 1];
@@ -672,10 +795,32 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_stream_kernel(const Args<
             const int clo = t == 0 ? A.clip_lo : 0;
             const int chi = t == A.tile_count - 1 ? min(h.valid, static_cast<int>(A.clip_hi)) : h.valid;
             if (chi <= clo) continue;
-            if (!(clo == 0 && chi == TILE && (!needs_owner(KIND) || h.nseg == 1))) {
+            const bool full = clo == 0 && chi == TILE && (!needs_owner(KIND) || h.nseg == 1);
+            if constexpr (HAVE_PIECES) {
+                const TablePieces<KIND, GradT> pieces{A, h, clo, chi};
+                Piece s;
+                if ((FORM == BURST || !full) && pieces.only(s) && s.len() >= VEC) {
+                    if (!updates(KIND) || (h.flags & 1)) {             // (see below)
+                        asm volatile("; w and v cacheable" ::: "memory");
+                        one_piece<KIND, GradT, PT, NT_WV>(A, mrg, tile_base, s);
+                        asm volatile("; end w and v cacheable" ::: "memory");
+                    } else {
+                        asm volatile("; w and v streamed" ::: "memory");
+                        one_piece<KIND, GradT, PT, true>(A, mrg, tile_base, s);
+                        asm volatile("; end w and v streamed" ::: "memory");
+                    }
+                    continue;
+                }
+                if (!full && (!needs_owner(KIND) || h.nseg <= MGWFBP_PIECES)) {
+                    several_pieces<KIND, GradT, PT>(A, mrg, tile_base, pieces);
+                    continue;
+                }
+            }
+            if (!full) {
                 general_tile<KIND, GradT, PT>(A, mrg, h, tile_base, clo, chi, s_loc, s_layer, s_wave, s_ragged, &s_nragged);
                 continue;
             }
+            if constexpr (HAVE_PIECES && FORM == BURST) continue;      // taken above
             // A full tile inside one tensor.
             if constexpr (JOIN > 1) {
                 // (A clip cuts into the first and the last tile only.)
@@ -742,12 +887,10 @@ template <typename GradT> __device__ __forceinline__ FewSeg few_owner(const FewA
 }
 
 template <int KIND, typename GradT, int PT, int FORM>
-__global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_few_kernel(const FewArgs<GradT> A) {
+__global__ void __launch_bounds__(MGWFBP_BLOCK, KIND == K_REDUCE_UPDATE && PT == 16 && sizeof(GradT) == 4 ? 5 : 1) mgwfbp_few_kernel(const FewArgs<GradT> A) {
     static_assert(KIND >= 0 && HAVE_FEW, "a tile is one vector per lane of one wavefront");
     constexpr int SINGLE = FORM == PAIRS ? 1 : FORM;
     constexpr int JOIN = joined_tiles_of(KIND, FORM);
-    WorkerPtrs<GradT, PT> mrg;
-    if constexpr (reads_merge(KIND) || writes_merge(KIND)) mrg.fetch(A.merge_bufs, 1, 0, worker_base<KIND>());
     __shared__ __align__(16) float s_sums[FORM == PAIRS ? PAIRED : 4];
     const int lane = threadIdx.x;
     const int64_t arena = static_cast<int64_t>(A.tile_first) * TILE;
@@ -756,16 +899,36 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_few_kernel(const FewArgs<
     const int t_end = min((u + 1) * K, A.tile_count);
     for (int t = u * K; t < t_end; ++t) {
         const int b = t * TILE;
-        const FewSeg s = few_owner(A, b);                                  // uniform
-        if (s.start <= b && b + TILE <= s.end) {                           // a full tile inside one segment
+        auto mrg = [&] {                                                   // (fetched where it is used: 16 workers have no registers to keep it in)
+            WorkerPtrs<GradT, PT> m;
+            if constexpr (reads_merge(KIND) || writes_merge(KIND)) m.fetch(A.merge_bufs, 1, 0, worker_base<KIND>());
+            return m;
+        };
+        // Segment that ends in the tile or beyond it; all of the tile's if it is the last one or ends beyond it.
+        const MGWFBP_CONST FewArgs<GradT>* a = (const MGWFBP_CONST FewArgs<GradT>*)__builtin_amdgcn_kernarg_segment_ptr();
+        int j = 0;
+        while (j + 1 < A.n && a->end[j] <= b) ++j;
+        const int end = a->end[j];
+        int start = A.start0;
+        if (j > 0) {
+            const int e = a->end[j - 1];
+            start = (A.closes >> (j - 1)) & 1 ? (e + TILE - 1) & ~(TILE - 1) : e;
+        }
+        if (FORM != BURST && start <= b && b + TILE <= end) {              // a full tile inside one segment
             if constexpr (JOIN > 1) {
-                if (t + JOIN <= t_end && b + JOIN * TILE <= s.end) {
-                    joined_tiles<KIND, GradT, PT>(A, mrg, A.layer_hi - s.j, b - s.start, arena + b, s_sums);
+                if (t + JOIN <= t_end && b + JOIN * TILE <= end) {
+                    joined_tiles<KIND, GradT, PT>(A, mrg(), A.layer_hi - j, b - start, arena + b, s_sums);
                     t += JOIN - 1;
                     continue;
                 }
             }
-            fast_chunk<KIND, GradT, PT, true, SINGLE>(A, mrg, A.layer_hi - s.j, b - s.start, arena + b, TVECS);
+            fast_chunk<KIND, GradT, PT, true, SINGLE>(A, mrg(), A.layer_hi - j, b - start, arena + b, TVECS);
+            continue;
+        }
+        const Piece s{A.layer_hi - j, max(start - b, 0), min(end - b, TILE), b + max(start - b, 0) - start};
+        const bool only = j + 1 >= A.n || end >= b + TILE || ((A.closes >> j) & 1);
+        if (only && s.len() >= VEC) {
+            one_piece<KIND, GradT, PT, true>(A, mrg(), arena + b, s);
             continue;
         }
         // Whole vectors first, then the wanted elements of the others, one per lane (see general_tile).
@@ -774,14 +937,14 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK) mgwfbp_few_kernel(const FewArgs<
         const bool whole = p >= o.start && p + VEC <= o.end;
         const bool any = (p < o.end && p + VEC > o.start) || few_owner(A, p + VEC - 1).j != o.j;
         const uint64_t ragged = __ballot(any && !whole);
-        if (whole) do_one<KIND, GradT, PT, VEC>(A, mrg, A.layer_hi - o.j, p - o.start, arena + p);
+        if (whole) do_one<KIND, GradT, PT, VEC>(A, mrg(), A.layer_hi - o.j, p - o.start, arena + p);
         const int n_ragged = __popcll(ragged) * VEC;
         for (int e = lane; e < n_ragged; e += BLOCK) {
             uint64_t rest = ragged;
             for (int k = e / VEC; k > 0; --k) rest &= rest - 1;
             const int q = b + __builtin_ctzll(rest) * VEC + e % VEC;
             const FewSeg r = few_owner(A, q);
-            if (q >= r.start && q < r.end) do_one<KIND, GradT, PT, 1>(A, mrg, A.layer_hi - r.j, q - r.start, arena + q);
+            if (q >= r.start && q < r.end) do_one<KIND, GradT, PT, 1>(A, mrg(), A.layer_hi - r.j, q - r.start, arena + q);
         }
     }
 }

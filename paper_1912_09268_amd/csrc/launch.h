@@ -42,6 +42,14 @@ constexpr int PAIRED = PAIR * TILE;   // elements of a pair
 // What needs tiles of one vector per lane, and of one wavefront, is left out of builds with other tiles.
 constexpr bool HAVE_PAIRS = TVECS == 1;
 constexpr bool HAVE_FEW = TVECS == 1 && BLOCK == 64;
+constexpr bool HAVE_PIECES = TVECS == 1;
+// Most segments of a tile that the table form takes piece by piece; the walk over the pieces costs 0.15 us each, the general
+// path's prefix sum and search the same for any number.  us with one, up to three and up to eight, 8 workers, tensors in
+// groups of eight and more: of 301 elements pipeline 7.2 / 6.4 / 6.4, unpack_update 4.6 / 4.0 / 4.0; of 70 elements pipeline 7.4 /
+// 7.3 / 7.0, pack 8.7 / 8.7 / 7.8; of 20 elements (13 pieces, so the general path throughout) 4.5 / 4.5 / 4.5.
+#ifndef MGWFBP_PIECES
+#define MGWFBP_PIECES 8
+#endif
 // Kinds whose wavefronts have too little under way with one tile can take joined steps: PACK, a plain copy, always, and
 // the pipeline on 16-bit gradients, where a worker's share of a tile is 512 bytes, in kernels of their own: beside the
 // joined step, whose sums change hands through LDS, the single-tile kernel would need 105 instead of 74 registers (16
@@ -70,11 +78,11 @@ inline size_t lds_for_workgroups_per_cu(int32_t n, size_t static_lds) {
     return total - static_lds - 64;
 }
 
-// LDS the kernels declare themselves: the table form for its general path (REDUCE needs less of it), both forms for
-// the sums of joined steps.
+// LDS the kernels declare themselves: the table form for its general path (which REDUCE needs with tiles of several
+// vectors per lane only, and less of it), both forms for the sums of joined steps.
 constexpr size_t static_lds(int kind, bool few, int form) {
     const size_t joined = form == PAIRS ? sizeof(float) * PAIRED : 0;
-    return few ? joined : joined + sizeof(int) * static_cast<size_t>((needs_owner(kind) ? 2 * MAXSEG + 1 + BLOCK / 64 : 0) + TILE / VEC + 1);
+    return few || (HAVE_PIECES && !needs_owner(kind)) ? joined : joined + sizeof(int) * static_cast<size_t>((needs_owner(kind) ? 2 * MAXSEG + 1 + BLOCK / 64 : 0) + TILE / VEC + 1);
 }
 
 // Default caps, measured on the ResNet-50 shape (25.6 M elements, cold) with every cap that exists, worker counts

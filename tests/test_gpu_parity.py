@@ -525,6 +525,27 @@ def test_launches_over_few_segments(mode, P, dtype):
         _check_incremental(p, merged[::-1], lambda L: [1 + i % 10 for i in range(L)], misalign=5, label="runs of 1 to 10")
 
 
+@pytest.mark.parametrize("P,dtype", [(1, "bf16"), (2, "f32"), (3, "f32"), (5, "f16"), (7, "f32"), (8, "bf16"), (9, "f32"), (15, "bf16"),
+                                     (16, "f32"), (17, "f32"), (24, "f16")])
+def test_ragged_tiles_piece_by_piece(P, dtype):
+    """Tiles that hold one piece of a tensor (of 1 to 9 elements, and around every place where the last vector of a tile
+    can begin), two or three, exactly as many vectors as a wavefront has lanes and one more, pieces shorter than a
+    vector between longer ones, eight pieces and nine; worker counts around the groups of eight that go together where
+    the count is not compiled.  Two steps: a weight that two lanes hold would be updated twice."""
+    one = [[n] for n in (*range(1, 10), 63, 64, 65, *range(249, 261), 511, 515)]
+    several = [[1000, 1024], [1001, 1023], [1002, 3, 400], [64, 64, 4096], [65, 2, 66, 1, 67], [255, 255, 255], [20] * 8, [21] * 8,
+               [30] * 9, [1, 1, 1, 1], [3, 253, 3], [4, 252], [300, 5, 207, 1, 3, 252]]
+    arrival = [n for g in one + several for n in g]
+    merged = [m for g in one + several for m in [1] * (len(g) - 1) + [0]]
+    rng = np.random.default_rng(16)
+    p = W.Profile("pieces", np.asarray(arrival[::-1], np.uint64), rng.uniform(1e-6, 1e-5, len(arrival)), 1e-4, 1e-9, P, dtype, 1.0)
+    for mode in ("pipeline", "staged", "direct", "reduce_update", "pipeline_per_group"):
+        check_case(p, merged[::-1], mode, misalign=3, steps=2, label="pieces, everything at once")
+        check_case(p, merged[::-1], mode, steps=2, small_launch=0, label="pieces, paced")
+    check_case(p, merged[::-1], "pipeline", steps=2, resident=4096, label="pieces, a resident share")
+    _check_incremental(p, merged[::-1], lambda L: [1 + i % 11 for i in range(L)], misalign=5, label="runs of 1 to 11")
+
+
 @pytest.mark.parametrize("P,dtype", [(2, "bf16"), (3, "f16"), (8, "bf16"), (16, "f16")])
 def test_sixteen_bit_pipeline_takes_tiles_in_pairs(P, dtype):
     """Long 16-bit pipeline launches take two full tiles (512 elements) of one tensor in one step.  Tensors that end
