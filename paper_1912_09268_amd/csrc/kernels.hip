@@ -207,16 +207,29 @@ template <typename GradT> __device__ __forceinline__ int unit_of(const CallArgs<
     return b - within + ((within & 7) << r) + (within >> 3);
 }
 
+// What a path works out from x stays on that path.  The compiler moves whatever does not change from tile to tile in front
+// of the walk, where every workgroup pays for it: lane masks of the prefix sum, addresses of the segment tables and starts of
+// the segments of the few-segments form were some 100 instructions in front of tiles that need none of them, and a dozen
+// registers.  With the arguments fetched in one trip (see the kernels) a launch of 1 to 1000 tiles takes 0.1-0.5 us less: 10 tiles and
+// a ragged one, 8 workers, pipeline 2.32 -> 2.16, pack 1.97 -> 1.84, unpack_update 2.06 -> 1.87; 1000 tiles, unpack_update 3.22 -> 2.67.
+__device__ __forceinline__ void here_only(int32_t& x) { asm volatile("" : "+s"(x)); }          // the same for all lanes
+__device__ __forceinline__ void here_only_per_lane(int32_t& x) { asm volatile("" : "+v"(x)); }
+
 // The tables of one model lie in one block: seg_layer[S], seg_n[S] and seg_off[S + 1], ending where the tile headers
 // begin, so that the address of the headers and S lead to all of them.
-template <typename GradT> __device__ __forceinline__ const uint64_t* seg_off(const Args<GradT>& A) {
-    return reinterpret_cast<const uint64_t*>(A.tiles) - (A.n_seg + 1);
-}
-template <typename GradT> __device__ __forceinline__ const uint32_t* seg_n(const Args<GradT>& A) {
-    return reinterpret_cast<const uint32_t*>(seg_off(A)) - A.n_seg;
-}
-template <typename GradT> __device__ __forceinline__ const int32_t* seg_layer(const Args<GradT>& A) {
-    return reinterpret_cast<const int32_t*>(seg_n(A)) - A.n_seg;
+struct SegTables {
+    const uint64_t* off;
+    const uint32_t* n;
+    const int32_t* layer;
+};
+template <typename GradT> __device__ __forceinline__ SegTables seg_tables(const Args<GradT>& A) {
+    int32_t S = A.n_seg;
+    here_only(S);
+    SegTables t;
+    t.off = reinterpret_cast<const uint64_t*>(A.tiles) - (S + 1);
+    t.n = reinterpret_cast<const uint32_t*>(t.off) - S;
+    t.layer = reinterpret_cast<const int32_t*>(t.n) - S;
+    return t;
 }
 
 // First worker a workgroup serves.  PACK has no arithmetic across workers, so it is launched as P
@@ -573,7 +586,8 @@ __device__ __forceinline__ void one_piece(const CallArgs<GradT>& A, const Worker
 // vector: then the pieces are taken as many at a time as there are lanes for (a piece never in two parts, see element()).
 template <int KIND, typename GradT, int PT, typename Pieces>
 __device__ __forceinline__ void several_pieces(const CallArgs<GradT>& A, const WorkerPtrs<GradT, PT>& mrg, int64_t tile_base, Pieces pieces) {
-    const int lane = static_cast<int>(threadIdx.x);
+    int lane = static_cast<int>(threadIdx.x);
+    here_only_per_lane(lane);
     Piece s;
     bool more = pieces.next(s);
     while (more) {
@@ -601,9 +615,9 @@ __device__ __forceinline__ void several_pieces(const CallArgs<GradT>& A, const W
 
 // Inclusive prefix sum across the lanes of the workgroup: shift-and-add inside each wavefront,
 // wavefront totals combined through LDS.  Every lane of the workgroup must call it.
-__device__ __forceinline__ int block_inclusive_scan(int x, int* s_wave) {
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+__device__ __forceinline__ int block_inclusive_scan(int tid, int x, int* s_wave) {
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
         const int y = __shfl_up(x, d, 64);
@@ -629,7 +643,9 @@ __device__ void general_tile(const Args<GradT>& A, const WorkerPtrs<GradT, PT>& 
     // vector is under way the elements of those vectors are dealt out one per lane: a tile pays for its ragged
     // spots with one more step, not with up to four dependent ones in a row on a single lane while the
     // rest of the workgroup waits.
-    const int tid = threadIdx.x;
+    int tid = threadIdx.x;
+    here_only_per_lane(tid);
+    const SegTables seg = seg_tables(A);
     const int valid = h.valid;
     const int nseg = h.nseg;
     const int p_first = (clo & ~(VEC - 1)) + tid * VEC;
@@ -642,20 +658,20 @@ __device__ void general_tile(const Args<GradT>& A, const WorkerPtrs<GradT, PT>& 
         // j = 1 + 2*tid and j = 2 + 2*tid.
         const int j0 = 1 + 2 * tid, j1 = j0 + 1;
         int x0 = 0, x1 = 0;
-        if (j0 < nseg) x0 = (j0 == 1) ? h.first_end : static_cast<int>(ro(seg_n(A))[h.seg0 + j0 - 1]);
-        if (j1 < nseg) x1 = static_cast<int>(ro(seg_n(A))[h.seg0 + j1 - 1]);
-        const int incl = block_inclusive_scan(x0 + x1, s_wave);
+        if (j0 < nseg) x0 = (j0 == 1) ? h.first_end : static_cast<int>(ro(seg.n)[h.seg0 + j0 - 1]);
+        if (j1 < nseg) x1 = static_cast<int>(ro(seg.n)[h.seg0 + j1 - 1]);
+        const int incl = block_inclusive_scan(tid, x0 + x1, s_wave);
         if (j0 < nseg) s_loc[j0] = incl - x1;
         if (j1 < nseg) s_loc[j1] = incl;
-        for (int j = tid; j < nseg; j += BLOCK) s_layer[j] = ro(seg_layer(A))[h.seg0 + j];
+        for (int j = tid; j < nseg; j += BLOCK) s_layer[j] = ro(seg.layer)[h.seg0 + j];
         if (tid == 0) s_loc[nseg] = valid;
     }
     __syncthreads();
     auto start_of = [&](int j) -> int {         // j >= 1
-        return staged ? s_loc[j] : static_cast<int>(static_cast<int64_t>(ro(seg_off(A))[h.seg0 + j]) - tile_base);
+        return staged ? s_loc[j] : static_cast<int>(static_cast<int64_t>(ro(seg.off)[h.seg0 + j]) - tile_base);
     };
     auto end_of = [&](int j) -> int { return (j + 1 < nseg) ? start_of(j + 1) : valid; };
-    auto layer_of = [&](int j) -> int { return staged ? s_layer[j] : ro(seg_layer(A))[h.seg0 + j]; };
+    auto layer_of = [&](int j) -> int { return staged ? s_layer[j] : ro(seg.layer)[h.seg0 + j]; };
     auto owner_of = [&](int q) -> int {         // last j with start_of(j) <= q (segment 0 starts <= 0)
         int lo = 0, hi = nseg - 1;
         while (lo < hi) {
@@ -718,9 +734,9 @@ __device__ __forceinline__ TileHdr load_header(const TileHdr* p) {
 
 // The pieces of a tile in the table form.
 template <int KIND, typename GradT> struct TablePieces {
-    const Args<GradT>& A;
     const TileHdr& h;
     int clo, chi;
+    SegTables seg;
     int j = 0, end = 0;
     __device__ __forceinline__ bool only(Piece& s) const {
         if constexpr (needs_owner(KIND)) {
@@ -743,8 +759,8 @@ template <int KIND, typename GradT> struct TablePieces {
             end = h.first_end;
         } else {
             start = end;
-            s.layer = ro(seg_layer(A))[h.seg0 + j];
-            end = j + 1 < h.nseg ? end + static_cast<int>(ro(seg_n(A))[h.seg0 + j]) : h.valid;
+            s.layer = ro(seg.layer)[h.seg0 + j];
+            end = j + 1 < h.nseg ? end + static_cast<int>(ro(seg.n)[h.seg0 + j]) : h.valid;
         }
         s.lo = j == 0 ? clo : max(static_cast<int>(start), clo);
         s.hi = min(end, chi);
@@ -765,6 +781,9 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, KIND == K_PIPELINE && sizeof(Gra
     __shared__ int s_ragged[TILE / VEC];
     __shared__ int s_nragged;
     __shared__ __align__(16) float s_sums[FORM == PAIRS ? PAIRED : 4];
+
+    asm volatile("" ::"s"(A.tile_count), "s"(A.tiles), "s"(A.n_units), "s"(static_cast<int>(A.clip_lo)), "s"(A.merge_bufs), "s"(A.grad_ptrs), "s"(A.P));
+    if constexpr (updates(KIND)) asm volatile("" ::"s"(A.w_ptrs), "s"(A.v_ptrs), "s"(A.lr));      // (see mgwfbp_few_kernel)
 
     WorkerPtrs<GradT, PT> mrg;
     if constexpr (reads_merge(KIND) || writes_merge(KIND)) mrg.fetch(A.merge_bufs, 1, 0, worker_base<KIND>());
@@ -797,7 +816,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, KIND == K_PIPELINE && sizeof(Gra
             if (chi <= clo) continue;
             const bool full = clo == 0 && chi == TILE && (!needs_owner(KIND) || h.nseg == 1);
             if constexpr (HAVE_PIECES) {
-                const TablePieces<KIND, GradT> pieces{A, h, clo, chi};
+                TablePieces<KIND, GradT> pieces{h, clo, chi};
                 Piece s;
                 if ((FORM == BURST || !full) && pieces.only(s) && s.len() >= VEC) {
                     if (!updates(KIND) || (h.flags & 1)) {             // (see below)
@@ -812,6 +831,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, KIND == K_PIPELINE && sizeof(Gra
                     continue;
                 }
                 if (!full && (!needs_owner(KIND) || h.nseg <= MGWFBP_PIECES)) {
+                    pieces.seg = seg_tables(A);
                     several_pieces<KIND, GradT, PT>(A, mrg, tile_base, pieces);
                     continue;
                 }
@@ -868,7 +888,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, KIND == K_PIPELINE && sizeof(Gra
 // its arguments in scalar registers, so only the pointers lie between it and its data.  Segment j is tensor
 // layer_hi - j and starts where j - 1 ends, or on the next tile after the last segment of a group.  Kinds that
 // need no tensors (REDUCE) get whole groups as segments.
-template <typename GradT> __device__ __forceinline__ int few_start(const FewArgs<GradT>& A, int j) {   // j static
+template <typename GradT> __device__ __forceinline__ int few_start(const MGWFBP_CONST FewArgs<GradT>& A, int j) {   // j static
     if (j == 0) return A.start0;
     const int e = A.end[j - 1];
     return (A.closes >> (j - 1)) & 1 ? (e + TILE - 1) & ~(TILE - 1) : e;
@@ -876,7 +896,7 @@ template <typename GradT> __device__ __forceinline__ int few_start(const FewArgs
 
 // Segment that element q belongs to if it belongs to any: the last one that starts at or before q, or segment 0.
 struct FewSeg { int j, start, end; };
-template <typename GradT> __device__ __forceinline__ FewSeg few_owner(const FewArgs<GradT>& A, int q) {
+template <typename GradT> __device__ __forceinline__ FewSeg few_owner(const MGWFBP_CONST FewArgs<GradT>& A, int q) {
     FewSeg s{0, A.start0, A.end[0]};
 #pragma unroll
     for (int j = 1; j < FEW; ++j) {
@@ -892,7 +912,9 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, KIND == K_REDUCE_UPDATE && PT ==
     constexpr int SINGLE = FORM == PAIRS ? 1 : FORM;
     constexpr int JOIN = joined_tiles_of(KIND, FORM);
     __shared__ __align__(16) float s_sums[FORM == PAIRS ? PAIRED : 4];
-    const int lane = threadIdx.x;
+    // All arguments in one trip; left alone, the compiler fetches them where it needs them, in three.
+    asm volatile("" ::"s"(A.tile_count), "s"(A.layer_hi), "s"(static_cast<int>(A.n)), "s"(A.end[0]), "s"(A.merge_bufs), "s"(A.grad_ptrs), "s"(A.P));
+    if constexpr (updates(KIND)) asm volatile("" ::"s"(A.w_ptrs), "s"(A.v_ptrs), "s"(A.lr));
     const int64_t arena = static_cast<int64_t>(A.tile_first) * TILE;
     const int K = A.tiles_per_wg;
     const int u = unit_of(A);
@@ -904,15 +926,13 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, KIND == K_REDUCE_UPDATE && PT ==
             if constexpr (reads_merge(KIND) || writes_merge(KIND)) m.fetch(A.merge_bufs, 1, 0, worker_base<KIND>());
             return m;
         };
-        // Segment that ends in the tile or beyond it; all of the tile's if it is the last one or ends beyond it.
+        // Segment that ends in the tile or beyond it (the last one does); all of the tile's if it is the last one or ends
+        // beyond it.  The arguments are read where they lie, so that an index need not be known beforehand.
         const MGWFBP_CONST FewArgs<GradT>* a = (const MGWFBP_CONST FewArgs<GradT>*)__builtin_amdgcn_kernarg_segment_ptr();
-        int j = 0;
-        while (j + 1 < A.n && a->end[j] <= b) ++j;
-        const int end = a->end[j];
-        int start = A.start0;
-        if (j > 0) {
-            const int e = a->end[j - 1];
-            start = (A.closes >> (j - 1)) & 1 ? (e + TILE - 1) & ~(TILE - 1) : e;
+        int j = 0, start = A.start0, end = A.end[0];
+        while (end <= b && j < FEW - 1) {
+            start = (A.closes >> j) & 1 ? (end + TILE - 1) & ~(TILE - 1) : end;
+            end = a->end[++j];
         }
         if (FORM != BURST && start <= b && b + TILE <= end) {              // a full tile inside one segment
             if constexpr (JOIN > 1) {
@@ -932,10 +952,13 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, KIND == K_REDUCE_UPDATE && PT ==
             continue;
         }
         // Whole vectors first, then the wanted elements of the others, one per lane (see general_tile).
+        asm volatile("" : "+s"(a));            // (see here_only)
+        int lane = threadIdx.x;
+        here_only_per_lane(lane);
         const int p = b + lane * VEC;
-        const FewSeg o = few_owner(A, p);
+        const FewSeg o = few_owner(*a, p);
         const bool whole = p >= o.start && p + VEC <= o.end;
-        const bool any = (p < o.end && p + VEC > o.start) || few_owner(A, p + VEC - 1).j != o.j;
+        const bool any = (p < o.end && p + VEC > o.start) || few_owner(*a, p + VEC - 1).j != o.j;
         const uint64_t ragged = __ballot(any && !whole);
         if (whole) do_one<KIND, GradT, PT, VEC>(A, mrg(), A.layer_hi - o.j, p - o.start, arena + p);
         const int n_ragged = __popcll(ragged) * VEC;
@@ -943,7 +966,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, KIND == K_REDUCE_UPDATE && PT ==
             uint64_t rest = ragged;
             for (int k = e / VEC; k > 0; --k) rest &= rest - 1;
             const int q = b + __builtin_ctzll(rest) * VEC + e % VEC;
-            const FewSeg r = few_owner(A, q);
+            const FewSeg r = few_owner(*a, q);
             if (q >= r.start && q < r.end) do_one<KIND, GradT, PT, 1>(A, mrg(), A.layer_hi - r.j, q - r.start, arena + q);
         }
     }
