@@ -158,6 +158,7 @@ __device__ __forceinline__ float widen(_Float16 x) { return static_cast<float>(x
 // from 136 bytes on 3.3 us (the runtime writes the block into device memory), and a kernel that asks for gridDim
 // makes the runtime append 256 more.  So everything that can be derived from something else is, and the grid
 // size that the persistent form needs comes in as `turn`.
+constexpr int XCD_CONTIGUOUS = 1, ROLLING = 2;
 template <typename GradT> struct CallArgs {
     const GradT* const* grad_ptrs;   // [P*L]
     GradT* const* merge_bufs;        // [P]
@@ -168,7 +169,7 @@ template <typename GradT> struct CallArgs {
     int32_t L, P;
     int32_t tile_first, tile_count;
     int16_t tiles_per_wg;            // consecutive tiles one workgroup handles per turn, >= 1
-    int8_t xcd_contiguous;
+    int8_t flags;                    // XCD_CONTIGUOUS, ROLLING
     int8_t run_log2;                 // a die's turn is 2^run_log2 consecutive units, see unit_of()
 };
 template <typename GradT> struct Args : CallArgs<GradT> {      // table form: what a tile holds is in the tables
@@ -539,6 +540,76 @@ __device__ __forceinline__ void joined_tiles(const CallArgs<GradT>& A, const Wor
 }
 
 // ---------------------------------------------------------------------------------------------
+// rolling steps of the pipeline
+// ---------------------------------------------------------------------------------------------
+//
+// A tile of the pipeline with two loads under way instead of one: the next worker's goes out before this one's is stored,
+// and v and w follow the last worker's.  For the launches whose wavefronts are too few, or too narrow, to keep enough under
+// way with one each (see rolls()).
+template <typename GradT, int PT>
+__device__ __forceinline__ void rolling_tile(const CallArgs<GradT>& A, const WorkerPtrs<GradT, PT>& mrg, int layer, int64_t tensor_off,
+                                             int64_t tile_base) {
+    typedef typename VecOf<GradT, VEC>::type GV;
+    WorkerPtrs<const GradT, PT> src;
+    src.fetch(A.grad_ptrs, A.L, layer, 0);
+    float* wp = ro(A.w_ptrs)[layer];
+    float* vp = ro(A.v_ptrs)[layer];
+    const int lane_elem = static_cast<int>(threadIdx.x) * VEC;
+    const int64_t soff = tensor_off + lane_elem, apos = tile_base + lane_elem;
+    f32x4 acc;
+    auto load = [&](int k) {
+        const GV g = ld<NT_LD, GV>(src.get(k) + soff);
+        pace();
+        return g;
+    };
+    auto use = [&](const GV& g, int k) {
+        st<NT_ST, GV>(mrg.get(k) + apos, g);
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) {
+            const float x = widen(comp(g, c));
+            setc(acc, c, k == 0 ? x : comp(acc, c) + x);
+        }
+        pace();
+    };
+    GV g = load(0);
+    if constexpr (PT > 0) {
+#pragma unroll
+        for (int k = 0; k + 1 < PT; ++k) {
+            const GV next = load(k + 1);
+            use(g, k);
+            g = next;
+        }
+    } else {
+        for (int k = 0; k + 1 < A.P; ++k) {
+            const GV next = load(k + 1);
+            use(g, k);
+            g = next;
+        }
+    }
+    f32x4 v = ld<true, f32x4>(vp + soff);
+    pace();
+    use(g, (PT > 0 ? PT : A.P) - 1);
+    f32x4 w = ld<true, f32x4>(wp + soff);
+    pace();
+#pragma unroll
+    for (int c = 0; c < VEC; ++c) setc(acc, c, comp(acc, c) * A.inv_p);
+    if (A.reduced != nullptr) st<NT_ST, f32x4>(A.reduced + apos, acc);
+#pragma unroll
+    for (int c = 0; c < VEC; ++c) {
+        const float t1 = A.mu * comp(v, c);
+        setc(v, c, t1 + comp(acc, c));
+    }
+    st<true, f32x4>(vp + soff, v);
+    pace();
+#pragma unroll
+    for (int c = 0; c < VEC; ++c) {
+        const float t2 = A.lr * comp(v, c);
+        setc(w, c, comp(w, c) - t2);
+    }
+    st<true, f32x4>(wp + soff, w);
+}
+
+// ---------------------------------------------------------------------------------------------
 // ragged tiles: a few pieces of tensors
 // ---------------------------------------------------------------------------------------------
 //
@@ -792,7 +863,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, KIND == K_PIPELINE && sizeof(Gra
     const int K = A.tiles_per_wg;
     const int n_units = A.n_units;              // ceil(tile_count / K), computed on the host
     int u_begin, u_end, u_step;
-    if (A.xcd_contiguous) {
+    if (A.flags & XCD_CONTIGUOUS) {
         // workgroup ids are dealt round-robin to the 8 dies: die = id % 8.  Give each die one
         // contiguous eighth of the units.
         const int die = blockIdx.x & 7;
@@ -865,6 +936,12 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, KIND == K_PIPELINE && sizeof(Gra
             // The two arms differ only in the cache policy of their memory instructions; the empty asm
             // statements keep the optimiser from merging them back into one (which drops the policy).
             const int64_t toff = -h.first_start;
+            if constexpr (may_roll(KIND, FORM)) {
+                if ((A.flags & ROLLING) && !(h.flags & 1)) {
+                    rolling_tile<GradT, PT>(A, mrg, h.layer0, toff, tile_base);
+                    continue;
+                }
+            }
             if (!updates(KIND) || (h.flags & 1)) {
                 asm volatile("; w and v cacheable" ::: "memory");
                 fast_chunk<KIND, GradT, PT, NT_WV, SINGLE>(A, mrg, h.layer0, toff, tile_base, TVECS);
@@ -941,6 +1018,15 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, KIND == K_REDUCE_UPDATE && PT ==
                     t += JOIN - 1;
                     continue;
                 }
+            }
+            if constexpr (may_roll(KIND, FORM)) {
+                if (A.flags & ROLLING) {
+                    asm volatile("; rolling steps" ::: "memory");      // keeps the arms' addresses, and their registers, apart
+                    rolling_tile<GradT, PT>(A, mrg(), A.layer_hi - j, b - start, arena + b);
+                    asm volatile("; end rolling steps" ::: "memory");
+                    continue;
+                }
+                asm volatile("; single steps" ::: "memory");
             }
             fast_chunk<KIND, GradT, PT, true, SINGLE>(A, mrg(), A.layer_hi - j, b - start, arena + b, TVECS);
             continue;
@@ -1239,7 +1325,8 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
         typedef decltype(grad) GradT;
         const CallArgs<GradT> call{reinterpret_cast<const GradT* const*>(grad_ptrs), reinterpret_cast<GradT* const*>(merge_bufs),
                                    reduced, w_ptrs, v_ptrs, lr, mu, inv_p, c->host.L, c->P, sp.t0, count,
-                                   static_cast<int16_t>(s.tiles_per_wg), s.xcd_contiguous, s.run_log2};
+                                   static_cast<int16_t>(s.tiles_per_wg),
+                                   static_cast<int8_t>((s.xcd_contiguous ? XCD_CONTIGUOUS : 0) | (s.rolling ? ROLLING : 0)), s.run_log2};
         return launch<KIND, GradT>(c, sp, tiles, call, stream, s);
     };
     if (c->dtype == MGWFBP_F32) return go(float{});

@@ -259,6 +259,24 @@ inline bool few_form_pays(int kind, int32_t dtype, int32_t P, int32_t tiles, int
     return tiles <= 3072 || (per_cu > 24 && per_cu <= 32) || (per_cu > 48 && per_cu <= 56);
 }
 
+// Kernels with rolling steps beside the single ones (see rolling_tile).
+constexpr bool may_roll(int kind, int form) { return TVECS == 1 && kind == K_PIPELINE && form == 1; }
+// Launches of the pipeline in single tiles whose wavefronts, with one load each, have too little under way between them: binary32
+// up to 12 per compute unit, 16-bit gradients, whose loads are half as long, up to 16, and where a second round of them is
+// not full either.  us with one load at a time / rolling, over one tensor: binary32, 1900 tiles (8 per compute unit) P = 4 6.7 / 5.7, 6
+// 8.4 / 7.6, 8 9.7 / 7.9, 16 15.6 / 13.2; 2304 (9) 7.1 / 6.7, 9.4 / 8.9, 10.8 / 10.5, 18.0 / 17.7; 3072 (12) 8.5 / 8.4, 10.5 / 10.0, 12.5 / 12.8,
+// 21.0 / 21.3; 4096 (16) P = 6 13.2 / 13.2, 8 15.8 / 16.3, 16 26.3 / 27.8.  bfloat16, 3200 tiles (13) P = 2 6.3 / 5.5, 6 9.5 / 8.5, 8 10.5 /
+// 8.7, 16 17.0 / 13.4; 4096 (16) 6.9 / 6.5, 10.4 / 9.7, 11.8 / 10.6, 18.4 / 16.3; 6144 (24) 9.1 / 9.1, 13.9 / 14.3, 15.6 / 16.1, 24.3 / 26.1;
+// 6500 (26) P = 2 9.2 / 9.4, 4 11.6 / 12.1, 6 16.7 / 15.7, 8 18.9 / 16.6, 16 30.7 / 27.6; 9000 (36) 12.6 / 12.8, 16.2 / 16.0, 20.9 / 20.1, 23.2 /
+// 22.9, 37.5 / 37.0; 12,000 tiles over 600 tensors P = 8 30.4 / 31.7.  Where the worker count is not compiled the table form ends
+// earlier (12 tensors as views: binary32 2700 tiles P = 6 11.1 / 11.0, 12 16.4 / 16.5, 3071 12.2 / 12.7, 18.0 / 18.9; bfloat16 4095 tiles 10.9 /
+// 10.2, 16.0 / 15.0, 7500 18.1 / 18.8, 25.9 / 27.0).
+inline bool rolls(int32_t dtype, int32_t P, bool few, int32_t per_cu) {
+    const bool well = few || P == 2 || P == 4 || P == 8 || P == 16;
+    if (dtype == MGWFBP_F32) return per_cu <= (well ? 12 : 10);
+    return per_cu <= 16 || (well && per_cu > 24 && per_cu <= 36);
+}
+
 // What a caller has fixed (mgwfbp_ctx_set_*); the initial values are the library's defaults.
 struct LaunchSettings {
     int32_t blocks_per_cu = 0;        // > 0: a persistent grid of that many workgroups per compute unit.  0 = one workgroup
@@ -303,6 +321,7 @@ struct LaunchShape {
     bool may_be_few;                  // the few-segments form may take it
     int form;                         // BURST, PAIRS or the vectors per lane of a paced step
     int32_t wgs_per_cu;               // workgroups that may share a compute unit; <= 0: no cap
+    bool rolling;                     // two loads under way in a step (see rolls())
 };
 
 inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, int n_cu) {
@@ -352,6 +371,7 @@ inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, 
         if (s.form == PAIRS ? length < 2 * SHORT_LAUNCH_TILES : w.dtype == MGWFBP_F32 && w.kind != K_PACK && few_rounds(length, w.P))
             s.wgs_per_cu = short_launch_cap(s.wgs_per_cu, w.kind, w.P, s.may_be_few && s.form != PAIRS, per_cu);
     }
+    s.rolling = may_roll(w.kind, s.form) && set.step_vecs == 0 && set.wg_per_cu == 0 && rolls(w.dtype, w.P, s.may_be_few, per_cu);
     s.run_log2 = one_turn ? run_log2_of(w.kind, w.dtype, w.P, w.off_lines) : int8_t{0};
     return s;
 }

@@ -546,6 +546,20 @@ def test_ragged_tiles_piece_by_piece(P, dtype):
     _check_incremental(p, merged[::-1], lambda L: [1 + i % 11 for i in range(L)], misalign=5, label="runs of 1 to 11")
 
 
+@pytest.mark.parametrize("P,dtype", [(1, "f32"), (2, "bf16"), (3, "f32"), (6, "f16"), (8, "f32"), (8, "bf16"), (16, "f32"), (17, "f16")])
+def test_rolling_steps_of_the_pipeline(P, dtype):
+    """Pipeline launches of up to 10 or 12 tiles per compute unit (binary32), up to 16 and of 25 to 36 (16-bit gradients) load the
+    next worker's share before they store this one's: launches on both sides of these lines, over one tensor and over
+    ten, with and without the reduced arena, and with a resident share, whose tiles go without.  (On 256 compute units.)"""
+    rng = np.random.default_rng(17)
+    for tiles in (2500, 3000, 3100) if dtype == "f32" else (4000, 4100, 6300):
+        for sizes in ([tiles * 256 - 5], [256 * (tiles // 10) - 3 * (i % 2) for i in range(10)]):
+            p = W.Profile("rolling", np.asarray(sizes, np.uint64), rng.uniform(1e-6, 1e-5, len(sizes)), 1e-4, 1e-9, P, dtype, 1.0)
+            merged = [0] + [1] * (len(sizes) - 1)
+            check_case(p, merged, "pipeline", misalign=3, small_launch=0, label=f"{tiles} tiles")
+            check_case(p, merged, "pipeline_no_reduced", small_launch=0, resident=tiles * 256, label=f"{tiles} tiles, an eighth resident")
+
+
 @pytest.mark.parametrize("P,dtype", [(2, "bf16"), (3, "f16"), (8, "bf16"), (16, "f16")])
 def test_sixteen_bit_pipeline_takes_tiles_in_pairs(P, dtype):
     """Long 16-bit pipeline launches take two full tiles (512 elements) of one tensor in one step.  Tensors that end
