@@ -284,7 +284,9 @@ template <typename T> struct WorkerPtrs<T, 0> {
 #define MGWFBP_GENERAL_GROUP 64   // workers whose loads the general path issues together (64: all of them)
 #endif
 
-constexpr int SOME = 4;               // the same where every lane has pointers of its own
+// The same where every lane has pointers of its own.  us with four / eight at a time, 12 tensors of one group, 300 and 1100 tiles:
+// binary32 pipeline 5 workers 4.8 / 4.3, 7.4 / 6.4; 12 workers 7.7 / 6.6, 10.9 / 9.6; 32 workers 15.8 / 11.0, 23.7 / 19.2; direct 32 workers 14.1 / 9.6, 17.2 / 12.6.
+constexpr int SOME = 8;
 
 // keeps the compiler from moving the next group's loads above this group's arithmetic
 __device__ __forceinline__ void pace() { __builtin_amdgcn_sched_barrier(0); }
@@ -363,10 +365,10 @@ __device__ __forceinline__ void paced_step(const CallArgs<GradT>& A, const Worke
 #pragma unroll
                 for (int i = 0; i < N; ++i) g[j][i] = ld<NT_LD, GV>(from + i * stride);
             }
-            // kinds that store and add each worker's share: every load of the step is issued before the first
-            // value is used (left alone, the scheduler now and then puts an add, and with it a wait for the
-            // first load, in front of the second load)
-            if constexpr (writes_merge(KIND) && sums(KIND)) pace();
+            // every load of the group is issued before the first value is used (left alone, the scheduler now and then puts
+            // an add, and with it a wait for the first load, in front of the second load); with a compiled worker count the
+            // kinds that do not store each worker's share want the groups to run into one another instead
+            if constexpr ((writes_merge(KIND) && sums(KIND)) || PT == 0) pace();
 #pragma unroll
             for (int j = 0; j < COUNT; ++j) {
                 if constexpr (writes_merge(KIND)) {

@@ -120,19 +120,23 @@ constexpr int32_t SHORT_LAUNCH_TILES = 16384;
 constexpr int32_t LONG_LAUNCH_TILES = 262144;       // 67 M elements
 
 // Longest launch, in tiles, that takes the burst form.  Up to here the time is the latency of a tile, beyond it the
-// loads of all tiles at once are more than the memory system likes.  us burst / paced, one tensor, at 1024, 1792, 2048, 3072
-// and 4096 tiles: binary32 pipeline P = 8: 5.3 / 8.3, 9.0 / 9.6, 10.6 / 10.1, 13.3 / 12.7, 18.7 / 16.0; P = 16: 7.7 / 13.3, 14.2 /
-// 15.2, 17.9 / 16.1, 22.0 / 21.1, 32.7 / 26.5; P = 4: 4.5 / 5.9, 5.6 / 6.7, 6.8 / 7.1, 8.9 / 8.7, 12.2 / 10.7; P = 3: 3.7 / 5.3, 4.9 / 6.2, 6.0 /
-// 6.5, 6.8 / 7.9, 10.8 / 9.7; reduce_update P = 8: 4.0 / 5.3, 5.6 / 6.1, 7.6 / 6.3, 7.9 / 7.7, 11.5 / 9.9; unpack_update 3.1 / 3.5, 3.5 / 3.9,
-// 3.8 / 4.0, 4.5 / 4.6, 5.6 / 5.4.  bfloat16 pipeline P = 8: 4.3 / 7.6, 5.7 / 8.5, 7.1 / 8.8, 9.5 / 10.3, 11.7 / 11.6; P = 16: 5.7 / 12.0, 9.4 / 13.4,
-// 10.0 / 13.9, 13.8 / 16.0, 17.3 / 18.0; P = 4: 3.5 / 5.6, 4.7 / 6.1, 5.2 / 6.4, 6.8 / 7.6, 8.9 / 8.5; direct P = 8: 3.7 / 5.5, 4.6 / 6.1, 5.0 / 6.2,
-// 6.3 / 7.1, 7.9 / 7.6.  The lines lie where the burst form is ahead or level for every worker count they cover; some would bear
-// a later one (4096 tiles: bfloat16 pipeline P = 1 5.7 / 6.6, P = 3 7.4 / 8.1, P = 12 14.6 / 15.3, P = 32 29.3 / 30.9, reduce P = 12 6.6 / 7.3;
-// 2048 and 2560 tiles: binary32 pipeline P = 12 12.7 / 13.4 and 14.6 / 15.0, P = 32 26.1 / 28.5 and 32.2 / 33.5).  PACK has one form
-// (every load of a step under way, see joined_tiles); for it this is where the cap begins.
+// loads of all tiles at once are more than the memory system likes.  us burst / paced (the pipeline's rolling steps among
+// these, see rolls()), one tensor.  Binary32, 1400, 1800 and 2300 tiles: pipeline P = 4 4.9 / 5.2, 5.2 / 5.7, 7.1 / 7.0; 6 5.6 / 6.5,
+// 6.7 / 7.2, 9.1 / 9.1; 8 6.9 / 7.1, 8.1 / 8.0, 11.6 / 10.9; 12 9.1 / 9.3, 10.9 / 10.6, 15.9 / 14.4; 16 11.0 / 10.8, 13.5 / 12.5, 20.4 / 17.9.  1024, 1792
+// and 2560 tiles: reduce P = 4 3.0 / 3.2, 3.6 / 3.5, 4.2 / 3.8; 6 3.4 / 3.8, 4.6 / 4.3; 8 4.0 / 4.3, 5.5 / 4.7, 6.6 / 5.5; 16 6.4 / 6.7, 8.7 /
+// 7.3; reduce_update P = 4 3.2 / 4.2, 4.0 / 4.7, 5.3 / 5.2; 8 4.0 / 5.3, 5.4 / 6.1, 7.1 / 6.8; 12 4.8 / 6.5, 7.5 / 7.8, 9.5 / 8.9; 16 7.0 / 7.9, 9.9 /
+// 8.6; direct P = 4 3.2 / 4.3, 4.0 / 4.9, 5.2 / 5.5; 8 3.9 / 5.4, 5.2 / 6.2, 6.6 / 6.9; 12 4.9 / 6.8, 6.5 / 7.9, 8.2 / 8.7; 16 5.3 / 7.5, 7.6 / 8.7,
+// 10.1 / 9.9; 32 8.2 / 12.9, 11.6 / 14.5, 16.3 / 16.1.  3072 and 4096 tiles: binary32 P = 1 to 3 pipeline 5.3 / 6.0, 6.6 / 7.0; 6.0 / 6.3, 8.2 / 8.0; 7.5 /
+// 6.6, 10.0 / 9.5; update 4.5 / 4.6, 5.6 / 5.4; bfloat16 pipeline P = 2 5.1 / 5.5, 6.9 / 6.9; 4 6.5 / 6.6, 9.1 / 9.2; 6 7.7 / 7.9, 11.1 / 10.7; 8 8.9 / 8.7,
+// 13.2 / 12.8; 12 11.3 / 10.8, 16.9 / 16.4; reduce_update P = 3 4.6 / 5.8, 5.8 / 6.6; 8 6.0 / 6.6, 8.2 / 7.5; 12 6.9 / 8.5, 9.7 / 9.7; direct 3 4.8 / 5.7, 5.8 /
+// 6.4; 8 6.1 / 6.9, 7.5 / 7.8; 12 7.0 / 8.5, 9.9 / 9.4.  PACK has one form (every load of a step under way, see joined_tiles); for it this
+// is where the cap begins.
 inline int32_t default_burst_tiles(int kind, int32_t dtype, int32_t P) {
     if (kind == K_PACK) return 1024;
-    return dtype != MGWFBP_F32 || P < 4 || kind == K_UPDATE ? 3072 : 1792;
+    if (dtype != MGWFBP_F32 || P < 4 || kind == K_UPDATE) return 3072;
+    if (kind == K_DIRECT) return P == 16 ? 1792 : 2560;
+    if (kind == K_REDUCE) return P < 6 ? 1792 : 1280;
+    return P == 16 ? 1280 : 1792;
 }
 
 // Whether a workgroup of the pipeline takes two tiles in one step (see joined_tiles).  GB/s at 16-bit gradients,
