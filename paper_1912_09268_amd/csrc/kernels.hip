@@ -67,6 +67,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <type_traits>
 
 #include "launch.h"
 #include "mgwfbp.h"
@@ -1163,40 +1164,33 @@ int create_common(mgwfbp_ctx** out, const uint64_t* n_elems, int32_t L, const ui
     return MGWFBP_OK;
 }
 
-template <int KIND, typename GradT, int PT, int FORM>
-void start(const FewArgs<GradT>& A, hipStream_t stream, const LaunchShape& s, int grid_y) {
-    const size_t lds = lds_for_workgroups_per_cu(s.wgs_per_cu, static_lds(KIND, true, FORM));
-    hipLaunchKernelGGL((mgwfbp_few_kernel<KIND, GradT, PT, FORM>), dim3(s.grid, grid_y), dim3(BLOCK), lds, stream, A);
-}
-template <int KIND, typename GradT, int PT, int FORM>
-void start(const Args<GradT>& A, hipStream_t stream, const LaunchShape& s, int grid_y) {
-    const size_t lds = lds_for_workgroups_per_cu(s.wgs_per_cu, static_lds(KIND, false, FORM));
-    hipLaunchKernelGGL((mgwfbp_stream_kernel<KIND, GradT, PT, FORM>), dim3(s.grid, grid_y), dim3(BLOCK), lds, stream, A);
+// The launch itself, by the runtime's function and not by the <<<>>> syntax: that one leaves grid, LDS and stream with the
+// runtime, calls a stub that fetches them again, and reports through hipGetLastError.
+template <int KIND, typename GradT, int PT, int FORM, template <typename> class ArgsT>
+int start(const ArgsT<GradT>& A, hipStream_t stream, const LaunchShape& s, int grid_y) {
+    constexpr bool FEW_FORM = std::is_same<ArgsT<GradT>, FewArgs<GradT>>::value;
+    const void* kernel;
+    if constexpr (FEW_FORM) kernel = reinterpret_cast<const void*>(&mgwfbp_few_kernel<KIND, GradT, PT, FORM>);
+    else kernel = reinterpret_cast<const void*>(&mgwfbp_stream_kernel<KIND, GradT, PT, FORM>);
+    const size_t lds = lds_for_workgroups_per_cu(s.wgs_per_cu, static_lds(KIND, FEW_FORM, FORM));
+    void* args[1] = {const_cast<ArgsT<GradT>*>(&A)};
+    const hipError_t e = hipLaunchKernel(kernel, dim3(s.grid, grid_y), dim3(BLOCK), args, lds, stream);
+    if (e != hipSuccess) (void)hipGetLastError();        // reported here, not to whoever asks next
+    return note(e);
 }
 
 template <int KIND, typename GradT, int PT, template <typename> class ArgsT>
 int launch_one(const ArgsT<GradT>& A, hipStream_t stream, const LaunchShape& s, int grid_y = 1) {
-    bool started = false;
     if constexpr (KIND != K_PACK) {                       // PACK has one form
-        if (s.form == BURST) {
-            start<KIND, GradT, PT, BURST>(A, stream, s, grid_y);
-            started = true;
-        }
+        if (s.form == BURST) return start<KIND, GradT, PT, BURST>(A, stream, s, grid_y);
     }
     if constexpr (TVECS % 2 == 0) {
-        if (s.form == 2) {
-            start<KIND, GradT, PT, 2>(A, stream, s, grid_y);
-            started = true;
-        }
+        if (s.form == 2) return start<KIND, GradT, PT, 2>(A, stream, s, grid_y);
     }
     if constexpr (HAVE_PAIRS && KIND == K_PIPELINE && sizeof(GradT) == 2) {
-        if (s.form == PAIRS) {
-            start<KIND, GradT, PT, PAIRS>(A, stream, s, grid_y);
-            started = true;
-        }
+        if (s.form == PAIRS) return start<KIND, GradT, PT, PAIRS>(A, stream, s, grid_y);
     }
-    if (!started) start<KIND, GradT, PT, 1>(A, stream, s, grid_y);
-    return note(hipGetLastError());
+    return start<KIND, GradT, PT, 1>(A, stream, s, grid_y);
 }
 
 template <int KIND, typename GradT, template <typename> class ArgsT>
