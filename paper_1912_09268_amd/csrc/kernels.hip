@@ -468,7 +468,11 @@ __device__ __forceinline__ void fast_chunk(const CallArgs<GradT>& A, const Worke
         vp = ro(A.v_ptrs)[layer];
     }
     constexpr int STEP = BLOCK * VEC;
-    const int lane_elem = static_cast<int>(threadIdx.x) * VEC;
+    int lane_elem = static_cast<int>(threadIdx.x) * VEC;
+    // Left alone, the compiler sets up every arena's address plus this in front of the walk, two registers per worker: 138 for
+    // binary32 reductions of 16 workers instead of 91 (4000 tiles over 150 tensors 17.0 us, so 12.5).  A direct step has no arenas, and is
+    // faster as the compiler has it (bfloat16, 16 workers, 12,000 tiles 24.3 us, so 25.3).
+    if constexpr (KIND != K_DIRECT) here_only_per_lane(lane_elem);
     const int64_t soff = tensor_off + lane_elem;    // this lane's first element: in its tensor
     const int64_t apos = tile_base + lane_elem;     //                            in the arena
     if constexpr (STEPV == 0) {
@@ -495,7 +499,8 @@ __device__ __forceinline__ void joined_tiles(const CallArgs<GradT>& A, const Wor
                                              int64_t tensor_off, int64_t tile_base, float* s_sums) {
     WorkerPtrs<const GradT, PT> src;
     src.fetch(A.grad_ptrs, A.L, layer, worker_base<KIND>());
-    const int lane_elem = static_cast<int>(threadIdx.x) * VEC;
+    int lane_elem = static_cast<int>(threadIdx.x) * VEC;
+    here_only_per_lane(lane_elem);
     if constexpr (KIND == K_PACK) {
         paced_step<KIND, GradT, PT, VEC, PACK_TILES * TVECS, true>(A, src, mrg, nullptr, nullptr, tensor_off + lane_elem,
                                                              tile_base + lane_elem, BLOCK * VEC);
@@ -557,7 +562,8 @@ __device__ __forceinline__ void rolling_tile(const CallArgs<GradT>& A, const Wor
     src.fetch(A.grad_ptrs, A.L, layer, 0);
     float* wp = ro(A.w_ptrs)[layer];
     float* vp = ro(A.v_ptrs)[layer];
-    const int lane_elem = static_cast<int>(threadIdx.x) * VEC;
+    int lane_elem = static_cast<int>(threadIdx.x) * VEC;
+    here_only_per_lane(lane_elem);
     const int64_t soff = tensor_off + lane_elem, apos = tile_base + lane_elem;
     f32x4 acc;
     auto load = [&](int k) {
@@ -639,7 +645,8 @@ struct Piece {
 
 // One piece by itself: its pointers are the same for all lanes.  Of a full tile, too, in the burst form.
 template <int KIND, typename GradT, int PT, bool WVNT>
-__device__ __forceinline__ void one_piece(const CallArgs<GradT>& A, const WorkerPtrs<GradT, PT>& mrg, int64_t tile_base, const Piece& s) {
+__device__ __forceinline__ void one_piece(const CallArgs<GradT>& A, const WorkerPtrs<GradT, PT>& mrg, int64_t tile_base, const Piece& s,
+                                          int lane) {
     WorkerPtrs<const GradT, PT> src;
     float* wp = nullptr;
     float* vp = nullptr;
@@ -648,7 +655,6 @@ __device__ __forceinline__ void one_piece(const CallArgs<GradT>& A, const Worker
         wp = ro(A.w_ptrs)[s.layer];
         vp = ro(A.v_ptrs)[s.layer];
     }
-    const int lane = static_cast<int>(threadIdx.x);
     if (lane < s.lanes()) {
         const int e = s.element(lane);
         paced_step<KIND, GradT, PT, VEC, 1, WVNT, MGWFBP_TOGETHER>(A, src, mrg, wp, vp, s.off + e, tile_base + s.lo + e, 0);
@@ -845,8 +851,15 @@ template <int KIND, typename GradT> struct TablePieces {
 };
 
 // FORM: vectors per lane a fast tile is walked in (1, see paced_step), BURST or PAIRS.
+// 16-bit gradients run uncapped in single tiles and want the wavefronts; where the compiler stops a few registers short of one more,
+// it is told the number per SIMD.
+template <int KIND, typename GradT, int PT, int FORM> constexpr int wanted_waves() {
+    if (FORM != 1 || sizeof(GradT) != 2) return 1;
+    return KIND == K_PIPELINE && PT == 0 ? 8 : 1;
+}
+
 template <int KIND, typename GradT, int PT, int FORM>
-__global__ void __launch_bounds__(MGWFBP_BLOCK, KIND == K_PIPELINE && sizeof(GradT) == 2 && PT == 0 && FORM == 1 ? 8 : 1) mgwfbp_stream_kernel(const Args<GradT> A) {
+__global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_waves<KIND, GradT, PT, FORM>())) mgwfbp_stream_kernel(const Args<GradT> A) {
     constexpr int SINGLE = FORM == PAIRS ? 1 : FORM;     // single tiles
     constexpr int JOIN = joined_tiles_of(KIND, FORM);
     __shared__ int s_loc[MAXSEG + 1];
@@ -856,7 +869,9 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, KIND == K_PIPELINE && sizeof(Gra
     __shared__ int s_nragged;
     __shared__ __align__(16) float s_sums[FORM == PAIRS ? PAIRED : 4];
 
-    asm volatile("" ::"s"(A.tile_count), "s"(A.tiles), "s"(A.n_units), "s"(static_cast<int>(A.clip_lo)), "s"(A.merge_bufs), "s"(A.grad_ptrs), "s"(A.P));
+    asm volatile("" ::"s"(A.tile_count), "s"(A.tile_first), "s"(static_cast<int>(A.tiles_per_wg)), "s"(A.tiles), "s"(A.n_units), "s"(A.turn),
+                 "s"(static_cast<int>(A.clip_lo)), "s"(static_cast<int>(A.clip_hi)), "s"(A.merge_bufs), "s"(A.grad_ptrs), "s"(A.reduced),
+                 "s"(A.inv_p), "s"(A.P));
     if constexpr (updates(KIND)) asm volatile("" ::"s"(A.w_ptrs), "s"(A.v_ptrs), "s"(A.lr));      // (see mgwfbp_few_kernel)
 
     WorkerPtrs<GradT, PT> mrg;
@@ -882,7 +897,8 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, KIND == K_PIPELINE && sizeof(Gra
     for (int u = u_begin; u < u_end; u += u_step) {
         const int t_end = min((u + 1) * K, A.tile_count);
         for (int t = u * K; t < t_end; ++t) {
-            const int tile = A.tile_first + t;
+            int tile = A.tile_first + t;
+            if constexpr (KIND != K_DIRECT) here_only(tile);     // (addresses that run on from tile to tile would be set up, pointers waited for, first)
             const TileHdr h = load_header(A.tiles + tile);
             const int64_t tile_base = static_cast<int64_t>(tile) * TILE;
             const int clo = t == 0 ? A.clip_lo : 0;
@@ -893,13 +909,15 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, KIND == K_PIPELINE && sizeof(Gra
                 TablePieces<KIND, GradT> pieces{h, clo, chi};
                 Piece s;
                 if ((FORM == BURST || !full) && pieces.only(s) && s.len() >= VEC) {
+                    int lane = threadIdx.x;
+                    here_only_per_lane(lane);
                     if (!updates(KIND) || (h.flags & 1)) {             // (see below)
                         asm volatile("; w and v cacheable" ::: "memory");
-                        one_piece<KIND, GradT, PT, NT_WV>(A, mrg, tile_base, s);
+                        one_piece<KIND, GradT, PT, NT_WV>(A, mrg, tile_base, s, lane);
                         asm volatile("; end w and v cacheable" ::: "memory");
                     } else {
                         asm volatile("; w and v streamed" ::: "memory");
-                        one_piece<KIND, GradT, PT, true>(A, mrg, tile_base, s);
+                        one_piece<KIND, GradT, PT, true>(A, mrg, tile_base, s, lane);
                         asm volatile("; end w and v streamed" ::: "memory");
                     }
                     continue;
@@ -993,7 +1011,8 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, KIND == K_REDUCE_UPDATE && PT ==
     constexpr int JOIN = joined_tiles_of(KIND, FORM);
     __shared__ __align__(16) float s_sums[FORM == PAIRS ? PAIRED : 4];
     // All arguments in one trip; left alone, the compiler fetches them where it needs them, in three.
-    asm volatile("" ::"s"(A.tile_count), "s"(A.layer_hi), "s"(static_cast<int>(A.n)), "s"(A.end[0]), "s"(A.merge_bufs), "s"(A.grad_ptrs), "s"(A.P));
+    asm volatile("" ::"s"(A.tile_count), "s"(A.layer_hi), "s"(static_cast<int>(A.n)), "s"(A.end[0]), "s"(A.merge_bufs), "s"(A.grad_ptrs),
+                 "s"(A.reduced), "s"(A.inv_p), "s"(A.P));
     if constexpr (updates(KIND)) asm volatile("" ::"s"(A.w_ptrs), "s"(A.v_ptrs), "s"(A.lr));
     const int64_t arena = static_cast<int64_t>(A.tile_first) * TILE;
     const int K = A.tiles_per_wg;
@@ -1037,7 +1056,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, KIND == K_REDUCE_UPDATE && PT ==
         const Piece s{A.layer_hi - j, max(start - b, 0), min(end - b, TILE), b + max(start - b, 0) - start};
         const bool only = j + 1 >= A.n || end >= b + TILE || ((A.closes >> j) & 1);
         if (only && s.len() >= VEC) {
-            one_piece<KIND, GradT, PT, true>(A, mrg(), arena + b, s);
+            one_piece<KIND, GradT, PT, true>(A, mrg(), arena + b, s, threadIdx.x);
             continue;
         }
         // Whole vectors first, then the wanted elements of the others, one per lane (see general_tile).

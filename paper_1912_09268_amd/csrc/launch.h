@@ -274,7 +274,8 @@ constexpr bool may_roll(int kind, int form) { return TVECS == 1 && kind == K_PIP
 // 6500 (26) P = 2 9.2 / 9.4, 4 11.6 / 12.1, 6 16.7 / 15.7, 8 18.9 / 16.6, 16 30.7 / 27.6; 9000 (36) 12.6 / 12.8, 16.2 / 16.0, 20.9 / 20.1, 23.2 /
 // 22.9, 37.5 / 37.0; 12,000 tiles over 600 tensors P = 8 30.4 / 31.7.  Where the worker count is not compiled the table form ends
 // earlier (12 tensors as views: binary32 2700 tiles P = 6 11.1 / 11.0, 12 16.4 / 16.5, 3071 12.2 / 12.7, 18.0 / 18.9; bfloat16 4095 tiles 10.9 /
-// 10.2, 16.0 / 15.0, 7500 18.1 / 18.8, 25.9 / 27.0).
+// 10.2, 16.0 / 15.0, 7500 18.1 / 18.8, 25.9 / 27.0).  The other side of 16 tiles to a CU, 16 workers: bfloat16, 4000 tiles of one tensor 18.4 /
+// 16.3, over 150 tensors 19.6 / 20.2.
 inline bool rolls(int32_t dtype, int32_t P, bool few, int32_t per_cu) {
     const bool well = few || P == 2 || P == 4 || P == 8 || P == 16;
     if (dtype == MGWFBP_F32) return per_cu <= (well ? 12 : 10);
