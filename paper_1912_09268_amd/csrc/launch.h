@@ -52,9 +52,9 @@ constexpr bool HAVE_PIECES = TVECS == 1;
 #endif
 // Kinds whose wavefronts have too little under way with one tile can take joined steps: PACK, a plain copy, always, and
 // the pipeline on 16-bit gradients, where a worker's share of a tile is 512 bytes, in kernels of their own: beside the
-// joined step, whose sums change hands through LDS, the single-tile kernel would need 105 instead of 74 registers (16
-// workers; 77 instead of 57 with 8) and as uncapped launches hold 16 instead of 24 wavefronts per compute unit (16
-// workers, 6000 tiles: 30.0 us against 23.4).
+// joined step, whose sums change hands through LDS, the single-tile kernel would need the joined one's 96 registers instead of 59 (16
+// workers; 63 instead of 43 with 8) and as uncapped launches hold 20 instead of 32 wavefronts per compute unit (16
+// workers, 6000 tiles: 30.0 us against 23.4, at 16 against 24 wavefronts).
 constexpr int joined_tiles_of(int kind, int form) { return form == PAIRS ? PAIR : kind == K_PACK && form != BURST ? PACK_TILES : 1; }
 
 // Dynamic LDS per workgroup that lets at most n workgroups share the 160 KiB of a compute unit.  A workgroup's
@@ -103,13 +103,16 @@ constexpr size_t static_lds(int kind, bool few, int form) {
 //   - A launch of a few rounds of the chip (the compute units times the cap) should not end in a nearly empty one, see
 //     short_launch_cap().
 //   - A ragged tile (see general_tile) spends most of its time waiting for one thing after the other, longest where the
-//     worker count is not a compiled one (four workers' loads at a time): a launch that consists of them needs every wave
-//     slot.  Time uncapped over capped, binary32, log-normal sizes with 45 and 17 % of the tiles ragged: pipeline 1 / 3 / 6 / 12 /
+//     worker count is not a compiled one (pointers and loads of eight workers at a time): a launch that consists of them needs every wave
+//     slot.  Time uncapped over capped (measured with four workers at a time, and every ragged tile on the general path), binary32, log-normal sizes with 45 and 17 % of the tiles ragged: pipeline 1 / 3 / 6 / 12 /
 //     32 workers 0.95 / 0.97 / 0.90 / 0.90 / 0.97 and 0.99 / 0.99 / 0.98 / 0.98 / 0.98, reduce_update 6 / 12 / 32 workers 0.97 / 0.92 / 0.97
 //     and 1.00 / 0.97 / 1.00, direct 0.95 / 0.81 / 0.87 and 0.99 / 0.87 / 0.93.  With 8 workers it is no gain (45 %: pipeline 1.04,
 //     reduce_update 0.99, direct 1.01; equal tensors, 25 / 40 / 60 % ragged: pipeline 1.06 / 1.03 / 1.05, reduce_update 1.00 / 1.07 / 1.02,
 //     direct 0.99 / 1.05 / 1.03), and with 16 the registers cap it anyway.
-//   - 16-bit gradients need every wave slot (direct, P = 8: 6559 uncapped / 5729 at 16), but for REDUCE with all of
+//   - 16-bit gradients need every wave slot (direct, P = 8: 6559 uncapped / 5729 at 16), but for long REDUCE_UPDATE, which has the
+//     registers for 28 to 32 wavefronts (bfloat16, 12 and 150 tensors, us uncapped / at 25: 40,000 tiles P = 4 39.7 / 39.1, 42.1 / 40.3,
+//     8 52.6 / 52.5, 54.6 / 54.3, 16 80.1 / 79.9, 82.2 / 82.2; 100,000 tiles P = 4 96.4 / 93.4, 103.6 / 98.3, 8 129.8 / 126.6, 136.0 / 131.9, 16
+//     193.3 / 191.5, 201.4 / 199.4; P = 1 level; 12,000 tiles level, 7000 tiles P = 4 8.9 / 9.7, 8 11.4 / 12.6), for REDUCE with all of
 //     8 or 16 workers' loads in flight (P = 16: 6381 at 16 / 6220 uncapped; P = 12, two at a time: 6512 / 5265) and
 //     for the pipeline's joined steps, which have 1 KiB under way like binary32 (P = 8: 6164 at 14 / 5886 uncapped).
 //     The longest of those like a smaller window where they write the reduced arena as well.  us at 12 / 14, P = 8, with it: 46 M
@@ -146,7 +149,7 @@ inline int32_t default_burst_tiles(int kind, int32_t dtype, int32_t P) {
 // Nor does a model of many ragged tiles, whose turns come one after the other in a pair: with 0.9 / 2 / 3 / 11 / 45 % of
 // its tiles ragged, bf16, P = 8: 5706 / 5583 / 5789 / 5408 / 4364 joined, 5528 / 5446 / 5891 / 5532 / 4640 not.
 // In launches of up to twice SHORT_LAUNCH_TILES a single ragged tile counts where the worker count is not a compiled one: it
-// takes its workers four at a time, after or before the other tile of its pair, and the launch waits for it (bfloat16, one
+// takes its workers a few at a time, after or before the other tile of its pair, and the launch waits for it (at four, bfloat16, one
 // tensor that ends in a ragged second half of a pair, time over that of single tiles: 16,500 tiles 6 / 12 / 32 workers 1.09 /
 // 1.13 / 1.17, 4 / 8 / 16 workers 1.01 / 1.02 / 1.02; 24,000 tiles 1.04 / 1.06 / 1.08; 31,000 tiles 1.00 / 1.00 / 1.01, from 45,000 on
 // below 1; without it 0.9-1.0).
@@ -189,7 +192,7 @@ inline int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int
             if (many_halves(dtype, P, static_cast<int64_t>(tiles) * P, ragged)) return 21;
             if (!wide || ragged > SOME_RAGGED) return -1;
             return tiles < SHORT_LAUNCH_TILES ? 18 : 14;
-        case K_REDUCE_UPDATE: return wide ? (P < 4 ? 25 : P < 8 ? 16 : 14) : -1;
+        case K_REDUCE_UPDATE: return wide ? (P < 4 ? 25 : P < 8 ? 16 : 14) : P >= 4 && P <= 16 && tiles >= 2 * SHORT_LAUNCH_TILES ? 25 : -1;
         case K_DIRECT: return wide ? (P < 4 ? 25 : P <= 8 ? 16 : 14) : -1;
         default:                                         // pipeline
             if (wide) return P < 6 ? 18 : !reduced && P <= 12 ? 16 : 14;
@@ -199,8 +202,8 @@ inline int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int
 }
 
 // The cap of a launch of a few rounds, binary32 or in pairs of tiles, next to the `cap` of long ones: all workgroups at
-// once where 25 per compute unit hold them (16 workers, but for REDUCE: 20 in the few-segments form, 16 in the table form
-// and in pairs, by their registers), else the neighbour whose rounds come out fullest.  Pipeline, 8 workers, one tensor of 5000 tiles (19.5 per compute unit): 21.4 / 22.1 / 22.5 us in two
+// once where 25 per compute unit hold them (16 workers, but for REDUCE: 20 in the few-segments form, by its registers, 16 in the
+// table form and in pairs), else the neighbour whose rounds come out fullest.  Pipeline, 8 workers, one tensor of 5000 tiles (19.5 per compute unit): 21.4 / 22.1 / 22.5 us in two
 // rounds at 14 / 16 / 18, 19.1 in one.  Per cent above the best of 14 / 16 / 18 / 21, mean of reduce, direct and pipeline with
 // 8, 12, 16 and 32 workers: 7100 tiles 0.2 / 0.7 / 2.9 / 5.0, 7200 12.0 / 0.3 / 1.9 / 3.4, 8250 6.0 / 9.4 / 0.0 / 1.7, 9250 0.3 / 4.2 / 7.8 /
 // 1.8, 11000 7.5 / 0.0 / 2.3 / 6.6, 13000 1.4 / 5.3 / 0.3 / 2.2, 13900 0.5 / 2.8 / 5.7 / 1.9, 18000 2.3 / 1.5 / 0.4 / 3.0, 24000 0.9 / 0.2 /

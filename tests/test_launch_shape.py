@@ -277,3 +277,12 @@ def test_burst_form_ends_where_pacing_is_ahead(ask):
                                   ("reduce_update", "f32", 16, 1280), ("direct", "f32", 4, 2560), ("direct", "f32", 16, 1792), ("direct", "f16", 8, 3072),
                                   ("update", "f32", 8, 3072)):
         assert [s.form for s in shapes(ask, [dict(kind=kind, dtype=dtype, P=P, tiles=t) for t in (1, tiles, tiles + 1)])] == [BURST, BURST, SINGLE], (kind, P)
+
+
+def test_long_sixteen_bit_reduce_update_is_capped(ask):
+    """Capped from twice SHORT_LAUNCH_TILES on with 4 to 16 workers; every wave slot otherwise."""
+    def cap(P, tiles, dtype="bf16"):
+        return shapes(ask, [dict(kind="reduce_update", dtype=dtype, P=P, tiles=tiles)])[0].wgs_per_cu
+    for dtype in ("bf16", "f16"):
+        assert [cap(P, 32768, dtype) for P in (1, 3, 4, 12, 16, 17, 32)] == [-1, -1, 25, 25, 25, -1, -1]
+        assert [cap(P, 32767, dtype) for P in (4, 16)] == [-1, -1]
