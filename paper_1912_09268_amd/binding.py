@@ -1,7 +1,7 @@
 """ctypes binding with the same names as the C ABI declared in include/mgwfbp.h.
 
 Argument marshalling only; the device calls, which a training loop makes once per group or tensor, do theirs in
-the extension module built from csrc/calls.cpp where that is there (a call takes 2.75 us instead of 3.4-3.7).  Device buffers are passed as integer addresses (e.g. torch's
+the extension module built from csrc/calls.cpp where that is there (a call takes 2.7 us instead of 3.4-3.7).  Device buffers are passed as integer addresses (e.g. torch's
 `tensor.data_ptr()`), streams as integer handles (e.g. `torch.cuda.current_stream().cuda_stream`)."""
 from __future__ import annotations
 

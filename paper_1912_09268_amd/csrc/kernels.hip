@@ -36,7 +36,8 @@
 //     so they issue every load of a tile at once (the burst form); what follows is for the rest;
 //   - PACING.  For these read/write mixes MI355X delivers most when every compute unit keeps about
 //     16-24 KiB of loads in flight and a tenth less beyond that, so a lane has one 16-byte load outstanding
-//     (one worker's share of the tile; two workers' in the kinds that only read between their stores) and each
+//     (one worker's share of the tile; two workers' in the kinds that only read between their stores, and in the
+//     pipeline's launches whose wavefronts are few or have little under way, see rolls()) and each
 //     launch asks for enough unused LDS that only so many workgroups share a compute unit, 12 to 25 or all of them
 //     by kind, gradient width, worker count, length and what the launch covers (the rules are in launch.h);
 //   - SMALL WORKGROUPS.  A workgroup is one wavefront and a tile the 256 elements it covers with one vector per
@@ -155,9 +156,9 @@ __device__ __forceinline__ float widen(_Float16 x) { return static_cast<float>(x
 // kernel arguments
 // ---------------------------------------------------------------------------------------------
 //
-// What a launch costs the host depends on the size of this block: up to 112 bytes an empty launch takes 2.4 us,
-// from 136 bytes on 3.3 us (the runtime writes the block into device memory), and a kernel that asks for gridDim
-// makes the runtime append 256 more.  So everything that can be derived from something else is, and the grid
+// What a launch costs the host depends on the size of this block: up to 112 bytes a launch takes 2.5 us (1.35 without any
+// argument), from 136 bytes on 3.3 us (the runtime writes the block into device memory and reads back from it before it rings
+// the doorbell), and a kernel that asks for gridDim makes the runtime append 256 more.  So everything that can be derived from something else is, and the grid
 // size that the persistent form needs comes in as `turn`.
 constexpr int XCD_CONTIGUOUS = 1, ROLLING = 2;
 template <typename GradT> struct CallArgs {
