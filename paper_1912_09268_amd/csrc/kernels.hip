@@ -639,8 +639,9 @@ struct Piece {
     __device__ __forceinline__ int len() const { return hi - lo; }
     __device__ __forceinline__ int lanes() const { return (hi - lo + VEC - 1) / VEC; }
     // First element of the vector lane k takes.  The last one ends with the piece and so overlaps the one before it where
-    // the piece is no whole number of vectors.  That is harmless: both belong to one wavefront, which has read all it
-    // needs of them before it writes, and both lanes write the same values.
+    // the piece is no whole number of vectors.  That is harmless in workgroups of one wavefront (HAVE_PIECES), which has read
+    // all it needs of both before it writes, and both lanes write the same values; a second wavefront could read w and v after
+    // the first has updated them.
     __device__ __forceinline__ int element(int k) const { return min(k * VEC, len() - VEC); }
 };
 
@@ -648,6 +649,7 @@ struct Piece {
 template <int KIND, typename GradT, int PT, bool WVNT>
 __device__ __forceinline__ void one_piece(const CallArgs<GradT>& A, const WorkerPtrs<GradT, PT>& mrg, int64_t tile_base, const Piece& s,
                                           int lane) {
+    static_assert(BLOCK == 64 || KIND < 0, "lanes that share elements are in one wavefront");
     WorkerPtrs<const GradT, PT> src;
     float* wp = nullptr;
     float* vp = nullptr;
@@ -667,6 +669,7 @@ __device__ __forceinline__ void one_piece(const CallArgs<GradT>& A, const Worker
 // vector: then the pieces are taken as many at a time as there are lanes for (a piece never in two parts, see element()).
 template <int KIND, typename GradT, int PT, typename Pieces>
 __device__ __forceinline__ void several_pieces(const CallArgs<GradT>& A, const WorkerPtrs<GradT, PT>& mrg, int64_t tile_base, Pieces pieces) {
+    static_assert(BLOCK == 64 || KIND < 0, "lanes that share elements are in one wavefront");
     int lane = static_cast<int>(threadIdx.x);
     here_only_per_lane(lane);
     Piece s;

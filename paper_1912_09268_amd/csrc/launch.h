@@ -42,7 +42,7 @@ constexpr int PAIRED = PAIR * TILE;   // elements of a pair
 // What needs tiles of one vector per lane, and of one wavefront, is left out of builds with other tiles.
 constexpr bool HAVE_PAIRS = TVECS == 1;
 constexpr bool HAVE_FEW = TVECS == 1 && BLOCK == 64;
-constexpr bool HAVE_PIECES = TVECS == 1;
+constexpr bool HAVE_PIECES = TVECS == 1 && BLOCK == 64;
 // Most segments of a tile that the table form takes piece by piece; the walk over the pieces costs 0.15 us each, the general
 // path's prefix sum and search the same for any number.  us with one, up to three and up to eight, 8 workers, tensors in
 // groups of eight and more: of 301 elements pipeline 7.2 / 6.4 / 6.4, unpack_update 4.6 / 4.0 / 4.0; of 70 elements pipeline 7.4 /
@@ -78,8 +78,8 @@ inline size_t lds_for_workgroups_per_cu(int32_t n, size_t static_lds) {
     return total - static_lds - 64;
 }
 
-// LDS the kernels declare themselves: the table form for its general path (which REDUCE needs with tiles of several
-// vectors per lane only, and less of it), both forms for the sums of joined steps.
+// LDS the kernels declare themselves: the table form for its general path (which REDUCE needs only where tiles are not taken
+// piece by piece, and less of it), both forms for the sums of joined steps.
 constexpr size_t static_lds(int kind, bool few, int form) {
     const size_t joined = form == PAIRS ? sizeof(float) * PAIRED : 0;
     return few || (HAVE_PIECES && !needs_owner(kind)) ? joined : joined + sizeof(int) * static_cast<size_t>((needs_owner(kind) ? 2 * MAXSEG + 1 + BLOCK / 64 : 0) + TILE / VEC + 1);

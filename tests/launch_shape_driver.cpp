@@ -14,6 +14,8 @@ int main() {
             if (std::scanf("%d %d %d %d", &kind, &few, &form, &cap) != 4) return 1;
             const size_t own = static_lds(kind, few != 0, form);
             std::printf("%zu %zu\n", own, lds_for_workgroups_per_cu(cap, own));
+        } else if (!std::strcmp(what, "have")) {      // have: what this build's tiles allow
+            std::printf("%d %d %d\n", HAVE_PAIRS, HAVE_FEW, HAVE_PIECES);
         } else if (!std::strcmp(what, "shape")) {     // shape <work> <settings> n_cu
             LaunchWork w{};
             LaunchSettings set;

@@ -22,11 +22,11 @@ Kernel = namedtuple("Kernel", "few kind half P form lds vgprs")
 Shape = namedtuple("Shape", "tiles_per_wg units grid xcd_contiguous run_log2 may_be_few form wgs_per_cu")
 
 
-@pytest.fixture(scope="module")
-def ask(tmp_path_factory):
-    exe = str(tmp_path_factory.mktemp("launch") / "driver")
-    r = subprocess.run(["g++", "-std=c++17", "-Wall", "-Wno-unused-function", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-                        os.path.join(ROOT, "tests", "launch_shape_driver.cpp"), os.path.join(CSRC, "layout.cpp"), "-o", exe], capture_output=True, text=True)
+def build_driver(folder, *defines):
+    exe = str(folder / "driver")
+    r = subprocess.run(["g++", "-std=c++17", "-Wall", "-Wno-unused-function", *(f"-D{d}" for d in defines), "-I", os.path.join(ROOT, "include"),
+                        "-I", CSRC, os.path.join(ROOT, "tests", "launch_shape_driver.cpp"), os.path.join(CSRC, "layout.cpp"), "-o", exe],
+                       capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
 
     def ask(lines):
@@ -36,6 +36,11 @@ def ask(tmp_path_factory):
         assert len(out) == len(lines)
         return out
     return ask
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    return build_driver(tmp_path_factory.mktemp("launch"))
 
 
 @pytest.fixture(scope="module")
@@ -286,3 +291,15 @@ def test_long_sixteen_bit_reduce_update_is_capped(ask):
     for dtype in ("bf16", "f16"):
         assert [cap(P, 32768, dtype) for P in (1, 3, 4, 12, 16, 17, 32)] == [-1, -1, 25, 25, 25, -1, -1]
         assert [cap(P, 32767, dtype) for P in (4, 16)] == [-1, -1]
+
+
+@pytest.mark.parametrize("block,tile_vecs", [(64, 1), (64, 2), (128, 1), (128, 2), (256, 1)])
+def test_tiles_go_piece_by_piece_in_workgroups_of_one_wavefront(tmp_path, block, tile_vecs):
+    """The last vector of a piece shares elements with the one before it, so the lanes that take them (of 257 to 259
+    elements lanes 63 and 64) must be of one wavefront: another could update w and v before they are read.  Without the
+    pieces reductions have the general path's LDS."""
+    ask = build_driver(tmp_path, f"MGWFBP_BLOCK={block}", f"MGWFBP_TILE_VECS={tile_vecs}")
+    (pairs, few, pieces), = ask(["have"])
+    assert (pairs, few, pieces) == (tile_vecs == 1, tile_vecs == 1 and block == 64, tile_vecs == 1 and block == 64)
+    (own, _), = ask(["lds %d 0 1 0" % KINDS.index("reduce")])
+    assert own == (0 if pieces else 4 * (block * tile_vecs + 1))
