@@ -334,7 +334,7 @@ template <int MOST, typename F> __device__ __forceinline__ void some_sizes(int n
     }
 }
 
-template <int KIND, typename GradT, int PT, int W, int N, bool WVNT, int TOGETHER = 0>
+template <int KIND, typename GradT, int PT, int W, int N, bool WVNT, int TOGETHER = 0, int GENERAL = MGWFBP_GENERAL_GROUP>
 __device__ __forceinline__ void paced_step(const CallArgs<GradT>& A, const WorkerPtrs<const GradT, PT>& src,
                                            const WorkerPtrs<GradT, PT>& mrg, float* wp, float* vp,
                                            int64_t soff, int64_t apos, int stride) {
@@ -355,7 +355,7 @@ __device__ __forceinline__ void paced_step(const CallArgs<GradT>& A, const Worke
         // workers whose loads are issued together: one (kinds that store each worker's share before the next
         // load), MGWFBP_READ_GROUP (kinds that only read them), or all of them / TOGETHER at a time (the burst form and
         // the ragged tiles, whose time is the chain of trips to memory)
-        constexpr int GW = TOGETHER > 0 ? (PT > 0 ? (PT < MGWFBP_GENERAL_GROUP ? PT : MGWFBP_GENERAL_GROUP) : TOGETHER) : (writes_merge(KIND) ? 1 : MGWFBP_READ_GROUP);
+        constexpr int GW = TOGETHER > 0 ? (PT > 0 ? (PT < GENERAL ? PT : GENERAL) : TOGETHER) : (writes_merge(KIND) ? 1 : MGWFBP_READ_GROUP);
         auto some_workers = [&](auto size, int w0) {      // workers w0 .. w0 + size - 1
             constexpr int COUNT = decltype(size)::value;
             GV g[COUNT][N];
@@ -646,7 +646,7 @@ struct Piece {
 };
 
 // One piece by itself: its pointers are the same for all lanes.  Of a full tile, too, in the burst form.
-template <int KIND, typename GradT, int PT, bool WVNT>
+template <int KIND, typename GradT, int PT, bool WVNT, int GENERAL = MGWFBP_GENERAL_GROUP>
 __device__ __forceinline__ void one_piece(const CallArgs<GradT>& A, const WorkerPtrs<GradT, PT>& mrg, int64_t tile_base, const Piece& s,
                                           int lane) {
     static_assert(BLOCK == 64 || KIND < 0, "lanes that share elements are in one wavefront");
@@ -660,7 +660,7 @@ __device__ __forceinline__ void one_piece(const CallArgs<GradT>& A, const Worker
     }
     if (lane < s.lanes()) {
         const int e = s.element(lane);
-        paced_step<KIND, GradT, PT, VEC, 1, WVNT, MGWFBP_TOGETHER>(A, src, mrg, wp, vp, s.off + e, tile_base + s.lo + e, 0);
+        paced_step<KIND, GradT, PT, VEC, 1, WVNT, MGWFBP_TOGETHER, GENERAL>(A, src, mrg, wp, vp, s.off + e, tile_base + s.lo + e, 0);
     }
 }
 
@@ -856,10 +856,11 @@ template <int KIND, typename GradT> struct TablePieces {
 
 // FORM: vectors per lane a fast tile is walked in (1, see paced_step), BURST or PAIRS.
 // 16-bit gradients run uncapped in single tiles and want the wavefronts; where the compiler stops a few registers short of one more,
-// it is told the number per SIMD.
+// it is told the number per SIMD.  So it is in pairs of binary16 where the worker count is not compiled, which take 95 registers
+// otherwise, 63 so (table form; 96 and 79 in the few-segments form).
 template <int KIND, typename GradT, int PT, int FORM> constexpr int wanted_waves() {
-    if (FORM != 1 || sizeof(GradT) != 2) return 1;
-    return KIND == K_PIPELINE && PT == 0 ? 8 : 1;
+    if (sizeof(GradT) != 2 || KIND != K_PIPELINE || PT != 0) return 1;
+    return FORM == 1 ? 8 : FORM == PAIRS ? 6 : 1;
 }
 
 template <int KIND, typename GradT, int PT, int FORM>
@@ -990,96 +991,154 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_waves<KIND, GradT, PT, F
 // its arguments in scalar registers, so only the pointers lie between it and its data.  Segment j is tensor
 // layer_hi - j and starts where j - 1 ends, or on the next tile after the last segment of a group.  Kinds that
 // need no tensors (REDUCE) get whole groups as segments.
-template <typename GradT> __device__ __forceinline__ int few_start(const MGWFBP_CONST FewArgs<GradT>& A, int j) {   // j static
+template <typename GradT> __device__ __forceinline__ int few_start(const FewArgs<GradT>& A, int j) {   // j static
     if (j == 0) return A.start0;
     const int e = A.end[j - 1];
     return (A.closes >> (j - 1)) & 1 ? (e + TILE - 1) & ~(TILE - 1) : e;
 }
 
-// Segment that element q belongs to if it belongs to any: the last one that starts at or before q, or segment 0.
+// Segment that element q belongs to if it belongs to any: the last one that starts at or before q, or segment 0.  (Past the
+// segments there are lie empty ones; who they own does not matter.)
 struct FewSeg { int j, start, end; };
-template <typename GradT> __device__ __forceinline__ FewSeg few_owner(const MGWFBP_CONST FewArgs<GradT>& A, int q) {
+template <typename GradT> __device__ __forceinline__ FewSeg few_owner(const FewArgs<GradT>& A, int q) {
     FewSeg s{0, A.start0, A.end[0]};
 #pragma unroll
     for (int j = 1; j < FEW; ++j) {
         const int start = few_start(A, j);
-        if (j < A.n && q >= start) s = FewSeg{j, start, A.end[j]};
+        if (q >= start) s = FewSeg{j, start, A.end[j]};
     }
     return s;
 }
 
+// Whether the ends of all segments come with the other arguments.  Where they do, a tile that needs them has them a trip
+// earlier; where they do not, the single tensors of long launches have the scalar registers.  us with the ends in the general
+// part only / with the other arguments, burst form: three tensors of 300 elements, 8 workers, binary32: pipeline 2.63 / 2.40,
+// reduce_update 2.55 / 2.36; seven of 9 to 2000, 16 workers, bfloat16: 4.05 / 3.55, 3.37 / 3.02; pack 2.56 / 2.25.
+constexpr bool ends_early(int kind, int form) { return form == BURST || kind == K_PACK; }
+
+// One tile of the few-segments form (of PACK or in pairs: a joined step); the tiles taken.
 template <int KIND, typename GradT, int PT, int FORM>
-__global__ void __launch_bounds__(MGWFBP_BLOCK, KIND == K_REDUCE_UPDATE && PT == 16 && sizeof(GradT) == 4 ? 5 : 1) mgwfbp_few_kernel(const FewArgs<GradT> A) {
-    static_assert(KIND >= 0 && HAVE_FEW, "a tile is one vector per lane of one wavefront");
+__device__ __forceinline__ int few_tile(const FewArgs<GradT>& A, const MGWFBP_CONST FewArgs<GradT>* a, int t, int t_end, float* s_sums) {
     constexpr int SINGLE = FORM == PAIRS ? 1 : FORM;
     constexpr int JOIN = joined_tiles_of(KIND, FORM);
+    constexpr bool EARLY = ends_early(KIND, FORM);
+    // Paced steps of 16-bit gradients that store nothing between 16 workers want every wave slot (see few_form_pays): their
+    // ragged tiles go in groups of eight.
+    constexpr bool TIGHT = PT == 16 && sizeof(GradT) == 2 && FORM == 1 && !writes_merge(KIND);
+    constexpr int LANES = TIGHT ? 0 : PT;
+    const int64_t arena = static_cast<int64_t>(A.tile_first) * TILE;
+    const int b = t * TILE;
+    auto mrg = [&](auto count) {                                       // (fetched where it is used: 16 workers have no registers to keep it in)
+        WorkerPtrs<GradT, decltype(count)::value> m;
+        if constexpr (reads_merge(KIND) || writes_merge(KIND)) m.fetch(A.merge_bufs, 1, 0, worker_base<KIND>());
+        return m;
+    };
+    // Segment that ends in the tile or beyond it (the last one does); all of the tile's if it is the last one or ends
+    // beyond it.
+    int j = 0, start = A.start0, end = A.end[0];
+    auto next = [&](int i, int its_end) {
+        start = (A.closes >> i) & 1 ? (end + TILE - 1) & ~(TILE - 1) : end;
+        end = its_end;
+        j = i + 1;
+    };
+    if constexpr (EARLY) {
+#pragma unroll
+        for (int i = 0; i < FEW - 1; ++i) {
+            if (end > b) break;
+            next(i, A.end[i + 1]);
+        }
+    } else {
+        while (end <= b && j < FEW - 1) next(j, a->end[j + 1]);        // read where they lie: the index need not be known beforehand
+    }
+    if (FORM != BURST && start <= b && b + TILE <= end) {              // a full tile inside one segment
+        if constexpr (JOIN > 1) {
+            if (t + JOIN <= t_end && b + JOIN * TILE <= end) {
+                joined_tiles<KIND, GradT, PT>(A, mrg(Int<PT>()), A.layer_hi - j, b - start, arena + b, s_sums);
+                return JOIN;
+            }
+        }
+        if constexpr (may_roll(KIND, FORM)) {
+            if (A.flags & ROLLING) {
+                asm volatile("; rolling steps" ::: "memory");      // keeps the arms' addresses, and their registers, apart
+                rolling_tile<GradT, PT>(A, mrg(Int<PT>()), A.layer_hi - j, b - start, arena + b);
+                asm volatile("; end rolling steps" ::: "memory");
+                return 1;
+            }
+            asm volatile("; single steps" ::: "memory");
+        }
+        fast_chunk<KIND, GradT, PT, true, SINGLE>(A, mrg(Int<PT>()), A.layer_hi - j, b - start, arena + b, TVECS);
+        return 1;
+    }
+    const Piece s{A.layer_hi - j, max(start - b, 0), min(end - b, TILE), b + max(start - b, 0) - start};
+    const bool only = j + 1 >= A.n || end >= b + TILE || ((A.closes >> j) & 1);
+    if (only && s.len() >= VEC) {
+        one_piece<KIND, GradT, PT, true, TIGHT ? 8 : MGWFBP_GENERAL_GROUP>(A, mrg(Int<PT>()), arena + b, s, threadIdx.x);
+        return 1;
+    }
+    // Whole vectors first, then the wanted elements of the others, one per lane (see general_tile).  (Where segments start is
+    // worked out here only, see here_only.)
+    FewArgs<GradT> B = A;
+    if constexpr (EARLY) {
+        int32_t closes = A.closes;
+        here_only(closes);
+        B.closes = static_cast<uint8_t>(closes);
+    } else {
+        asm volatile("" : "+s"(a));
+        B = *(const FewArgs<GradT>*)a;
+    }
+    int lane = threadIdx.x;
+    here_only_per_lane(lane);
+    const int p = b + lane * VEC;
+    const FewSeg o = few_owner(B, p);
+    const bool whole = p >= o.start && p + VEC <= o.end;
+    const bool any = (p < o.end && p + VEC > o.start) || few_owner(B, p + VEC - 1).j != o.j;
+    const uint64_t ragged = __ballot(any && !whole);
+    if (whole) do_one<KIND, GradT, LANES, VEC>(A, mrg(Int<LANES>()), A.layer_hi - o.j, p - o.start, arena + p);
+    const int n_ragged = __popcll(ragged) * VEC;
+    for (int e = lane; e < n_ragged; e += BLOCK) {
+        uint64_t rest = ragged;
+        for (int k = e / VEC; k > 0; --k) rest &= rest - 1;
+        const int q = b + __builtin_ctzll(rest) * VEC + e % VEC;
+        const FewSeg r = few_owner(B, q);
+        if (q >= r.start && q < r.end) do_one<KIND, GradT, LANES, 1>(A, mrg(Int<LANES>()), A.layer_hi - r.j, q - r.start, arena + q);
+    }
+    return 1;
+}
+
+// Wavefronts per SIMD that the compiler is told to leave registers for: 16 workers' loads take 98 registers in the burst form of
+// a binary32 reduce_update otherwise (20 instead of 16 wavefronts per compute unit).
+template <int KIND, typename GradT, int PT, int FORM> constexpr int wanted_few_waves() {
+    if (FORM == PAIRS) return wanted_waves<KIND, GradT, PT, FORM>();
+    return PT == 16 && KIND == K_REDUCE_UPDATE && sizeof(GradT) == 4 ? 5 : 1;
+}
+
+// Scalar registers bound the wavefronts of these kernels: a SIMD has 800, and a wavefront takes what it needs in blocks of 16
+// and 16 more, so eight fit with up to 80, seven with up to 96 and six beyond (the compiler's own figure leaves the 16 out; seen
+// where a launch no longer fits at once: 93 registers at 28 tiles per compute unit, 80 at 32, 103 at 24).  us with 83 to 103 / 55
+// to 80, bfloat16, one tensor of 7500 tiles: direct, 4 / 8 / 16 / 32 workers 9.3 / 8.2, 12.7 / 10.6, 18.9 / 15.4, 29.9 / 24.9; reduce_update 9.3 / 8.3,
+// 12.4 / 10.4, 18.1 / 15.2, 29.2 / 23.9.
+template <int KIND, typename GradT, int PT, int FORM>
+__global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_few_waves<KIND, GradT, PT, FORM>())) mgwfbp_few_kernel(FewArgs<GradT> A) {
+    static_assert(KIND >= 0 && HAVE_FEW, "a tile is one vector per lane of one wavefront");
     __shared__ __align__(16) float s_sums[FORM == PAIRS ? PAIRED : 4];
     // All arguments in one trip; left alone, the compiler fetches them where it needs them, in three.
     asm volatile("" ::"s"(A.tile_count), "s"(A.layer_hi), "s"(static_cast<int>(A.n)), "s"(A.end[0]), "s"(A.merge_bufs), "s"(A.grad_ptrs),
                  "s"(A.reduced), "s"(A.inv_p), "s"(A.P));
     if constexpr (updates(KIND)) asm volatile("" ::"s"(A.w_ptrs), "s"(A.v_ptrs), "s"(A.lr));
-    const int64_t arena = static_cast<int64_t>(A.tile_first) * TILE;
-    const int K = A.tiles_per_wg;
-    const int u = unit_of(A);
-    const int t_end = min((u + 1) * K, A.tile_count);
-    for (int t = u * K; t < t_end; ++t) {
-        const int b = t * TILE;
-        auto mrg = [&] {                                                   // (fetched where it is used: 16 workers have no registers to keep it in)
-            WorkerPtrs<GradT, PT> m;
-            if constexpr (reads_merge(KIND) || writes_merge(KIND)) m.fetch(A.merge_bufs, 1, 0, worker_base<KIND>());
-            return m;
-        };
-        // Segment that ends in the tile or beyond it (the last one does); all of the tile's if it is the last one or ends
-        // beyond it.  The arguments are read where they lie, so that an index need not be known beforehand.
-        const MGWFBP_CONST FewArgs<GradT>* a = (const MGWFBP_CONST FewArgs<GradT>*)__builtin_amdgcn_kernarg_segment_ptr();
-        int j = 0, start = A.start0, end = A.end[0];
-        while (end <= b && j < FEW - 1) {
-            start = (A.closes >> j) & 1 ? (end + TILE - 1) & ~(TILE - 1) : end;
-            end = a->end[++j];
-        }
-        if (FORM != BURST && start <= b && b + TILE <= end) {              // a full tile inside one segment
-            if constexpr (JOIN > 1) {
-                if (t + JOIN <= t_end && b + JOIN * TILE <= end) {
-                    joined_tiles<KIND, GradT, PT>(A, mrg(), A.layer_hi - j, b - start, arena + b, s_sums);
-                    t += JOIN - 1;
-                    continue;
-                }
-            }
-            if constexpr (may_roll(KIND, FORM)) {
-                if (A.flags & ROLLING) {
-                    asm volatile("; rolling steps" ::: "memory");      // keeps the arms' addresses, and their registers, apart
-                    rolling_tile<GradT, PT>(A, mrg(), A.layer_hi - j, b - start, arena + b);
-                    asm volatile("; end rolling steps" ::: "memory");
-                    continue;
-                }
-                asm volatile("; single steps" ::: "memory");
-            }
-            fast_chunk<KIND, GradT, PT, true, SINGLE>(A, mrg(), A.layer_hi - j, b - start, arena + b, TVECS);
-            continue;
-        }
-        const Piece s{A.layer_hi - j, max(start - b, 0), min(end - b, TILE), b + max(start - b, 0) - start};
-        const bool only = j + 1 >= A.n || end >= b + TILE || ((A.closes >> j) & 1);
-        if (only && s.len() >= VEC) {
-            one_piece<KIND, GradT, PT, true>(A, mrg(), arena + b, s, threadIdx.x);
-            continue;
-        }
-        // Whole vectors first, then the wanted elements of the others, one per lane (see general_tile).
-        asm volatile("" : "+s"(a));            // (see here_only)
-        int lane = threadIdx.x;
-        here_only_per_lane(lane);
-        const int p = b + lane * VEC;
-        const FewSeg o = few_owner(*a, p);
-        const bool whole = p >= o.start && p + VEC <= o.end;
-        const bool any = (p < o.end && p + VEC > o.start) || few_owner(*a, p + VEC - 1).j != o.j;
-        const uint64_t ragged = __ballot(any && !whole);
-        if (whole) do_one<KIND, GradT, PT, VEC>(A, mrg(), A.layer_hi - o.j, p - o.start, arena + p);
-        const int n_ragged = __popcll(ragged) * VEC;
-        for (int e = lane; e < n_ragged; e += BLOCK) {
-            uint64_t rest = ragged;
-            for (int k = e / VEC; k > 0; --k) rest &= rest - 1;
-            const int q = b + __builtin_ctzll(rest) * VEC + e % VEC;
-            const FewSeg r = few_owner(*a, q);
-            if (q >= r.start && q < r.end) do_one<KIND, GradT, PT, 1>(A, mrg(), A.layer_hi - r.j, q - r.start, arena + q);
+    if constexpr (ends_early(KIND, FORM))
+        asm volatile("" ::"s"(A.end[1]), "s"(A.end[2]), "s"(A.end[3]), "s"(A.end[4]), "s"(A.end[5]), "s"(A.end[6]), "s"(A.end[7]));
+    const MGWFBP_CONST FewArgs<GradT>* a = (const MGWFBP_CONST FewArgs<GradT>*)__builtin_amdgcn_kernarg_segment_ptr();
+    int t = unit_of(A) * A.tiles_per_wg;
+    const int t_end = min(t + A.tiles_per_wg, A.tile_count);
+    while (t < t_end) {
+        t += few_tile<KIND, GradT, PT, FORM>(A, a, t, t_end, s_sums);
+        if (t >= t_end) break;
+        // A further tile, where the caller asked for several: the arguments again, so that no path keeps them, or what the
+        // compiler works out from them beforehand, in registers for it (10 scalar registers).  PACK takes several by itself and
+        // has the registers (bfloat16, 32 workers, 40,000 tiles 198 us, with the arguments again 212).
+        if constexpr (KIND != K_PACK) {
+            asm volatile("" : "+s"(a));
+            A = *(const FewArgs<GradT>*)a;
         }
     }
 }

@@ -18,7 +18,7 @@ READELF = shutil.which("llvm-readelf") or "/opt/rocm/llvm/bin/llvm-readelf"
 KINDS = ["pack", "reduce", "update", "reduce_update", "pipeline", "direct"]
 DTYPES = ["f32", "bf16", "f16"]
 CU_LDS, LDS_GRAIN = 160 << 10, 1280
-Kernel = namedtuple("Kernel", "few kind half P form lds vgprs")
+Kernel = namedtuple("Kernel", "few kind half P form lds vgprs sgprs")
 Shape = namedtuple("Shape", "tiles_per_wg units grid xcd_contiguous run_log2 may_be_few form wgs_per_cu")
 
 
@@ -64,7 +64,8 @@ def kernels(tmp_path_factory):
                 field = lambda key: int(re.search(r"\.%s:\s+(\d+)" % key, text).group(1))  # noqa: E731
                 assert field("private_segment_fixed_size") == 0, "spills"
                 found.append(Kernel(m.group(1) == "few", int(m.group(2)), m.group(3) != "f", int(m.group(4)),
-                                    int(m.group(5).replace("n", "-")), field("group_segment_fixed_size"), field("vgpr_count")))
+                                    int(m.group(5).replace("n", "-")), field("group_segment_fixed_size"), field("vgpr_count"),
+                                    field("sgpr_count")))
         at += 24
     assert len(found) > 100
     return found
@@ -303,3 +304,19 @@ def test_tiles_go_piece_by_piece_in_workgroups_of_one_wavefront(tmp_path, block,
     assert (pairs, few, pieces) == (tile_vecs == 1, tile_vecs == 1 and block == 64, tile_vecs == 1 and block == 64)
     (own, _), = ask(["lds %d 0 1 0" % KINDS.index("reduce")])
     assert own == (0 if pieces else 4 * (block * tile_vecs + 1))
+
+
+def wavefronts(k):
+    """That a compute unit holds of a kernel, by its registers: a SIMD has 512 vector registers, granted in eights, and 800
+    scalar ones, granted in sixteens, of which every wavefront takes one block more than it asks for."""
+    return 4 * min(8, 512 // (-(-k.vgprs // 8) * 8), 800 // (-(-k.sgprs // 16) * 16 + 16))
+
+
+def test_few_segments_kernels_of_sixteen_bit_gradients_keep_their_wave_slots(kernels):
+    """Launches over one 16-bit tensor of 25 to 32 tiles per compute unit take the few-segments form because they fit at once
+    in it: scalar registers, above all, must not keep them from that."""
+    least = {"direct": {}, "update": {}, "reduce_update": {}, "pipeline": {8: 28, 16: 24}}
+    paced = [k for k in kernels if k.few and k.half and k.form == 1 and KINDS[k.kind] in least]
+    assert len(paced) == 2 * (1 + 3 * 5)
+    for k in paced:
+        assert wavefronts(k) >= least[KINDS[k.kind]].get(k.P, 32), k
