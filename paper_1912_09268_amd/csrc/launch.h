@@ -124,21 +124,43 @@ constexpr int32_t LONG_LAUNCH_TILES = 262144;       // 67 M elements
 
 // Longest launch, in tiles, that takes the burst form.  Up to here the time is the latency of a tile, beyond it the
 // loads of all tiles at once are more than the memory system likes.  us burst / paced (the pipeline's rolling steps among
-// these, see rolls()), one tensor.  Binary32, 1400, 1800 and 2300 tiles: pipeline P = 4 4.9 / 5.2, 5.2 / 5.7, 7.1 / 7.0; 6 5.6 / 6.5,
-// 6.7 / 7.2, 9.1 / 9.1; 8 6.9 / 7.1, 8.1 / 8.0, 11.6 / 10.9; 12 9.1 / 9.3, 10.9 / 10.6, 15.9 / 14.4; 16 11.0 / 10.8, 13.5 / 12.5, 20.4 / 17.9.  1024, 1792
-// and 2560 tiles: reduce P = 4 3.0 / 3.2, 3.6 / 3.5, 4.2 / 3.8; 6 3.4 / 3.8, 4.6 / 4.3; 8 4.0 / 4.3, 5.5 / 4.7, 6.6 / 5.5; 16 6.4 / 6.7, 8.7 /
-// 7.3; reduce_update P = 4 3.2 / 4.2, 4.0 / 4.7, 5.3 / 5.2; 8 4.0 / 5.3, 5.4 / 6.1, 7.1 / 6.8; 12 4.8 / 6.5, 7.5 / 7.8, 9.5 / 8.9; 16 7.0 / 7.9, 9.9 /
-// 8.6; direct P = 4 3.2 / 4.3, 4.0 / 4.9, 5.2 / 5.5; 8 3.9 / 5.4, 5.2 / 6.2, 6.6 / 6.9; 12 4.9 / 6.8, 6.5 / 7.9, 8.2 / 8.7; 16 5.3 / 7.5, 7.6 / 8.7,
-// 10.1 / 9.9; 32 8.2 / 12.9, 11.6 / 14.5, 16.3 / 16.1.  3072 and 4096 tiles: binary32 P = 1 to 3 pipeline 5.3 / 6.0, 6.6 / 7.0; 6.0 / 6.3, 8.2 / 8.0; 7.5 /
-// 6.6, 10.0 / 9.5; update 4.5 / 4.6, 5.6 / 5.4; bfloat16 pipeline P = 2 5.1 / 5.5, 6.9 / 6.9; 4 6.5 / 6.6, 9.1 / 9.2; 6 7.7 / 7.9, 11.1 / 10.7; 8 8.9 / 8.7,
-// 13.2 / 12.8; 12 11.3 / 10.8, 16.9 / 16.4; reduce_update P = 3 4.6 / 5.8, 5.8 / 6.6; 8 6.0 / 6.6, 8.2 / 7.5; 12 6.9 / 8.5, 9.7 / 9.7; direct 3 4.8 / 5.7, 5.8 /
-// 6.4; 8 6.1 / 6.9, 7.5 / 7.8; 12 7.0 / 8.5, 9.9 / 9.4.  PACK has one form (every load of a step under way, see joined_tiles); for it this
-// is where the cap begins.
+// these, see rolls()).
+//   binary32, one tensor          1400         1800         2300 tiles
+//     pipeline        P = 4    4.9 / 5.2    5.2 / 5.7    7.1 / 7.0
+//                         6    5.6 / 6.5    6.7 / 7.2    9.1 / 9.1
+//                         8    6.9 / 7.1    8.1 / 8.0   11.6 / 10.9
+//                        12    9.1 / 9.3   10.9 / 10.6  15.9 / 14.4
+//                        16   11.0 / 10.8  13.5 / 12.5  20.4 / 17.9
+//   binary32, 150 equal tensors   1350         1650         1950 tiles
+//     reduce          P = 4    2.3 / 2.2    2.4 / 2.3    2.6 / 2.6
+//                         6    2.9 / 3.3    3.0 / 3.4    3.2 / 3.4
+//                         8    4.0 / 4.0    4.0 / 4.1    4.3 / 4.1
+//                        12    4.6 / 5.4    5.0 / 5.6    5.5 / 5.8
+//                        16    6.3 / 6.5    6.9 / 6.6    8.4 / 6.9
+//                        32   10.7 / 11.8  11.4 / 12.2  12.5 / 12.5
+//     reduce_update   P = 4    3.2 / 4.0    3.6 / 4.3    3.9 / 4.4
+//                         8    4.6 / 5.4    5.0 / 5.6    5.7 / 5.8
+//                        12    5.6 / 7.0    6.2 / 7.3    7.1 / 7.5
+//                        16    7.4 / 8.0    8.6 / 8.3    9.7 / 8.4
+//                        32   11.7 / 13.2  12.7 / 13.7  13.6 / 14.2
+//   binary32, one tensor          1024         1792         2560 tiles
+//     direct          P = 4    3.2 / 4.3    4.0 / 4.9    5.2 / 5.5
+//                         8    3.9 / 5.4    5.2 / 6.2    6.6 / 6.9
+//                        12    4.9 / 6.8    6.5 / 7.9    8.2 / 8.7
+//                        16    5.3 / 7.5    7.6 / 8.7   10.1 / 9.9
+//                        32    8.2 / 12.9  11.6 / 14.5  16.3 / 16.1
+//   one tensor                    3072         4096 tiles
+//     binary32 pipeline P = 1, 2, 3        5.3 / 6.0, 6.0 / 6.3, 7.5 / 6.6      6.6 / 7.0, 8.2 / 8.0, 10.0 / 9.5
+//     binary32 update                      4.5 / 4.6                            5.6 / 5.4
+//     bfloat16 pipeline P = 2, 4, 8, 12    5.1 / 5.5, 6.5 / 6.6, 8.9 / 8.7, 11.3 / 10.8    6.9 / 6.9, 9.1 / 9.2, 13.2 / 12.8, 16.9 / 16.4
+//     bfloat16 reduce_update P = 3, 8, 12  4.6 / 5.8, 6.0 / 6.6, 6.9 / 8.5      5.8 / 6.6, 8.2 / 7.5, 9.7 / 9.7
+//     bfloat16 direct P = 3, 8, 12         4.8 / 5.7, 6.1 / 6.9, 7.0 / 8.5      5.8 / 6.4, 7.5 / 7.8, 9.9 / 9.4
+// PACK has one form (every load of a step under way, see joined_tiles); for it this is where the cap begins.
 inline int32_t default_burst_tiles(int kind, int32_t dtype, int32_t P) {
     if (kind == K_PACK) return 1024;
     if (dtype != MGWFBP_F32 || P < 4 || kind == K_UPDATE) return 3072;
     if (kind == K_DIRECT) return P == 16 ? 1792 : 2560;
-    if (kind == K_REDUCE) return P < 6 ? 1792 : 1280;
+    if (kind == K_REDUCE || kind == K_REDUCE_UPDATE) return P == 16 ? 1536 : 1792;
     return P == 16 ? 1280 : 1792;
 }
 
