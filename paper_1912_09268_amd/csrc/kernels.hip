@@ -863,10 +863,21 @@ template <int KIND, typename GradT, int PT, int FORM> constexpr int wanted_waves
     return FORM == 1 ? 8 : FORM == PAIRS ? 6 : 1;
 }
 
+// Most pieces of a tile that are taken one after the other, see MGWFBP_PIECES.  Paced steps of 16-bit gradients that store
+// nothing between the workers: the general path is ahead with 16 workers, and with 8 a reduce_update is left registers for 32
+// wavefronts per compute unit instead of 28.  us with pieces / without, 300 tensors of log-normal sizes, bfloat16: direct, 16
+// workers, 4700 tiles 15.5 / 14.4, reduce_update 11.8 / 11.5; a thousand around 1000 elements in groups of four 16.8 / 15.7; 8
+// workers, 8000 tiles 13.7 / 12.4, 4700 tiles 8.5 / 8.6.  Fewer workers gain from pieces (direct, 4 workers, 4700 tiles 7.3 / 8.2).
+template <int KIND, typename GradT, int PT, int FORM> constexpr int most_pieces() {
+    constexpr bool one = FORM != BURST && sizeof(GradT) == 2 && ((KIND == K_DIRECT && PT == 16) || (KIND == K_REDUCE_UPDATE && (PT == 8 || PT == 16)));
+    return one ? 1 : MGWFBP_PIECES;
+}
+
 template <int KIND, typename GradT, int PT, int FORM>
 __global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_waves<KIND, GradT, PT, FORM>())) mgwfbp_stream_kernel(const Args<GradT> A) {
     constexpr int SINGLE = FORM == PAIRS ? 1 : FORM;     // single tiles
     constexpr int JOIN = joined_tiles_of(KIND, FORM);
+    constexpr int MOST = most_pieces<KIND, GradT, PT, FORM>();
     __shared__ int s_loc[MAXSEG + 1];
     __shared__ int s_layer[MAXSEG];
     __shared__ int s_wave[BLOCK / 64];
@@ -927,7 +938,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_waves<KIND, GradT, PT, F
                     }
                     continue;
                 }
-                if (!full && (!needs_owner(KIND) || h.nseg <= MGWFBP_PIECES)) {
+                if (!full && (!needs_owner(KIND) || h.nseg <= MOST)) {
                     pieces.seg = seg_tables(A);
                     several_pieces<KIND, GradT, PT>(A, mrg, tile_base, pieces);
                     continue;

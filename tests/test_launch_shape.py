@@ -18,7 +18,7 @@ READELF = shutil.which("llvm-readelf") or "/opt/rocm/llvm/bin/llvm-readelf"
 KINDS = ["pack", "reduce", "update", "reduce_update", "pipeline", "direct"]
 DTYPES = ["f32", "bf16", "f16"]
 CU_LDS, LDS_GRAIN = 160 << 10, 1280
-Kernel = namedtuple("Kernel", "few kind half P form lds vgprs sgprs")
+Kernel = namedtuple("Kernel", "few kind half P form lds vgprs sgprs dtype")
 Shape = namedtuple("Shape", "tiles_per_wg units grid xcd_contiguous run_log2 may_be_few form wgs_per_cu")
 
 
@@ -65,7 +65,7 @@ def kernels(tmp_path_factory):
                 assert field("private_segment_fixed_size") == 0, "spills"
                 found.append(Kernel(m.group(1) == "few", int(m.group(2)), m.group(3) != "f", int(m.group(4)),
                                     int(m.group(5).replace("n", "-")), field("group_segment_fixed_size"), field("vgpr_count"),
-                                    field("sgpr_count")))
+                                    field("sgpr_count"), {"f": "f32", "t": "bf16"}.get(m.group(3), "f16")))
         at += 24
     assert len(found) > 100
     return found
@@ -320,3 +320,9 @@ def test_few_segments_kernels_of_sixteen_bit_gradients_keep_their_wave_slots(ker
     assert len(paced) == 2 * (1 + 3 * 5)
     for k in paced:
         assert wavefronts(k) >= least[KINDS[k.kind]].get(k.P, 32), k
+
+
+def test_general_path_where_pieces_cost_wavefronts(kernels):
+    """Paced 16-bit steps of reduce_update leave ragged tiles of several tensors to the general path with 8 and 16 workers."""
+    of = {(k.dtype, k.P): wavefronts(k) for k in kernels if KINDS[k.kind] == "reduce_update" and k.form == 1 and not k.few}
+    assert of["bf16", 8] == 32 and of["bf16", 16] == 28 and of["f16", 8] == 28
