@@ -290,21 +290,31 @@ inline bool few_form_pays(int kind, int32_t dtype, int32_t P, int32_t tiles, int
 
 // Kernels with rolling steps beside the single ones (see rolling_tile).
 constexpr bool may_roll(int kind, int form) { return TVECS == 1 && kind == K_PIPELINE && form == 1; }
+constexpr bool compiled(int32_t P) { return P == 2 || P == 4 || P == 8 || P == 16; }
+// Wavefronts per compute unit that the pipeline's single-tile kernels on 16-bit gradients have registers for.
+inline int32_t pipeline_wavefronts(int32_t P, bool few) {
+    if (P == 16) return 24;
+    if (few) return P == 8 ? 28 : 32;
+    return P == 2 ? 28 : compiled(P) ? 24 : 32;
+}
 // Launches of the pipeline in single tiles whose wavefronts, with one load each, have too little under way between them: binary32
 // up to 12 per compute unit, 16-bit gradients, whose loads are half as long, up to 16, and where a second round of them is
-// not full either.  us with one load at a time / rolling, over one tensor: binary32, 1900 tiles (8 per compute unit) P = 4 6.7 / 5.7, 6
-// 8.4 / 7.6, 8 9.7 / 7.9, 16 15.6 / 13.2; 2304 (9) 7.1 / 6.7, 9.4 / 8.9, 10.8 / 10.5, 18.0 / 17.7; 3072 (12) 8.5 / 8.4, 10.5 / 10.0, 12.5 / 12.8,
-// 21.0 / 21.3; 4096 (16) P = 6 13.2 / 13.2, 8 15.8 / 16.3, 16 26.3 / 27.8.  bfloat16, 3200 tiles (13) P = 2 6.3 / 5.5, 6 9.5 / 8.5, 8 10.5 /
-// 8.7, 16 17.0 / 13.4; 4096 (16) 6.9 / 6.5, 10.4 / 9.7, 11.8 / 10.6, 18.4 / 16.3; 6144 (24) 9.1 / 9.1, 13.9 / 14.3, 15.6 / 16.1, 24.3 / 26.1;
-// 6500 (26) P = 2 9.2 / 9.4, 4 11.6 / 12.1, 6 16.7 / 15.7, 8 18.9 / 16.6, 16 30.7 / 27.6; 9000 (36) 12.6 / 12.8, 16.2 / 16.0, 20.9 / 20.1, 23.2 /
-// 22.9, 37.5 / 37.0; 12,000 tiles over 600 tensors P = 8 30.4 / 31.7.  Where the worker count is not compiled the table form ends
-// earlier (12 tensors as views: binary32 2700 tiles P = 6 11.1 / 11.0, 12 16.4 / 16.5, 3071 12.2 / 12.7, 18.0 / 18.9; bfloat16 4095 tiles 10.9 /
-// 10.2, 16.0 / 15.0, 7500 18.1 / 18.8, 25.9 / 27.0).  The other side of 16 tiles to a CU, 16 workers: bfloat16, 4000 tiles of one tensor 18.4 /
-// 16.3, over 150 tensors 19.6 / 20.2.
+// nearly empty.  Time of rolling steps over that of single ones, one tensor (few-segments form) / 150 equal tensors / 12 as views /
+// 300 of log-normal sizes as views (table form):
+//   binary32     8 per CU  P = 4 0.84 / 0.84 / 0.84 / 0.94, 8 0.85 / 0.82 / 0.84 / 0.87, 12 0.91 / 0.90 / 0.90 / 0.91, 16 0.84 / 0.80 / 0.84 / 0.89
+//               10         P = 4 0.92 / 0.91 / 0.95 / 0.99, 8 0.98 / 0.90 / 0.98 / 1.00, 12 0.95 / 0.93 / 0.96 / 0.96, 16 1.00 / 0.94 / 1.00 / 1.01
+//               12         P = 4 0.99 / 0.93 / 0.98 / 1.05, 8 1.00 / 0.96 / 1.00 / 1.02, 12 0.97 / 0.95 / 0.97 / 0.98, 16 1.00 / 0.99 / 1.03 / 1.00
+//               13         P = 4 1.04 / 0.99 / 1.04 / 1.04, 8 1.05 / 1.01 / 1.05 / 1.04, 12 0.97 / 0.96 / 0.98 / 0.97, 16 1.05 / 1.05 / 1.08 / 1.04
+//   bfloat16    16         P = 2 0.93 / 0.93 / 0.95 / 1.04, 4 0.93 / 0.92 / 0.94 / 1.01, 8 0.91 / 0.89 / 0.93 / 1.01, 16 0.88 / 0.87 / 0.92 / 0.97
+//               26         P = 2 0.99 / 0.99 / 1.00 / 1.02, 4 1.05 / 0.89 / 0.91 / 0.95, 8 1.06 / 0.87 / 0.91 / 0.93, 16 0.90 / 0.85 / 0.90 / 0.93
+//               30         P = 2 0.98 / 0.94 / 0.96 / 0.99, 4 1.02 / 0.92 / 0.96 / 0.97, 8 0.94 / 0.89 / 0.94 / 0.96, 16 0.91 / 0.88 / 0.95 / 0.97
+//               34         P = 2 0.98 / 0.97 / 0.96 / 1.01, 4 0.97 / 0.97 / 1.00 / 1.01, 8 0.96 / 0.96 / 0.99 / 1.00, 16 0.96 / 0.96 / 0.99 / 1.00
+//               36         P = 2 0.99 / 0.98 / 0.99 / 1.03, 4 0.98 / 0.98 / 1.00 / 1.04, 8 1.01 / 0.96 / 1.00 / 1.01, 16 1.01 / 0.97 / 1.01 / 1.01
+// (at 34 and 36 one tensor takes the table form, too).  Where the worker count is not compiled single steps hold 32 wavefronts:
+// 12 workers at 26 / 30 0.99 / 1.01, 32 workers over 12 tensors at 30 1.11.
 inline bool rolls(int32_t dtype, int32_t P, bool few, int32_t per_cu) {
-    const bool well = few || P == 2 || P == 4 || P == 8 || P == 16;
-    if (dtype == MGWFBP_F32) return per_cu <= (well ? 12 : 10);
-    return per_cu <= 16 || (well && per_cu > 24 && per_cu <= 36);
+    if (dtype == MGWFBP_F32) return per_cu <= (few || P == 2 || P == 4 ? 12 : 10);
+    return per_cu <= 16 || (compiled(P) && per_cu > pipeline_wavefronts(P, few) && per_cu <= (P < 8 ? 36 : 34));
 }
 
 // What a caller has fixed (mgwfbp_ctx_set_*); the initial values are the library's defaults.

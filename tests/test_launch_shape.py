@@ -19,7 +19,7 @@ KINDS = ["pack", "reduce", "update", "reduce_update", "pipeline", "direct"]
 DTYPES = ["f32", "bf16", "f16"]
 CU_LDS, LDS_GRAIN = 160 << 10, 1280
 Kernel = namedtuple("Kernel", "few kind half P form lds vgprs sgprs dtype")
-Shape = namedtuple("Shape", "tiles_per_wg units grid xcd_contiguous run_log2 may_be_few form wgs_per_cu")
+Shape = namedtuple("Shape", "tiles_per_wg units grid xcd_contiguous run_log2 may_be_few form wgs_per_cu rolling")
 
 
 def build_driver(folder, *defines):
@@ -326,3 +326,35 @@ def test_general_path_where_pieces_cost_wavefronts(kernels):
     """Paced 16-bit steps of reduce_update leave ragged tiles of several tensors to the general path with 8 and 16 workers."""
     of = {(k.dtype, k.P): wavefronts(k) for k in kernels if KINDS[k.kind] == "reduce_update" and k.form == 1 and not k.few}
     assert of["bf16", 8] == 32 and of["bf16", 16] == 28 and of["f16", 8] == 28
+
+
+def per_cu(*counts):
+    return [int(256 * c) for c in counts]
+
+
+def test_pipeline_rolls_where_that_is_no_slower(ask, kernels):
+    """Both sides of every line: binary32 up to 12 tiles per compute unit, 10 in the table form where that is no gain; 16-bit
+    gradients up to 16, and up to 36, 34 of 8 and 16 workers, where the kernel cannot hold them all at once; never beside a caller's pacing,
+    nor in the burst form or in pairs, nor in another kind."""
+    def rolls(counts, segments, **c):
+        return [bool(s.rolling) for s in shapes(ask, [dict(tiles=t, segments=segments, burst_tiles=0) | c for t in per_cu(*counts)])]
+    for P in (1, 3, 4, 8, 12, 16, 32):
+        assert rolls((1, 10, 11, 12, 13, 30), 8, P=P) == [True] * 4 + [False] * 2, P
+        assert rolls((1, 10, 11, 12, 13, 30), 9, P=P) == [True] * 2 + [P == 4] * 2 + [False] * 2, P
+        for dtype in ("bf16", "f16"):
+            few, table = {4: 32, 8: 28, 16: 24}.get(P, 99), {4: 24, 8: 24, 16: 24}.get(P, 99)
+            for segments, held in ((8, few), (9, table)):
+                counts = range(1, 60)
+                assert rolls(counts, segments, P=P, dtype=dtype) == [n <= 16 or held < n <= (36 if P == 4 else 34) for n in counts], (P, segments)
+    assert rolls((28, 29, 36, 37), 9, P=2, dtype="bf16") == [False, True, True, False]
+    assert rolls((32, 33, 36, 37), 8, P=2, dtype="bf16") == [False, True, True, False]
+    for off in (dict(wg_per_cu=25), dict(wg_per_cu=-1), dict(step_vecs=1), dict(step_vecs=-1), dict(burst_tiles=1 << 20), dict(kind="direct"),
+                dict(kind="pack"), dict(dtype="bf16", tiles_per_wg=2)):
+        assert not any(rolls((4, 12), 9, **off)), off
+    # the wavefronts that the lines of 16-bit gradients rest on
+    single = [k for k in kernels if k.half and k.form == 1 and KINDS[k.kind] == "pipeline"]
+    for few, held in ((True, {2: 32, 4: 32, 8: 28, 16: 24}), (False, {2: 28, 4: 24, 8: 24, 16: 24, 0: 32})):
+        assert {k.P: wavefronts(k) for k in single if k.few == few and k.P in held} == held
+    # and the sizes at which the GPU tests run rolling steps and single ones
+    assert rolls((2500 / 256, 3000 / 256, 3100 / 256), 1) == [True, True, False] and rolls((2500 / 256, 3000 / 256), 10) == [True, False]
+    assert [rolls((4000 / 256, 4100 / 256, 6300 / 256, 34), n, dtype="bf16") for n in (1, 10)] == [[True, False, False, True], [True, False, True, True]]
