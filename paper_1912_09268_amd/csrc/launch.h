@@ -300,7 +300,8 @@ inline int32_t pipeline_wavefronts(int32_t P, bool few) {
 // Launches of the pipeline in single tiles whose wavefronts, with one load each, have too little under way between them: binary32
 // up to 12 per compute unit, 16-bit gradients, whose loads are half as long, up to 16, and where a second round of them is
 // nearly empty.  Time of rolling steps over that of single ones, one tensor (few-segments form) / 150 equal tensors / 12 as views /
-// 300 of log-normal sizes as views (table form):
+// 300 of log-normal sizes as views (table form); thousands of tensors of some hundred elements are at 11 per compute unit 0.96 with 8
+// workers and 0.93 with 16:
 //   binary32     8 per CU  P = 4 0.84 / 0.84 / 0.84 / 0.94, 8 0.85 / 0.82 / 0.84 / 0.87, 12 0.91 / 0.90 / 0.90 / 0.91, 16 0.84 / 0.80 / 0.84 / 0.89
 //               10         P = 4 0.92 / 0.91 / 0.95 / 0.99, 8 0.98 / 0.90 / 0.98 / 1.00, 12 0.95 / 0.93 / 0.96 / 0.96, 16 1.00 / 0.94 / 1.00 / 1.01
 //               12         P = 4 0.99 / 0.93 / 0.98 / 1.05, 8 1.00 / 0.96 / 1.00 / 1.02, 12 0.97 / 0.95 / 0.97 / 0.98, 16 1.00 / 0.99 / 1.03 / 1.00
@@ -310,11 +311,27 @@ inline int32_t pipeline_wavefronts(int32_t P, bool few) {
 //               30         P = 2 0.98 / 0.94 / 0.96 / 0.99, 4 1.02 / 0.92 / 0.96 / 0.97, 8 0.94 / 0.89 / 0.94 / 0.96, 16 0.91 / 0.88 / 0.95 / 0.97
 //               34         P = 2 0.98 / 0.97 / 0.96 / 1.01, 4 0.97 / 0.97 / 1.00 / 1.01, 8 0.96 / 0.96 / 0.99 / 1.00, 16 0.96 / 0.96 / 0.99 / 1.00
 //               36         P = 2 0.99 / 0.98 / 0.99 / 1.03, 4 0.98 / 0.98 / 1.00 / 1.04, 8 1.01 / 0.96 / 1.00 / 1.01, 16 1.01 / 0.97 / 1.01 / 1.01
-// (at 34 and 36 one tensor takes the table form, too).  Where the worker count is not compiled single steps hold 32 wavefronts:
-// 12 workers at 26 / 30 0.99 / 1.01, 32 workers over 12 tensors at 30 1.11.
+// (At 34 and 36 one tensor takes the table form, too; a little below 36, at 9000 tiles on 256 compute units, 8 workers gain 4 %, 16
+// 3 %.)  Where the worker count is not compiled single steps hold 32 wavefronts: 12 workers at 26 / 30 0.99 / 1.01, 32 over 12
+// tensors at 30 1.11.  At 33 to 36, with the cap of even_rounds() in both: 6 / 12 / 32 workers over five tensors 0.95 / 0.96 / 0.95, 150 0.95 /
+// 0.95 / 0.95, 12 as views 0.96 / 0.96 / 0.96, log-normal 0.96 / 0.95 / 0.96.
 inline bool rolls(int32_t dtype, int32_t P, bool few, int32_t per_cu) {
-    if (dtype == MGWFBP_F32) return per_cu <= (few || P == 2 || P == 4 ? 12 : 10);
-    return per_cu <= 16 || (compiled(P) && per_cu > pipeline_wavefronts(P, few) && per_cu <= (P < 8 ? 36 : 34));
+    if (dtype == MGWFBP_F32) return per_cu <= (P == 8 || P == 16 ? 11 : few || compiled(P) ? 12 : 10);
+    return per_cu <= 16 || (per_cu > pipeline_wavefronts(P, few) && per_cu <= 36);
+}
+
+// 16-bit gradients in single tiles run uncapped, but a launch that takes as many rounds of the chip with 24 wavefronts per
+// compute unit as with the 32 (or 28) there are registers for does not fill the last of these.  Time at the cap of 25 (24 of such a
+// kernel) over uncapped, bfloat16, tiles per compute unit in brackets: pipeline over 150 tensors, 6 / 12 / 32 workers (34) 0.99 / 0.96 / 0.94, (37)
+// 0.95 / 0.92 / 0.91, (39) 0.96 / 0.93 / 0.89, (45) 0.99 / 0.96 / 0.92, but (49) 1.01 / 0.99 / 0.97, (53) 1.08 / 1.08 / 1.08; over five, 12 workers (37) 0.93, (45) 0.95, (53)
+// 1.08; reduce_update over 150, 4 workers (34) 0.94, (37) 0.95, (45) 0.99, (53) 1.05, (67) 0.97, (71) 0.98, (80) 1.03; 16 workers, 28 wavefronts, (29)
+// 0.98, (64) 0.97, (74) 0.98, (80) 1.05; direct over five, 8 / 16 workers (34) 0.94 / 0.93, (37) 0.97 / 0.96, (45) 0.98 / 0.97, (53) 1.08 / 1.11.  Kernels with registers
+// for 24 do not mind; the pipeline's of 2 to 16 workers, in part such, would lose 1-5 % at 34.
+inline bool even_rounds(int kind, int32_t dtype, int32_t P, bool few, int form, int32_t per_cu) {
+    if (dtype == MGWFBP_F32 || form != 1) return false;
+    if (kind != K_REDUCE_UPDATE && kind != K_DIRECT && !(kind == K_PIPELINE && !compiled(P))) return false;
+    const int32_t held = kind == K_REDUCE_UPDATE && !few && (P == 16 || (P == 8 && dtype == MGWFBP_F16)) ? 28 : 32;
+    return per_cu > held && (per_cu + held - 1) / held == (per_cu + 23) / 24;
 }
 
 // What a caller has fixed (mgwfbp_ctx_set_*); the initial values are the library's defaults.
@@ -410,6 +427,7 @@ inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, 
         s.wgs_per_cu = burst ? -1 : default_workgroups_per_cu(w.kind, w.dtype, w.P, length, w.ragged, w.reduced, s.form);
         if (s.form == PAIRS ? length < 2 * SHORT_LAUNCH_TILES : w.dtype == MGWFBP_F32 && w.kind != K_PACK && few_rounds(length, w.P))
             s.wgs_per_cu = short_launch_cap(s.wgs_per_cu, w.kind, w.P, s.may_be_few && s.form != PAIRS, per_cu);
+        if (s.wgs_per_cu <= 0 && w.ragged <= 0.25 && even_rounds(w.kind, w.dtype, w.P, s.may_be_few, s.form, per_cu)) s.wgs_per_cu = 25;
     }
     s.rolling = may_roll(w.kind, s.form) && set.step_vecs == 0 && set.wg_per_cu == 0 && rolls(w.dtype, w.P, s.may_be_few, per_cu);
     s.run_log2 = one_turn ? run_log2_of(w.kind, w.dtype, w.P, w.off_lines) : int8_t{0};

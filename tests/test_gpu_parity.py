@@ -566,7 +566,7 @@ def test_ragged_tiles_of_sixteen_bit_gradients_of_many_workers(P, dtype):
 
 @pytest.mark.parametrize("P,dtype", [(1, "f32"), (2, "bf16"), (3, "f32"), (6, "f16"), (8, "f32"), (8, "bf16"), (16, "f32"), (17, "f16")])
 def test_rolling_steps_of_the_pipeline(P, dtype):
-    """Pipeline launches of up to 10 or 12 tiles per compute unit (binary32), up to 16 and of 25 or 29 to 34 or 36 (16-bit gradients) load
+    """Pipeline launches of up to 10 to 12 tiles per compute unit (binary32), up to 16 and of 25 to 33 up to 36 (16-bit gradients) load
     the next worker's share before they store this one's: launches on both sides of these lines, over one tensor and over
     ten, with and without the reduced arena, and with a resident share, whose tiles go without.  (On 256 compute units;
     test_pipeline_rolls_where_that_is_no_slower has which of them roll.)"""

@@ -333,28 +333,51 @@ def per_cu(*counts):
 
 
 def test_pipeline_rolls_where_that_is_no_slower(ask, kernels):
-    """Both sides of every line: binary32 up to 12 tiles per compute unit, 10 in the table form where that is no gain; 16-bit
-    gradients up to 16, and up to 36, 34 of 8 and 16 workers, where the kernel cannot hold them all at once; never beside a caller's pacing,
-    nor in the burst form or in pairs, nor in another kind."""
+    """Both sides of every line: binary32 up to 12 tiles per compute unit, 11 with 8 and 16 workers, 10 over many tensors where
+    the worker count is not compiled; 16-bit gradients up to 16, and up to 36 where the kernel cannot hold them all at once;
+    never beside a caller's pacing, nor in the burst form or in pairs, nor in another kind."""
     def rolls(counts, segments, **c):
         return [bool(s.rolling) for s in shapes(ask, [dict(tiles=t, segments=segments, burst_tiles=0) | c for t in per_cu(*counts)])]
-    for P in (1, 3, 4, 8, 12, 16, 32):
-        assert rolls((1, 10, 11, 12, 13, 30), 8, P=P) == [True] * 4 + [False] * 2, P
-        assert rolls((1, 10, 11, 12, 13, 30), 9, P=P) == [True] * 2 + [P == 4] * 2 + [False] * 2, P
-        for dtype in ("bf16", "f16"):
-            few, table = {4: 32, 8: 28, 16: 24}.get(P, 99), {4: 24, 8: 24, 16: 24}.get(P, 99)
-            for segments, held in ((8, few), (9, table)):
+    for P in (1, 2, 3, 4, 8, 12, 16, 32):
+        last = {8: (11, 11), 16: (11, 11), 2: (12, 12), 4: (12, 12)}.get(P, (12, 10))
+        held = {2: (32, 28), 4: (32, 24), 8: (28, 24), 16: (24, 24)}.get(P, (32, 32))
+        for segments, end, at_once in zip((8, 9), last, held):
+            assert rolls(range(1, 31), segments, P=P) == [n <= end for n in range(1, 31)], (P, segments)
+            for dtype in ("bf16", "f16"):
                 counts = range(1, 60)
-                assert rolls(counts, segments, P=P, dtype=dtype) == [n <= 16 or held < n <= (36 if P == 4 else 34) for n in counts], (P, segments)
-    assert rolls((28, 29, 36, 37), 9, P=2, dtype="bf16") == [False, True, True, False]
-    assert rolls((32, 33, 36, 37), 8, P=2, dtype="bf16") == [False, True, True, False]
+                assert rolls(counts, segments, P=P, dtype=dtype) == [n <= 16 or at_once < n <= 36 for n in counts], (P, segments)
     for off in (dict(wg_per_cu=25), dict(wg_per_cu=-1), dict(step_vecs=1), dict(step_vecs=-1), dict(burst_tiles=1 << 20), dict(kind="direct"),
                 dict(kind="pack"), dict(dtype="bf16", tiles_per_wg=2)):
         assert not any(rolls((4, 12), 9, **off)), off
     # the wavefronts that the lines of 16-bit gradients rest on
     single = [k for k in kernels if k.half and k.form == 1 and KINDS[k.kind] == "pipeline"]
-    for few, held in ((True, {2: 32, 4: 32, 8: 28, 16: 24}), (False, {2: 28, 4: 24, 8: 24, 16: 24, 0: 32})):
+    for few, held in ((True, {2: 32, 4: 32, 8: 28, 16: 24, 0: 32}), (False, {2: 28, 4: 24, 8: 24, 16: 24, 0: 32})):
         assert {k.P: wavefronts(k) for k in single if k.few == few and k.P in held} == held
     # and the sizes at which the GPU tests run rolling steps and single ones
     assert rolls((2500 / 256, 3000 / 256, 3100 / 256), 1) == [True, True, False] and rolls((2500 / 256, 3000 / 256), 10) == [True, False]
     assert [rolls((4000 / 256, 4100 / 256, 6300 / 256, 34), n, dtype="bf16") for n in (1, 10)] == [[True, False, False, True], [True, False, True, True]]
+
+
+def test_sixteen_bit_launches_of_a_few_rounds_fill_them(ask, kernels):
+    """Uncapped 16-bit launches in single tiles are held to 24 wavefronts per compute unit where that takes no more rounds than
+    the 32 or 28 their kernel has registers for, and only there."""
+    counts = list(range(13, 128))
+
+    def capped(**c):
+        got = shapes(ask, [dict(dtype="bf16", tiles=t) | c for t in per_cu(*counts)])
+        assert {s.wgs_per_cu for s in got} <= {25, -1} and {s.form for s in got} <= {SINGLE}
+        return [n for n, s in zip(counts, got) if s.wgs_per_cu == 25]
+    at_32, at_28 = [*range(33, 49), *range(65, 73)], [*range(29, 49), *range(57, 73), *range(85, 97), *range(113, 121)]
+    assert capped(kind="direct", segments=9, ragged=0.3) == []                     # ragged launches want every slot
+    for segments in (5, 9):
+        for P in (1, 2, 3, 4, 8, 12, 16, 32):
+            assert capped(kind="direct", P=P, segments=segments) == at_32
+            held = at_28 if P == 16 and segments == 9 else at_32
+            assert capped(kind="reduce_update", P=P, segments=segments) == held, P
+            if P not in (2, 4, 8, 16):
+                assert capped(P=P, segments=segments, ragged=0.03) == at_32
+            else:
+                assert capped(P=P, segments=segments, ragged=0.03) == []
+    assert capped(kind="reduce_update", P=8, dtype="f16") == at_28 and capped(kind="update") == [] and capped(kind="direct", wg_per_cu=-1) == []
+    slots = {(KINDS[k.kind], k.few, k.P): wavefronts(k) for k in kernels if k.half and k.form == 1}
+    assert all(slots["reduce_update", True, P] == 32 for P in (0, 2, 4, 8, 16)) and slots["pipeline", False, 0] == 32
