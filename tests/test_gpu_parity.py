@@ -571,7 +571,7 @@ def test_rolling_steps_of_the_pipeline(P, dtype):
     ten, with and without the reduced arena, and with a resident share, whose tiles go without.  (On 256 compute units;
     test_pipeline_rolls_where_that_is_no_slower has which of them roll.)"""
     rng = np.random.default_rng(17)
-    for tiles in (2500, 3000, 3100) if dtype == "f32" else (4000, 4100, 6300, 8704):
+    for tiles in (2500, 2816, 3000, 3100) if dtype == "f32" else (4000, 4100, 6300, 8704):
         for sizes in ([tiles * 256 - 5], [256 * (tiles // 10) - 3 * (i % 2) for i in range(10)]):
             p = W.Profile("rolling", np.asarray(sizes, np.uint64), rng.uniform(1e-6, 1e-5, len(sizes)), 1e-4, 1e-9, P, dtype, 1.0)
             merged = [0] + [1] * (len(sizes) - 1)

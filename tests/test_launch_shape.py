@@ -354,7 +354,8 @@ def test_pipeline_rolls_where_that_is_no_slower(ask, kernels):
     for few, held in ((True, {2: 32, 4: 32, 8: 28, 16: 24, 0: 32}), (False, {2: 28, 4: 24, 8: 24, 16: 24, 0: 32})):
         assert {k.P: wavefronts(k) for k in single if k.few == few and k.P in held} == held
     # and the sizes at which the GPU tests run rolling steps and single ones
-    assert rolls((2500 / 256, 3000 / 256, 3100 / 256), 1) == [True, True, False] and rolls((2500 / 256, 3000 / 256), 10) == [True, False]
+    assert rolls((2500 / 256, 11, 3000 / 256, 3100 / 256), 1) == rolls((2500 / 256, 11, 3000 / 256, 3100 / 256), 10) == [True, True, False, False]
+    assert rolls((2500 / 256, 11, 3000 / 256, 3100 / 256), 1, P=3) == [True, True, True, False] and rolls((2500 / 256, 11), 10, P=3) == [True, False]
     assert [rolls((4000 / 256, 4100 / 256, 6300 / 256, 34), n, dtype="bf16") for n in (1, 10)] == [[True, False, False, True], [True, False, True, True]]
 
 
