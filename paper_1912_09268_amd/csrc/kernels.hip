@@ -160,7 +160,7 @@ __device__ __forceinline__ float widen(_Float16 x) { return static_cast<float>(x
 // argument), from 136 bytes on 3.3 us (the runtime writes the block into device memory and reads back from it before it rings
 // the doorbell), and a kernel that asks for gridDim makes the runtime append 256 more.  So everything that can be derived from something else is, and the grid
 // size that the persistent form needs comes in as `turn`.
-constexpr int XCD_CONTIGUOUS = 1, ROLLING = 2;
+constexpr int XCD_CONTIGUOUS = 1, ROLLING = 2, IN_PIECES = 4;
 template <typename GradT> struct CallArgs {
     const GradT* const* grad_ptrs;   // [P*L]
     GradT* const* merge_bufs;        // [P]
@@ -171,7 +171,7 @@ template <typename GradT> struct CallArgs {
     int32_t L, P;
     int32_t tile_first, tile_count;
     int16_t tiles_per_wg;            // consecutive tiles one workgroup handles per turn, >= 1
-    int8_t flags;                    // XCD_CONTIGUOUS, ROLLING
+    int8_t flags;                    // XCD_CONTIGUOUS, ROLLING, IN_PIECES
     int8_t run_log2;                 // a die's turn is 2^run_log2 consecutive units, see unit_of()
 };
 template <typename GradT> struct Args : CallArgs<GradT> {      // table form: what a tile holds is in the tables
@@ -867,7 +867,9 @@ template <int KIND, typename GradT, int PT, int FORM> constexpr int wanted_waves
 // nothing between the workers: the general path is ahead with 16 workers, and with 8 a reduce_update is left registers for 32
 // wavefronts per compute unit instead of 28.  us with pieces / without, 300 tensors of log-normal sizes, bfloat16: direct, 16
 // workers, 4700 tiles 15.5 / 14.4, reduce_update 11.8 / 11.5; a thousand around 1000 elements in groups of four 16.8 / 15.7; 8
-// workers, 8000 tiles 13.7 / 12.4, 4700 tiles 8.5 / 8.6.  Fewer workers gain from pieces (direct, 4 workers, 4700 tiles 7.3 / 8.2).
+// workers, 8000 tiles 13.7 / 12.4, 4700 tiles 8.5 / 8.6.  Fewer workers gain from pieces (direct, 4 workers, 4700 tiles 7.3 / 8.2), and so does
+// a direct step of 16 where most tiles are ragged, which the launch says (thousands of tensors around 100 elements in groups of
+// four, 9700 / 17,200 / 37,300 tiles 33.9 / 35.6, 54.5 / 58.4, 106.6 / 116.3; around 230 and 400 elements level).
 template <int KIND, typename GradT, int PT, int FORM> constexpr int most_pieces() {
     constexpr bool one = FORM != BURST && sizeof(GradT) == 2 && ((KIND == K_DIRECT && PT == 16) || (KIND == K_REDUCE_UPDATE && (PT == 8 || PT == 16)));
     return one ? 1 : MGWFBP_PIECES;
@@ -938,7 +940,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_waves<KIND, GradT, PT, F
                     }
                     continue;
                 }
-                if (!full && (!needs_owner(KIND) || h.nseg <= MOST)) {
+                if (!full && (!needs_owner(KIND) || h.nseg <= (KIND == K_DIRECT && MOST == 1 && (A.flags & IN_PIECES) ? MGWFBP_PIECES : MOST))) {
                     pieces.seg = seg_tables(A);
                     several_pieces<KIND, GradT, PT>(A, mrg, tile_base, pieces);
                     continue;
@@ -1415,7 +1417,7 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
         const CallArgs<GradT> call{reinterpret_cast<const GradT* const*>(grad_ptrs), reinterpret_cast<GradT* const*>(merge_bufs),
                                    reduced, w_ptrs, v_ptrs, lr, mu, inv_p, c->host.L, c->P, sp.t0, count,
                                    static_cast<int16_t>(s.tiles_per_wg),
-                                   static_cast<int8_t>((s.xcd_contiguous ? XCD_CONTIGUOUS : 0) | (s.rolling ? ROLLING : 0)), s.run_log2};
+                                   static_cast<int8_t>((s.xcd_contiguous ? XCD_CONTIGUOUS : 0) | (s.rolling ? ROLLING : 0) | (s.in_pieces ? IN_PIECES : 0)), s.run_log2};
         return launch<KIND, GradT>(c, sp, tiles, call, stream, s);
     };
     if (c->dtype == MGWFBP_F32) return go(float{});

@@ -379,6 +379,7 @@ struct LaunchShape {
     int form;                         // BURST, PAIRS or the vectors per lane of a paced step
     int32_t wgs_per_cu;               // workgroups that may share a compute unit; <= 0: no cap
     bool rolling;                     // two loads under way in a step (see rolls())
+    bool in_pieces;                   // ragged tiles piece by piece also where the kernel would rather not (see most_pieces())
 };
 
 inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, int n_cu) {
@@ -430,6 +431,7 @@ inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, 
         if (s.wgs_per_cu <= 0 && w.ragged <= 0.25 && even_rounds(w.kind, w.dtype, w.P, s.may_be_few, s.form, per_cu)) s.wgs_per_cu = 25;
     }
     s.rolling = may_roll(w.kind, s.form) && set.step_vecs == 0 && set.wg_per_cu == 0 && rolls(w.dtype, w.P, s.may_be_few, per_cu);
+    s.in_pieces = w.ragged > 0.5;
     s.run_log2 = one_turn ? run_log2_of(w.kind, w.dtype, w.P, w.off_lines) : int8_t{0};
     return s;
 }

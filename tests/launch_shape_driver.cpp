@@ -28,8 +28,8 @@ int main() {
             w.reduced = reduced != 0;
             set.resident_bytes = static_cast<uint64_t>(resident_bytes);
             const LaunchShape s = launch_shape(set, w, n_cu);
-            std::printf("%d %d %d %d %d %d %d %d %d\n", s.tiles_per_wg, s.units, s.grid, s.xcd_contiguous, s.run_log2, s.may_be_few,
-                        s.form, s.wgs_per_cu, s.rolling);
+            std::printf("%d %d %d %d %d %d %d %d %d %d\n", s.tiles_per_wg, s.units, s.grid, s.xcd_contiguous, s.run_log2, s.may_be_few,
+                        s.form, s.wgs_per_cu, s.rolling, s.in_pieces);
         } else if (!std::strcmp(what, "shares")) {    // shares L {n merged}... g0 g1: of the launch over groups [g0, g1)
             int L, g0, g1;
             if (std::scanf("%d", &L) != 1) return 1;

@@ -549,16 +549,18 @@ def test_ragged_tiles_piece_by_piece(P, dtype):
 @pytest.mark.parametrize("P,dtype", [(8, "f16"), (16, "bf16"), (16, "f16")])
 def test_ragged_tiles_of_sixteen_bit_gradients_of_many_workers(P, dtype):
     """In paced steps that store nothing between the workers, tiles of several tensors take the general path in launches over
-    the whole model, and go in groups of eight workers in launches over up to eight tensors."""
+    the whole model (a direct step's not where most tiles are ragged), and go in groups of eight workers in launches over
+    up to eight tensors."""
     groups = [[1000, 1024], [1001, 1023], [1002, 3, 400], [65, 2, 66, 1, 67], [255, 255, 255], [21] * 8, [30] * 9, [3, 253, 3], [257], [3],
               [300, 5, 207, 1, 3, 252]]
-    arrival = [n for g in groups for n in g]
-    merged = [m for g in groups for m in [1] * (len(g) - 1) + [0]]
     rng = np.random.default_rng(18)
-    p = W.Profile("many", np.asarray(arrival[::-1], np.uint64), rng.uniform(1e-6, 1e-5, len(arrival)), 1e-4, 1e-9, P, dtype, 1.0)
-    for mode in ("direct", "reduce_update", "direct_per_group_with_reduced"):
-        check_case(p, merged[::-1], mode, misalign=3, steps=2, small_launch=0, label="ragged, paced")
-        check_case(p, merged[::-1], mode, steps=2, small_launch=0, launch=(0, False, 3), label="ragged, paced, three tiles per workgroup")
+    for more in ([], [[256 * 200]]):
+        arrival = [n for g in groups + more for n in g]
+        merged = [m for g in groups + more for m in [1] * (len(g) - 1) + [0]]
+        p = W.Profile("many", np.asarray(arrival[::-1], np.uint64), rng.uniform(1e-6, 1e-5, len(arrival)), 1e-4, 1e-9, P, dtype, 1.0)
+        for mode in ("direct", "reduce_update", "direct_per_group_with_reduced"):
+            check_case(p, merged[::-1], mode, misalign=3, steps=2, small_launch=0, label="ragged, paced")
+            check_case(p, merged[::-1], mode, steps=2, small_launch=0, launch=(0, False, 3), label="ragged, paced, three tiles per workgroup")
     for g in groups:
         p = W.Profile("one group", np.asarray(g[::-1], np.uint64), rng.uniform(1e-6, 1e-5, len(g)), 1e-4, 1e-9, P, dtype, 1.0)
         check_case(p, [0] + [1] * (len(g) - 1), "reduce_update", misalign=1, steps=2, small_launch=0, label="one group, paced")

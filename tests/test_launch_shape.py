@@ -19,7 +19,7 @@ KINDS = ["pack", "reduce", "update", "reduce_update", "pipeline", "direct"]
 DTYPES = ["f32", "bf16", "f16"]
 CU_LDS, LDS_GRAIN = 160 << 10, 1280
 Kernel = namedtuple("Kernel", "few kind half P form lds vgprs sgprs dtype")
-Shape = namedtuple("Shape", "tiles_per_wg units grid xcd_contiguous run_log2 may_be_few form wgs_per_cu rolling")
+Shape = namedtuple("Shape", "tiles_per_wg units grid xcd_contiguous run_log2 may_be_few form wgs_per_cu rolling in_pieces")
 
 
 def build_driver(folder, *defines):
@@ -382,3 +382,7 @@ def test_sixteen_bit_launches_of_a_few_rounds_fill_them(ask, kernels):
     assert capped(kind="reduce_update", P=8, dtype="f16") == at_28 and capped(kind="update") == [] and capped(kind="direct", wg_per_cu=-1) == []
     slots = {(KINDS[k.kind], k.few, k.P): wavefronts(k) for k in kernels if k.half and k.form == 1}
     assert all(slots["reduce_update", True, P] == 32 for P in (0, 2, 4, 8, 16)) and slots["pipeline", False, 0] == 32
+
+
+def test_launches_of_mostly_ragged_tiles_go_in_pieces(ask):
+    assert [bool(s.in_pieces) for s in shapes(ask, [dict(kind="direct", dtype="bf16", P=16, ragged=r) for r in (0.0, 0.5, 0.51, 1.0)])] == [False, False, True, True]
