@@ -155,13 +155,14 @@ constexpr int32_t LONG_LAUNCH_TILES = 262144;       // 67 M elements
 //     bfloat16 pipeline P = 2, 4, 8, 12    5.1 / 5.5, 6.5 / 6.6, 8.9 / 8.7, 11.3 / 10.8    6.9 / 6.9, 9.1 / 9.2, 13.2 / 12.8, 16.9 / 16.4
 //     bfloat16 reduce_update P = 3, 8, 12  4.6 / 5.8, 6.0 / 6.6, 6.9 / 8.5      5.8 / 6.6, 8.2 / 7.5, 9.7 / 9.7
 //     bfloat16 direct P = 3, 8, 12         4.8 / 5.7, 6.1 / 6.9, 7.0 / 8.5      5.8 / 6.4, 7.5 / 7.8, 9.9 / 9.4
+// Where reduce of 8 and 16 workers is level here, other runs have the paced form 3 % ahead (8 workers, 1600 tiles 4.5 / 4.3).
 // PACK has one form (every load of a step under way, see joined_tiles); for it this is where the cap begins.
 inline int32_t default_burst_tiles(int kind, int32_t dtype, int32_t P) {
     if (kind == K_PACK) return 1024;
     if (dtype != MGWFBP_F32 || P < 4 || kind == K_UPDATE) return 3072;
     if (kind == K_DIRECT) return P == 16 ? 1792 : 2560;
-    if (kind == K_REDUCE || kind == K_REDUCE_UPDATE) return P == 16 ? 1536 : 1792;
-    return P == 16 ? 1280 : 1792;
+    if (kind == K_REDUCE) return P == 8 || P == 16 ? 1280 : 1792;
+    return P != 16 ? 1792 : kind == K_REDUCE_UPDATE ? 1536 : 1280;
 }
 
 // Whether a workgroup of the pipeline takes two tiles in one step (see joined_tiles).  GB/s at 16-bit gradients,

@@ -279,7 +279,7 @@ def test_binary32_pipelines_without_the_reduced_arena_take_a_wider_window(ask):
 def test_burst_form_ends_where_pacing_is_ahead(ask):
     """The longest launch in the burst form by kind, gradient width and worker count."""
     for kind, dtype, P, tiles in (("pipeline", "f32", 3, 3072), ("pipeline", "f32", 8, 1792), ("pipeline", "f32", 16, 1280), ("pipeline", "bf16", 16, 3072),
-                                  ("reduce", "f32", 5, 1792), ("reduce", "f32", 6, 1792), ("reduce", "f32", 32, 1792), ("reduce", "f32", 16, 1536),
+                                  ("reduce", "f32", 5, 1792), ("reduce", "f32", 6, 1792), ("reduce", "f32", 32, 1792), ("reduce", "f32", 8, 1280), ("reduce", "f32", 16, 1280),
                                   ("reduce_update", "f32", 8, 1792), ("reduce_update", "f32", 16, 1536), ("direct", "f32", 4, 2560), ("direct", "f32", 16, 1792), ("direct", "f16", 8, 3072),
                                   ("update", "f32", 8, 3072)):
         assert [s.form for s in shapes(ask, [dict(kind=kind, dtype=dtype, P=P, tiles=t) for t in (1, tiles, tiles + 1)])] == [BURST, BURST, SINGLE], (kind, P)
