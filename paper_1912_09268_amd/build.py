@@ -33,7 +33,7 @@ def library_path() -> str:
 def build_library(out: Optional[str] = None, defines: Optional[Dict[str, object]] = None,
                   verbose: bool = False) -> str:
     """Always recompiles.  `defines` lets a tuning run override MGWFBP_TILE_VECS, MGWFBP_BLOCK,
-    MGWFBP_PACK_TILES, MGWFBP_NT, MGWFBP_READ_GROUP and MGWFBP_GENERAL_GROUP."""
+    MGWFBP_PACK_TILES, MGWFBP_NT, MGWFBP_READ_GROUP, MGWFBP_TOGETHER, MGWFBP_GENERAL_GROUP and MGWFBP_PIECES."""
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     out = out or library_path()
     cmd = [hipcc] + HIPCC_FLAGS + ["-I", os.path.join(ROOT, "include"), "-I", CSRC]

@@ -12,10 +12,10 @@
 //   PIPELINE        per-layer gradients (P), w, v  merge arenas (P), [reduced], w, v
 //   DIRECT          per-layer gradients (P), w, v  [reduced], w, v
 //
-// The arena side of every access is 16-byte aligned (tiles start on multiples of the tile size and
-// lanes step in 4-element vectors).  The per-layer side starts wherever the tensor starts, so it is
-// accessed through vector types that only promise element alignment; gfx950 executes those as the
-// same 16-byte (8-byte for 16-bit gradients) memory instructions.
+// The arena side of an access is 16-byte aligned in full tiles (they start on multiples of the tile size and
+// lanes step in 4-element vectors) and starts on any element in ragged ones.  The per-layer side starts wherever the
+// tensor starts.  So both are accessed through vector types that only promise element alignment; gfx950 executes those as
+// the same 16-byte (8-byte for 16-bit gradients) memory instructions.
 //
 // A tile that lies entirely inside one tensor takes the fast path: tensor index and source offset
 // come from the tile header, the pointer table is read once with wave-uniform addresses, and the tile is
@@ -175,7 +175,7 @@ template <typename GradT> struct CallArgs {
     int8_t run_log2;                 // a die's turn is 2^run_log2 consecutive units, see unit_of()
 };
 template <typename GradT> struct Args : CallArgs<GradT> {      // table form: what a tile holds is in the tables
-    const TileHdr* tiles;            // the segment tables lie right below, see seg_off() and its neighbours
+    const TileHdr* tiles;            // the segment tables lie right below, see seg_tables()
     int32_t n_seg;                   // segments of the model
     int32_t n_units;                 // ceil(tile_count / tiles_per_wg)
     int32_t turn;                    // units from one of a workgroup's turns to its next: the workgroups of a walk
@@ -279,16 +279,17 @@ template <typename T> struct WorkerPtrs<T, 0> {
 #ifndef MGWFBP_READ_GROUP
 #define MGWFBP_READ_GROUP 2
 #endif
+// Workers whose loads go out together in the burst form and in ragged tiles where the worker count is not compiled (where it
+// is: all of them).  us with four / eight, 12 tensors of one group, 300 and 1100 tiles, binary32: pipeline 5 workers 4.8 / 4.3, 7.4 / 6.4; 12
+// workers 7.7 / 6.6, 10.9 / 9.6; 32 workers 15.8 / 11.0, 23.7 / 19.2; direct 32 workers 14.1 / 9.6, 17.2 / 12.6.  The longest launches of the burst
+// form would rather have four: 150 equal tensors, binary32, 1650 tiles, 32 workers reduce 10.9 / 11.4, reduce_update 12.0 / 12.7; bfloat16
+// pipeline, 12 workers, 3000 tiles 10.7 / 11.3; three of three at once binary32, 3000 tiles 6.5 / 7.0.
 #ifndef MGWFBP_TOGETHER
-#define MGWFBP_TOGETHER 8         // workers whose loads go out together in the burst form and in ragged tiles of one tensor
-#endif                            // where the worker count is not compiled (where it is: all of them)
-#ifndef MGWFBP_GENERAL_GROUP
-#define MGWFBP_GENERAL_GROUP 64   // workers whose loads the general path issues together (64: all of them)
+#define MGWFBP_TOGETHER 8
 #endif
-
-// The same where every lane has pointers of its own.  us with four / eight at a time, 12 tensors of one group, 300 and 1100 tiles:
-// binary32 pipeline 5 workers 4.8 / 4.3, 7.4 / 6.4; 12 workers 7.7 / 6.6, 10.9 / 9.6; 32 workers 15.8 / 11.0, 23.7 / 19.2; direct 32 workers 14.1 / 9.6, 17.2 / 12.6.
-constexpr int SOME = 8;
+#ifndef MGWFBP_GENERAL_GROUP
+#define MGWFBP_GENERAL_GROUP 64   // workers whose loads ragged tiles issue together where the count is compiled (64: all of them)
+#endif
 
 // keeps the compiler from moving the next group's loads above this group's arithmetic
 __device__ __forceinline__ void pace() { __builtin_amdgcn_sched_barrier(0); }
@@ -342,7 +343,7 @@ __device__ __forceinline__ void paced_step(const CallArgs<GradT>& A, const Worke
     typedef typename VecOf<float, W>::type FV;
     constexpr int C = Lanes<GV>::n;
     FV acc[N];
-    // the general path wants everything under way at once: its v and w loads go out before the gradients'
+    // the burst form and ragged tiles want everything under way at once: their v and w loads go out before the gradients'
     constexpr int NE = (updates(KIND) && TOGETHER > 0) ? N : 1;
     FV v_early[NE], w_early[NE];
     if constexpr (updates(KIND) && TOGETHER > 0) {
@@ -449,7 +450,7 @@ __device__ __forceinline__ void do_one(const CallArgs<GradT>& A, const WorkerPtr
         wp = ro(A.w_ptrs)[layer];
         vp = ro(A.v_ptrs)[layer];
     }
-    paced_step<KIND, GradT, PT, W, 1, NT_WV, SOME>(A, src, mrg, wp, vp, soff, apos, 0);
+    paced_step<KIND, GradT, PT, W, 1, NT_WV, MGWFBP_TOGETHER>(A, src, mrg, wp, vp, soff, apos, 0);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -471,14 +472,15 @@ __device__ __forceinline__ void fast_chunk(const CallArgs<GradT>& A, const Worke
     constexpr int STEP = BLOCK * VEC;
     int lane_elem = static_cast<int>(threadIdx.x) * VEC;
     // Left alone, the compiler sets up every arena's address plus this in front of the walk, two registers per worker: 138 for
-    // binary32 reductions of 16 workers instead of 91 (4000 tiles over 150 tensors 17.0 us, so 12.5).  A direct step has no arenas, and is
+    // binary32 reductions of 16 workers instead of 70 (4000 tiles over 150 tensors 17.0 us, so 12.5).  A direct step has no arenas, and is
     // faster as the compiler has it (bfloat16, 16 workers, 12,000 tiles 24.3 us, so 25.3).
     if constexpr (KIND != K_DIRECT) here_only_per_lane(lane_elem);
     const int64_t soff = tensor_off + lane_elem;    // this lane's first element: in its tensor
     const int64_t apos = tile_base + lane_elem;     //                            in the arena
     if constexpr (STEPV == 0) {
         // burst: every load of the tile under way at once.  The form for a launch too small to fill the chip,
-        // where the time is the tile's own latency and not the memory system's throughput.
+        // where the time is the tile's own latency and not the memory system's throughput.  (Of builds that do not take
+        // tiles in pieces: the others take a full tile in the burst form as one piece.)
         for (int u = 0; u < nvec; u += TVECS)
             paced_step<KIND, GradT, PT, VEC, TVECS, WVNT, MGWFBP_TOGETHER>(A, src, mrg, wp, vp,
                                                                 soff + static_cast<int64_t>(u) * STEP,

@@ -53,7 +53,7 @@ constexpr bool HAVE_PIECES = TVECS == 1 && BLOCK == 64;
 // Kinds whose wavefronts have too little under way with one tile can take joined steps: PACK, a plain copy, always, and
 // the pipeline on 16-bit gradients, where a worker's share of a tile is 512 bytes, in kernels of their own: beside the
 // joined step, whose sums change hands through LDS, the single-tile kernel would need the joined one's 96 registers instead of 59 (16
-// workers; 63 instead of 43 with 8) and as uncapped launches hold 20 instead of 32 wavefronts per compute unit (16
+// workers; 63 instead of 43 with 8) and as uncapped launches hold 20 instead of 24 wavefronts per compute unit (16
 // workers, 6000 tiles: 30.0 us against 23.4, at 16 against 24 wavefronts).
 constexpr int joined_tiles_of(int kind, int form) { return form == PAIRS ? PAIR : kind == K_PACK && form != BURST ? PACK_TILES : 1; }
 
@@ -102,15 +102,14 @@ constexpr size_t static_lds(int kind, bool few, int form) {
 //     1.747; a thousand small layers, P = 12 0.261 / 0.254 and 0.253 / 0.251, P = 16 0.325 / 0.329 and 0.323 / 0.328.
 //   - A launch of a few rounds of the chip (the compute units times the cap) should not end in a nearly empty one, see
 //     short_launch_cap().
-//   - A ragged tile (see general_tile) spends most of its time waiting for one thing after the other, longest where the
-//     worker count is not a compiled one (pointers and loads of eight workers at a time): a launch that consists of them needs every wave
-//     slot.  Time uncapped over capped (measured with four workers at a time, and every ragged tile on the general path), binary32, log-normal sizes with 45 and 17 % of the tiles ragged: pipeline 1 / 3 / 6 / 12 /
-//     32 workers 0.95 / 0.97 / 0.90 / 0.90 / 0.97 and 0.99 / 0.99 / 0.98 / 0.98 / 0.98, reduce_update 6 / 12 / 32 workers 0.97 / 0.92 / 0.97
-//     and 1.00 / 0.97 / 1.00, direct 0.95 / 0.81 / 0.87 and 0.99 / 0.87 / 0.93.  With 8 workers it is no gain (45 %: pipeline 1.04,
-//     reduce_update 0.99, direct 1.01; equal tensors, 25 / 40 / 60 % ragged: pipeline 1.06 / 1.03 / 1.05, reduce_update 1.00 / 1.07 / 1.02,
-//     direct 0.99 / 1.05 / 1.03), and with 16 the registers cap it anyway.
-//   - 16-bit gradients need every wave slot (direct, P = 8: 6559 uncapped / 5729 at 16), but for long REDUCE_UPDATE, which has the
-//     registers for 28 to 32 wavefronts (bfloat16, 12 and 150 tensors, us uncapped / at 25: 40,000 tiles P = 4 39.7 / 39.1, 42.1 / 40.3,
+//   - Launches of which more than a quarter of the tiles is ragged are uncapped but with 8 and 16 workers.  The line dates from
+//     ragged tiles that took the general path with four workers at a time and needed every wave slot (uncapped over capped with
+//     45 % of the tiles ragged, 6 / 12 / 32 workers: pipeline 0.90 / 0.90 / 0.97, direct 0.95 / 0.81 / 0.87).  Piece by piece they hardly do any more:
+//     binary32, log-normal sizes around 500 elements in groups of four, 29,000 tiles, 1 / 3 / 6 / 8 / 12 / 16 / 32 workers: pipeline 0.95 / 0.99 / 1.00 /
+//     1.04 / 1.02 / 1.02 / 1.02, reduce_update 1.00 / 1.00 / 1.00 / 1.03 / 1.01 / 1.02 / 1.02, direct 1.00 / 1.00 / 0.98 / 1.00 / 0.98 / 1.01 / 1.00; around 1500 elements, 40,000
+//     tiles: pipeline 0.99 / 1.01 / 1.01 / 1.04 / 1.04 / 1.03 / 1.05, reduce_update 1.00 / 1.00 / 1.01 / 1.03 / 1.02 / 1.03 / 1.04, direct 0.99-1.01.
+//   - 16-bit gradients need every wave slot (direct, P = 8: 6559 uncapped / 5729 at 16), but for launches that would end in a
+//     nearly empty round (see even_rounds()), for long REDUCE_UPDATE, which has the registers for 24 to 32 wavefronts (bfloat16, 12 and 150 tensors, us uncapped / at 25: 40,000 tiles P = 4 39.7 / 39.1, 42.1 / 40.3,
 //     8 52.6 / 52.5, 54.6 / 54.3, 16 80.1 / 79.9, 82.2 / 82.2; 100,000 tiles P = 4 96.4 / 93.4, 103.6 / 98.3, 8 129.8 / 126.6, 136.0 / 131.9, 16
 //     193.3 / 191.5, 201.4 / 199.4; P = 1 level; 12,000 tiles level, 7000 tiles P = 4 8.9 / 9.7, 8 11.4 / 12.6), for REDUCE with all of
 //     8 or 16 workers' loads in flight (P = 16: 6381 at 16 / 6220 uncapped; P = 12, two at a time: 6512 / 5265) and
@@ -171,11 +170,11 @@ inline int32_t default_burst_tiles(int kind, int32_t dtype, int32_t P) {
 // binary32 arrays are most of the traffic.  A short launch needs its tiles spread over the chip.
 // Nor does a model of many ragged tiles, whose turns come one after the other in a pair: with 0.9 / 2 / 3 / 11 / 45 % of
 // its tiles ragged, bf16, P = 8: 5706 / 5583 / 5789 / 5408 / 4364 joined, 5528 / 5446 / 5891 / 5532 / 4640 not.
-// In launches of up to twice SHORT_LAUNCH_TILES a single ragged tile counts where the worker count is not a compiled one: it
-// takes its workers a few at a time, after or before the other tile of its pair, and the launch waits for it (at four, bfloat16, one
-// tensor that ends in a ragged second half of a pair, time over that of single tiles: 16,500 tiles 6 / 12 / 32 workers 1.09 /
-// 1.13 / 1.17, 4 / 8 / 16 workers 1.01 / 1.02 / 1.02; 24,000 tiles 1.04 / 1.06 / 1.08; 31,000 tiles 1.00 / 1.00 / 1.01, from 45,000 on
-// below 1; without it 0.9-1.0).
+// In launches of up to twice SHORT_LAUNCH_TILES a single ragged tile counts where the worker count is not a compiled one.  That
+// dates from ragged tiles that took four workers at a time on the general path (bfloat16, one tensor that ends in a ragged second
+// half of a pair, pairs over single tiles, 16,500 tiles 6 / 12 / 32 workers 1.09 / 1.13 / 1.17).  Piece by piece the ragged half costs little: 16,500
+// tiles 4 / 6 / 8 / 12 / 16 / 32 workers 1.00 / 0.98 / 1.00 / 0.97 / 1.04 / 0.97, 24,000 0.96 / 0.93 / 0.95 / 0.94 / 0.96 / 0.96, 31,000 0.97 / 0.94 / 0.93 / 0.93 / 0.94 / 0.97;
+// without it 1.00 / 0.96 / 0.99 / 0.95 / 1.03 / 0.96, 0.92-0.98, 0.91-0.97.
 inline bool joined_pipeline(int32_t dtype, int32_t P, int32_t tiles, double ragged) {
     const bool compiled = P == 4 || P == 8 || P == 16;
     return dtype != MGWFBP_F32 && P >= 3 && tiles >= (compiled || ragged == 0 ? 1 : 2) * SHORT_LAUNCH_TILES && ragged < 0.025;
@@ -226,7 +225,9 @@ inline int32_t default_workgroups_per_cu(int kind, int32_t dtype, int32_t P, int
 
 // The cap of a launch of a few rounds, binary32 or in pairs of tiles, next to the `cap` of long ones: all workgroups at
 // once where 25 per compute unit hold them (16 workers, but for REDUCE: 20 in the few-segments form, by its registers, 16 in the
-// table form and in pairs), else the neighbour whose rounds come out fullest.  Pipeline, 8 workers, one tensor of 5000 tiles (19.5 per compute unit): 21.4 / 22.1 / 22.5 us in two
+// table form and in pairs, which date from kernels that held 16; binary32 ones hold 20 now: us as launched / at once, 150 tensors of
+// 4200 / 4650 / 5100 tiles, pipeline 33.9 / 28.0, 35.9 / 31.2, 36.7 / 33.5, reduce_update 19.1 / 15.1, 19.8 / 17.4, 20.5 / 19.3, direct 18.6 / 14.9, 18.7 / 16.1,
+// 19.5 / 17.2, but 5400 37.5 / 41.2, 21.2 / 24.1, 19.5 / 21.6), else the neighbour whose rounds come out fullest.  Pipeline, 8 workers, one tensor of 5000 tiles (19.5 per compute unit): 21.4 / 22.1 / 22.5 us in two
 // rounds at 14 / 16 / 18, 19.1 in one.  Per cent above the best of 14 / 16 / 18 / 21, mean of reduce, direct and pipeline with
 // 8, 12, 16 and 32 workers: 7100 tiles 0.2 / 0.7 / 2.9 / 5.0, 7200 12.0 / 0.3 / 1.9 / 3.4, 8250 6.0 / 9.4 / 0.0 / 1.7, 9250 0.3 / 4.2 / 7.8 /
 // 1.8, 11000 7.5 / 0.0 / 2.3 / 6.6, 13000 1.4 / 5.3 / 0.3 / 2.2, 13900 0.5 / 2.8 / 5.7 / 1.9, 18000 2.3 / 1.5 / 0.4 / 3.0, 24000 0.9 / 0.2 /
@@ -274,11 +275,13 @@ inline int8_t run_log2_of(int kind, int32_t dtype, int32_t P, double off_lines) 
 //     binary32 1.08 / 1.10 / 1.09, bfloat16 1.05 / 1.17 / 1.26, 3 workers bfloat16 1.09 / 1.14 / 1.16.
 //   - 16-bit PACK, 2 workers: copies of tiles up to 4096 1.05-1.10 (ragged end: 0.95), 7000 / 18000 / 48000 1.11 / 1.12 / 1.08
 //     (1.00 / 1.03 / 1.06), beyond 65536 0.97-1.00.
-//   - The other kinds on 16-bit gradients, which run uncapped: direct, 2 / 4 / 8 workers, 3500 tiles 1.05 / 1.06 / 1.06, 5500 1.06 /
-//     1.06 / 1.05, 10500 1.05 / 1.04 / 1.04, 60000 1.01 / 1.01 / 1.03 (reduce_update 1.01-1.04, pipeline 1.01-1.02); but its kernels take
-//     fewer registers and hold 28 to 32 wavefronts per compute unit instead of 24 to 28, so that 25 to 32 tiles per compute
-//     unit run at once: 6800 tiles direct 1.06 / 1.05 / 0.86, reduce_update 0.97 / 1.03 / 0.84, 7800 tiles 0.94 / 0.91 / 0.93; and 49 to 56
-//     in two rounds: reduce_update 32 workers 0.86.  Over five tensors 0.9-1.03.
+//   - The other kinds on 16-bit gradients, which run uncapped.  Most few-segments kernels have registers for 32 wavefronts per
+//     compute unit, and most table kernels for 24 or 28, so that 25 to 32 tiles per compute unit run at once, and 49 to 56 in
+//     two rounds, in this form only: 2 / 4 / 8 / 16 / 32 workers, 6300 tiles direct 0.96 / 0.96 / 0.80 / 0.81 / 0.74, reduce_update 0.97 / 0.97 / 0.97 /
+//     0.78 / 0.73, pipeline 0.97 / 0.99 / 0.98 / 0.98 / 0.96, 7900 tiles direct 0.90 / 0.87 / 0.88 / 0.91 / 0.84, reduce_update 0.98 / 0.97 / 0.85 / 1.02 / 0.82;
+//     12,600 tiles direct 0.98 / 0.98 / 0.90 / 0.93 / 0.90, reduce_update 0.99 / 0.98 / 0.98 / 0.91 / 0.91.  Elsewhere it goes either way: 4700 tiles direct
+//     0.96 / 0.95 / 0.96 / 0.99 / 0.98, 8300 0.96 / 0.97 / 1.03 / 1.07 / 1.06, 17,000 1.01 / 1.00 / 1.05 / 1.08 / 1.10, reduce_update 0.94 / 0.96 / 0.95 / 0.97 / 0.98, 0.99 /
+//     0.98 / 0.99 / 1.03 / 1.06, 1.00 / 0.99 / 1.03 / 1.03 / 1.08 (without the cap of even_rounds()).  Over five tensors 0.9-1.03.
 //   - binary32: 0.95-1.04 over one tensor, 0.9-1.02 over five.
 constexpr int FEW = 8;                // segments that fit into a launch's arguments
 inline bool few_form_pays(int kind, int32_t dtype, int32_t P, int32_t tiles, int32_t segments, int32_t per_cu) {
@@ -365,7 +368,7 @@ struct LaunchWork {
     int kind;
     int32_t dtype, P;
     int32_t tiles;                    // > 0
-    double ragged;                    // share of the tiles that take the general path
+    double ragged;                    // share of the tiles that are not full or not inside one tensor
     double off_lines;                 // share of the elements of tensors whose tiles start inside the lines of the tensor
     bool reduced;                     // the reduced arena is written
     double resident;                  // share of the tiles whose w and v are kept cacheable

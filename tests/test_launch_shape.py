@@ -190,7 +190,7 @@ def test_few_segments_form_where_it_pays(ask):
     assert few(kind="pack", tiles=1 << 20) and few(kind="pack", dtype="bf16", tiles=512) and few(kind="pack", dtype="bf16", tiles=8193)
     assert not few(kind="pack", dtype="bf16", tiles=513) and not few(kind="pack", dtype="bf16", tiles=8192)
     assert few(kind="pack", dtype="bf16", tiles=513, segments=2)
-    # with 16 workers the table form has registers for 16 wavefronts per compute unit, the few-segments form for 20
+    # with 16 workers the table form runs 16 tiles per compute unit at once, the few-segments form 20
     caps = shapes(ask, [dict(P=16, tiles=t, segments=n) for t, n in ((4096, 9), (4097, 9), (5120, 1), (5121, 1))])
     assert [s.wgs_per_cu for s in caps] == [25, 14, 25, 14]
 
