@@ -49,8 +49,9 @@
 //     per die inside that window (unit_of());
 //   - 16-BIT GRADIENTS: a long pipeline launch takes two tiles per workgroup, 16 bytes of gradients per lane, so
 //     that a wavefront has as much under way as with binary32 (joined_tiles);
-//   - everything is streamed with non-temporal loads and stores; a caller may ask for a leading share of
-//     the weights and momenta to use ordinary accesses and stay in the 256 MB memory-side cache (tile flag);
+//   - everything is streamed with non-temporal loads and stores, but for what the next step will find in the 256 MB
+//     memory-side cache: the results of PACK and REDUCE at the sizes where that pays (keeps_results()), and the leading share of
+//     the weights and momenta that a caller may ask for (tile flag);
 //   - PACK, which has no arithmetic across workers, runs as P single-worker copies (gridDim.y = P),
 //     so the chip streams 2 arrays at a time instead of 2P; a workgroup copies 1 to 4 KiB of its worker's data,
 //     two tiles per step (more per workgroup stretches the window its compute unit covers and costs 8 %).
@@ -240,7 +241,7 @@ template <typename GradT> __device__ __forceinline__ SegTables seg_tables(const 
 // streams one worker's gradients at a time (2 streams instead of 2P), which the memory system serves
 // faster.
 template <int KIND> __device__ __forceinline__ int worker_base() {
-    return KIND == K_PACK ? static_cast<int>(blockIdx.y) : 0;
+    return packs(KIND) ? static_cast<int>(blockIdx.y) : 0;
 }
 
 // Pointers of the P workers, either held in registers (P known at compile time) or re-read from the
@@ -377,7 +378,7 @@ __device__ __forceinline__ void paced_step(const CallArgs<GradT>& A, const Worke
                 if constexpr (writes_merge(KIND)) {
                     GradT* to = mrg.get(w0 + j) + apos;
 #pragma unroll
-                    for (int i = 0; i < N; ++i) st<NT_ST, GV>(to + i * stride, g[j][i]);
+                    for (int i = 0; i < N; ++i) st<NT_ST && !kept(KIND), GV>(to + i * stride, g[j][i]);
                 }
                 if constexpr (sums(KIND)) {
 #pragma unroll
@@ -416,9 +417,9 @@ __device__ __forceinline__ void paced_step(const CallArgs<GradT>& A, const Worke
         for (int i = 0; i < N; ++i) acc[i] = ld<NT_LD, FV>(A.reduced + apos + i * stride);
     }
     if constexpr (writes_reduced(KIND)) {
-        if (KIND == K_REDUCE || A.reduced != nullptr) {
+        if (reduces(KIND) || A.reduced != nullptr) {
 #pragma unroll
-            for (int i = 0; i < N; ++i) st<NT_ST, FV>(A.reduced + apos + i * stride, acc[i]);
+            for (int i = 0; i < N; ++i) st<NT_ST && !kept(KIND), FV>(A.reduced + apos + i * stride, acc[i]);
         }
     }
     if constexpr (updates(KIND) && TOGETHER > 0) {
@@ -504,7 +505,7 @@ __device__ __forceinline__ void joined_tiles(const CallArgs<GradT>& A, const Wor
     src.fetch(A.grad_ptrs, A.L, layer, worker_base<KIND>());
     int lane_elem = static_cast<int>(threadIdx.x) * VEC;
     here_only_per_lane(lane_elem);
-    if constexpr (KIND == K_PACK) {
+    if constexpr (packs(KIND)) {
         paced_step<KIND, GradT, PT, VEC, PACK_TILES * TVECS, true>(A, src, mrg, nullptr, nullptr, tensor_off + lane_elem,
                                                              tile_base + lane_elem, BLOCK * VEC);
     } else {
@@ -877,8 +878,10 @@ template <int KIND, typename GradT, int PT, int FORM> constexpr int most_pieces(
     return one ? 1 : MGWFBP_PIECES;
 }
 
-template <int KIND, typename GradT, int PT, int FORM>
-__global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_waves<KIND, GradT, PT, FORM>())) mgwfbp_stream_kernel(const Args<GradT> A) {
+template <int ROLE, typename GradT, int PT, int KERNEL_FORM>
+__global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_waves<ROLE, GradT, PT, KERNEL_FORM>())) mgwfbp_stream_kernel(const Args<GradT> A) {
+    constexpr int KIND = kind_in(ROLE, KERNEL_FORM);
+    constexpr int FORM = KERNEL_FORM == KEPT ? 1 : KERNEL_FORM;
     constexpr int SINGLE = FORM == PAIRS ? 1 : FORM;     // single tiles
     constexpr int JOIN = joined_tiles_of(KIND, FORM);
     constexpr int MOST = most_pieces<KIND, GradT, PT, FORM>();
@@ -1029,7 +1032,7 @@ template <typename GradT> __device__ __forceinline__ FewSeg few_owner(const FewA
 // earlier; where they do not, the single tensors of long launches have the scalar registers.  us with the ends in the general
 // part only / with the other arguments, burst form: three tensors of 300 elements, 8 workers, binary32: pipeline 2.63 / 2.40,
 // reduce_update 2.55 / 2.36; seven of 9 to 2000, 16 workers, bfloat16: 4.05 / 3.55, 3.37 / 3.02; pack 2.56 / 2.25.
-constexpr bool ends_early(int kind, int form) { return form == BURST || kind == K_PACK; }
+constexpr bool ends_early(int kind, int form) { return form == BURST || packs(kind); }
 
 // One tile of the few-segments form (of PACK or in pairs: a joined step); the tiles taken.
 template <int KIND, typename GradT, int PT, int FORM>
@@ -1132,8 +1135,10 @@ template <int KIND, typename GradT, int PT, int FORM> constexpr int wanted_few_w
 // where a launch no longer fits at once: 93 registers at 28 tiles per compute unit, 80 at 32, 103 at 24).  us with 83 to 103 / 55
 // to 80, bfloat16, one tensor of 7500 tiles: direct, 4 / 8 / 16 / 32 workers 9.3 / 8.2, 12.7 / 10.6, 18.9 / 15.4, 29.9 / 24.9; reduce_update 9.3 / 8.3,
 // 12.4 / 10.4, 18.1 / 15.2, 29.2 / 23.9.
-template <int KIND, typename GradT, int PT, int FORM>
-__global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_few_waves<KIND, GradT, PT, FORM>())) mgwfbp_few_kernel(FewArgs<GradT> A) {
+template <int ROLE, typename GradT, int PT, int KERNEL_FORM>
+__global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_few_waves<ROLE, GradT, PT, KERNEL_FORM>())) mgwfbp_few_kernel(FewArgs<GradT> A) {
+    constexpr int KIND = kind_in(ROLE, KERNEL_FORM);
+    constexpr int FORM = KERNEL_FORM == KEPT ? 1 : KERNEL_FORM;
     static_assert(KIND >= 0 && HAVE_FEW, "a tile is one vector per lane of one wavefront");
     __shared__ __align__(16) float s_sums[FORM == PAIRS ? PAIRED : 4];
     // All arguments in one trip; left alone, the compiler fetches them where it needs them, in three.
@@ -1151,7 +1156,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_few_waves<KIND, GradT, P
         // A further tile, where the caller asked for several: the arguments again, so that no path keeps them, or what the
         // compiler works out from them beforehand, in registers for it (10 scalar registers).  PACK takes several by itself and
         // has the registers (bfloat16, 32 workers, 40,000 tiles 198 us, with the arguments again 212).
-        if constexpr (KIND != K_PACK) {
+        if constexpr (!packs(KIND)) {
             asm volatile("" : "+s"(a));
             A = *(const FewArgs<GradT>*)a;
         }
@@ -1280,6 +1285,11 @@ template <int KIND, typename GradT, int PT, template <typename> class ArgsT>
 int launch_one(const ArgsT<GradT>& A, hipStream_t stream, const LaunchShape& s, int grid_y = 1) {
     if constexpr (KIND != K_PACK) {                       // PACK has one form
         if (s.form == BURST) return start<KIND, GradT, PT, BURST>(A, stream, s, grid_y);
+    }
+    // (a REDUCE long enough for it is in the table form)
+    constexpr bool TABLE = !std::is_same<ArgsT<GradT>, FewArgs<GradT>>::value;
+    if constexpr (HAVE_KEPT && (KIND == K_PACK || (KIND == K_REDUCE && TABLE && PT * sizeof(GradT) <= 16))) {
+        if (s.kept) return start<KIND, GradT, PT, KEPT>(A, stream, s, grid_y);
     }
     if constexpr (TVECS % 2 == 0) {
         if (s.form == 2) return start<KIND, GradT, PT, 2>(A, stream, s, grid_y);

@@ -24,25 +24,32 @@ constexpr int TILE = MGWFBP_TILE_ELEMS;
 constexpr int MAXSEG = MGWFBP_MAXSEG;
 constexpr int PACK_TILES = MGWFBP_PACK_TILES;
 
-enum Kind { K_PACK = 0, K_REDUCE = 1, K_UPDATE = 2, K_REDUCE_UPDATE = 3, K_PIPELINE = 4, K_DIRECT = 5 };
+enum Kind { K_PACK = 0, K_REDUCE = 1, K_UPDATE = 2, K_REDUCE_UPDATE = 3, K_PIPELINE = 4, K_DIRECT = 5,
+            K_PACK_KEPT = 6, K_REDUCE_KEPT = 7 };      // what PACK and REDUCE are in kernels of the form KEPT
 
-constexpr bool reads_grads(int k) { return k == K_PACK || k == K_PIPELINE || k == K_DIRECT; }
-constexpr bool reads_merge(int k) { return k == K_REDUCE || k == K_REDUCE_UPDATE; }
-constexpr bool writes_merge(int k) { return k == K_PACK || k == K_PIPELINE; }
-constexpr bool sums(int k) { return k == K_REDUCE || k == K_REDUCE_UPDATE || k == K_PIPELINE || k == K_DIRECT; }
-constexpr bool writes_reduced(int k) { return k == K_REDUCE || k == K_PIPELINE || k == K_DIRECT; }
+constexpr bool packs(int k) { return k == K_PACK || k == K_PACK_KEPT; }
+constexpr bool reduces(int k) { return k == K_REDUCE || k == K_REDUCE_KEPT; }
+constexpr bool kept(int k) { return k == K_PACK_KEPT || k == K_REDUCE_KEPT; }
+constexpr bool reads_grads(int k) { return packs(k) || k == K_PIPELINE || k == K_DIRECT; }
+constexpr bool reads_merge(int k) { return reduces(k) || k == K_REDUCE_UPDATE; }
+constexpr bool writes_merge(int k) { return packs(k) || k == K_PIPELINE; }
+constexpr bool sums(int k) { return reduces(k) || k == K_REDUCE_UPDATE || k == K_PIPELINE || k == K_DIRECT; }
+constexpr bool writes_reduced(int k) { return reduces(k) || k == K_PIPELINE || k == K_DIRECT; }
 constexpr bool updates(int k) { return k == K_UPDATE || k == K_REDUCE_UPDATE || k == K_PIPELINE || k == K_DIRECT; }
-constexpr bool needs_owner(int k) { return k != K_REDUCE; }
+constexpr bool needs_owner(int k) { return !reduces(k); }
 
 // Forms of the fast path, beside the number of vectors per lane of a paced step (1 and up).
 constexpr int BURST = 0;              // every load of a tile under way at once
 constexpr int PAIRS = -1;             // two full tiles of one tensor in one step, single ones in paced steps of one vector
+constexpr int KEPT = -2;              // PACK and REDUCE in paced steps of one vector whose results stay in the memory-side cache, see keeps_results()
+constexpr int kind_in(int kind, int form) { return form != KEPT ? kind : kind == K_PACK ? K_PACK_KEPT : K_REDUCE_KEPT; }
 constexpr int PAIR = 2;
 constexpr int PAIRED = PAIR * TILE;   // elements of a pair
 // What needs tiles of one vector per lane, and of one wavefront, is left out of builds with other tiles.
 constexpr bool HAVE_PAIRS = TVECS == 1;
 constexpr bool HAVE_FEW = TVECS == 1 && BLOCK == 64;
 constexpr bool HAVE_PIECES = TVECS == 1 && BLOCK == 64;
+constexpr bool HAVE_KEPT = TVECS == 1;
 // Most segments of a tile that the table form takes piece by piece; the walk over the pieces costs 0.15 us each, the general
 // path's prefix sum and search the same for any number.  us with one, up to three and up to eight, 8 workers, tensors in
 // groups of eight and more: of 301 elements pipeline 7.2 / 6.4 / 6.4, unpack_update 4.6 / 4.0 / 4.0; of 70 elements pipeline 7.4 /
@@ -55,7 +62,7 @@ constexpr bool HAVE_PIECES = TVECS == 1 && BLOCK == 64;
 // joined step, whose sums change hands through LDS, the single-tile kernel would need the joined one's 96 registers instead of 59 (16
 // workers; 63 instead of 43 with 8) and as uncapped launches hold 20 instead of 24 wavefronts per compute unit (16
 // workers, 6000 tiles: 30.0 us against 23.4, at 16 against 24 wavefronts).
-constexpr int joined_tiles_of(int kind, int form) { return form == PAIRS ? PAIR : kind == K_PACK && form != BURST ? PACK_TILES : 1; }
+constexpr int joined_tiles_of(int kind, int form) { return form == PAIRS ? PAIR : packs(kind) && form != BURST ? PACK_TILES : 1; }
 
 // Dynamic LDS per workgroup that lets at most n workgroups share the 160 KiB of a compute unit.  A workgroup's
 // LDS (static + dynamic) is granted in blocks of 1280 bytes (a 128th of the compute unit's; seen in the cap
@@ -338,6 +345,25 @@ inline bool even_rounds(int kind, int32_t dtype, int32_t P, bool few, int form, 
     return per_cu > held && (per_cu + held - 1) / held == (per_cu + 23) / 24;
 }
 
+// Whether what a long PACK or REDUCE writes stays in the 256 MB memory-side cache for the step that reads it: stored with ordinary
+// stores it does, streamed it passes by.  PACK's stores then take longer (1.04-1.10 of a PACK by itself, up to 1.14 with 32
+// workers), and the reduction that follows gains more, as long as a good part of the arenas fits.  Time over streamed, P merge arenas of
+// 24 / 50 / 100 / 200 / 400 / 600 / 800 MB together, 150 tensors, pack and reduce_update: binary32 1 worker 1.05 / 1.02 / 0.98 / 0.95 / 0.97 / 1.00 /
+// 1.01, 2 workers 1.00 / 1.00 / 0.97 / 0.94 / 0.96 / 0.99 / 1.00, 8 workers 1.02 / 0.99 / 0.97 / 0.94 / 0.94 / 0.97 / 0.99, 32 workers 0.98 / 0.98 / 0.92 / 0.92 /
+// 0.96 / 0.98 / 1.00; bfloat16 2 workers 1.01 / 0.97 / 0.96 / 0.95 / 0.98 / 1.00 / 1.01, 8 workers 1.06 / 0.99 / 0.96 / 0.93 / 0.98 / 0.99 / 1.01, 32 workers 1.11 /
+// 0.98 / 0.96 / 0.95 / 0.98 / 1.01 / 1.04.  In short launches what the stores leave in the L2s is written back when the kernel ends.  One
+// worker's gradients are packed for an exchange, not for a reduction here.
+// REDUCE pays where the reduced arena is no small part of what it moves and unpack_update follows: the three steps, reduced arena of
+// 48 / 72 / 100 / 200 / 400 / 800 MB, binary32 1 worker 0.99 / 0.98 / 0.97 / 0.95 / 0.96 / 0.98, 4 workers 1.00 / 0.97 / 0.98 / 0.98 / 1.00 / -, bfloat16 1
+// worker 1.01 / 0.98 / 0.97 / 0.95 / 0.98 / 1.02, 4 workers 0.98 / 0.98 / 0.98 / 0.97 / 1.00 / 1.01, 8 workers 0.99 / 1.02 / 0.98 / 0.98 / 0.99 / -, 16 workers 1.00-1.01.
+inline bool keeps_results(int kind, int32_t dtype, int32_t P, int32_t tiles) {
+    constexpr int64_t MiB = 1 << 20;
+    const bool wide = dtype == MGWFBP_F32;
+    const int64_t reduced = static_cast<int64_t>(tiles) * 1024, merged = reduced * P / (wide ? 1 : 2);      // bytes
+    if (kind == K_PACK) return P > 1 && merged >= 48 * MiB && merged <= (wide || P < 16 ? 448 : 320) * MiB;
+    return kind == K_REDUCE && merged <= 4 * reduced && reduced >= 80 * MiB && reduced <= 512 * MiB;
+}
+
 // What a caller has fixed (mgwfbp_ctx_set_*); the initial values are the library's defaults.
 struct LaunchSettings {
     int32_t blocks_per_cu = 0;        // > 0: a persistent grid of that many workgroups per compute unit.  0 = one workgroup
@@ -383,6 +409,7 @@ struct LaunchShape {
     int form;                         // BURST, PAIRS or the vectors per lane of a paced step
     int32_t wgs_per_cu;               // workgroups that may share a compute unit; <= 0: no cap
     bool rolling;                     // two loads under way in a step (see rolls())
+    bool kept;                        // the results stay in the memory-side cache (see keeps_results())
     bool in_pieces;                   // ragged tiles piece by piece also where the kernel would rather not (see most_pieces())
 };
 
@@ -436,6 +463,7 @@ inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, 
     }
     s.rolling = may_roll(w.kind, s.form) && set.step_vecs == 0 && set.wg_per_cu == 0 && rolls(w.dtype, w.P, s.may_be_few, per_cu);
     s.in_pieces = w.ragged > 0.5;
+    s.kept = s.form == 1 && keeps_results(w.kind, w.dtype, w.P, length);
     s.run_log2 = one_turn ? run_log2_of(w.kind, w.dtype, w.P, w.off_lines) : int8_t{0};
     return s;
 }
