@@ -64,6 +64,7 @@
 #include <atomic>
 #include <chrono>
 #include <cmath>
+#include <cstddef>
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
@@ -881,7 +882,8 @@ template <int KIND, typename GradT, int PT, int FORM> constexpr int most_pieces(
 template <int ROLE, typename GradT, int PT, int KERNEL_FORM>
 __global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_waves<ROLE, GradT, PT, KERNEL_FORM>())) mgwfbp_stream_kernel(const Args<GradT> A) {
     constexpr int KIND = kind_in(ROLE, KERNEL_FORM);
-    constexpr int FORM = KERNEL_FORM == KEPT ? 1 : KERNEL_FORM;
+    constexpr int FORM = single_steps(KERNEL_FORM) ? 1 : KERNEL_FORM;
+    constexpr bool SHIFTS = KERNEL_FORM == ON_LINES;
     constexpr int SINGLE = FORM == PAIRS ? 1 : FORM;     // single tiles
     constexpr int JOIN = joined_tiles_of(KIND, FORM);
     constexpr int MOST = most_pieces<KIND, GradT, PT, FORM>();
@@ -925,8 +927,42 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_waves<ROLE, GradT, PT, K
             const TileHdr h = load_header(A.tiles + tile);
             const int64_t tile_base = static_cast<int64_t>(tile) * TILE;
             const int clo = t == 0 ? A.clip_lo : 0;
-            const int chi = t == A.tile_count - 1 ? min(h.valid, static_cast<int>(A.clip_hi)) : h.valid;
+            int chi = t == A.tile_count - 1 ? min(h.valid, static_cast<int>(A.clip_hi)) : h.valid;
             if (chi <= clo) continue;
+            if constexpr (SHIFTS) {
+                // The tile's share of a tensor begins on a line of the weights (see on_lines_pays()).  Whether the tensor goes on is in the
+                // header, and the next tile's is read where it does only: reading both in front of every tile cost up to 7 % (100,000 tiles, 1
+                // worker).  Launches are over whole groups, so a tensor that goes on does so in the launch's next tile.
+                constexpr int LINE = line_elems(KIND, sizeof(GradT));
+                auto shift_of = [&](const TileHdr& x) { return line_shift(reinterpret_cast<uint64_t>(ro(A.w_ptrs)[x.layer0]), x.first_start, LINE); };
+                const bool goes_on = (h.flags & TILE_GOES_ON) != 0;
+                int ahead = shift_of(h);
+                if (h.nseg == 1 && goes_on && -h.first_start >= ahead) {
+                    if (h.flags & TILE_RESIDENT) {             // (see below)
+                        asm volatile("; w and v cacheable" ::: "memory");
+                        fast_chunk<KIND, GradT, PT, NT_WV, 1>(A, mrg, h.layer0, -h.first_start - ahead, tile_base - ahead, TVECS);
+                        asm volatile("; end w and v cacheable" ::: "memory");
+                    } else {
+                        asm volatile("; w and v streamed" ::: "memory");
+                        fast_chunk<KIND, GradT, PT, true, 1>(A, mrg, h.layer0, -h.first_start - ahead, tile_base - ahead, TVECS);
+                        asm volatile("; end w and v streamed" ::: "memory");
+                    }
+                    continue;
+                }
+                // A tile that a tensor begins or ends in: what lies before the tile, then the rest up to the next one's share.
+                ahead = starts_early(h.first_start, ahead);
+                int left = 0;
+                if (goes_on) {
+                    const TileHdr next = load_header(A.tiles + tile + 1);
+                    left = starts_early(next.first_start, shift_of(next));
+                }
+                const Piece s{h.layer0, -ahead, 0, -h.first_start - ahead};
+                int lane = threadIdx.x;
+                here_only_per_lane(lane);
+                if (ahead >= VEC) one_piece<KIND, GradT, PT, true>(A, mrg, tile_base, s, lane);
+                else if (lane < ahead) do_one<KIND, GradT, PT, 1>(A, mrg, s.layer, s.off + lane, tile_base + s.lo + lane);
+                chi -= left;
+            }
             const bool full = clo == 0 && chi == TILE && (!needs_owner(KIND) || h.nseg == 1);
             if constexpr (HAVE_PIECES) {
                 TablePieces<KIND, GradT> pieces{h, clo, chi};
@@ -934,7 +970,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_waves<ROLE, GradT, PT, K
                 if ((FORM == BURST || !full) && pieces.only(s) && s.len() >= VEC) {
                     int lane = threadIdx.x;
                     here_only_per_lane(lane);
-                    if (!updates(KIND) || (h.flags & 1)) {             // (see below)
+                    if (!updates(KIND) || (h.flags & TILE_RESIDENT)) {             // (see below)
                         asm volatile("; w and v cacheable" ::: "memory");
                         one_piece<KIND, GradT, PT, NT_WV>(A, mrg, tile_base, s, lane);
                         asm volatile("; end w and v cacheable" ::: "memory");
@@ -968,7 +1004,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_waves<ROLE, GradT, PT, K
                         same = same && hk.valid == TILE && hk.nseg == 1 && hk.layer0 == h.layer0;
                         flags |= hk.flags;
                     }
-                    if (same && (!updates(KIND) || !(flags & 1))) {
+                    if (same && (!updates(KIND) || !(flags & TILE_RESIDENT))) {
                         joined_tiles<KIND, GradT, PT>(A, mrg, h.layer0, -h.first_start, tile_base, s_sums);
                         t += JOIN - 1;
                         continue;
@@ -981,12 +1017,12 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_waves<ROLE, GradT, PT, K
             // statements keep the optimiser from merging them back into one (which drops the policy).
             const int64_t toff = -h.first_start;
             if constexpr (may_roll(KIND, FORM)) {
-                if ((A.flags & ROLLING) && !(h.flags & 1)) {
+                if ((A.flags & ROLLING) && !(h.flags & TILE_RESIDENT)) {
                     rolling_tile<GradT, PT>(A, mrg, h.layer0, toff, tile_base);
                     continue;
                 }
             }
-            if (!updates(KIND) || (h.flags & 1)) {
+            if (!updates(KIND) || (h.flags & TILE_RESIDENT)) {
                 asm volatile("; w and v cacheable" ::: "memory");
                 fast_chunk<KIND, GradT, PT, NT_WV, SINGLE>(A, mrg, h.layer0, toff, tile_base, TVECS);
                 asm volatile("; end w and v cacheable" ::: "memory");
@@ -1138,7 +1174,7 @@ template <int KIND, typename GradT, int PT, int FORM> constexpr int wanted_few_w
 template <int ROLE, typename GradT, int PT, int KERNEL_FORM>
 __global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_few_waves<ROLE, GradT, PT, KERNEL_FORM>())) mgwfbp_few_kernel(FewArgs<GradT> A) {
     constexpr int KIND = kind_in(ROLE, KERNEL_FORM);
-    constexpr int FORM = KERNEL_FORM == KEPT ? 1 : KERNEL_FORM;
+    constexpr int FORM = single_steps(KERNEL_FORM) ? 1 : KERNEL_FORM;
     static_assert(KIND >= 0 && HAVE_FEW, "a tile is one vector per lane of one wavefront");
     __shared__ __align__(16) float s_sums[FORM == PAIRS ? PAIRED : 4];
     // All arguments in one trip; left alone, the compiler fetches them where it needs them, in three.
@@ -1205,11 +1241,11 @@ int32_t mark_resident_tiles(HostTables& h, uint64_t budget) {
     for (size_t i = 0; i < h.tiles.size(); ++i) {
         const uint64_t need = static_cast<uint64_t>(h.tiles[i].valid) * 8u;
         if (used + need <= budget) {
-            h.tiles[i].flags = 1;
+            h.tiles[i].flags |= TILE_RESIDENT;
             used += need;
             end = static_cast<int32_t>(i + 1);
         } else {
-            h.tiles[i].flags = 0;
+            h.tiles[i].flags &= ~TILE_RESIDENT;
         }
     }
     return end;
@@ -1286,10 +1322,12 @@ int launch_one(const ArgsT<GradT>& A, hipStream_t stream, const LaunchShape& s, 
     if constexpr (KIND != K_PACK) {                       // PACK has one form
         if (s.form == BURST) return start<KIND, GradT, PT, BURST>(A, stream, s, grid_y);
     }
-    // (a REDUCE long enough for it is in the table form)
     constexpr bool TABLE = !std::is_same<ArgsT<GradT>, FewArgs<GradT>>::value;
     if constexpr (HAVE_KEPT && (KIND == K_PACK || (KIND == K_REDUCE && TABLE && PT * sizeof(GradT) <= 16))) {
         if (s.kept) return start<KIND, GradT, PT, KEPT>(A, stream, s, grid_y);
+    }
+    if constexpr (HAVE_PIECES && (KIND == K_UPDATE || KIND == K_DIRECT) && TABLE) {
+        if (s.on_lines) return start<KIND, GradT, PT, ON_LINES>(A, stream, s, grid_y);
     }
     if constexpr (TVECS % 2 == 0) {
         if (s.form == 2) return start<KIND, GradT, PT, 2>(A, stream, s, grid_y);
@@ -1429,7 +1467,7 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
         const CallArgs<GradT> call{reinterpret_cast<const GradT* const*>(grad_ptrs), reinterpret_cast<GradT* const*>(merge_bufs),
                                    reduced, w_ptrs, v_ptrs, lr, mu, inv_p, c->host.L, c->P, sp.t0, count,
                                    static_cast<int16_t>(s.tiles_per_wg),
-                                   static_cast<int8_t>((s.xcd_contiguous ? XCD_CONTIGUOUS : 0) | (s.rolling ? ROLLING : 0) | (s.in_pieces ? IN_PIECES : 0)), s.run_log2};
+                                   static_cast<int8_t>((s.xcd_contiguous ? XCD_CONTIGUOUS : 0) | (s.rolling ? ROLLING : 0) | (s.in_pieces ? IN_PIECES : 0)), s.on_lines ? int8_t{0} : s.run_log2};
         return launch<KIND, GradT>(c, sp, tiles, call, stream, s);
     };
     if (c->dtype == MGWFBP_F32) return go(float{});
@@ -1498,7 +1536,13 @@ int mgwfbp_ctx_tables(const mgwfbp_ctx* c, int32_t* n_segments, void* tiles_out,
     const HostTables& h = c->host;
     const size_t S = h.seg_layer.size();
     if (n_segments) *n_segments = static_cast<int32_t>(S);
-    if (tiles_out && !h.tiles.empty()) std::memcpy(tiles_out, h.tiles.data(), sizeof(TileHdr) * h.tiles.size());
+    if (tiles_out && !h.tiles.empty()) {
+        std::memcpy(tiles_out, h.tiles.data(), sizeof(TileHdr) * h.tiles.size());
+        for (size_t i = 0; i < h.tiles.size(); ++i) {
+            const int32_t shown = h.tiles[i].flags & TILE_RESIDENT;
+            std::memcpy(static_cast<unsigned char*>(tiles_out) + i * sizeof(TileHdr) + offsetof(TileHdr, flags), &shown, sizeof shown);
+        }
+    }
     if (seg_off_out) std::memcpy(seg_off_out, h.seg_off.data(), sizeof(uint64_t) * (S + 1));
     if (seg_n_out && S) std::memcpy(seg_n_out, h.seg_n.data(), sizeof(uint32_t) * S);
     if (seg_layer_out && S) std::memcpy(seg_layer_out, h.seg_layer.data(), sizeof(int32_t) * S);

@@ -43,6 +43,8 @@ constexpr int BURST = 0;              // every load of a tile under way at once
 constexpr int PAIRS = -1;             // two full tiles of one tensor in one step, single ones in paced steps of one vector
 constexpr int KEPT = -2;              // PACK and REDUCE in paced steps of one vector whose results stay in the memory-side cache, see keeps_results()
 constexpr int kind_in(int kind, int form) { return form != KEPT ? kind : kind == K_PACK ? K_PACK_KEPT : K_REDUCE_KEPT; }
+constexpr int ON_LINES = -3;          // UPDATE and DIRECT in paced steps of one vector that begin on lines of the weights, see on_lines_pays()
+constexpr bool single_steps(int form) { return form == 1 || form == KEPT || form == ON_LINES; }
 constexpr int PAIR = 2;
 constexpr int PAIRED = PAIR * TILE;   // elements of a pair
 // What needs tiles of one vector per lane, and of one wavefront, is left out of builds with other tiles.
@@ -274,6 +276,38 @@ inline int8_t run_log2_of(int kind, int32_t dtype, int32_t P, double off_lines) 
     return kind == K_PIPELINE ? 2 : 3;
 }
 
+// Shares of tiles that begin on lines of the weights.  A tile is 256 elements of the arena, and a tensor of odd size, or after one, lies
+// somewhere else in its lines of 128 bytes: a wavefront then touches nine lines of w, v and every worker's gradients for eight (five for
+// four of 16-bit gradients), neighbours fetch the line they share twice and each write a part of it.  UPDATE and DIRECT, which touch the arenas
+// not at all or only to read the reduced one, need not cut a tensor where its tiles are: inside a tensor a tile's share begins at the last line
+// before its first element, and ends where the next tile's begins.
+//   line_shift: elements from there to the tile's first element; address of the tensor's weights, its start as seen from the tile
+//   starts_early: what the share really begins earlier by, no earlier than the tensor (first_start: 0 where it begins with the tile)
+constexpr int line_shift(uint64_t weights, int64_t first_start, int line) {
+    return static_cast<int>(weights / sizeof(float) - static_cast<uint64_t>(first_start)) & (line - 1);
+}
+constexpr int starts_early(int64_t first_start, int shift) { return -first_start < shift ? static_cast<int>(-first_start) : shift; }
+constexpr int line_elems(int kind, size_t grad_bytes) { return 128 / static_cast<int>(kind == K_DIRECT ? grad_bytes : sizeof(float)); }
+
+// Where that pays: time over tiles cut in the arena with runs of tiles per die (see above).  300 tensors of log-normal odd sizes, views of flat
+// buffers / allocations of their own in groups of five / a group each (where every tensor begins on a line and nothing is gained) / views of
+// sizes that are multiples of 64:
+//   binary32   update  8000 tiles 0.98 / 0.97 / 1.02 / 1.00    20,000 0.98 / 0.97 / 1.02 / 1.00    100,000 0.94 / 0.94 / 1.00 / 1.01
+//              direct, 1 worker   8000 0.95 / 0.94 / 1.01 / 1.01    20,000 0.98 / 0.95 / 1.01 / 1.01    100,000 0.96 / 0.97 / 1.00 / 1.01
+//                      3 workers  8000 0.96 / 0.97 / 1.04 / 1.01    20,000 0.97 / 0.97 / 1.01 / 1.00    100,000 0.96 / 0.96 / 0.99 / 1.00
+//                      8 workers  8000 0.99 / 1.02 / 1.04 / 1.00    20,000 0.97 / 0.99 / 1.01 / 1.00    100,000 0.96 / 0.97 / 0.98 / 1.00
+//   bfloat16   direct, 3 workers  8000 0.95 / 0.95 / 1.03 / 1.00    20,000 0.95 / 0.95 / 1.00 / 1.00    100,000 0.93 / 0.95 / 1.00 / 1.00
+//                      8 workers  8000 0.94 / 0.97 / 1.02 / 1.00    20,000 0.91 / 0.93 / 1.01 / 1.00    100,000 0.92 / 0.93 / 1.01 / 1.00
+//                      16 workers 8000 0.87 / 0.93 / 1.03 / 1.00    20,000 0.84 / 0.90 / 1.01 / 1.00    100,000 0.88 / 0.91 / 1.00 / 1.00
+// With 12,000 tensors of 100,000 tiles, update 0.97 / 0.98 / 1.01 / 1.01, direct 8 workers 0.97 / 0.98 / 1.02 / 1.02 and bfloat16 0.93 / 0.94 / 1.02 / 1.01; the
+// tiles a tensor begins or ends in take a step more.  The pipeline would have its arenas off the lines instead (0.84-0.97 of the rate), reduce_update
+// gains with one or two 16-bit workers only.
+inline bool on_lines_pays(int kind, int32_t dtype, bool reduced, int32_t tiles, int32_t segments, double off_lines) {
+    if (kind != K_UPDATE && (kind != K_DIRECT || reduced)) return false;
+    const int32_t least = kind == K_DIRECT && dtype != MGWFBP_F32 ? SHORT_LAUNCH_TILES : SHORT_LAUNCH_TILES / 2 * 3;
+    return off_lines > 0.25 && tiles >= least && tiles / 16 >= segments;
+}
+
 // Which of the launches that could take the few-segments form do.  It reaches a ragged tile's data several memory trips
 // sooner (a launch of up to 1000 tiles over five tensors takes 0.76-0.9 of the table form's time, over one tensor that ends in a
 // ragged tile 0.9-1.0), but full tiles cost it a little more, and that adds up where every wavefront counts.  Time over that
@@ -346,12 +380,13 @@ inline bool even_rounds(int kind, int32_t dtype, int32_t P, bool few, int form, 
 }
 
 // Whether what a long PACK or REDUCE writes stays in the 256 MB memory-side cache for the step that reads it: stored with ordinary
-// stores it does, streamed it passes by.  PACK's stores then take longer (1.04-1.10 of a PACK by itself, up to 1.14 with 32
-// workers), and the reduction that follows gains more, as long as a good part of the arenas fits.  Time over streamed, P merge arenas of
+// stores it does, streamed it passes by.  PACK's stores then take longer (1.04-1.14 of a PACK repeated by itself, 1.1-1.37 where
+// most tiles are ragged), and the reduction that follows gains more, as long as a good part of the arenas fits.  Time over streamed, P merge arenas of
 // 24 / 50 / 100 / 200 / 400 / 600 / 800 MB together, 150 tensors, pack and reduce_update: binary32 1 worker 1.05 / 1.02 / 0.98 / 0.95 / 0.97 / 1.00 /
 // 1.01, 2 workers 1.00 / 1.00 / 0.97 / 0.94 / 0.96 / 0.99 / 1.00, 8 workers 1.02 / 0.99 / 0.97 / 0.94 / 0.94 / 0.97 / 0.99, 32 workers 0.98 / 0.98 / 0.92 / 0.92 /
 // 0.96 / 0.98 / 1.00; bfloat16 2 workers 1.01 / 0.97 / 0.96 / 0.95 / 0.98 / 1.00 / 1.01, 8 workers 1.06 / 0.99 / 0.96 / 0.93 / 0.98 / 0.99 / 1.01, 32 workers 1.11 /
-// 0.98 / 0.96 / 0.95 / 0.98 / 1.01 / 1.04.  In short launches what the stores leave in the L2s is written back when the kernel ends.  One
+// 0.98 / 0.96 / 0.95 / 0.98 / 1.01 / 1.04; models of tensors around 500 elements, a group each, 60 / 120 / 200 / 300 MB, binary32 8 workers 0.97 / 0.96 /
+// 0.95 / 0.96, bfloat16 0.99 / 0.95 / 0.93 / 0.95.  In short launches what the stores leave in the L2s is written back when the kernel ends.  One
 // worker's gradients are packed for an exchange, not for a reduction here.
 // REDUCE pays where the reduced arena is no small part of what it moves and unpack_update follows: the three steps, reduced arena of
 // 48 / 72 / 100 / 200 / 400 / 800 MB, binary32 1 worker 0.99 / 0.98 / 0.97 / 0.95 / 0.96 / 0.98, 4 workers 1.00 / 0.97 / 0.98 / 0.98 / 1.00 / -, bfloat16 1
@@ -404,11 +439,12 @@ struct LaunchWork {
 struct LaunchShape {
     int32_t tiles_per_wg, units, grid;
     int8_t xcd_contiguous;
-    int8_t run_log2;                  // a die's turn is 2^run_log2 consecutive units
+    int8_t run_log2;                  // a die's turn is 2^run_log2 consecutive units (not where shares begin on lines)
     bool may_be_few;                  // the few-segments form may take it
     int form;                         // BURST, PAIRS or the vectors per lane of a paced step
     int32_t wgs_per_cu;               // workgroups that may share a compute unit; <= 0: no cap
     bool rolling;                     // two loads under way in a step (see rolls())
+    bool on_lines;                    // steps begin on lines of the weights (see on_lines_pays())
     bool kept;                        // the results stay in the memory-side cache (see keeps_results())
     bool in_pieces;                   // ragged tiles piece by piece also where the kernel would rather not (see most_pieces())
 };
@@ -464,6 +500,7 @@ inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, 
     s.rolling = may_roll(w.kind, s.form) && set.step_vecs == 0 && set.wg_per_cu == 0 && rolls(w.dtype, w.P, s.may_be_few, per_cu);
     s.in_pieces = w.ragged > 0.5;
     s.kept = s.form == 1 && keeps_results(w.kind, w.dtype, w.P, length);
+    s.on_lines = HAVE_PIECES && s.form == 1 && !s.may_be_few && on_lines_pays(w.kind, w.dtype, w.reduced, length, w.segments, w.off_lines);
     s.run_log2 = one_turn ? run_log2_of(w.kind, w.dtype, w.P, w.off_lines) : int8_t{0};
     return s;
 }

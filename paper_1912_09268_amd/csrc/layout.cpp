@@ -89,7 +89,7 @@ int mgwfbp_build_tables(const uint64_t* n_elems, int32_t L, const uint8_t* merge
                 h.nseg = static_cast<int32_t>(e - s + 1);
                 h.valid = static_cast<int32_t>(valid);
                 h.layer0 = out.seg_layer[s];
-                h.flags = 0;
+                h.flags = hi < seg_hi(e) ? TILE_GOES_ON : 0;
                 out.tiles.push_back(h);
                 if (h.nseg > 1 || valid < TILE) ++out.seg_sums[e + 1].ragged;
             }

@@ -16,6 +16,41 @@ int main() {
             std::printf("%zu %zu\n", own, lds_for_workgroups_per_cu(cap, own));
         } else if (!std::strcmp(what, "have")) {      // have: what this build's tiles allow
             std::printf("%d %d %d\n", HAVE_PAIRS, HAVE_FEW, HAVE_PIECES);
+        } else if (!std::strcmp(what, "on_lines")) {  // on_lines kind dtype reduced tiles segments off_lines
+            LaunchWork w{};
+            int reduced;
+            if (std::scanf("%d %d %d %d %d %lf", &w.kind, &w.dtype, &reduced, &w.tiles, &w.segments, &w.off_lines) != 6) return 1;
+            w.P = 3;
+            w.reduced = reduced != 0;
+            std::printf("%d\n", launch_shape(LaunchSettings{}, w, 256).on_lines);
+        } else if (!std::strcmp(what, "cuts")) {      // cuts line L {n merged weights}...: tensor, begin and end of every tile's shares
+            int line, L;
+            if (std::scanf("%d %d", &line, &L) != 2) return 1;
+            std::vector<uint64_t> n(static_cast<size_t>(L)), weights(static_cast<size_t>(L));
+            std::vector<uint8_t> merged(static_cast<size_t>(L));
+            for (size_t i = 0; i < n.size(); ++i) {
+                unsigned long long elems, address;
+                int m;
+                if (std::scanf("%llu %d %llu", &elems, &m, &address) != 3) return 1;
+                n[i] = elems;
+                merged[i] = static_cast<uint8_t>(m);
+                weights[i] = address;
+            }
+            HostTables h;
+            if (mgwfbp_build_tables(n.data(), L, merged.data(), h) != MGWFBP_OK) return 1;
+            for (size_t t = 0; t < h.tiles.size(); ++t) {
+                const TileHdr& x = h.tiles[t];
+                const int64_t base = static_cast<int64_t>(t) * TILE;
+                auto early = [&](const TileHdr& y) { return starts_early(y.first_start, line_shift(weights[static_cast<size_t>(y.layer0)], y.first_start, line)); };
+                const int64_t end = x.valid - (x.flags & TILE_GOES_ON ? early(h.tiles[t + 1]) : 0);
+                for (int j = 0; j < x.nseg; ++j) {
+                    const size_t q = static_cast<size_t>(x.seg0 + j);
+                    const int64_t start = static_cast<int64_t>(h.seg_off[q]) - base, own = start + static_cast<int64_t>(h.seg_n[q]);
+                    const int64_t lo = start < 0 ? -early(x) : start, hi = own < end ? own : end;
+                    std::printf("%d %lld %lld ", h.seg_layer[q], static_cast<long long>(lo - start), static_cast<long long>(hi - start));
+                }
+            }
+            std::printf("\n");
         } else if (!std::strcmp(what, "kept")) {      // kept kind dtype P tiles: whether the results stay in the memory-side cache
             LaunchWork w{};
             if (std::scanf("%d %d %d %d", &w.kind, &w.dtype, &w.P, &w.tiles) != 4) return 1;

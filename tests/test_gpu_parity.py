@@ -648,6 +648,25 @@ def test_results_that_stay_in_the_memory_side_cache(P, dtype, tiles):
         check_case(p, [0] + [int(x) for x in rng.random(31) < 0.7], mode, misalign=3, label=f"{tiles} tiles")
 
 
+@pytest.mark.parametrize("P,dtype", [(1, "f32"), (3, "f32"), (8, "f16"), (16, "bf16"), (5, "bf16"), (2, "f16"), (4, "f32")])
+def test_shares_of_tiles_that_begin_on_lines(P, dtype):
+    """UPDATE and DIRECT over long models of odd sizes: tensors that begin and end one to 64 elements before and after the end of a tile,
+    of a few elements, of one tile and of many, one after the other and in groups of their own; more in a tile than are taken piece by
+    piece; some of the weights kept cacheable."""
+    rng = np.random.default_rng(22)
+    sizes = []
+    for _ in range(150):
+        sizes += [int(x) for x in rng.choice([1, 2, 3, 4, 5, 31, 33, 63, 64, 65, 129, 191, 193, 224, 253, 255, 256, 257, 300, 511, 512, 513, 700, 3000], 8)]
+        sizes.append(int(rng.integers(30000, 60000)) if len(sizes) % 5 else 256 * int(rng.integers(100, 250)) + int(rng.integers(-64, 65)))
+    L = len(sizes)
+    merged = [0] + [int(x) for x in rng.random(L - 1) < 0.7]
+    p = W.Profile("lines", np.asarray(sizes, np.uint64), rng.uniform(1e-6, 1e-5, L), 1e-4, 1e-9, P, dtype, 1.0)
+    check_case(p, merged, "direct", misalign=3, label="direct")
+    check_case(p, merged, "staged", misalign=3, label="staged")
+    check_case(p, merged, "direct", label="direct, tensors at the start of allocations")
+    check_case(p, merged, "direct", misalign=5, resident=10 << 20, label="direct, some of w and v resident")
+
+
 # ------------------------------------------------------------------------------------------
 # the benchmark configurations at full size, in the launch configuration bench.py times
 # ------------------------------------------------------------------------------------------

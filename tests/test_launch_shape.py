@@ -406,3 +406,43 @@ def test_results_stay_in_the_memory_side_cache_where_that_pays(ask):
         assert kept("reduce", dtype, most + 1, [100 * mib]) == [0]
     for kind in ("update", "reduce_update", "pipeline", "direct"):
         assert kept(kind, "f32", 4, [50 * mib, 100 * mib]) == [0, 0]
+
+
+@pytest.mark.parametrize("line", [32, 64])
+def test_shares_that_begin_on_lines_cover_every_element_once(ask, line):
+    """Where UPDATE and DIRECT cut the tensors: tensors of one element to several tiles, tiles with many of them, weights at any address.
+    Every element belongs to one tile, and every cut inside a tensor lies on a line of its weights."""
+    rng = np.random.default_rng(line)
+    lines, models = [], []
+    for _ in range(60):
+        L = int(rng.integers(1, 40))
+        n = [int(x) for x in rng.choice([0, 1, 2, 3, 5, 31, 33, 63, 64, 65, 191, 193, 224, 255, 256, 257, 511, 512, 513, 700, 3000], L)]
+        weights = [4 * int(x) for x in rng.integers(1 << 20, 1 << 30, L)]
+        merged = [0] + [int(x) for x in rng.random(L - 1) < 0.7]
+        models.append((n, weights))
+        lines.append(f"cuts {line} {L} " + " ".join(f"{a} {m} {w}" for a, m, w in zip(n, merged, weights)))
+    for (n, weights), out in zip(models, ask(lines)):
+        shares = {i: [] for i in range(len(n))}
+        for layer, lo, hi in zip(out[::3], out[1::3], out[2::3]):
+            assert lo <= hi
+            if lo < hi:
+                shares[layer].append((lo, hi))
+        for i, size in enumerate(n):
+            at = 0
+            for lo, hi in shares[i]:                   # in tile order
+                assert lo == at
+                at = hi
+                assert hi == size or (weights[i] // 4 + hi) % line == 0
+            assert at == size
+
+
+def test_shares_begin_on_lines_where_that_pays(ask):
+    """Long launches of UPDATE, and of DIRECT without the reduced arena, over models off their lines."""
+    def on_lines(kind, dtype, tiles, segments=100, off=0.5, reduced=0):
+        return ask([f"on_lines {KINDS.index(kind)} {DTYPES.index(dtype)} {reduced} {tiles} {segments} {off}"])[0][0]
+    for kind, dtype, least in (("update", "f32", 24576), ("update", "bf16", 24576), ("direct", "f32", 24576), ("direct", "f16", 16384), ("direct", "bf16", 16384)):
+        assert [on_lines(kind, dtype, t) for t in (least - 1, least)] == [0, 1]
+        assert [on_lines(kind, dtype, 32000, segments=x) for x in (2000, 2001)] == [1, 0]
+        assert [on_lines(kind, dtype, 100000, off=x) for x in (0.25, 0.26)] == [0, 1]
+    assert [on_lines("direct", d, 100000, reduced=1) for d in DTYPES] == [0, 0, 0]
+    assert [on_lines(k, "f32", 100000) for k in ("pack", "reduce", "reduce_update", "pipeline")] == [0, 0, 0, 0]
