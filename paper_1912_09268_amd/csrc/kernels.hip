@@ -49,7 +49,7 @@
 //     per die inside that window (unit_of());
 //   - 16-BIT GRADIENTS: a long pipeline launch takes two tiles per workgroup, 16 bytes of gradients per lane, so
 //     that a wavefront has as much under way as with binary32 (joined_tiles);
-//   - everything is streamed with non-temporal loads and stores, but for what the next step will find in the 256 MB
+//   - everything is streamed with non-temporal loads and stores (long binary32 launches also write through the L2, goes_through()), but for what the next step will find in the 256 MB
 //     memory-side cache: the results of PACK and REDUCE at the sizes where that pays (keeps_results()), and the leading share of
 //     the weights and momenta that a caller may ask for (tile flag);
 //   - PACK, which has no arithmetic across workers, runs as P single-worker copies (gridDim.y = P),
@@ -140,9 +140,13 @@ template <bool NT, typename V> __device__ __forceinline__ V ld(const void* p) {
     if constexpr (NT) return __builtin_nontemporal_load(q);
     else return *q;
 }
-template <bool NT, typename V> __device__ __forceinline__ void st(void* p, const V& x) {
+// THROUGH_L2: 16-byte vectors are written through the L2 (system scope) as well as streamed.  There is no builtin for that on vectors.  The no-op
+// is the two wait states gfx950 wants between a store of more than 8 bytes and the next write of its registers, which the compiler
+// sees to after the stores it knows.
+template <bool NT, typename V, bool THROUGH_L2 = false> __device__ __forceinline__ void st(void* p, const V& x) {
     MGWFBP_GLOBAL V* q = (MGWFBP_GLOBAL V*)p;
-    if constexpr (NT) __builtin_nontemporal_store(x, q);
+    if constexpr (NT && THROUGH_L2 && sizeof(V) == 16) asm volatile("global_store_dwordx4 %0, %1, off sc1 nt\n\ts_nop 1" ::"v"(q), "v"(x) : "memory");
+    else if constexpr (NT) __builtin_nontemporal_store(x, q);
     else *q = x;
 }
 
@@ -297,7 +301,7 @@ template <typename T> struct WorkerPtrs<T, 0> {
 __device__ __forceinline__ void pace() { __builtin_amdgcn_sched_barrier(0); }
 
 // the last part of a paced step: v, then w
-template <int N, bool WVNT, typename GradT, typename FV>
+template <int N, bool WVNT, bool THROUGH_L2, typename GradT, typename FV>
 __device__ __forceinline__ void update_step(const CallArgs<GradT>& A, float* wp, float* vp, int64_t soff, int stride,
                                             const FV* acc) {
     constexpr int C = Lanes<FV>::n;
@@ -311,7 +315,7 @@ __device__ __forceinline__ void update_step(const CallArgs<GradT>& A, float* wp,
             const float t1 = A.mu * comp(v[i], c);
             setc(v[i], c, t1 + comp(acc[i], c));
         }
-        st<WVNT, FV>(vp + soff + i * stride, v[i]);
+        st<WVNT, FV, THROUGH_L2>(vp + soff + i * stride, v[i]);
     }
     pace();
     FV w[N];
@@ -324,7 +328,7 @@ __device__ __forceinline__ void update_step(const CallArgs<GradT>& A, float* wp,
             const float t2 = A.lr * comp(v[i], c);
             setc(w[i], c, comp(w[i], c) - t2);
         }
-        st<WVNT, FV>(wp + soff + i * stride, w[i]);
+        st<WVNT, FV, THROUGH_L2>(wp + soff + i * stride, w[i]);
     }
 }
 
@@ -379,7 +383,7 @@ __device__ __forceinline__ void paced_step(const CallArgs<GradT>& A, const Worke
                 if constexpr (writes_merge(KIND)) {
                     GradT* to = mrg.get(w0 + j) + apos;
 #pragma unroll
-                    for (int i = 0; i < N; ++i) st<NT_ST && !kept(KIND), GV>(to + i * stride, g[j][i]);
+                    for (int i = 0; i < N; ++i) st<NT_ST && !kept(KIND), GV, through(KIND)>(to + i * stride, g[j][i]);
                 }
                 if constexpr (sums(KIND)) {
 #pragma unroll
@@ -420,7 +424,7 @@ __device__ __forceinline__ void paced_step(const CallArgs<GradT>& A, const Worke
     if constexpr (writes_reduced(KIND)) {
         if (reduces(KIND) || A.reduced != nullptr) {
 #pragma unroll
-            for (int i = 0; i < N; ++i) st<NT_ST && !kept(KIND), FV>(A.reduced + apos + i * stride, acc[i]);
+            for (int i = 0; i < N; ++i) st<NT_ST && !kept(KIND), FV, through(KIND)>(A.reduced + apos + i * stride, acc[i]);
         }
     }
     if constexpr (updates(KIND) && TOGETHER > 0) {
@@ -437,7 +441,7 @@ __device__ __forceinline__ void paced_step(const CallArgs<GradT>& A, const Worke
             st<WVNT, FV>(wp + soff + i * stride, w_early[i]);
         }
     } else if constexpr (updates(KIND)) {
-        update_step<N, WVNT>(A, wp, vp, soff, stride, acc);
+        update_step<N, WVNT, through(KIND)>(A, wp, vp, soff, stride, acc);
     }
 }
 // one vector or element of the general path
@@ -476,7 +480,7 @@ __device__ __forceinline__ void fast_chunk(const CallArgs<GradT>& A, const Worke
     // Left alone, the compiler sets up every arena's address plus this in front of the walk, two registers per worker: 138 for
     // binary32 reductions of 16 workers instead of 70 (4000 tiles over 150 tensors 17.0 us, so 12.5).  A direct step has no arenas, and is
     // faster as the compiler has it (bfloat16, 16 workers, 12,000 tiles 24.3 us, so 25.3).
-    if constexpr (KIND != K_DIRECT) here_only_per_lane(lane_elem);
+    if constexpr (!directs(KIND)) here_only_per_lane(lane_elem);
     const int64_t soff = tensor_off + lane_elem;    // this lane's first element: in its tensor
     const int64_t apos = tile_base + lane_elem;     //                            in the arena
     if constexpr (STEPV == 0) {
@@ -548,7 +552,7 @@ __device__ __forceinline__ void joined_tiles(const CallArgs<GradT>& A, const Wor
 #pragma unroll
             for (int i = 0; i < N; ++i) st<NT_ST, f32x4>(A.reduced + tile_base + lane_elem + i * BLOCK * VEC, acc[i]);
         }
-        update_step<N, true>(A, wp, vp, tensor_off + lane_elem, BLOCK * VEC, acc);
+        update_step<N, true, false>(A, wp, vp, tensor_off + lane_elem, BLOCK * VEC, acc);
     }
 }
 
@@ -875,7 +879,7 @@ template <int KIND, typename GradT, int PT, int FORM> constexpr int wanted_waves
 // a direct step of 16 where most tiles are ragged, which the launch says (thousands of tensors around 100 elements in groups of
 // four, 9700 / 17,200 / 37,300 tiles 33.9 / 35.6, 54.5 / 58.4, 106.6 / 116.3; around 230 and 400 elements level).
 template <int KIND, typename GradT, int PT, int FORM> constexpr int most_pieces() {
-    constexpr bool one = FORM != BURST && sizeof(GradT) == 2 && ((KIND == K_DIRECT && PT == 16) || (KIND == K_REDUCE_UPDATE && (PT == 8 || PT == 16)));
+    constexpr bool one = FORM != BURST && sizeof(GradT) == 2 && ((directs(KIND) && PT == 16) || (reduce_updates(KIND) && (PT == 8 || PT == 16)));
     return one ? 1 : MGWFBP_PIECES;
 }
 
@@ -923,7 +927,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_waves<ROLE, GradT, PT, K
         const int t_end = min((u + 1) * K, A.tile_count);
         for (int t = u * K; t < t_end; ++t) {
             int tile = A.tile_first + t;
-            if constexpr (KIND != K_DIRECT) here_only(tile);     // (addresses that run on from tile to tile would be set up, pointers waited for, first)
+            if constexpr (!directs(KIND)) here_only(tile);     // (addresses that run on from tile to tile would be set up, pointers waited for, first)
             const TileHdr h = load_header(A.tiles + tile);
             const int64_t tile_base = static_cast<int64_t>(tile) * TILE;
             const int clo = t == 0 ? A.clip_lo : 0;
@@ -981,7 +985,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_waves<ROLE, GradT, PT, K
                     }
                     continue;
                 }
-                if (!full && (!needs_owner(KIND) || h.nseg <= (KIND == K_DIRECT && MOST == 1 && (A.flags & IN_PIECES) ? MGWFBP_PIECES : MOST))) {
+                if (!full && (!needs_owner(KIND) || h.nseg <= (directs(KIND) && MOST == 1 && (A.flags & IN_PIECES) ? MGWFBP_PIECES : MOST))) {
                     pieces.seg = seg_tables(A);
                     several_pieces<KIND, GradT, PT>(A, mrg, tile_base, pieces);
                     continue;
@@ -1328,6 +1332,9 @@ int launch_one(const ArgsT<GradT>& A, hipStream_t stream, const LaunchShape& s, 
     }
     if constexpr (HAVE_PIECES && (KIND == K_UPDATE || KIND == K_DIRECT) && TABLE) {
         if (s.on_lines) return start<KIND, GradT, PT, ON_LINES>(A, stream, s, grid_y);
+    }
+    if constexpr (TVECS == 1 && TABLE && sizeof(GradT) == 4 && (KIND == K_REDUCE_UPDATE || KIND == K_DIRECT || KIND == K_PIPELINE)) {
+        if (s.through) return start<KIND, GradT, PT, THROUGH>(A, stream, s, grid_y);
     }
     if constexpr (TVECS % 2 == 0) {
         if (s.form == 2) return start<KIND, GradT, PT, 2>(A, stream, s, grid_y);

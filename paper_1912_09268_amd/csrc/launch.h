@@ -25,26 +25,36 @@ constexpr int MAXSEG = MGWFBP_MAXSEG;
 constexpr int PACK_TILES = MGWFBP_PACK_TILES;
 
 enum Kind { K_PACK = 0, K_REDUCE = 1, K_UPDATE = 2, K_REDUCE_UPDATE = 3, K_PIPELINE = 4, K_DIRECT = 5,
-            K_PACK_KEPT = 6, K_REDUCE_KEPT = 7 };      // what PACK and REDUCE are in kernels of the form KEPT
+            // what kinds are in kernels of the forms KEPT and THROUGH
+            K_PACK_KEPT = 6, K_REDUCE_KEPT = 7, K_REDUCE_UPDATE_THROUGH = 8, K_PIPELINE_THROUGH = 9, K_DIRECT_THROUGH = 10 };
 
 constexpr bool packs(int k) { return k == K_PACK || k == K_PACK_KEPT; }
 constexpr bool reduces(int k) { return k == K_REDUCE || k == K_REDUCE_KEPT; }
 constexpr bool kept(int k) { return k == K_PACK_KEPT || k == K_REDUCE_KEPT; }
-constexpr bool reads_grads(int k) { return packs(k) || k == K_PIPELINE || k == K_DIRECT; }
-constexpr bool reads_merge(int k) { return reduces(k) || k == K_REDUCE_UPDATE; }
-constexpr bool writes_merge(int k) { return packs(k) || k == K_PIPELINE; }
-constexpr bool sums(int k) { return reduces(k) || k == K_REDUCE_UPDATE || k == K_PIPELINE || k == K_DIRECT; }
-constexpr bool writes_reduced(int k) { return reduces(k) || k == K_PIPELINE || k == K_DIRECT; }
-constexpr bool updates(int k) { return k == K_UPDATE || k == K_REDUCE_UPDATE || k == K_PIPELINE || k == K_DIRECT; }
+constexpr bool through(int k) { return k >= K_REDUCE_UPDATE_THROUGH; }
+constexpr bool reduce_updates(int k) { return k == K_REDUCE_UPDATE || k == K_REDUCE_UPDATE_THROUGH; }
+constexpr bool pipelines(int k) { return k == K_PIPELINE || k == K_PIPELINE_THROUGH; }
+constexpr bool directs(int k) { return k == K_DIRECT || k == K_DIRECT_THROUGH; }
+constexpr bool reads_grads(int k) { return packs(k) || pipelines(k) || directs(k); }
+constexpr bool reads_merge(int k) { return reduces(k) || reduce_updates(k); }
+constexpr bool writes_merge(int k) { return packs(k) || pipelines(k); }
+constexpr bool sums(int k) { return reduces(k) || reduce_updates(k) || pipelines(k) || directs(k); }
+constexpr bool writes_reduced(int k) { return reduces(k) || pipelines(k) || directs(k); }
+constexpr bool updates(int k) { return k == K_UPDATE || reduce_updates(k) || pipelines(k) || directs(k); }
 constexpr bool needs_owner(int k) { return !reduces(k); }
 
 // Forms of the fast path, beside the number of vectors per lane of a paced step (1 and up).
 constexpr int BURST = 0;              // every load of a tile under way at once
 constexpr int PAIRS = -1;             // two full tiles of one tensor in one step, single ones in paced steps of one vector
 constexpr int KEPT = -2;              // PACK and REDUCE in paced steps of one vector whose results stay in the memory-side cache, see keeps_results()
-constexpr int kind_in(int kind, int form) { return form != KEPT ? kind : kind == K_PACK ? K_PACK_KEPT : K_REDUCE_KEPT; }
+constexpr int THROUGH = -4;           // binary32 pipelines, reduce_updates and direct updates in paced steps of one vector that write through the L2, see goes_through()
+constexpr int kind_in(int kind, int form) {
+    if (form == KEPT) return kind == K_PACK ? K_PACK_KEPT : K_REDUCE_KEPT;
+    if (form == THROUGH) return kind == K_REDUCE_UPDATE ? K_REDUCE_UPDATE_THROUGH : kind == K_PIPELINE ? K_PIPELINE_THROUGH : K_DIRECT_THROUGH;
+    return kind;
+}
 constexpr int ON_LINES = -3;          // UPDATE and DIRECT in paced steps of one vector that begin on lines of the weights, see on_lines_pays()
-constexpr bool single_steps(int form) { return form == 1 || form == KEPT || form == ON_LINES; }
+constexpr bool single_steps(int form) { return form == 1 || form == KEPT || form == ON_LINES || form == THROUGH; }
 constexpr int PAIR = 2;
 constexpr int PAIRED = PAIR * TILE;   // elements of a pair
 // What needs tiles of one vector per lane, and of one wavefront, is left out of builds with other tiles.
@@ -399,6 +409,22 @@ inline bool keeps_results(int kind, int32_t dtype, int32_t P, int32_t tiles) {
     return kind == K_REDUCE && merged <= 4 * reduced && reduced >= 80 * MiB && reduced <= 512 * MiB;
 }
 
+// Binary32 launches whose vectors are written through the L2 to memory (system scope) as well as streamed: the L2 then does not choose when
+// a line leaves it, and the write stream stays in the order of the walk.  Time over streamed alone, models on their lines, 1 / 3 / 4 / 8 / 16 / 32
+// workers:
+//    66,000 tiles  pipeline 0.991 / 0.987 / 0.989 / 0.988 / 0.987 / 0.991, reduce_update 1.001 / 0.996 / 0.974 / 0.986 / 0.992 / 0.997, direct 1.010 / 0.991 /
+//                  0.961 / 0.974 / 0.984 / 0.995
+//   200,000 tiles  pipeline 0.976 / 0.981 / 0.993 / 0.980 / 0.984 / 0.988, reduce_update 0.984 / 0.996 / 0.983 / 0.985 / 0.991 / 0.994, direct 0.993 / 0.992 /
+//                  0.977 / 0.991 / 0.992 / 0.995
+//   500,000 tiles  pipeline 0.971 / 0.985 / 0.988 / 0.989 / 0.996 / 0.997, reduce_update 0.990 / 0.988 / 0.989 / 0.993 / 0.991 / 0.997, direct 0.993 / 0.997 /
+//                  0.982 / 0.993 / 0.991 / 0.995; VGG-16 shape, pipeline 0.982 to 0.996 from box to box
+// Shorter, pipeline 30,000 tiles 1.00-1.02.  bfloat16 is level (pipeline 0.995-1.005, reduce_update and direct 0.98-1.01), UPDATE and REDUCE are 0.98-1.01, and PACK
+// and models off their lines lose (PACK 1.02-1.08, a thousand small layers 1.02: two tiles write a part of a line each, which the L2 joins).
+inline bool goes_through(int kind, int32_t dtype, int32_t tiles, double off_lines, double ragged) {
+    if (dtype != MGWFBP_F32 || (kind != K_REDUCE_UPDATE && kind != K_DIRECT && kind != K_PIPELINE)) return false;
+    return tiles >= LONG_LAUNCH_TILES / 4 && off_lines <= 0.25 && ragged < 0.025;
+}
+
 // What a caller has fixed (mgwfbp_ctx_set_*); the initial values are the library's defaults.
 struct LaunchSettings {
     int32_t blocks_per_cu = 0;        // > 0: a persistent grid of that many workgroups per compute unit.  0 = one workgroup
@@ -445,6 +471,7 @@ struct LaunchShape {
     int32_t wgs_per_cu;               // workgroups that may share a compute unit; <= 0: no cap
     bool rolling;                     // two loads under way in a step (see rolls())
     bool on_lines;                    // steps begin on lines of the weights (see on_lines_pays())
+    bool through;                     // vectors are written through the L2 (see goes_through())
     bool kept;                        // the results stay in the memory-side cache (see keeps_results())
     bool in_pieces;                   // ragged tiles piece by piece also where the kernel would rather not (see most_pieces())
 };
@@ -499,6 +526,7 @@ inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, 
     }
     s.rolling = may_roll(w.kind, s.form) && set.step_vecs == 0 && set.wg_per_cu == 0 && rolls(w.dtype, w.P, s.may_be_few, per_cu);
     s.in_pieces = w.ragged > 0.5;
+    s.through = s.form == 1 && !s.may_be_few && !s.on_lines && goes_through(w.kind, w.dtype, length, w.off_lines, w.ragged);
     s.kept = s.form == 1 && keeps_results(w.kind, w.dtype, w.P, length);
     s.on_lines = HAVE_PIECES && s.form == 1 && !s.may_be_few && on_lines_pays(w.kind, w.dtype, w.reduced, length, w.segments, w.off_lines);
     s.run_log2 = one_turn ? run_log2_of(w.kind, w.dtype, w.P, w.off_lines) : int8_t{0};

@@ -23,6 +23,11 @@ int main() {
             w.P = 3;
             w.reduced = reduced != 0;
             std::printf("%d\n", launch_shape(LaunchSettings{}, w, 256).on_lines);
+        } else if (!std::strcmp(what, "through")) {   // through kind dtype tiles off_lines ragged segments
+            LaunchWork w{};
+            if (std::scanf("%d %d %d %lf %lf %d", &w.kind, &w.dtype, &w.tiles, &w.off_lines, &w.ragged, &w.segments) != 6) return 1;
+            w.P = 8;
+            std::printf("%d\n", launch_shape(LaunchSettings{}, w, 256).through);
         } else if (!std::strcmp(what, "cuts")) {      // cuts line L {n merged weights}...: tensor, begin and end of every tile's shares
             int line, L;
             if (std::scanf("%d %d", &line, &L) != 2) return 1;

@@ -667,6 +667,20 @@ def test_shares_of_tiles_that_begin_on_lines(P, dtype):
     check_case(p, merged, "direct", misalign=5, resident=10 << 20, label="direct, some of w and v resident")
 
 
+@pytest.mark.parametrize("P", [1, 2, 3, 4])
+def test_long_binary32_launches_that_write_through_the_l2(P):
+    """The shortest such launches, with ragged tiles of one and of several tensors between the large ones (8 and 16 workers: the profiles
+    below).  Every store is followed by writes to its registers at the shortest distance there is."""
+    rng = np.random.default_rng(23)
+    small = [int(x) for x in rng.integers(1, 3000, 40)]
+    sizes = [1 << 20, *small[:20], 65536 * 200, *small[20:], 1 << 21, 64]
+    p = W.Profile("through", np.asarray(sizes, np.uint64), rng.uniform(1e-6, 1e-5, len(sizes)), 1e-4, 1e-9, P, "f32", 1.0)
+    merged = [0] + [int(x) for x in rng.random(len(sizes) - 1) < 0.7]
+    for mode in ("pipeline", "pipeline_no_reduced", "reduce_update", "direct"):
+        check_case(p, merged, mode, label=mode)
+    check_case(p, merged, "pipeline", resident=4 << 20, label="some of w and v resident")
+
+
 # ------------------------------------------------------------------------------------------
 # the benchmark configurations at full size, in the launch configuration bench.py times
 # ------------------------------------------------------------------------------------------

@@ -446,3 +446,16 @@ def test_shares_begin_on_lines_where_that_pays(ask):
         assert [on_lines(kind, dtype, 100000, off=x) for x in (0.25, 0.26)] == [0, 1]
     assert [on_lines("direct", d, 100000, reduced=1) for d in DTYPES] == [0, 0, 0]
     assert [on_lines(k, "f32", 100000) for k in ("pack", "reduce", "reduce_update", "pipeline")] == [0, 0, 0, 0]
+
+
+def test_long_binary32_launches_write_through_the_l2(ask):
+    """From a quarter of LONG_LAUNCH_TILES on, models on their lines with few ragged tiles, in the table form."""
+    def through(kind, dtype="f32", tiles=65536, off=0.0, ragged=0.0, segments=100):
+        return ask([f"through {KINDS.index(kind)} {DTYPES.index(dtype)} {tiles} {off} {ragged} {segments}"])[0][0]
+    for kind in ("reduce_update", "pipeline", "direct"):
+        assert [through(kind, tiles=t) for t in (65535, 65536, 1000000)] == [0, 1, 1]
+        assert [through(kind, off=x) for x in (0.25, 0.26)] == [1, 0]
+        assert [through(kind, ragged=x) for x in (0.024, 0.025)] == [1, 0]
+        assert [through(kind, segments=x) for x in (8, 9)] == [0, 1]
+        assert [through(kind, dtype=d) for d in DTYPES] == [1, 0, 0]
+    assert [through(k) for k in ("pack", "reduce", "update")] == [0, 0, 0]
