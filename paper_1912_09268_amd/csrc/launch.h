@@ -310,7 +310,9 @@ constexpr int line_elems(int kind, size_t grad_bytes) { return 128 / static_cast
 //                      8 workers  8000 0.94 / 0.97 / 1.02 / 1.00    20,000 0.91 / 0.93 / 1.01 / 1.00    100,000 0.92 / 0.93 / 1.01 / 1.00
 //                      16 workers 8000 0.87 / 0.93 / 1.03 / 1.00    20,000 0.84 / 0.90 / 1.01 / 1.00    100,000 0.88 / 0.91 / 1.00 / 1.00
 // With 12,000 tensors of 100,000 tiles, update 0.97 / 0.98 / 1.01 / 1.01, direct 8 workers 0.97 / 0.98 / 1.02 / 1.02 and bfloat16 0.93 / 0.94 / 1.02 / 1.01; the
-// tiles a tensor begins or ends in take a step more.  The pipeline would have its arenas off the lines instead (0.84-0.97 of the rate), reduce_update
+// tiles a tensor begins or ends in take a step more.  Over the few tensors of the few-segments form (five odd ones as views / one that begins
+// off its lines), against that form: 40,000 tiles, binary32 update 0.97 / 0.94, direct 1 / 8 / 16 workers 0.97 / 0.94, 0.95 / 0.94, 0.94 / 0.94, bfloat16
+// 0.98 / 0.93, 0.93 / 0.85, 0.90 / 0.79.  The pipeline would have its arenas off the lines instead (0.84-0.97 of the rate), reduce_update
 // gains with one or two 16-bit workers only.
 inline bool on_lines_pays(int kind, int32_t dtype, bool reduced, int32_t tiles, int32_t segments, double off_lines) {
     if (kind != K_UPDATE && (kind != K_DIRECT || reduced)) return false;
@@ -515,6 +517,10 @@ inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, 
     const bool one_turn = s.grid == s.units && !s.xcd_contiguous;
     s.may_be_few = HAVE_FEW && one_turn && !(updates(w.kind) && set.resident_bytes > 0) && (w.segments <= FEW || !needs_owner(w.kind)) &&
                    few_form_pays(w.kind, w.dtype, w.P, length, w.segments, per_cu);
+    // Forms of long launches, in the table form only.
+    s.on_lines = HAVE_PIECES && s.form == 1 && on_lines_pays(w.kind, w.dtype, w.reduced, length, w.segments, w.off_lines);
+    if (s.on_lines) s.may_be_few = false;
+    s.through = s.form == 1 && !s.may_be_few && !s.on_lines && goes_through(w.kind, w.dtype, length, w.off_lines, w.ragged);
     // With the form, the workgroups that may share a compute unit set the loads it has in flight (1 KiB of a binary32 array
     // per vector of a step and workgroup, half that of a 16-bit one).
     s.wgs_per_cu = set.wg_per_cu;
@@ -526,9 +532,7 @@ inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, 
     }
     s.rolling = may_roll(w.kind, s.form) && set.step_vecs == 0 && set.wg_per_cu == 0 && rolls(w.dtype, w.P, s.may_be_few, per_cu);
     s.in_pieces = w.ragged > 0.5;
-    s.through = s.form == 1 && !s.may_be_few && !s.on_lines && goes_through(w.kind, w.dtype, length, w.off_lines, w.ragged);
     s.kept = s.form == 1 && keeps_results(w.kind, w.dtype, w.P, length);
-    s.on_lines = HAVE_PIECES && s.form == 1 && !s.may_be_few && on_lines_pays(w.kind, w.dtype, w.reduced, length, w.segments, w.off_lines);
     s.run_log2 = one_turn ? run_log2_of(w.kind, w.dtype, w.P, w.off_lines) : int8_t{0};
     return s;
 }

@@ -665,6 +665,9 @@ def test_shares_of_tiles_that_begin_on_lines(P, dtype):
     check_case(p, merged, "staged", misalign=3, label="staged")
     check_case(p, merged, "direct", label="direct, tensors at the start of allocations")
     check_case(p, merged, "direct", misalign=5, resident=10 << 20, label="direct, some of w and v resident")
+    few = W.Profile("lines", np.asarray([256 * 12000 - 1, 77, 256 * 13000 + 191], np.uint64), p.t_backward[:3], 1e-4, 1e-9, P, dtype, 1.0)
+    check_case(few, [0, 1, 1], "direct", misalign=3, label="direct, three tensors")
+    check_case(few, [0, 1, 1], "staged", misalign=3, label="staged, three tensors")
 
 
 @pytest.mark.parametrize("P", [1, 2, 3, 4])

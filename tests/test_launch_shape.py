@@ -444,6 +444,7 @@ def test_shares_begin_on_lines_where_that_pays(ask):
         assert [on_lines(kind, dtype, t) for t in (least - 1, least)] == [0, 1]
         assert [on_lines(kind, dtype, 32000, segments=x) for x in (2000, 2001)] == [1, 0]
         assert [on_lines(kind, dtype, 100000, off=x) for x in (0.25, 0.26)] == [0, 1]
+        assert [on_lines(kind, dtype, 100000, segments=x) for x in (1, 8, 9)] == [1, 1, 1]          # in the table form, also where the other could take it
     assert [on_lines("direct", d, 100000, reduced=1) for d in DTYPES] == [0, 0, 0]
     assert [on_lines(k, "f32", 100000) for k in ("pack", "reduce", "reduce_update", "pipeline")] == [0, 0, 0, 0]
 
