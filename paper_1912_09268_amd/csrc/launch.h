@@ -419,7 +419,7 @@ inline bool keeps_results(int kind, int32_t dtype, int32_t P, int32_t tiles) {
 //   200,000 tiles  pipeline 0.976 / 0.981 / 0.993 / 0.980 / 0.984 / 0.988, reduce_update 0.984 / 0.996 / 0.983 / 0.985 / 0.991 / 0.994, direct 0.993 / 0.992 /
 //                  0.977 / 0.991 / 0.992 / 0.995
 //   500,000 tiles  pipeline 0.971 / 0.985 / 0.988 / 0.989 / 0.996 / 0.997, reduce_update 0.990 / 0.988 / 0.989 / 0.993 / 0.991 / 0.997, direct 0.993 / 0.997 /
-//                  0.982 / 0.993 / 0.991 / 0.995; VGG-16 shape, pipeline 0.982 to 0.996 from box to box
+//                  0.982 / 0.993 / 0.991 / 0.995; VGG-16 shape, pipeline 0.982 to 0.996 in several runs
 // Shorter, pipeline 30,000 tiles 1.00-1.02.  bfloat16 is level (pipeline 0.995-1.005, reduce_update and direct 0.98-1.01), UPDATE and REDUCE are 0.98-1.01, and PACK
 // and models off their lines lose (PACK 1.02-1.08, a thousand small layers 1.02: two tiles write a part of a line each, which the L2 joins).
 inline bool goes_through(int kind, int32_t dtype, int32_t tiles, double off_lines, double ragged) {
