@@ -50,7 +50,7 @@
 //   - 16-BIT GRADIENTS: a long pipeline launch takes two tiles per workgroup, 16 bytes of gradients per lane, so
 //     that a wavefront has as much under way as with binary32 (joined_tiles);
 //   - everything is streamed with non-temporal loads and stores (long binary32 launches also write through the L2, goes_through()), but for what the next step will find in the 256 MB
-//     memory-side cache: the results of PACK and REDUCE at the sizes where that pays (keeps_results()), and the leading share of
+//     memory-side cache: the results of REDUCE at the sizes where that pays (keeps_results()), and the leading share of
 //     the weights and momenta that a caller may ask for (tile flag);
 //   - PACK, which has no arithmetic across workers, runs as P single-worker copies (gridDim.y = P),
 //     so the chip streams 2 arrays at a time instead of 2P; a workgroup copies 1 to 4 KiB of its worker's data,
@@ -246,7 +246,7 @@ template <typename GradT> __device__ __forceinline__ SegTables seg_tables(const 
 // streams one worker's gradients at a time (2 streams instead of 2P), which the memory system serves
 // faster.
 template <int KIND> __device__ __forceinline__ int worker_base() {
-    return packs(KIND) ? static_cast<int>(blockIdx.y) : 0;
+    return KIND == K_PACK ? static_cast<int>(blockIdx.y) : 0;
 }
 
 // Pointers of the P workers, either held in registers (P known at compile time) or re-read from the
@@ -383,7 +383,7 @@ __device__ __forceinline__ void paced_step(const CallArgs<GradT>& A, const Worke
                 if constexpr (writes_merge(KIND)) {
                     GradT* to = mrg.get(w0 + j) + apos;
 #pragma unroll
-                    for (int i = 0; i < N; ++i) st<NT_ST && !kept(KIND), GV, through(KIND)>(to + i * stride, g[j][i]);
+                    for (int i = 0; i < N; ++i) st<NT_ST, GV, through(KIND)>(to + i * stride, g[j][i]);
                 }
                 if constexpr (sums(KIND)) {
 #pragma unroll
@@ -424,7 +424,7 @@ __device__ __forceinline__ void paced_step(const CallArgs<GradT>& A, const Worke
     if constexpr (writes_reduced(KIND)) {
         if (reduces(KIND) || A.reduced != nullptr) {
 #pragma unroll
-            for (int i = 0; i < N; ++i) st<NT_ST && !kept(KIND), FV, through(KIND)>(A.reduced + apos + i * stride, acc[i]);
+            for (int i = 0; i < N; ++i) st<NT_ST && KIND != K_REDUCE_KEPT, FV, through(KIND)>(A.reduced + apos + i * stride, acc[i]);
         }
     }
     if constexpr (updates(KIND) && TOGETHER > 0) {
@@ -510,7 +510,7 @@ __device__ __forceinline__ void joined_tiles(const CallArgs<GradT>& A, const Wor
     src.fetch(A.grad_ptrs, A.L, layer, worker_base<KIND>());
     int lane_elem = static_cast<int>(threadIdx.x) * VEC;
     here_only_per_lane(lane_elem);
-    if constexpr (packs(KIND)) {
+    if constexpr (KIND == K_PACK) {
         paced_step<KIND, GradT, PT, VEC, PACK_TILES * TVECS, true>(A, src, mrg, nullptr, nullptr, tensor_off + lane_elem,
                                                              tile_base + lane_elem, BLOCK * VEC);
     } else {
@@ -1072,7 +1072,7 @@ template <typename GradT> __device__ __forceinline__ FewSeg few_owner(const FewA
 // earlier; where they do not, the single tensors of long launches have the scalar registers.  us with the ends in the general
 // part only / with the other arguments, burst form: three tensors of 300 elements, 8 workers, binary32: pipeline 2.63 / 2.40,
 // reduce_update 2.55 / 2.36; seven of 9 to 2000, 16 workers, bfloat16: 4.05 / 3.55, 3.37 / 3.02; pack 2.56 / 2.25.
-constexpr bool ends_early(int kind, int form) { return form == BURST || packs(kind); }
+constexpr bool ends_early(int kind, int form) { return form == BURST || kind == K_PACK; }
 
 // One tile of the few-segments form (of PACK or in pairs: a joined step); the tiles taken.
 template <int KIND, typename GradT, int PT, int FORM>
@@ -1196,7 +1196,7 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_few_waves<ROLE, GradT, P
         // A further tile, where the caller asked for several: the arguments again, so that no path keeps them, or what the
         // compiler works out from them beforehand, in registers for it (10 scalar registers).  PACK takes several by itself and
         // has the registers (bfloat16, 32 workers, 40,000 tiles 198 us, with the arguments again 212).
-        if constexpr (!packs(KIND)) {
+        if constexpr (KIND != K_PACK) {
             asm volatile("" : "+s"(a));
             A = *(const FewArgs<GradT>*)a;
         }
@@ -1327,7 +1327,7 @@ int launch_one(const ArgsT<GradT>& A, hipStream_t stream, const LaunchShape& s, 
         if (s.form == BURST) return start<KIND, GradT, PT, BURST>(A, stream, s, grid_y);
     }
     constexpr bool TABLE = !std::is_same<ArgsT<GradT>, FewArgs<GradT>>::value;
-    if constexpr (HAVE_KEPT && (KIND == K_PACK || (KIND == K_REDUCE && TABLE && PT * sizeof(GradT) <= 16))) {
+    if constexpr (HAVE_KEPT && KIND == K_REDUCE && TABLE && PT * sizeof(GradT) <= 16) {
         if (s.kept) return start<KIND, GradT, PT, KEPT>(A, stream, s, grid_y);
     }
     if constexpr (HAVE_PIECES && (KIND == K_UPDATE || KIND == K_DIRECT) && TABLE) {

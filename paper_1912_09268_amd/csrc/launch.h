@@ -26,18 +26,16 @@ constexpr int PACK_TILES = MGWFBP_PACK_TILES;
 
 enum Kind { K_PACK = 0, K_REDUCE = 1, K_UPDATE = 2, K_REDUCE_UPDATE = 3, K_PIPELINE = 4, K_DIRECT = 5,
             // what kinds are in kernels of the forms KEPT and THROUGH
-            K_PACK_KEPT = 6, K_REDUCE_KEPT = 7, K_REDUCE_UPDATE_THROUGH = 8, K_PIPELINE_THROUGH = 9, K_DIRECT_THROUGH = 10 };
+            K_REDUCE_KEPT = 6, K_REDUCE_UPDATE_THROUGH = 7, K_PIPELINE_THROUGH = 8, K_DIRECT_THROUGH = 9 };
 
-constexpr bool packs(int k) { return k == K_PACK || k == K_PACK_KEPT; }
 constexpr bool reduces(int k) { return k == K_REDUCE || k == K_REDUCE_KEPT; }
-constexpr bool kept(int k) { return k == K_PACK_KEPT || k == K_REDUCE_KEPT; }
 constexpr bool through(int k) { return k >= K_REDUCE_UPDATE_THROUGH; }
 constexpr bool reduce_updates(int k) { return k == K_REDUCE_UPDATE || k == K_REDUCE_UPDATE_THROUGH; }
 constexpr bool pipelines(int k) { return k == K_PIPELINE || k == K_PIPELINE_THROUGH; }
 constexpr bool directs(int k) { return k == K_DIRECT || k == K_DIRECT_THROUGH; }
-constexpr bool reads_grads(int k) { return packs(k) || pipelines(k) || directs(k); }
+constexpr bool reads_grads(int k) { return k == K_PACK || pipelines(k) || directs(k); }
 constexpr bool reads_merge(int k) { return reduces(k) || reduce_updates(k); }
-constexpr bool writes_merge(int k) { return packs(k) || pipelines(k); }
+constexpr bool writes_merge(int k) { return k == K_PACK || pipelines(k); }
 constexpr bool sums(int k) { return reduces(k) || reduce_updates(k) || pipelines(k) || directs(k); }
 constexpr bool writes_reduced(int k) { return reduces(k) || pipelines(k) || directs(k); }
 constexpr bool updates(int k) { return k == K_UPDATE || reduce_updates(k) || pipelines(k) || directs(k); }
@@ -46,10 +44,10 @@ constexpr bool needs_owner(int k) { return !reduces(k); }
 // Forms of the fast path, beside the number of vectors per lane of a paced step (1 and up).
 constexpr int BURST = 0;              // every load of a tile under way at once
 constexpr int PAIRS = -1;             // two full tiles of one tensor in one step, single ones in paced steps of one vector
-constexpr int KEPT = -2;              // PACK and REDUCE in paced steps of one vector whose results stay in the memory-side cache, see keeps_results()
+constexpr int KEPT = -2;              // REDUCE in paced steps of one vector whose results stay in the memory-side cache, see keeps_results()
 constexpr int THROUGH = -4;           // binary32 pipelines, reduce_updates and direct updates in paced steps of one vector that write through the L2, see goes_through()
 constexpr int kind_in(int kind, int form) {
-    if (form == KEPT) return kind == K_PACK ? K_PACK_KEPT : K_REDUCE_KEPT;
+    if (form == KEPT) return K_REDUCE_KEPT;
     if (form == THROUGH) return kind == K_REDUCE_UPDATE ? K_REDUCE_UPDATE_THROUGH : kind == K_PIPELINE ? K_PIPELINE_THROUGH : K_DIRECT_THROUGH;
     return kind;
 }
@@ -74,7 +72,7 @@ constexpr bool HAVE_KEPT = TVECS == 1;
 // joined step, whose sums change hands through LDS, the single-tile kernel would need the joined one's 96 registers instead of 59 (16
 // workers; 63 instead of 43 with 8) and as uncapped launches hold 20 instead of 24 wavefronts per compute unit (16
 // workers, 6000 tiles: 30.0 us against 23.4, at 16 against 24 wavefronts).
-constexpr int joined_tiles_of(int kind, int form) { return form == PAIRS ? PAIR : packs(kind) && form != BURST ? PACK_TILES : 1; }
+constexpr int joined_tiles_of(int kind, int form) { return form == PAIRS ? PAIR : kind == K_PACK && form != BURST ? PACK_TILES : 1; }
 
 // Dynamic LDS per workgroup that lets at most n workgroups share the 160 KiB of a compute unit.  A workgroup's
 // LDS (static + dynamic) is granted in blocks of 1280 bytes (a 128th of the compute unit's; seen in the cap
@@ -391,23 +389,19 @@ inline bool even_rounds(int kind, int32_t dtype, int32_t P, bool few, int form, 
     return per_cu > held && (per_cu + held - 1) / held == (per_cu + 23) / 24;
 }
 
-// Whether what a long PACK or REDUCE writes stays in the 256 MB memory-side cache for the step that reads it: stored with ordinary
-// stores it does, streamed it passes by.  PACK's stores then take longer (1.04-1.14 of a PACK repeated by itself, 1.1-1.37 where
-// most tiles are ragged), and the reduction that follows gains more, as long as a good part of the arenas fits.  Time over streamed, P merge arenas of
-// 24 / 50 / 100 / 200 / 400 / 600 / 800 MB together, 150 tensors, pack and reduce_update: binary32 1 worker 1.05 / 1.02 / 0.98 / 0.95 / 0.97 / 1.00 /
-// 1.01, 2 workers 1.00 / 1.00 / 0.97 / 0.94 / 0.96 / 0.99 / 1.00, 8 workers 1.02 / 0.99 / 0.97 / 0.94 / 0.94 / 0.97 / 0.99, 32 workers 0.98 / 0.98 / 0.92 / 0.92 /
-// 0.96 / 0.98 / 1.00; bfloat16 2 workers 1.01 / 0.97 / 0.96 / 0.95 / 0.98 / 1.00 / 1.01, 8 workers 1.06 / 0.99 / 0.96 / 0.93 / 0.98 / 0.99 / 1.01, 32 workers 1.11 /
-// 0.98 / 0.96 / 0.95 / 0.98 / 1.01 / 1.04; models of tensors around 500 elements, a group each, 60 / 120 / 200 / 300 MB, binary32 8 workers 0.97 / 0.96 /
-// 0.95 / 0.96, bfloat16 0.99 / 0.95 / 0.93 / 0.95.  In short launches what the stores leave in the L2s is written back when the kernel ends.  One
-// worker's gradients are packed for an exchange, not for a reduction here.
-// REDUCE pays where the reduced arena is no small part of what it moves and unpack_update follows: the three steps, reduced arena of
-// 48 / 72 / 100 / 200 / 400 / 800 MB, binary32 1 worker 0.99 / 0.98 / 0.97 / 0.95 / 0.96 / 0.98, 4 workers 1.00 / 0.97 / 0.98 / 0.98 / 1.00 / -, bfloat16 1
-// worker 1.01 / 0.98 / 0.97 / 0.95 / 0.98 / 1.02, 4 workers 0.98 / 0.98 / 0.98 / 0.97 / 1.00 / 1.01, 8 workers 0.99 / 1.02 / 0.98 / 0.98 / 0.99 / -, 16 workers 1.00-1.01.
+// Whether what a long REDUCE writes stays in the 256 MB memory-side cache for the step that reads it: stored with ordinary
+// stores it does, streamed it passes by.  That pays where the reduced arena is no small part of what it moves and unpack_update follows:
+// the three steps, reduced arena of 48 / 72 / 100 / 200 / 400 / 800 MB, binary32 1 worker 0.99 / 0.98 / 0.97 / 0.95 / 0.96 / 0.98, 4 workers 1.00 / 0.97 /
+// 0.98 / 0.98 / 1.00 / -, bfloat16 1 worker 1.01 / 0.98 / 0.97 / 0.95 / 0.98 / 1.02, 4 workers 0.98 / 0.98 / 0.98 / 0.97 / 1.00 / 1.01, 8 workers 0.99 / 1.02 / 0.98 /
+// 0.98 / 0.99 / -, 16 workers 1.00-1.01.
+// Not PACK, whose arenas an exchange reads first.  Time with ordinary stores over streamed, merge arenas of 60 / 120 / 200 / 300 MB together, from an
+// emptied cache | repeated over three sets of buffers; 150 even tensors, binary32 8 workers: PACK 0.95 / 0.97 / 0.98 / 0.98 | 1.01 / 1.04 / 1.02 / 1.03, a copy
+// of the arenas and reduce_update after it 0.95 / 0.92 / 1.02 / 1.04 | 0.90 / 0.98 / 1.11 / 1.05, reduce_update right after it 0.97 / 0.98 / 0.99 / 0.99 | 0.97 /
+// 0.95 / 0.95 / 0.95; tensors around 500 elements, a group each, bfloat16 16 workers: PACK 1.01 / 1.00 / 0.99 / 1.00 | 1.02 / 1.17 / 1.25 / -, with the copy
+// 1.06 / 1.09 / 1.12 / - | 1.06 / 1.15 / 1.10 / -, without 1.04 / 1.02 / 1.02 / - | 1.00 / 0.97 / 0.94 / -.
 inline bool keeps_results(int kind, int32_t dtype, int32_t P, int32_t tiles) {
     constexpr int64_t MiB = 1 << 20;
-    const bool wide = dtype == MGWFBP_F32;
-    const int64_t reduced = static_cast<int64_t>(tiles) * 1024, merged = reduced * P / (wide ? 1 : 2);      // bytes
-    if (kind == K_PACK) return P > 1 && merged >= 48 * MiB && merged <= (wide || P < 16 ? 448 : 320) * MiB;
+    const int64_t reduced = static_cast<int64_t>(tiles) * 1024, merged = reduced * P / (dtype == MGWFBP_F32 ? 1 : 2);      // bytes
     return kind == K_REDUCE && merged <= 4 * reduced && reduced >= 80 * MiB && reduced <= 512 * MiB;
 }
 

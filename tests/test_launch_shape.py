@@ -388,24 +388,20 @@ def test_launches_of_mostly_ragged_tiles_go_in_pieces(ask):
     assert [bool(s.in_pieces) for s in shapes(ask, [dict(kind="direct", dtype="bf16", P=16, ragged=r) for r in (0.0, 0.5, 0.51, 1.0)])] == [False, False, True, True]
 
 
-def test_results_stay_in_the_memory_side_cache_where_that_pays(ask):
-    """Packed arenas of 48 to 448 MiB together (320 with many workers' 16-bit gradients) and reduced ones of 80 to 512 MiB that are
-    at least a quarter of the merge arenas' size; the other kinds have no such kernels."""
+def test_results_stay_in_the_memory_side_cache_where_that_pays(ask, kernels):
+    """Reduced arenas of 80 to 512 MiB that are at least a quarter of the merge arenas' size; the other kinds, PACK among them, have no
+    such kernels."""
     def kept(kind, dtype, P, tiles):
         return [x[0] for x in ask([f"kept {KINDS.index(kind)} {DTYPES.index(dtype)} {P} {t}" for t in tiles])]
     mib = 1024                                    # tiles whose binary32 elements take one
-    for P in (2, 8, 32):
-        edges = [48 * mib // P, 448 * mib // P]
-        assert kept("pack", "f32", P, [edges[0] - 1, edges[0], edges[1], edges[1] + 1]) == [0, 1, 1, 0]
-    assert kept("pack", "f16", 4, [24 * mib - 1, 24 * mib, 224 * mib, 224 * mib + 1]) == [0, 1, 1, 0]
-    assert kept("pack", "bf16", 16, [6 * mib - 1, 6 * mib, 40 * mib, 40 * mib + 1]) == [0, 1, 1, 0]
-    assert kept("pack", "f32", 1, [100 * mib]) == [0]
     for dtype, most in (("f32", 4), ("bf16", 8), ("f16", 8)):
         for P in (1, most):
             assert kept("reduce", dtype, P, [80 * mib - 1, 80 * mib, 512 * mib, 512 * mib + 1]) == [0, 1, 1, 0]
         assert kept("reduce", dtype, most + 1, [100 * mib]) == [0]
-    for kind in ("update", "reduce_update", "pipeline", "direct"):
-        assert kept(kind, "f32", 4, [50 * mib, 100 * mib]) == [0, 0]
+    for kind in ("pack", "update", "reduce_update", "pipeline", "direct"):
+        for P in (1, 2, 4, 8, 32):
+            assert kept(kind, "f32", P, [8 * mib, 50 * mib, 100 * mib]) == [0, 0, 0]
+    assert not [k for k in kernels if k.form == -2 and KINDS[k.kind] != "reduce"]
 
 
 @pytest.mark.parametrize("line", [32, 64])
