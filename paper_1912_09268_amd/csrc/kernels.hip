@@ -49,9 +49,9 @@
 //     per die inside that window (unit_of());
 //   - 16-BIT GRADIENTS: a long pipeline launch takes two tiles per workgroup, 16 bytes of gradients per lane, so
 //     that a wavefront has as much under way as with binary32 (joined_tiles);
-//   - everything is streamed with non-temporal loads and stores (long binary32 launches also write through the L2, goes_through()), but for what the next step will find in the 256 MB
-//     memory-side cache: the results of REDUCE at the sizes where that pays (keeps_results()), and the leading share of
-//     the weights and momenta that a caller may ask for (tile flag);
+//   - everything is streamed with non-temporal loads and stores (long binary32 launches also write through the L2, goes_through());
+//     a caller may ask for a leading share of the weights and momenta to use ordinary accesses and stay in the 256 MB memory-side
+//     cache (tile flag);
 //   - PACK, which has no arithmetic across workers, runs as P single-worker copies (gridDim.y = P),
 //     so the chip streams 2 arrays at a time instead of 2P; a workgroup copies 1 to 4 KiB of its worker's data,
 //     two tiles per step (more per workgroup stretches the window its compute unit covers and costs 8 %).
@@ -422,9 +422,9 @@ __device__ __forceinline__ void paced_step(const CallArgs<GradT>& A, const Worke
         for (int i = 0; i < N; ++i) acc[i] = ld<NT_LD, FV>(A.reduced + apos + i * stride);
     }
     if constexpr (writes_reduced(KIND)) {
-        if (reduces(KIND) || A.reduced != nullptr) {
+        if (KIND == K_REDUCE || A.reduced != nullptr) {
 #pragma unroll
-            for (int i = 0; i < N; ++i) st<NT_ST && KIND != K_REDUCE_KEPT, FV, through(KIND)>(A.reduced + apos + i * stride, acc[i]);
+            for (int i = 0; i < N; ++i) st<NT_ST, FV, through(KIND)>(A.reduced + apos + i * stride, acc[i]);
         }
     }
     if constexpr (updates(KIND) && TOGETHER > 0) {
@@ -1327,9 +1327,6 @@ int launch_one(const ArgsT<GradT>& A, hipStream_t stream, const LaunchShape& s, 
         if (s.form == BURST) return start<KIND, GradT, PT, BURST>(A, stream, s, grid_y);
     }
     constexpr bool TABLE = !std::is_same<ArgsT<GradT>, FewArgs<GradT>>::value;
-    if constexpr (HAVE_KEPT && KIND == K_REDUCE && TABLE && PT * sizeof(GradT) <= 16) {
-        if (s.kept) return start<KIND, GradT, PT, KEPT>(A, stream, s, grid_y);
-    }
     if constexpr (HAVE_PIECES && (KIND == K_UPDATE || KIND == K_DIRECT) && TABLE) {
         if (s.on_lines) return start<KIND, GradT, PT, ON_LINES>(A, stream, s, grid_y);
     }

@@ -25,41 +25,37 @@ constexpr int MAXSEG = MGWFBP_MAXSEG;
 constexpr int PACK_TILES = MGWFBP_PACK_TILES;
 
 enum Kind { K_PACK = 0, K_REDUCE = 1, K_UPDATE = 2, K_REDUCE_UPDATE = 3, K_PIPELINE = 4, K_DIRECT = 5,
-            // what kinds are in kernels of the forms KEPT and THROUGH
-            K_REDUCE_KEPT = 6, K_REDUCE_UPDATE_THROUGH = 7, K_PIPELINE_THROUGH = 8, K_DIRECT_THROUGH = 9 };
+            // what kinds are in kernels of the form THROUGH
+            K_REDUCE_UPDATE_THROUGH = 6, K_PIPELINE_THROUGH = 7, K_DIRECT_THROUGH = 8 };
 
-constexpr bool reduces(int k) { return k == K_REDUCE || k == K_REDUCE_KEPT; }
 constexpr bool through(int k) { return k >= K_REDUCE_UPDATE_THROUGH; }
 constexpr bool reduce_updates(int k) { return k == K_REDUCE_UPDATE || k == K_REDUCE_UPDATE_THROUGH; }
 constexpr bool pipelines(int k) { return k == K_PIPELINE || k == K_PIPELINE_THROUGH; }
 constexpr bool directs(int k) { return k == K_DIRECT || k == K_DIRECT_THROUGH; }
 constexpr bool reads_grads(int k) { return k == K_PACK || pipelines(k) || directs(k); }
-constexpr bool reads_merge(int k) { return reduces(k) || reduce_updates(k); }
+constexpr bool reads_merge(int k) { return k == K_REDUCE || reduce_updates(k); }
 constexpr bool writes_merge(int k) { return k == K_PACK || pipelines(k); }
-constexpr bool sums(int k) { return reduces(k) || reduce_updates(k) || pipelines(k) || directs(k); }
-constexpr bool writes_reduced(int k) { return reduces(k) || pipelines(k) || directs(k); }
+constexpr bool sums(int k) { return k == K_REDUCE || reduce_updates(k) || pipelines(k) || directs(k); }
+constexpr bool writes_reduced(int k) { return k == K_REDUCE || pipelines(k) || directs(k); }
 constexpr bool updates(int k) { return k == K_UPDATE || reduce_updates(k) || pipelines(k) || directs(k); }
-constexpr bool needs_owner(int k) { return !reduces(k); }
+constexpr bool needs_owner(int k) { return k != K_REDUCE; }
 
 // Forms of the fast path, beside the number of vectors per lane of a paced step (1 and up).
 constexpr int BURST = 0;              // every load of a tile under way at once
 constexpr int PAIRS = -1;             // two full tiles of one tensor in one step, single ones in paced steps of one vector
-constexpr int KEPT = -2;              // REDUCE in paced steps of one vector whose results stay in the memory-side cache, see keeps_results()
-constexpr int THROUGH = -4;           // binary32 pipelines, reduce_updates and direct updates in paced steps of one vector that write through the L2, see goes_through()
+constexpr int THROUGH = -3;           // binary32 pipelines, reduce_updates and direct updates in paced steps of one vector that write through the L2, see goes_through()
 constexpr int kind_in(int kind, int form) {
-    if (form == KEPT) return K_REDUCE_KEPT;
     if (form == THROUGH) return kind == K_REDUCE_UPDATE ? K_REDUCE_UPDATE_THROUGH : kind == K_PIPELINE ? K_PIPELINE_THROUGH : K_DIRECT_THROUGH;
     return kind;
 }
-constexpr int ON_LINES = -3;          // UPDATE and DIRECT in paced steps of one vector that begin on lines of the weights, see on_lines_pays()
-constexpr bool single_steps(int form) { return form == 1 || form == KEPT || form == ON_LINES || form == THROUGH; }
+constexpr int ON_LINES = -2;          // UPDATE and DIRECT in paced steps of one vector that begin on lines of the weights, see on_lines_pays()
+constexpr bool single_steps(int form) { return form == 1 || form == ON_LINES || form == THROUGH; }
 constexpr int PAIR = 2;
 constexpr int PAIRED = PAIR * TILE;   // elements of a pair
 // What needs tiles of one vector per lane, and of one wavefront, is left out of builds with other tiles.
 constexpr bool HAVE_PAIRS = TVECS == 1;
 constexpr bool HAVE_FEW = TVECS == 1 && BLOCK == 64;
 constexpr bool HAVE_PIECES = TVECS == 1 && BLOCK == 64;
-constexpr bool HAVE_KEPT = TVECS == 1;
 // Most segments of a tile that the table form takes piece by piece; the walk over the pieces costs 0.15 us each, the general
 // path's prefix sum and search the same for any number.  us with one, up to three and up to eight, 8 workers, tensors in
 // groups of eight and more: of 301 elements pipeline 7.2 / 6.4 / 6.4, unpack_update 4.6 / 4.0 / 4.0; of 70 elements pipeline 7.4 /
@@ -389,21 +385,25 @@ inline bool even_rounds(int kind, int32_t dtype, int32_t P, bool few, int form, 
     return per_cu > held && (per_cu + held - 1) / held == (per_cu + 23) / 24;
 }
 
-// Whether what a long REDUCE writes stays in the 256 MB memory-side cache for the step that reads it: stored with ordinary
-// stores it does, streamed it passes by.  That pays where the reduced arena is no small part of what it moves and unpack_update follows:
-// the three steps, reduced arena of 48 / 72 / 100 / 200 / 400 / 800 MB, binary32 1 worker 0.99 / 0.98 / 0.97 / 0.95 / 0.96 / 0.98, 4 workers 1.00 / 0.97 /
-// 0.98 / 0.98 / 1.00 / -, bfloat16 1 worker 1.01 / 0.98 / 0.97 / 0.95 / 0.98 / 1.02, 4 workers 0.98 / 0.98 / 0.98 / 0.97 / 1.00 / 1.01, 8 workers 0.99 / 1.02 / 0.98 /
-// 0.98 / 0.99 / -, 16 workers 1.00-1.01.
-// Not PACK, whose arenas an exchange reads first.  Time with ordinary stores over streamed, merge arenas of 60 / 120 / 200 / 300 MB together, from an
-// emptied cache | repeated over three sets of buffers; 150 even tensors, binary32 8 workers: PACK 0.95 / 0.97 / 0.98 / 0.98 | 1.01 / 1.04 / 1.02 / 1.03, a copy
-// of the arenas and reduce_update after it 0.95 / 0.92 / 1.02 / 1.04 | 0.90 / 0.98 / 1.11 / 1.05, reduce_update right after it 0.97 / 0.98 / 0.99 / 0.99 | 0.97 /
-// 0.95 / 0.95 / 0.95; tensors around 500 elements, a group each, bfloat16 16 workers: PACK 1.01 / 1.00 / 0.99 / 1.00 | 1.02 / 1.17 / 1.25 / -, with the copy
-// 1.06 / 1.09 / 1.12 / - | 1.06 / 1.15 / 1.10 / -, without 1.04 / 1.02 / 1.02 / - | 1.00 / 0.97 / 0.94 / -.
-inline bool keeps_results(int kind, int32_t dtype, int32_t P, int32_t tiles) {
-    constexpr int64_t MiB = 1 << 20;
-    const int64_t reduced = static_cast<int64_t>(tiles) * 1024, merged = reduced * P / (dtype == MGWFBP_F32 ? 1 : 2);      // bytes
-    return kind == K_REDUCE && merged <= 4 * reduced && reduced >= 80 * MiB && reduced <= 512 * MiB;
-}
+// Results are streamed by every kind, also those that the next step reads.  Ordinary stores would leave them in the 256 MB memory-side cache, but
+// that pays only where nothing lies between the steps, and then reduce_update or the pipeline does them in one pass; a caller of single steps has
+// the exchange in between, and PACK and REDUCE themselves take longer.  Time with ordinary stores over streamed, repeated
+// over three sets of buffers | from an emptied cache:
+//   REDUCE, 150 even tensors, reduced arena of 120 / 200 / 300 / 500 MiB
+//     binary32 1 worker    by itself 1.00 / 1.02 / 1.04 / 1.03 | 0.96 / 0.95 / 0.95 / 0.96, unpack_update right after it 0.95 / 0.94 / 0.95 / 0.99 | 0.98 / 0.97 / 0.98 /
+//                          1.00, a copy of the arena in between 1.04 / 1.05 / 1.01 / 1.02 | 0.92 / 1.02 / 1.02 / 1.01
+//     binary32 4 workers   1.04 / 1.05 / 1.04 / 1.03 | 1.00 / 1.00 / 1.00 / 0.99, 0.96 / 0.96 / 0.98 / 1.00 | 1.00 / 0.99 / 1.00 / 1.01, 1.04 / 1.03 / 1.02 / 1.02 |
+//                          0.94 / 1.02 / 1.02 / 1.01
+//     bfloat16 1 worker    1.12 / 1.17 / 1.16 / 1.14 | 0.98 / 0.98 / 0.98 / 0.98, 0.96 / 0.95 / 0.98 / 1.01 | 1.00 / 0.98 / 1.00 / 1.01, 1.06 / 1.06 / 1.02 / 1.02 | 0.92 /
+//                          1.02 / 1.03 / 1.01
+//     bfloat16 8 workers   1.06 / 1.05 / 1.05 / 1.05 | 1.08 / 1.07 / 1.07 / 1.05, 0.97 / 0.96 / 0.98 / 1.00 | 1.04 / 1.03 / 1.03 / 1.03, 1.03 / 1.06 / 1.03 / 1.05 | 0.98 /
+//                          1.05 / 1.05 / 1.03
+//     tensors around 500 elements, a group each, 82 / 140 / 220 / 320 MiB, bfloat16 4 workers   1.02 / 1.34 / 1.34 / 1.38 | 1.03 / 1.03 / 1.04 / 1.11, 0.96 / 0.95 / 0.93 /
+//                          0.97 | 1.01 / 1.01 / 1.00 / 1.04, 1.06 / 1.08 / 1.07 / 1.06 | 1.02 / 1.06 / 1.07 / 1.07
+//   PACK, merge arenas of 60 / 120 / 200 / 300 MB together, 150 even tensors, binary32 8 workers: by itself 1.01 / 1.04 / 1.02 / 1.03 | 0.95 / 0.97 / 0.98 / 0.98, a
+//   copy of the arenas and reduce_update after it 0.90 / 0.98 / 1.11 / 1.05 | 0.95 / 0.92 / 1.02 / 1.04, reduce_update right after it 0.97 / 0.95 / 0.95 / 0.95 | 0.97 /
+//   0.98 / 0.99 / 0.99; tensors around 500 elements, a group each, bfloat16 16 workers: PACK 1.02 / 1.17 / 1.25 / - | 1.01 / 1.00 / 0.99 / 1.00, with the copy
+//   1.06 / 1.15 / 1.10 / - | 1.06 / 1.09 / 1.12 / -, without 1.00 / 0.97 / 0.94 / - | 1.04 / 1.02 / 1.02 / -.
 
 // Binary32 launches whose vectors are written through the L2 to memory (system scope) as well as streamed: the L2 then does not choose when
 // a line leaves it, and the write stream stays in the order of the walk.  Time over streamed alone, models on their lines, 1 / 3 / 4 / 8 / 16 / 32
@@ -468,7 +468,6 @@ struct LaunchShape {
     bool rolling;                     // two loads under way in a step (see rolls())
     bool on_lines;                    // steps begin on lines of the weights (see on_lines_pays())
     bool through;                     // vectors are written through the L2 (see goes_through())
-    bool kept;                        // the results stay in the memory-side cache (see keeps_results())
     bool in_pieces;                   // ragged tiles piece by piece also where the kernel would rather not (see most_pieces())
 };
 
@@ -526,7 +525,6 @@ inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, 
     }
     s.rolling = may_roll(w.kind, s.form) && set.step_vecs == 0 && set.wg_per_cu == 0 && rolls(w.dtype, w.P, s.may_be_few, per_cu);
     s.in_pieces = w.ragged > 0.5;
-    s.kept = s.form == 1 && keeps_results(w.kind, w.dtype, w.P, length);
     s.run_log2 = one_turn ? run_log2_of(w.kind, w.dtype, w.P, w.off_lines) : int8_t{0};
     return s;
 }

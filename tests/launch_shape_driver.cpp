@@ -56,11 +56,6 @@ int main() {
                 }
             }
             std::printf("\n");
-        } else if (!std::strcmp(what, "kept")) {      // kept kind dtype P tiles: whether the results stay in the memory-side cache
-            LaunchWork w{};
-            if (std::scanf("%d %d %d %d", &w.kind, &w.dtype, &w.P, &w.tiles) != 4) return 1;
-            w.segments = 1000;
-            std::printf("%d\n", launch_shape(LaunchSettings{}, w, 256).kept);
         } else if (!std::strcmp(what, "shape")) {     // shape <work> <settings> n_cu
             LaunchWork w{};
             LaunchSettings set;

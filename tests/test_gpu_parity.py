@@ -638,12 +638,12 @@ def test_long_launches_over_ragged_models(P, dtype, median):
 
 @pytest.mark.parametrize("P,dtype,tiles", [(2, "f32", 24 * 1024), (5, "f16", 20 * 1024), (16, "bf16", 6 * 1024), (1, "f32", 80 * 1024), (3, "bf16", 80 * 1024),
                                            (8, "f16", 80 * 1024)])
-def test_results_that_stay_in_the_memory_side_cache(P, dtype, tiles):
-    """REDUCE at the smallest sizes whose results are stored for the next step to find in the cache, and PACK of 48 MiB together, over one
-    tensor and odd ones of a few elements to a third of the model."""
+def test_packs_and_reductions_of_many_mebibytes(P, dtype, tiles):
+    """PACK of merge arenas of 48 MiB and more together and REDUCE to arenas of 6 to 80 MiB, over one tensor and odd ones of a few elements to a
+    third of the model."""
     rng = np.random.default_rng(21)
     small = [int(x) for x in rng.integers(1, 3000, 30)]
-    p = W.Profile("kept", np.asarray([tiles * 256 * 2 // 3, *small, tiles * 256 // 3 + 17], np.uint64), rng.uniform(1e-6, 1e-5, 32), 1e-4, 1e-9, P, dtype, 1.0)
+    p = W.Profile("mebibytes", np.asarray([tiles * 256 * 2 // 3, *small, tiles * 256 // 3 + 17], np.uint64), rng.uniform(1e-6, 1e-5, 32), 1e-4, 1e-9, P, dtype, 1.0)
     for mode in ("staged", "reduce_update") if P > 1 else ("staged",):
         check_case(p, [0] + [int(x) for x in rng.random(31) < 0.7], mode, misalign=3, label=f"{tiles} tiles")
 

@@ -388,20 +388,10 @@ def test_launches_of_mostly_ragged_tiles_go_in_pieces(ask):
     assert [bool(s.in_pieces) for s in shapes(ask, [dict(kind="direct", dtype="bf16", P=16, ragged=r) for r in (0.0, 0.5, 0.51, 1.0)])] == [False, False, True, True]
 
 
-def test_results_stay_in_the_memory_side_cache_where_that_pays(ask, kernels):
-    """Reduced arenas of 80 to 512 MiB that are at least a quarter of the merge arenas' size; the other kinds, PACK among them, have no
-    such kernels."""
-    def kept(kind, dtype, P, tiles):
-        return [x[0] for x in ask([f"kept {KINDS.index(kind)} {DTYPES.index(dtype)} {P} {t}" for t in tiles])]
-    mib = 1024                                    # tiles whose binary32 elements take one
-    for dtype, most in (("f32", 4), ("bf16", 8), ("f16", 8)):
-        for P in (1, most):
-            assert kept("reduce", dtype, P, [80 * mib - 1, 80 * mib, 512 * mib, 512 * mib + 1]) == [0, 1, 1, 0]
-        assert kept("reduce", dtype, most + 1, [100 * mib]) == [0]
-    for kind in ("pack", "update", "reduce_update", "pipeline", "direct"):
-        for P in (1, 2, 4, 8, 32):
-            assert kept(kind, "f32", P, [8 * mib, 50 * mib, 100 * mib]) == [0, 0, 0]
-    assert not [k for k in kernels if k.form == -2 and KINDS[k.kind] != "reduce"]
+def test_pack_and_reduce_have_no_kernels_of_another_store_policy(kernels):
+    """Both stream what they write at every size, in kernels of the burst form and of paced steps of one vector only."""
+    assert {k.form for k in kernels if KINDS[k.kind] == "pack"} == {SINGLE}
+    assert {k.form for k in kernels if KINDS[k.kind] == "reduce"} == {BURST, SINGLE}
 
 
 @pytest.mark.parametrize("line", [32, 64])
