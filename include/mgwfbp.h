@@ -210,8 +210,10 @@ int mgwfbp_ctx_tables(const mgwfbp_ctx* ctx, int32_t* n_segments, void* tiles_ou
 
 /* Launch shape.  A tile is 256 consecutive arena elements.  By default a call launches one workgroup of 64 lanes
  * (one wavefront) per tile it covers; mgwfbp_pack, which runs as P single-worker copies, gives a workgroup one to
- * eight tiles of its worker's data and a long pipeline launch on 16-bit gradients two, and a launch whose tiles mostly
- * start inside the 128-byte lines of its tensors deals runs of 4 or 8 consecutive tiles to each accelerator die.
+ * eight tiles of its worker's data and a long pipeline launch on 16-bit gradients two.  Where the tiles of a launch mostly
+ * start inside the 128-byte lines of its tensors, it may deal runs of 4 or 8 consecutive tiles to each accelerator die, and
+ * in long launches of mgwfbp_unpack_update, and of mgwfbp_direct_update without `reduced`, a workgroup's share of a
+ * tensor begins at the last line of the weights before its tile, up to 63 elements early.
  *   blocks_per_cu > 0        caps the grid at compute units * blocks_per_cu workgroups, which then stride
  *                            over the work; <= 0 restores the default
  *   xcd_contiguous != 0      renumbers workgroups so that each of the 8 accelerator dies walks one

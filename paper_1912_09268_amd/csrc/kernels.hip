@@ -1471,7 +1471,7 @@ int run(mgwfbp_ctx* c, int32_t group, const void* const* grad_ptrs, void* const*
         const CallArgs<GradT> call{reinterpret_cast<const GradT* const*>(grad_ptrs), reinterpret_cast<GradT* const*>(merge_bufs),
                                    reduced, w_ptrs, v_ptrs, lr, mu, inv_p, c->host.L, c->P, sp.t0, count,
                                    static_cast<int16_t>(s.tiles_per_wg),
-                                   static_cast<int8_t>((s.xcd_contiguous ? XCD_CONTIGUOUS : 0) | (s.rolling ? ROLLING : 0) | (s.in_pieces ? IN_PIECES : 0)), s.on_lines ? int8_t{0} : s.run_log2};
+                                   static_cast<int8_t>((s.xcd_contiguous ? XCD_CONTIGUOUS : 0) | (s.rolling ? ROLLING : 0) | (s.in_pieces ? IN_PIECES : 0)), s.run_log2};
         return launch<KIND, GradT>(c, sp, tiles, call, stream, s);
     };
     if (c->dtype == MGWFBP_F32) return go(float{});

@@ -303,11 +303,18 @@ constexpr int line_elems(int kind, size_t grad_bytes) { return 128 / static_cast
 //   bfloat16   direct, 3 workers  8000 0.95 / 0.95 / 1.03 / 1.00    20,000 0.95 / 0.95 / 1.00 / 1.00    100,000 0.93 / 0.95 / 1.00 / 1.00
 //                      8 workers  8000 0.94 / 0.97 / 1.02 / 1.00    20,000 0.91 / 0.93 / 1.01 / 1.00    100,000 0.92 / 0.93 / 1.01 / 1.00
 //                      16 workers 8000 0.87 / 0.93 / 1.03 / 1.00    20,000 0.84 / 0.90 / 1.01 / 1.00    100,000 0.88 / 0.91 / 1.00 / 1.00
-// With 12,000 tensors of 100,000 tiles, update 0.97 / 0.98 / 1.01 / 1.01, direct 8 workers 0.97 / 0.98 / 1.02 / 1.02 and bfloat16 0.93 / 0.94 / 1.02 / 1.01; the
-// tiles a tensor begins or ends in take a step more.  Over the few tensors of the few-segments form (five odd ones as views / one that begins
-// off its lines), against that form: 40,000 tiles, binary32 update 0.97 / 0.94, direct 1 / 8 / 16 workers 0.97 / 0.94, 0.95 / 0.94, 0.94 / 0.94, bfloat16
-// 0.98 / 0.93, 0.93 / 0.85, 0.90 / 0.79.  The pipeline would have its arenas off the lines instead (0.84-0.97 of the rate), reduce_update
-// gains with one or two 16-bit workers only.
+// (those without runs; see runs_on_lines()).  With 12,000 tensors of 100,000 tiles, update 0.97 / 0.98 / 1.01 / 1.01, direct 8 workers 0.97 / 0.98 / 1.02 / 1.02 and
+// bfloat16 0.93 / 0.94 / 1.02 / 1.01; the tiles a tensor begins or ends in take a step more.  The lines lie where a group each in allocations of their own, which the
+// host takes for views, no longer pays: at 24,600 tiles update 1.00, direct binary32 1 / 3 / 8 / 16 workers 1.01 / 1.00 / 1.00 / 1.00, bfloat16 at 16,400 1.00-1.01 (4 workers
+// between 18,500 and 25,500 tiles 0.98-1.05, the others 1.00-1.01).
+// Over the few tensors of the few-segments form, against that form, one large odd one behind a small one / five as views / five in allocations of their own:
+//   16,400 tiles  direct, bfloat16 1 / 4 / 8 / 16 workers 0.97 / 0.98 / 0.98, 0.91 / 0.97 / 0.96, 0.86 / 0.97 / 0.92, 0.79 / 0.95 / 0.86
+//   20,000        the same 0.98 / 0.98 / 0.98, 0.95 / 0.99 / 0.98, 0.91 / 0.99 / 0.96, 0.82 / 0.94 / 0.89
+//   24,600        the same 0.96 / 0.97 / 0.98, 0.92 / 0.94 / 0.94, 0.90 / 0.91 / 0.93, 0.82 / 0.88 / 0.89; binary32 update 0.96 / 0.99 / 0.98, direct 1 / 8 / 16 workers 0.97 /
+//                 0.97 / 0.98, 0.95 / 0.95 / 0.95, 0.92 / 0.96 / 0.94
+//   40,000        the same 0.94 / 0.95 / 0.97, 0.89 / 0.92 / 0.93, 0.86 / 0.90 / 0.90, 0.79 / 0.87 / 0.85; 0.95 / 0.97 / 0.97, 0.95 / 0.95 / 0.96, 0.94 / 0.93 / 0.94, 0.95 / 0.94 / 0.93
+// Eight odd tensors, a group each, in allocations of their own pay 1-4 % with bfloat16 of up to 8 workers to 24,600 tiles (20,000: 1 / 4 / 8 workers 1.04 / 1.02 / 1.03) and gain 0-5 %
+// from 30,000 on.  The pipeline would have its arenas off the lines instead (0.84-0.97 of the rate), reduce_update gains with one or two 16-bit workers only.
 inline bool on_lines_pays(int kind, int32_t dtype, bool reduced, int32_t tiles, int32_t segments, double off_lines) {
     if (kind != K_UPDATE && (kind != K_DIRECT || reduced)) return false;
     const int32_t least = kind == K_DIRECT && dtype != MGWFBP_F32 ? SHORT_LAUNCH_TILES : SHORT_LAUNCH_TILES / 2 * 3;
@@ -337,6 +344,30 @@ inline bool few_form_pays(int kind, int32_t dtype, int32_t P, int32_t tiles, int
     const int64_t copies = static_cast<int64_t>(tiles) * P;
     if (kind == K_PACK) return copies <= 4096 || copies > FEW_COPIES;
     return tiles <= 3072 || (per_cu > 24 && per_cu <= 32) || (per_cu > 48 && per_cu <= 56);
+}
+
+// Which of the launches that begin on lines have runs of tiles per die all the same.  No line is shared any more, but two dies still take turns in the pages; time with runs over
+// without, tensors as views / in allocations of their own in groups of five / a group each / eight a group each, at 30,000, 50,000, 70,000 and 140,000 tiles
+// (50,000: the first, third and fourth):
+//   update                     0.986 / 0.978 / 1.002 / 1.007    0.977 / 0.996 / 1.006    0.970 / 0.978 / 0.987 / 1.002    0.976 / 0.984 / 1.014 / 1.009
+//   direct  binary32, 1        0.996 / 0.993 / 1.003 / 1.014    0.983 / 0.990 / 1.015    0.959 / 0.960 / 0.955 / 0.998    0.975 / 0.976 / 0.975 / 1.005
+//           binary32, 3        1.000 / 0.996 / 1.002 / 1.020    1.007 / 1.012 / 1.021    1.001 / 1.005 / 0.999 / 1.012    1.019 / 1.030 / 1.030 / 1.023
+//           binary32, 8        1.004 / 1.000 / 1.013 / 1.030             -               1.020 / 1.031 / 1.022 / 1.034    1.016 / 1.027 / 1.036 / 1.037
+//           bfloat16, 1        0.986 / 0.993 / 1.006 / 1.026    0.979 / 0.993 / 1.006    0.961 / 0.961 / 0.955 / 0.983    0.968 / 0.967 / 0.971 / 0.987
+//           bfloat16, 3        0.994 / 1.002 / 1.004 / 1.012    0.981 / 0.991 / 1.011    0.962 / 0.967 / 0.962 / 0.983    0.975 / 0.974 / 0.976 / 0.996
+//           bfloat16, 8        0.993 / 0.997 / 1.002 / 1.015    0.990 / 0.993 / 1.006    0.979 / 0.981 / 0.981 / 0.992    0.990 / 0.988 / 0.996 / 0.998
+//           bfloat16, 16       0.996 / 0.997 / 1.003 / 1.014    0.989 / 0.990 / 1.024    0.988 / 0.986 / 0.992 / 1.000    0.989 / 0.991 / 0.991 / 1.005
+//           bfloat16, 32       0.994 / 0.998 / 1.002 / 1.041             -               0.981 / 0.985 / 0.993 / 0.995    0.994 / 0.995 / 0.988 / 1.008
+// Few tensors gain less: eight a group each and five as views at 52,000 tiles 1.00-1.02 throughout, at 70,000 and 100,000 update 1.002 / 0.982, 1.012 / 0.980, bfloat16
+// 8 workers 0.997 / 0.999, 1.009 / 0.997, 16 workers 1.002 / 1.018, 1.016 / 1.018, binary32 of one worker 0.99-1.00,
+// at 200,000 1.008 / 1.014.  Updates of 200,000 tiles are 0.984 / 0.985 / 1.029 / 1.022, other direct steps of one worker level again.  Time over the
+// tiles cut in the arena with their runs, a group each in allocations of their own, which are on lines in truth, 60,000 to 140,000 tiles: direct binary32 of one
+// worker and bfloat16 of 1 to 6 1.02-1.055 without runs here, 1.00 with them.
+inline bool runs_on_lines(int kind, int32_t dtype, int32_t P, int32_t tiles, int32_t segments) {
+    const bool few = segments <= FEW;
+    if (tiles < (few ? 4 : 3) * SHORT_LAUNCH_TILES) return false;
+    if (kind == K_UPDATE) return !few && tiles <= LONG_LAUNCH_TILES / 2;
+    return dtype == MGWFBP_F32 ? P == 1 && !few : P <= (few ? 7 : 16);
 }
 
 // Kernels with rolling steps beside the single ones (see rolling_tile).
@@ -461,7 +492,7 @@ struct LaunchWork {
 struct LaunchShape {
     int32_t tiles_per_wg, units, grid;
     int8_t xcd_contiguous;
-    int8_t run_log2;                  // a die's turn is 2^run_log2 consecutive units (not where shares begin on lines)
+    int8_t run_log2;                  // a die's turn is 2^run_log2 consecutive units
     bool may_be_few;                  // the few-segments form may take it
     int form;                         // BURST, PAIRS or the vectors per lane of a paced step
     int32_t wgs_per_cu;               // workgroups that may share a compute unit; <= 0: no cap
@@ -525,7 +556,7 @@ inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, 
     }
     s.rolling = may_roll(w.kind, s.form) && set.step_vecs == 0 && set.wg_per_cu == 0 && rolls(w.dtype, w.P, s.may_be_few, per_cu);
     s.in_pieces = w.ragged > 0.5;
-    s.run_log2 = one_turn ? run_log2_of(w.kind, w.dtype, w.P, w.off_lines) : int8_t{0};
+    s.run_log2 = one_turn && !(s.on_lines && !runs_on_lines(w.kind, w.dtype, w.P, length, w.segments)) ? run_log2_of(w.kind, w.dtype, w.P, w.off_lines) : int8_t{0};
     return s;
 }
 

@@ -435,6 +435,25 @@ def test_shares_begin_on_lines_where_that_pays(ask):
     assert [on_lines(k, "f32", 100000) for k in ("pack", "reduce", "reduce_update", "pipeline")] == [0, 0, 0, 0]
 
 
+def test_runs_per_die_of_launches_that_begin_on_lines(ask):
+    """They stay in the longer ones of updates, of direct steps of one binary32 worker and of up to 16 16-bit ones (over few tensors: of
+    up to 7 16-bit ones); shorter launches, and those of other kinds and of the table form, are as the rule of runs says."""
+    def runs(kind, dtype, P, tiles, **more):
+        return [s.run_log2 for s in shapes(ask, [dict(kind=kind, dtype=dtype, P=P, tiles=t, off_lines=0.6, reduced=0) | dict(segments=100) | more for t in tiles])]
+    edge, few = [49151, 49152, 1000000], [65535, 65536, 1000000]
+    for dtype, P in [("f32", 1)] + [(d, P) for d in ("bf16", "f16") for P in (1, 3, 7, 8, 16)]:
+        assert runs("direct", dtype, P, edge) == [0, 3, 3], (dtype, P)
+        assert runs("direct", dtype, P, edge, blocks_per_cu=4) == [0, 0, 0]
+        assert runs("direct", dtype, P, few, segments=8) == ([0, 3, 3] if P < 8 and dtype != "f32" else [0, 0, 0]), (dtype, P)
+    for dtype, P in (("f32", 2), ("f32", 8), ("bf16", 17), ("f16", 32)):
+        assert runs("direct", dtype, P, edge) == [0, 0, 0], (dtype, P)
+    for dtype in DTYPES:
+        assert runs("update", dtype, 8, [24575, 24576, 49151, 49152, 131072, 131073]) == [3, 0, 0, 3, 3, 0]       # on lines from 24576
+        assert runs("update", dtype, 8, few, segments=8) == [0, 0, 0]
+    assert runs("pipeline", "f32", 8, edge) == [2, 2, 2]
+    assert [runs("direct", "f32", 1, [30000], reduced=r) for r in (0, 1)] == [[0], [3]]
+
+
 def test_long_binary32_launches_write_through_the_l2(ask):
     """From a quarter of LONG_LAUNCH_TILES on, models on their lines with few ragged tiles, in the table form."""
     def through(kind, dtype="f32", tiles=65536, off=0.0, ragged=0.0, segments=100):
