@@ -963,8 +963,17 @@ __global__ void __launch_bounds__(MGWFBP_BLOCK, (wanted_waves<ROLE, GradT, PT, K
                 const Piece s{h.layer0, -ahead, 0, -h.first_start - ahead};
                 int lane = threadIdx.x;
                 here_only_per_lane(lane);
-                if (ahead >= VEC) one_piece<KIND, GradT, PT, true>(A, mrg, tile_base, s, lane);
-                else if (lane < ahead) do_one<KIND, GradT, PT, 1>(A, mrg, s.layer, s.off + lane, tile_base + s.lo + lane);
+                if (ahead >= VEC) {
+                    if (h.flags & TILE_RESIDENT) {
+                        asm volatile("; w and v cacheable" ::: "memory");
+                        one_piece<KIND, GradT, PT, NT_WV>(A, mrg, tile_base, s, lane);
+                        asm volatile("; end w and v cacheable" ::: "memory");
+                    } else {
+                        asm volatile("; w and v streamed" ::: "memory");
+                        one_piece<KIND, GradT, PT, true>(A, mrg, tile_base, s, lane);
+                        asm volatile("; end w and v streamed" ::: "memory");
+                    }
+                } else if (lane < ahead) do_one<KIND, GradT, PT, 1>(A, mrg, s.layer, s.off + lane, tile_base + s.lo + lane);
                 chi -= left;
             }
             const bool full = clo == 0 && chi == TILE && (!needs_owner(KIND) || h.nseg == 1);
