@@ -362,7 +362,8 @@ inline bool few_form_pays(int kind, int32_t dtype, int32_t P, int32_t tiles, int
 // 8 workers 0.997 / 0.999, 1.009 / 0.997, 16 workers 1.002 / 1.018, 1.016 / 1.018, binary32 of one worker 0.99-1.00,
 // at 200,000 1.008 / 1.014.  Updates of 200,000 tiles are 0.984 / 0.985 / 1.029 / 1.022, other direct steps of one worker level again.  Time over the
 // tiles cut in the arena with their runs, a group each in allocations of their own, which are on lines in truth, 60,000 to 140,000 tiles: direct binary32 of one
-// worker and bfloat16 of 1 to 6 1.02-1.055 without runs here, 1.00 with them.
+// worker and bfloat16 of 1 to 6 1.02-1.055 without runs here, 1.00 with them.  Where some of the weights and momenta are kept cacheable (64 MiB of them, 100,000
+// tiles) runs bring nothing (1.00-1.03, five tensors bfloat16 4 workers 1.05).
 inline bool runs_on_lines(int kind, int32_t dtype, int32_t P, int32_t tiles, int32_t segments) {
     const bool few = segments <= FEW;
     if (tiles < (few ? 4 : 3) * SHORT_LAUNCH_TILES) return false;
@@ -556,7 +557,7 @@ inline LaunchShape launch_shape(const LaunchSettings& set, const LaunchWork& w, 
     }
     s.rolling = may_roll(w.kind, s.form) && set.step_vecs == 0 && set.wg_per_cu == 0 && rolls(w.dtype, w.P, s.may_be_few, per_cu);
     s.in_pieces = w.ragged > 0.5;
-    s.run_log2 = one_turn && !(s.on_lines && !runs_on_lines(w.kind, w.dtype, w.P, length, w.segments)) ? run_log2_of(w.kind, w.dtype, w.P, w.off_lines) : int8_t{0};
+    s.run_log2 = one_turn && (!s.on_lines || (w.resident == 0 && runs_on_lines(w.kind, w.dtype, w.P, length, w.segments))) ? run_log2_of(w.kind, w.dtype, w.P, w.off_lines) : int8_t{0};
     return s;
 }
 

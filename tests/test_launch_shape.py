@@ -444,6 +444,7 @@ def test_runs_per_die_of_launches_that_begin_on_lines(ask):
     for dtype, P in [("f32", 1)] + [(d, P) for d in ("bf16", "f16") for P in (1, 3, 7, 8, 16)]:
         assert runs("direct", dtype, P, edge) == [0, 3, 3], (dtype, P)
         assert runs("direct", dtype, P, edge, blocks_per_cu=4) == [0, 0, 0]
+        assert runs("direct", dtype, P, edge, resident=0.01, resident_bytes=1 << 20) == [0, 0, 0]
         assert runs("direct", dtype, P, few, segments=8) == ([0, 3, 3] if P < 8 and dtype != "f32" else [0, 0, 0]), (dtype, P)
     for dtype, P in (("f32", 2), ("f32", 8), ("bf16", 17), ("f16", 32)):
         assert runs("direct", dtype, P, edge) == [0, 0, 0], (dtype, P)
