@@ -70,6 +70,33 @@ int main() {
             const LaunchShape s = launch_shape(set, w, n_cu);
             std::printf("%d %d %d %d %d %d %d %d %d %d\n", s.tiles_per_wg, s.units, s.grid, s.xcd_contiguous, s.run_log2, s.may_be_few,
                         s.form, s.wgs_per_cu, s.rolling, s.in_pieces);
+        } else if (!std::strcmp(what, "forms")) {     // forms P dtype reduced L {n merged}...: launches over all of a model, each kind's form,
+                                                      // on_lines, through, may_be_few and run_log2
+            LaunchWork w{};
+            int reduced, L;
+            if (std::scanf("%d %d %d %d", &w.P, &w.dtype, &reduced, &L) != 4) return 1;
+            std::vector<uint64_t> n(static_cast<size_t>(L));
+            std::vector<uint8_t> merged(static_cast<size_t>(L));
+            for (size_t i = 0; i < n.size(); ++i) {
+                unsigned long long elems;
+                int m;
+                if (std::scanf("%llu %d", &elems, &m) != 2) return 1;
+                n[i] = elems;
+                merged[i] = static_cast<uint8_t>(m);
+            }
+            HostTables h;
+            if (mgwfbp_build_tables(n.data(), L, merged.data(), h) != MGWFBP_OK) return 1;
+            w.reduced = reduced != 0;
+            w.tiles = static_cast<int32_t>(h.tiles.size());
+            w.segments = static_cast<int32_t>(h.seg_layer.size());
+            const LaunchShares shares = shares_of(h, 0, w.segments, w.tiles);
+            w.ragged = shares.ragged;
+            w.off_lines = shares.off_lines;
+            for (w.kind = K_PACK; w.kind <= K_DIRECT; ++w.kind) {
+                const LaunchShape s = launch_shape(LaunchSettings{}, w, 256);
+                std::printf("%d %d %d %d %d ", s.form, s.on_lines, s.through, s.may_be_few, s.run_log2);
+            }
+            std::printf("\n");
         } else if (!std::strcmp(what, "shares")) {    // shares L {n merged}... g0 g1: of the launch over groups [g0, g1)
             int L, g0, g1;
             if (std::scanf("%d", &L) != 1) return 1;

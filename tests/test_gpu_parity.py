@@ -6,6 +6,7 @@ import time
 import numpy as np
 import pytest
 
+import test_launch_shape as TS
 import workloads as W
 from oracle import pipeline as OD
 from oracle import plan as OP
@@ -648,37 +649,71 @@ def test_packs_and_reductions_of_many_mebibytes(P, dtype, tiles):
         check_case(p, [0] + [int(x) for x in rng.random(31) < 0.7], mode, misalign=3, label=f"{tiles} tiles")
 
 
-@pytest.mark.parametrize("P,dtype", [(1, "f32"), (3, "f32"), (8, "f16"), (16, "bf16"), (5, "bf16"), (2, "f16"), (4, "f32")])
-def test_shares_of_tiles_that_begin_on_lines(P, dtype):
-    """UPDATE and DIRECT over long models of odd sizes: tensors that begin and end one to 64 elements before and after the end of a tile,
-    of a few elements, of one tile and of many, one after the other and in groups of their own; more in a tile than are taken piece by
-    piece; some of the weights kept cacheable."""
+@pytest.fixture(scope="module")
+def forms(tmp_path_factory):
+    """The forms that launches over all of a profile take, as the library's rules say: a test of a form names it."""
+    ask = TS.build_driver(tmp_path_factory.mktemp("forms"))
+    return lambda p, merged, reduced=0: TS.forms_of(ask, [int(x) for x in p.n_elems], merged, p.P, p.grad_dtype, reduced)
+
+
+def _odd_model(P, dtype, blocks, scale=1):
+    """Tensors that begin and end one to 64 elements before and after the end of a tile, of a few elements, of one tile and of many, one after
+    the other and in groups of their own; more in a tile than are taken piece by piece."""
     rng = np.random.default_rng(22)
     sizes = []
-    for _ in range(150):
+    for _ in range(blocks):
         sizes += [int(x) for x in rng.choice([1, 2, 3, 4, 5, 31, 33, 63, 64, 65, 129, 191, 193, 224, 253, 255, 256, 257, 300, 511, 512, 513, 700, 3000], 8)]
-        sizes.append(int(rng.integers(30000, 60000)) if len(sizes) % 5 else 256 * int(rng.integers(100, 250)) + int(rng.integers(-64, 65)))
+        sizes.append(int(rng.integers(30000, 60000)) * scale if len(sizes) % 5 else 256 * scale * int(rng.integers(100, 250)) + int(rng.integers(-64, 65)))
     L = len(sizes)
     merged = [0] + [int(x) for x in rng.random(L - 1) < 0.7]
-    p = W.Profile("lines", np.asarray(sizes, np.uint64), rng.uniform(1e-6, 1e-5, L), 1e-4, 1e-9, P, dtype, 1.0)
+    return W.Profile("lines", np.asarray(sizes, np.uint64), rng.uniform(1e-6, 1e-5, L), 1e-4, 1e-9, P, dtype, 1.0), merged
+
+
+@pytest.mark.parametrize("P,dtype", [(1, "f32"), (3, "f32"), (8, "f16"), (16, "bf16"), (5, "bf16"), (2, "f16"), (4, "f32")])
+def test_shares_of_tiles_that_begin_on_lines(forms, P, dtype):
+    """UPDATE and DIRECT over long models of odd sizes; some of the weights kept cacheable."""
+    p, merged = _odd_model(P, dtype, 150)
+    launches = forms(p, merged)
+    assert launches["update"].on_lines and launches["direct"].on_lines
     check_case(p, merged, "direct", misalign=3, label="direct")
     check_case(p, merged, "staged", misalign=3, label="staged")
     check_case(p, merged, "direct", label="direct, tensors at the start of allocations")
     check_case(p, merged, "direct", misalign=5, resident=10 << 20, label="direct, some of w and v resident")
     few = W.Profile("lines", np.asarray([256 * 12000 - 1, 77, 256 * 13000 + 191], np.uint64), p.t_backward[:3], 1e-4, 1e-9, P, dtype, 1.0)
+    launches = forms(few, [0, 1, 1])
+    assert launches["update"].on_lines and launches["direct"].on_lines
     check_case(few, [0, 1, 1], "direct", misalign=3, label="direct, three tensors")
     check_case(few, [0, 1, 1], "staged", misalign=3, label="staged, three tensors")
 
 
-@pytest.mark.parametrize("P", [1, 2, 3, 4])
-def test_long_binary32_launches_that_write_through_the_l2(P):
-    """The shortest such launches, with ragged tiles of one and of several tensors between the large ones (8 and 16 workers: the profiles
-    below).  Every store is followed by writes to its registers at the shortest distance there is."""
+@pytest.mark.parametrize("P,dtype,scale,runs", [(2, "f32", 1, 0), (8, "f32", 1, 0), (16, "f32", 1, 0), (2, "bf16", 1, 0), (4, "bf16", 1, 0), (8, "bf16", 1, 0),
+                                                (3, "f16", 1, 0), (4, "f16", 1, 0), (16, "f16", 1, 0), (1, "f32", 2, 3), (5, "bf16", 2, 3), (8, "f16", 2, 3), (3, "f32", 2, 0)])
+def test_every_direct_kernel_that_begins_on_lines(forms, P, dtype, scale, runs):
+    """The other kernels of that form, and the lengths at which tiles go to the dies in runs (of 2^`runs`) or one by one all the same."""
+    p, merged = _odd_model(P, dtype, 150, scale)
+    direct = forms(p, merged)["direct"]
+    assert direct.on_lines and direct.run_log2 == runs
+    check_case(p, merged, "direct", misalign=3, label="direct")
+    if runs:
+        assert forms(p, merged)["update"].run_log2 == runs
+        check_case(p, merged, "staged", misalign=3, label="staged")
+
+
+@pytest.mark.parametrize("P", [1, 2, 3, 4, 8, 12, 16])
+def test_long_binary32_launches_that_write_through_the_l2(forms, P):
+    """The shortest such launches of every kernel (and of a worker count beyond the eight that are taken together where it is not compiled in), with
+    ragged tiles of one and of several tensors between the large ones.  Every store is followed by writes to its registers at the
+    shortest distance there is."""
     rng = np.random.default_rng(23)
-    small = [int(x) for x in rng.integers(1, 3000, 40)]
-    sizes = [1 << 20, *small[:20], 65536 * 200, *small[20:], 1 << 21, 64]
+    groups = [[64 * int(rng.integers(22000, 24000))] + [int(x) for x in rng.integers(1, 3000, 4)] for _ in range(10)]     # in the arena's order
+    groups.append([33, 64 * 20000 + 17, 5, 700])
+    groups.append([1 << 20, 64])
+    sizes = [n for g in groups for n in g][::-1]
+    merged = [int(i > 0) for g in groups for i in reversed(range(len(g)))][::-1]
     p = W.Profile("through", np.asarray(sizes, np.uint64), rng.uniform(1e-6, 1e-5, len(sizes)), 1e-4, 1e-9, P, "f32", 1.0)
-    merged = [0] + [int(x) for x in rng.random(len(sizes) - 1) < 0.7]
+    for reduced in (0, 1):
+        launches = forms(p, merged, reduced)
+        assert all(launches[kind].through and not launches[kind].may_be_few for kind in ("reduce_update", "pipeline", "direct"))
     for mode in ("pipeline", "pipeline_no_reduced", "reduce_update", "direct"):
         check_case(p, merged, mode, label=mode)
     check_case(p, merged, "pipeline", resident=4 << 20, label="some of w and v resident")

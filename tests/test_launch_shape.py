@@ -38,6 +38,15 @@ def build_driver(folder, *defines):
     return ask
 
 
+Form = namedtuple("Form", "form on_lines through may_be_few run_log2")
+
+
+def forms_of(ask, n_elems, merged, P, dtype, reduced=0):
+    """What the rules make of launches over all of a model: a Form for each kind."""
+    out = ask([f"forms {P} {DTYPES.index(dtype)} {reduced} {len(n_elems)} " + " ".join(f"{n} {m}" for n, m in zip(n_elems, merged))])[0]
+    return {kind: Form(*out[5 * k:5 * k + 5]) for k, kind in enumerate(KINDS)}
+
+
 @pytest.fixture(scope="module")
 def ask(tmp_path_factory):
     return build_driver(tmp_path_factory.mktemp("launch"))
