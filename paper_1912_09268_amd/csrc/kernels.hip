@@ -140,7 +140,7 @@ template <bool NT, typename V> __device__ __forceinline__ V ld(const void* p) {
     if constexpr (NT) return __builtin_nontemporal_load(q);
     else return *q;
 }
-// THROUGH_L2: 16-byte vectors are written through the L2 (system scope) as well as streamed.  There is no builtin for that on vectors.  The no-op
+// THROUGH_L2: 16-byte vectors are written through the L2 (sc1: agent scope) as well as streamed.  There is no builtin for that on vectors.  The no-op
 // is the two wait states gfx950 wants between a store of more than 8 bytes and the next write of its registers, which the compiler
 // sees to after the stores it knows.
 template <bool NT, typename V, bool THROUGH_L2 = false> __device__ __forceinline__ void st(void* p, const V& x) {
@@ -427,7 +427,7 @@ __device__ __forceinline__ void paced_step(const CallArgs<GradT>& A, const Worke
             for (int i = 0; i < N; ++i) st<NT_ST, FV, through(KIND)>(A.reduced + apos + i * stride, acc[i]);
         }
     }
-    if constexpr (updates(KIND) && TOGETHER > 0) {
+    if constexpr (updates(KIND) && TOGETHER > 0) {              // (never through the L2: a launch that is has few ragged tiles)
 #pragma unroll
         for (int i = 0; i < N; ++i) {
 #pragma unroll

@@ -437,7 +437,7 @@ inline bool even_rounds(int kind, int32_t dtype, int32_t P, bool few, int form, 
 //   0.98 / 0.99 / 0.99; tensors around 500 elements, a group each, bfloat16 16 workers: PACK 1.02 / 1.17 / 1.25 / - | 1.01 / 1.00 / 0.99 / 1.00, with the copy
 //   1.06 / 1.15 / 1.10 / - | 1.06 / 1.09 / 1.12 / -, without 1.00 / 0.97 / 0.94 / - | 1.04 / 1.02 / 1.02 / -.
 
-// Binary32 launches whose vectors are written through the L2 to memory (system scope) as well as streamed: the L2 then does not choose when
+// Binary32 launches whose vectors are written through the L2 to memory (agent scope, sc1) as well as streamed (nt): the L2 then does not choose when
 // a line leaves it, and the write stream stays in the order of the walk.  Time over streamed alone, models on their lines, 1 / 3 / 4 / 8 / 16 / 32
 // workers:
 //    66,000 tiles  pipeline 0.991 / 0.987 / 0.989 / 0.988 / 0.987 / 0.991, reduce_update 1.001 / 0.996 / 0.974 / 0.986 / 0.992 / 0.997, direct 1.010 / 0.991 /
@@ -446,7 +446,10 @@ inline bool even_rounds(int kind, int32_t dtype, int32_t P, bool few, int form, 
 //                  0.977 / 0.991 / 0.992 / 0.995
 //   500,000 tiles  pipeline 0.971 / 0.985 / 0.988 / 0.989 / 0.996 / 0.997, reduce_update 0.990 / 0.988 / 0.989 / 0.993 / 0.991 / 0.997, direct 0.993 / 0.997 /
 //                  0.982 / 0.993 / 0.991 / 0.995; VGG-16 shape, pipeline 0.982 to 0.996 in several runs
-// Shorter, pipeline 30,000 tiles 1.00-1.02.  bfloat16 is level (pipeline 0.995-1.005, reduce_update and direct 0.98-1.01), UPDATE and REDUCE are 0.98-1.01, and PACK
+// Another card, 65,600 / 80,000 / 100,000 / 150,000 tiles: 1 worker pipeline 0.980 / 0.980 / 0.979 / 0.979, reduce_update 0.991 / 0.984 / 0.988 / 0.994, direct 0.994 /
+// 0.983 / 0.988 / 0.993; 2 workers reduce_update 1.000 / 1.006 / 0.997 / 1.002; every other worker count and kind 0.955-1.002.  System scope (sc0 sc1 nt) is the same
+// (0.997-1.007); sc1 without nt, in either scope, takes 1.01-1.05 of the time of sc1 nt from 100,000 tiles on.
+// The line is the shortest length measured at which nothing is behind: pipeline 30,000 tiles 1.00-1.02.  bfloat16 is level (pipeline 0.995-1.005, reduce_update and direct 0.98-1.01), UPDATE and REDUCE are 0.98-1.01, and PACK
 // and models off their lines lose (PACK 1.02-1.08, a thousand small layers 1.02: two tiles write a part of a line each, which the L2 joins).
 inline bool goes_through(int kind, int32_t dtype, int32_t tiles, double off_lines, double ragged) {
     if (dtype != MGWFBP_F32 || (kind != K_REDUCE_UPDATE && kind != K_DIRECT && kind != K_PIPELINE)) return false;
