@@ -313,8 +313,9 @@ constexpr int line_elems(int kind, size_t grad_bytes) { return 128 / static_cast
 //   24,600        the same 0.96 / 0.97 / 0.98, 0.92 / 0.94 / 0.94, 0.90 / 0.91 / 0.93, 0.82 / 0.88 / 0.89; binary32 update 0.96 / 0.99 / 0.98, direct 1 / 8 / 16 workers 0.97 /
 //                 0.97 / 0.98, 0.95 / 0.95 / 0.95, 0.92 / 0.96 / 0.94
 //   40,000        the same 0.94 / 0.95 / 0.97, 0.89 / 0.92 / 0.93, 0.86 / 0.90 / 0.90, 0.79 / 0.87 / 0.85; 0.95 / 0.97 / 0.97, 0.95 / 0.95 / 0.96, 0.94 / 0.93 / 0.94, 0.95 / 0.94 / 0.93
-// Eight odd tensors, a group each, in allocations of their own pay 1-4 % with bfloat16 of up to 8 workers to 24,600 tiles (20,000: 1 / 4 / 8 workers 1.04 / 1.02 / 1.03) and gain 0-5 %
-// from 30,000 on.  The pipeline would have its arenas off the lines instead (0.84-0.97 of the rate), reduce_update gains with one or two 16-bit workers only.
+// Eight odd tensors, a group each, in allocations of their own pay up to 4 % with bfloat16 of up to 8 workers to 24,600 tiles (20,000: 1 / 4 / 8 workers 1.03-1.04 / 1.02 /
+// 1.01-1.03) and gain 0-5 % from 30,000 on; as views of one buffer, for which they are taken, they gain from 16,400 on (20,000: 0.98 / 0.96 / 0.94, 16 workers 0.89).
+// The pipeline would have its arenas off the lines instead (0.84-0.97 of the rate), reduce_update gains with one or two 16-bit workers only.
 inline bool on_lines_pays(int kind, int32_t dtype, bool reduced, int32_t tiles, int32_t segments, double off_lines) {
     if (kind != K_UPDATE && (kind != K_DIRECT || reduced)) return false;
     const int32_t least = kind == K_DIRECT && dtype != MGWFBP_F32 ? SHORT_LAUNCH_TILES : SHORT_LAUNCH_TILES / 2 * 3;
@@ -346,9 +347,9 @@ inline bool few_form_pays(int kind, int32_t dtype, int32_t P, int32_t tiles, int
     return tiles <= 3072 || (per_cu > 24 && per_cu <= 32) || (per_cu > 48 && per_cu <= 56);
 }
 
-// Which of the launches that begin on lines have runs of tiles per die all the same.  No line is shared any more, but two dies still take turns in the pages; time with runs over
-// without, tensors as views / in allocations of their own in groups of five / a group each / eight a group each, at 30,000, 50,000, 70,000 and 140,000 tiles
-// (50,000: the first, third and fourth):
+// Which of the launches that begin on lines have runs of tiles per die all the same.  No line is shared any more; that runs still pay in some
+// of them is what the times say.  Time with runs over without, 300 tensors as views / in allocations of their own in groups of five / a group
+// each / eight tensors a group each, at 30,000, 50,000 (without the groups of five), 70,000 and 140,000 tiles:
 //   update                     0.986 / 0.978 / 1.002 / 1.007    0.977 / 0.996 / 1.006    0.970 / 0.978 / 0.987 / 1.002    0.976 / 0.984 / 1.014 / 1.009
 //   direct  binary32, 1        0.996 / 0.993 / 1.003 / 1.014    0.983 / 0.990 / 1.015    0.959 / 0.960 / 0.955 / 0.998    0.975 / 0.976 / 0.975 / 1.005
 //           binary32, 3        1.000 / 0.996 / 1.002 / 1.020    1.007 / 1.012 / 1.021    1.001 / 1.005 / 0.999 / 1.012    1.019 / 1.030 / 1.030 / 1.023
@@ -359,8 +360,8 @@ inline bool few_form_pays(int kind, int32_t dtype, int32_t P, int32_t tiles, int
 //           bfloat16, 16       0.996 / 0.997 / 1.003 / 1.014    0.989 / 0.990 / 1.024    0.988 / 0.986 / 0.992 / 1.000    0.989 / 0.991 / 0.991 / 1.005
 //           bfloat16, 32       0.994 / 0.998 / 1.002 / 1.041             -               0.981 / 0.985 / 0.993 / 0.995    0.994 / 0.995 / 0.988 / 1.008
 // Few tensors gain less: eight a group each and five as views at 52,000 tiles 1.00-1.02 throughout, at 70,000 and 100,000 update 1.002 / 0.982, 1.012 / 0.980, bfloat16
-// 8 workers 0.997 / 0.999, 1.009 / 0.997, 16 workers 1.002 / 1.018, 1.016 / 1.018, binary32 of one worker 0.99-1.00,
-// at 200,000 1.008 / 1.014.  Updates of 200,000 tiles are 0.984 / 0.985 / 1.029 / 1.022, other direct steps of one worker level again.  Time over the
+// 8 workers 0.997 / 0.999, 1.009 / 0.997, 16 workers 1.002 / 1.018, 1.016 / 1.018, binary32 of one worker 0.99-1.00, at 200,000 1.008 /
+// 1.014.  Updates of 200,000 tiles are 0.984 / 0.985 / 1.029 / 1.022, other direct steps of one worker level again.  Time over the
 // tiles cut in the arena with their runs, a group each in allocations of their own, which are on lines in truth, 60,000 to 140,000 tiles: direct binary32 of one
 // worker and bfloat16 of 1 to 6 1.02-1.055 without runs here, 1.00 with them.  Where some of the weights and momenta are kept cacheable (64 MiB of them, 100,000
 // tiles) runs bring nothing (1.00-1.03, five tensors bfloat16 4 workers 1.05).
